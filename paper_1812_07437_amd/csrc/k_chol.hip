@@ -5,21 +5,36 @@
 // Factoring the first n columns of M leaves y = L^-1 d~ in its last row, and
 // (S/N)^2 = y^T y.
 //
-// Left-looking over 256-wide panels: each panel first receives the update
-// from every column to its left in one long-k MFMA product (k_update.hip),
-// then is factored right-looking in 64-wide steps: the 64 x 64 diagonal block
-// factored and inverted by one wavefront, the rows below multiplied by the
-// inverse on MFMA, and the rest of the panel updated with a short product.
+// Panels of 128 columns, two launches each: the rows below the factored diagonal
+// block are solved against it (k_solve), then the trailing columns receive the
+// panel's update while one workgroup of the same launch already updates and
+// factors the next diagonal block (k_trail), so that the serial chain runs
+// beside the update.  Up to RIGHT_MAX columns the trailing update covers the
+// whole remaining matrix.  Beyond it the matrix is read and written too often
+// that way, and blocks of 256 columns first receive the update from every
+// column to their left in one long-k MFMA product (k_update.hip); the panels'
+// own updates then stay within the block.
+//
+// Measured, one factorisation (before: 64-wide diagonal blocks in launches of
+// their own, left-looking over 256 columns at every size): n = 818
+// 0.99 -> 0.35 ms, 2420 3.1 -> 0.96 ms, 4550 6.0 -> 2.05 ms, 10000
+// 15.1 -> 10.4 ms, 25044 106 -> 94 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 
+#include "dev.h"
 #include "kernels.h"
 
 namespace wlc {
 
-constexpr int NB = 64;       // inner panel width
-constexpr int NB_OUT = 256;  // outer panel width
+constexpr int NB = 128;      // panel width
+constexpr int NB_OUT = 256;  // columns that take one long-k update together
+// Up to this size every panel's update goes to the whole trailing matrix.
+// Measured with and without: n = 6550 4.0 against 5.8 ms, 10000 10.4 against
+// 10.4 ms, 12768 19.6 against 17.1 ms (the trailing matrix is then read and
+// written once per 128 columns, which the long-k product does not need).
+constexpr int64_t RIGHT_MAX = 10000;
 constexpr int64_t PART_ROWS = 524288;  // split-k scratch: slices x rows of 256 doubles
 
 // ------------------------------------------------------------- prepare
@@ -59,199 +74,639 @@ void launch_chol_prep(const void *C, int c_f32, const int32_t *row_exp2, const d
   }
 }
 
-// ------------------------------------------------------------- diagonal block
-// One workgroup of 256 threads on the jb x jb diagonal block at j0 (rows
-// beyond jb padded with the identity), held in registers: thread
-// t = 16 tj + ti owns rows 4 ti .. 4 ti + 3 and columns 4 tj .. 4 tj + 3.
-// The factorisation runs square-root free, as A = U D U^T with U unit lower,
-// and inverts U in the same pass: at step k the owners of column k publish
-// it in LDS as it stands (the Schur complement column, d_k = its diagonal
-// entry, U[i][k] = a[i][k] / d_k), the owners of row k of V publish that
-// row (final after step k - 1), and after one barrier every thread applies
-// -a[i][k] a[j][k] / d_k to its block of A and -U[i][k] V[k][j] to its block
-// of V (V = I at the start, V = U^-1 at the end: forward substitution with
-// a unit diagonal).  Each step is one chain of dependent instructions with
-// no square root and one division; the updates mask the broadcast factors
-// rather than each product, and entries above the diagonal of a thread's
-// block take harmless updates that are never read.  The published vectors
-// alternate between two LDS buffers, so one barrier per step suffices.
-// Afterwards d_k is the diagonal of A, and in one parallel pass
-// L = U D^1/2 (L[i][k] = a[i][k] / sqrt(d_k)) goes back to the matrix and
-// X = L^-1 = D^-1/2 V to Linv (row-major, NB columns).
-__device__ __forceinline__ double pick4(const double (&v)[4], int c) {
-  return c == 0 ? v[0] : c == 1 ? v[1] : c == 2 ? v[2] : v[3];
+// ------------------------------------------------------------- panels of 128
+// Everything inside a panel works on 16 x 16 tiles held transposed in
+// registers: T(w, j), row block w and column block j, has in lane l = 16 g + r
+// and element v the entry of row 16 w + r, column 16 j + g + 4 v.  That is the
+// accumulator of v_mfma_f64_16x16x4 for the product (columns of block j) x
+// (rows of block w), and the same registers are, as they stand, its two
+// operands: element v is what step v of a 16-deep product wants from either
+// side.  So T(w, t) -= L(t, j) T(w, j) and T(w, j) <- L_jj^-1 T(w, j) chain from
+// register to register, and a tile that other wavefronts need goes through
+// memory as it stands, lane after lane ("packed": element pairs (0, 1) of the
+// 64 lanes, then (2, 3)).
+constexpr int RB = 16;          // rows of a tile
+constexpr int NT = NB / RB;     // tiles across a panel
+constexpr int TILE = RB * RB;   // doubles of a tile
+constexpr int PACK_ROW = NT * TILE;                    // doubles of a packed row block: 16 rows x 128 columns
+constexpr int PACK_DIAG = NT * (NT + 1) / 2 * TILE;    // packed diagonal block: L(t, j), t > j, and L_jj^-1
+
+__device__ __forceinline__ int diag_at(int t, int j) { return (t * (t + 1) / 2 + j) * TILE; }
+
+// tile <-> packed memory
+__device__ __forceinline__ void put_tile(double *dst, int lane, const f64x4 &t) {
+  *reinterpret_cast<double2 *>(dst + 2 * lane) = make_double2(t[0], t[1]);
+  *reinterpret_cast<double2 *>(dst + 128 + 2 * lane) = make_double2(t[2], t[3]);
+}
+__device__ __forceinline__ f64x4 get_tile(const double *src, int lane) {
+  const double2 a = *reinterpret_cast<const double2 *>(src + 2 * lane);
+  const double2 b = *reinterpret_cast<const double2 *>(src + 128 + 2 * lane);
+  return f64x4{a.x, a.y, b.x, b.y};
 }
 
-__global__ __launch_bounds__(256) void k_potrf_diag(double *__restrict__ Wm, int64_t ld, int64_t j0, int jb,
-                                                    double *__restrict__ Linv, int *__restrict__ flag) {
-  __shared__ double vcol[2][NB];  // column k of the Schur complement
-  __shared__ double vrow[2][NB];  // row k of V
-  __shared__ double dsq[NB], dinv[NB];  // sqrt(d_k) and its reciprocal
-  __shared__ int bad;
-  const int tid = threadIdx.x;
-  const int ti = tid & 15, tj = tid >> 4;
-  const int i0 = 4 * ti, c0 = 4 * tj;
-  double a[4][4], x[4][4];
+// acc +- A B over one 16-deep step of tiles
+__device__ __forceinline__ f64x4 tile_fma(const f64x4 &a, const f64x4 &b, f64x4 acc) {
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+  for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[v], b[v], acc, 0, 0, 0);
+  return acc;
+}
+__device__ __forceinline__ f64x4 tile_fms(const f64x4 &a, const f64x4 &b, f64x4 acc) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      // every load unconditional, from the block's lower triangle (the
-      // mirror position above the diagonal, clamped to the block), and
-      // masked arithmetically, so all are in flight at once
-      const int i = i0 + r, j = c0 + c;
-      const double w = Wm[(j0 + min(max(i, j), jb - 1)) * ld + j0 + min(min(i, j), jb - 1)];
-      a[r][c] = w * ((i < jb && j <= i) ? 1.0 : 0.0) + ((i >= jb && i == j) ? 1.0 : 0.0);
-      x[r][c] = i == j ? 1.0 : 0.0;
-    }
-  if (tid == 0) bad = 0;
-  // unrolled by four so that the column within a thread's block is a constant
-#pragma unroll 4
-  for (int k = 0; k < NB; ++k) {
-    const int kb = k >> 2, kc = k & 3, buf = k & 1;
-    if (tj == kb) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) vcol[buf][i0 + r] = pick4(a[r], kc);
-    }
-    if (ti == kb) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const double col[4] = {x[0][c], x[1][c], x[2][c], x[3][c]};
-        vrow[buf][c0 + c] = pick4(col, kc);
-      }
-    }
-    __syncthreads();
-    // all reads first and unconditionally (masked afterwards), so that
-    // they overlap one another and the division
-    const double dk = vcol[buf][k];
-    double ci[4], cj[4], vk[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      ci[q] = vcol[buf][i0 + q];
-      cj[q] = vcol[buf][c0 + q];
-      vk[q] = vrow[buf][c0 + q];
-    }
-    const double rd = dk > 0.0 ? 1.0 / dk : 0.0;
-    double li[4], lj[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      li[q] = i0 + q > k ? ci[q] : 0.0;
-      lj[q] = c0 + q > k ? cj[q] * rd : 0.0;
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const double u = li[r] * rd;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        a[r][c] -= li[r] * lj[c];
-        x[r][c] -= u * vk[c];
-      }
-    }
-  }
-  if (ti == tj) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const double dk = a[r][r];
-      if (!(dk > 0.0)) bad = 1;
-      const double sq = sqrt(dk > 0.0 ? dk : 1.0);
-      dsq[i0 + r] = sq;
-      dinv[i0 + r] = 1.0 / sq;
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int i = i0 + r, j = c0 + c;
-      if (i < jb && j <= i) Wm[(j0 + i) * ld + j0 + j] = j < i ? a[r][c] * dinv[j] : dsq[j];
-      Linv[i * NB + j] = j <= i ? x[r][c] * dinv[i] : 0.0;
-    }
-  if (tid == 0 && bad) atomicOr(flag, 1);
+  for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[v], b[v], acc, 0, 0, 0);
+  return acc;
 }
 
-// ------------------------------------------------------------- panel solve
-// Rows [r0, r1) of columns [j0, j0 + jb): X = B L^-T, 64 rows per
-// workgroup; four wavefronts each compute a 32 x 32 quadrant on
-// v_mfma_f64_16x16x4 (accumulator rows l / 16 + 4 v, columns l % 16).
-__global__ __launch_bounds__(256) void k_trsm(double *__restrict__ Wm, int64_t ld, int64_t j0, int jb, int64_t r0,
-                                              int64_t r1, const double *__restrict__ Linv) {
-  __shared__ double Li[NB][NB + 1];
-  __shared__ double B[NB][NB + 1];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t rb = r0 + (int64_t)blockIdx.x * NB;
-  // all 32 loads of a thread in flight together: unconditional, from
-  // addresses clamped into the panel (entries below the diagonal block,
-  // finite), masked arithmetically afterwards
-  double lv[NB * NB / 256], bv[NB * NB / 256];
-#pragma unroll
-  for (int m = 0; m < NB * NB / 256; ++m) {
-    const int q = tid + 256 * m, i = q / NB, c = q % NB;
-    lv[m] = Linv[q];
-    const double w = Wm[min(rb + i, r1 - 1) * ld + j0 + min(c, jb - 1)];
-    bv[m] = w * ((rb + i < r1 && c < jb) ? 1.0 : 0.0);
+// lane K of each 16-lane row, to the whole row
+template <int K>
+__device__ __forceinline__ double row_bcast(double x) {
+  return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, __double_as_longlong(x), 0x150 + K, 0xf, 0xf, true));
+}
+
+// 1 / sqrt(d): the hardware estimate and one third-order step,
+// y (1 + e/2 + 3 e^2 / 8) with e = 1 - d y^2.  An infinite d counts as the
+// largest number, whose root is as good as infinite.
+__device__ __forceinline__ double rsqrt_full(double d) {
+  const double c = fmin(d, 1.7976931348623157e308);
+  const double y = __builtin_amdgcn_rsq(c);
+  const double e = fma(-c * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// acc[J + q] += (lane J + q of the 16-lane row of x) * m for q < N, one
+// instruction each (the compiler would move the broadcast to a register first,
+// which doubles the instructions).  A broadcast may not read a register within
+// two issue slots of its write: a block opens with that wait, and leaves as
+// much behind the first register that it writes, the next pivot's.
+#define WLC_BCAST(q) "v_fmac_f64_dpp %[a" #q "], %[x], %[m] row_newbcast:%[j" #q "] row_mask:0xf bank_mask:0xf\n\t"
+template <int J, int N>
+__device__ __forceinline__ void fmac_cols(double *a, double x, double m) {
+  if constexpr (N >= 8) {
+    asm("s_nop 1\n\t" WLC_BCAST(0) WLC_BCAST(1) WLC_BCAST(2) WLC_BCAST(3) WLC_BCAST(4) WLC_BCAST(5) WLC_BCAST(6)
+            WLC_BCAST(7)
+        : [a0] "+v"(a[J]), [a1] "+v"(a[J + 1]), [a2] "+v"(a[J + 2]), [a3] "+v"(a[J + 3]), [a4] "+v"(a[J + 4]),
+          [a5] "+v"(a[J + 5]), [a6] "+v"(a[J + 6]), [a7] "+v"(a[J + 7])
+        : [x] "v"(x), [m] "v"(m), [j0] "n"(J), [j1] "n"(J + 1), [j2] "n"(J + 2), [j3] "n"(J + 3), [j4] "n"(J + 4),
+          [j5] "n"(J + 5), [j6] "n"(J + 6), [j7] "n"(J + 7));
+    fmac_cols<J + 8, N - 8>(a, x, m);
+  } else if constexpr (N >= 4) {
+    asm("s_nop 1\n\t" WLC_BCAST(0) WLC_BCAST(1) WLC_BCAST(2) WLC_BCAST(3)
+        : [a0] "+v"(a[J]), [a1] "+v"(a[J + 1]), [a2] "+v"(a[J + 2]), [a3] "+v"(a[J + 3])
+        : [x] "v"(x), [m] "v"(m), [j0] "n"(J), [j1] "n"(J + 1), [j2] "n"(J + 2), [j3] "n"(J + 3));
+    fmac_cols<J + 4, N - 4>(a, x, m);
+  } else if constexpr (N == 3) {
+    asm("s_nop 1\n\t" WLC_BCAST(0) WLC_BCAST(1) WLC_BCAST(2)
+        : [a0] "+v"(a[J]), [a1] "+v"(a[J + 1]), [a2] "+v"(a[J + 2])
+        : [x] "v"(x), [m] "v"(m), [j0] "n"(J), [j1] "n"(J + 1), [j2] "n"(J + 2));
+  } else if constexpr (N == 2) {
+    asm("s_nop 1\n\t" WLC_BCAST(0) WLC_BCAST(1) "s_nop 0"
+        : [a0] "+v"(a[J]), [a1] "+v"(a[J + 1])
+        : [x] "v"(x), [m] "v"(m), [j0] "n"(J), [j1] "n"(J + 1));
+  } else if constexpr (N == 1) {
+    asm("s_nop 1\n\t" WLC_BCAST(0) "s_nop 1" : [a0] "+v"(a[J]) : [x] "v"(x), [m] "v"(m), [j0] "n"(J));
   }
-#pragma unroll
-  for (int m = 0; m < NB * NB / 256; ++m) {
-    const int q = tid + 256 * m;
-    Li[q / NB][q % NB] = lv[m];
-    B[q / NB][q % NB] = bv[m];
+}
+#undef WLC_BCAST
+// x[v] += (lane K of the row of x[v]) * m for v <= K / 4: row K of V is zero
+// right of its diagonal
+#define WLC_BCAST(v) "v_fmac_f64_dpp %[x" #v "], %[x" #v "], %[m] row_newbcast:%[k] row_mask:0xf bank_mask:0xf\n\t"
+template <int K>
+__device__ __forceinline__ void fmac_rows(double (&x)[4], double m) {
+  if constexpr (K < 4)
+    asm("s_nop 1\n\t" WLC_BCAST(0) "s_nop 1" : [x0] "+v"(x[0]) : [m] "v"(m), [k] "n"(K));
+  else if constexpr (K < 8)
+    asm("s_nop 1\n\t" WLC_BCAST(0) WLC_BCAST(1) "s_nop 1"
+        : [x0] "+v"(x[0]), [x1] "+v"(x[1])
+        : [m] "v"(m), [k] "n"(K));
+  else if constexpr (K < 12)
+    asm("s_nop 1\n\t" WLC_BCAST(0) WLC_BCAST(1) WLC_BCAST(2) "s_nop 1"
+        : [x0] "+v"(x[0]), [x1] "+v"(x[1]), [x2] "+v"(x[2])
+        : [m] "v"(m), [k] "n"(K));
+  else
+    asm("s_nop 1\n\t" WLC_BCAST(0) WLC_BCAST(1) WLC_BCAST(2) WLC_BCAST(3) "s_nop 1"
+        : [x0] "+v"(x[0]), [x1] "+v"(x[1]), [x2] "+v"(x[2]), [x3] "+v"(x[3])
+        : [m] "v"(m), [k] "n"(K));
+}
+#undef WLC_BCAST
+
+// Column K of a 16 x 16 factorisation A = L L^T: lane 16 g + r of every group g
+// holds row r (a[c] = A[r][c]; entries right of the diagonal take harmless
+// updates that are never read) and the columns g + 4 v of row r of V, L^-1
+// but for the scaling of its rows, by forward substitution in the same pass
+// (V = I at the start); own collects row r's pivot.  The pivot and the column's
+// entries reach the lanes by row broadcasts, so a column is one chain of
+// registers: broadcast, 1 / sqrt, scale, update.  What follows from a pivot
+// that is not positive is not used.
+template <int K>
+__device__ __forceinline__ void factor_col(double (&a)[RB], double (&x)[4], double &own, int r) {
+  const double d = row_bcast<K>(a[K]);
+  const double y = rsqrt_full(d);
+  a[K] *= y;
+  fmac_cols<K + 1, RB - 1 - K>(a, a[K], -a[K]);
+  own = r == K ? d : own;
+  if constexpr (K + 1 < RB) {
+    fmac_rows<K>(x, (r > K ? -a[K] : 0.0) * y);
+    factor_col<K + 1>(a, x, own, r);
   }
+}
+
+// Factor the diagonal tile t by one wavefront.  row[] = row r of L (junk right
+// of the diagonal), the result L^-1 in tile layout.  sh: 16 x 18 doubles of
+// this wavefront's own.
+__device__ __forceinline__ f64x4 factor_tile(const f64x4 &t, double *sh, int lane, double (&row)[RB], bool &bad) {
+  const int r = lane & 15, g = lane >> 4;
+  constexpr int P = RB + 2;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) sh[r * P + g + 4 * v] = t[v];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+  for (int q = 0; q < RB / 2; ++q) {
+    const double2 w = *reinterpret_cast<const double2 *>(&sh[r * P + 2 * q]);
+    row[2 * q] = w.x;
+    row[2 * q + 1] = w.y;
+  }
+  double x[4], own = 1.0;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) x[v] = r == g + 4 * v ? 1.0 : 0.0;
+  factor_col<0>(row, x, own, r);
+  // the rows are complete here: later selections among them must not pull the
+  // arithmetic that makes them behind branches of their own
+#pragma unroll
+  for (int c = 0; c < RB; ++c) asm volatile("" : "+v"(row[c]));
+  bad |= !(own > 0.0);
+  const double ys = rsqrt_full(own);
+  return f64x4{x[0] * ys, x[1] * ys, x[2] * ys, x[3] * ys};
+}
+
+// A 128 x 128 diagonal block: the 36 tiles of its lower triangle at diag_at,
+// first as the matrix has them and in the end as L (off the diagonal packed; on
+// it rows with their 16-byte chunks exchanged by diag_row), the inverse of the
+// current diagonal tile, and a scratch row block.
+struct DiagLds {
+  double tile[PACK_DIAG];
+  double inv[TILE];
+  double row[RB * (RB + 2)];
+};
+__device__ __forceinline__ int diag_row(int r, int c) { return r * RB + 2 * ((c >> 1) ^ (r & 7)) + (c & 1); }
+// place of (row r, column c) of a tile in its packed form
+__device__ __forceinline__ int packed_at(int r, int c) { return (c >> 3) * 128 + 2 * (16 * (c & 3) + r) + ((c >> 2) & 1); }
+
+// The row blocks of wavefront W: 1 and 0 for the one that walks down the
+// diagonal, (7, 2), (6, 3), (5, 4) for the others, which have the same number of
+// tiles to update at every column (9, 7, 5, ... in all).
+template <int W>
+struct DiagRows {
+  static constexpr int R0 = W == 0 ? 1 : NT - W, R1 = W == 0 ? 0 : W + 1;
+  f64x4 a[R0 + 1], b[R1 + 1];
+};
+
+// Start the copies of row block rb (column blocks 0 .. rb) of the jb x jb block
+// at j0 straight into LDS, eight rows of 128 B each, in the order of diag_row:
+// lane l copies row l / 8 and the 16-byte chunk that belongs into its slot.
+// The descriptor ends at the block's last row, and columns are clamped to it:
+// rows and columns from jb on hold something or zero.
+template <int RBK>
+__device__ __forceinline__ void diag_copy(DiagLds &S, const double *__restrict__ Wm, int64_t ld, int64_t j0, int jb,
+                                          int lane) {
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)(Wm + j0 * ld + j0), 0, (int)(((jb - 1) * ld + ((jb + 1) & ~1)) * 8), 0x00020000);
+#pragma unroll
+  for (int t = 0; t <= RBK; ++t)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r = 8 * h + (lane >> 3);
+      const int c = min(t * RB + 2 * ((lane & 7) ^ (r & 7)), (jb - 1) & ~1);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rs, (__attribute__((address_space(3))) void *)(S.tile + diag_at(RBK, t) + h * 8 * RB), 16,
+          (uint32_t)(((RBK * RB + r) * ld + c) * 8), 0, 0, 0);
+    }
+}
+
+// acc += the row block as diag_copy left it: the mirror image above the
+// diagonal, the identity (and no acc) from jb on.
+template <int RBK>
+__device__ __forceinline__ void diag_add(const DiagLds &S, int jb, int lane, f64x4 (&acc)[RBK + 1]) {
+  const int r = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int t = 0; t <= RBK; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int c = g + 4 * v, i = RBK * RB + r, j = t * RB + c;
+      const int hi = t == RBK ? max(r, c) : r, lo = t == RBK ? min(r, c) : c;
+      const double x = S.tile[diag_at(RBK, t) + diag_row(hi, lo)] + acc[t][v];
+      acc[t][v] = max(i, j) < jb ? x : i == j ? 1.0 : 0.0;
+    }
+}
+
+// Barrier over LDS alone: global stores stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// A wavefront's row blocks of the diagonal block at r0, less (UPDATE) X X^T over
+// the first 128 rows of the panel just solved, a 16-deep step's tiles read from
+// the L2 while the one before is multiplied.
+template <int W, bool UPDATE>
+__device__ __forceinline__ void diag_load(DiagLds &S, const double *__restrict__ Wm, int64_t ld, int64_t r0, int jb,
+                                          const double *__restrict__ rows_pack, int64_t n_blk, int lane,
+                                          DiagRows<W> &T) {
+  constexpr int R0 = DiagRows<W>::R0, R1 = DiagRows<W>::R1;
+#pragma unroll
+  for (int t = 0; t <= R0; ++t) T.a[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int t = 0; t <= R1; ++t) T.b[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+  if constexpr (UPDATE) {
+    f64x4 x[2][R0 + 1];
+    auto read = [&](f64x4(&d)[R0 + 1], int s) {
+#pragma unroll
+      for (int t = 0; t <= R0; ++t) d[t] = get_tile(rows_pack + min((int64_t)t, n_blk - 1) * PACK_ROW + s * TILE, lane);
+    };
+    auto mul = [&](const f64x4(&d)[R0 + 1]) {
+#pragma unroll
+      for (int t = 0; t <= R0; ++t) T.a[t] = tile_fms(d[t], d[R0], T.a[t]);
+#pragma unroll
+      for (int t = 0; t <= R1; ++t) T.b[t] = tile_fms(d[t], d[R1], T.b[t]);
+    };
+    read(x[0], 0);
+    diag_copy<R0>(S, Wm, ld, r0, jb, lane);
+    diag_copy<R1>(S, Wm, ld, r0, jb, lane);
+#pragma unroll 1
+    for (int s = 0; s < NT; s += 2) {
+      read(x[1], s + 1);
+      mul(x[0]);
+      read(x[0], min(s + 2, NT - 1));
+      mul(x[1]);
+    }
+  } else {
+    diag_copy<R0>(S, Wm, ld, r0, jb, lane);
+    diag_copy<R1>(S, Wm, ld, r0, jb, lane);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's copies
+  diag_add<R0>(S, jb, lane, T.a);
+  diag_add<R1>(S, jb, lane, T.b);
+}
+
+// Factorisation of a diagonal block, right-looking over its eight column blocks.
+// Wavefront 0 walks down the diagonal: it factors and inverts tile (j, j), then
+// multiplies tile (j + 1, j) by the inverse and updates tile (j + 1, j + 1),
+// while the others, their tiles in registers, apply column j - 1, hand tiles
+// (j + 1, j) and (j + 1, j + 1) over, and multiply their tiles of column j by the
+// inverse.  Two barriers per column.
+//
+// Bound by wavefront 0's chain of 128 pivots (broadcast, estimate and
+// refinement of 1 / sqrt, scaling, the next column's update: 160 cycles each)
+// and the eight hand-overs between tiles (1600 cycles each): 17 us, where a
+// workgroup-wide 64 x 64 factorisation with one barrier per column took 28 us
+// and had to run twice.  Its loop is not unrolled, so that one copy of the code,
+// still in the instruction cache, runs all eight columns.
+__device__ __forceinline__ void diag_walk(DiagLds &S, const DiagRows<0> &T, int lane, double *__restrict__ pack,
+                                          int *__restrict__ flag) {
+  const int r = lane & 15, g = lane >> 4;
+  const f64x4 z = f64x4{0.0, 0.0, 0.0, 0.0};
+  bool bad = false;
+  put_tile(S.tile + diag_at(1, 0), lane, T.a[0]);
+  put_tile(S.tile + diag_at(1, 1), lane, T.a[1]);
+  f64x4 next = T.b[0];
+#pragma unroll 1
+  for (int j = 0; j < NT; ++j) {
+    double row[RB];
+    const f64x4 inv = factor_tile(next, S.row, lane, row, bad);
+    put_tile(S.inv, lane, inv);
+    put_tile(pack + diag_at(j, j), lane, inv);
+    lds_barrier();
+    const int j1 = min(j + 1, NT - 1);
+    double *dst = S.tile + diag_at(j1, j), *own = S.tile + diag_at(j, j);
+    const f64x4 t = get_tile(S.tile + diag_at(j1, j1), lane), b = get_tile(dst, lane);
+    const f64x4 x = tile_fma(inv, b, z);
+    // the rows of the diagonal tile go to LDS under the products, four columns
+    // from each lane group
+    double o[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double c0 = row[q], c1 = row[4 + q], c2 = row[8 + q], c3 = row[12 + q];
+      const double lo = g & 1 ? c1 : c0, hi = g & 1 ? c3 : c2;
+      o[q] = g & 2 ? hi : lo;
+    }
+    *reinterpret_cast<double2 *>(own + diag_row(r, 4 * g)) = make_double2(o[0], o[1]);
+    *reinterpret_cast<double2 *>(own + diag_row(r, 4 * g + 2)) = make_double2(o[2], o[3]);
+    if (j + 1 < NT) put_tile(dst, lane, x);
+    next = tile_fms(x, x, t);
+    lds_barrier();
+  }
+  if (bad) atomicOr(flag, 1);
+}
+
+template <int W>
+__device__ __forceinline__ void diag_follow(DiagLds &S, DiagRows<W> &T, int lane) {
+  constexpr int R0 = DiagRows<W>::R0, R1 = DiagRows<W>::R1;  // R0 > R1
+  const f64x4 z = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    if (j > 0) {
+      // column j - 1, but for tile (j, j), which wavefront 0 has
+#pragma unroll
+      for (int t = j; t <= R0; ++t) {
+        if (R0 > j) {
+          const f64x4 l = t == R0 ? T.a[j - 1] : get_tile(S.tile + diag_at(t, j - 1), lane);
+          T.a[t] = tile_fms(l, T.a[j - 1], T.a[t]);
+          if (R1 > j && t <= R1) T.b[t] = tile_fms(l, T.b[j - 1 < R1 ? j - 1 : 0], T.b[t <= R1 ? t : 0]);
+        }
+      }
+    }
+    if (R0 == j + 1) {
+      put_tile(S.tile + diag_at(R0, R0 - 1), lane, T.a[R0 - 1]);
+      put_tile(S.tile + diag_at(R0, R0), lane, T.a[R0]);
+    }
+    if (R1 == j + 1) {
+      put_tile(S.tile + diag_at(R1, R1 - 1), lane, T.b[R1 - 1]);
+      put_tile(S.tile + diag_at(R1, R1), lane, T.b[R1]);
+    }
+    lds_barrier();
+    if (R0 > j + 1) {
+      const f64x4 inv = get_tile(S.inv, lane);
+      T.a[j < R0 ? j : 0] = tile_fma(inv, T.a[j < R0 ? j : 0], z);
+      put_tile(S.tile + diag_at(R0, j < R0 ? j : 0), lane, T.a[j < R0 ? j : 0]);
+      if (R1 > j + 1) {
+        T.b[j < R1 ? j : 0] = tile_fma(inv, T.b[j < R1 ? j : 0], z);
+        put_tile(S.tile + diag_at(R1, j < R1 ? j : 0), lane, T.b[j < R1 ? j : 0]);
+      }
+    }
+    lds_barrier();
+  }
+}
+
+template <bool UPDATE>
+__device__ __forceinline__ void diag_block(DiagLds &S, double *__restrict__ Wm, int64_t ld, int64_t j0, int jb,
+                                           const double *__restrict__ rows_pack, int64_t n_blk, int w, int lane,
+                                           double *__restrict__ pack, int *__restrict__ flag) {
+  if (w == 0) {
+    DiagRows<0> T;
+    diag_load<0, UPDATE>(S, Wm, ld, j0, jb, rows_pack, n_blk, lane, T);
+    diag_walk(S, T, lane, pack, flag);
+  } else if (w == 1) {
+    DiagRows<1> T;
+    diag_load<1, UPDATE>(S, Wm, ld, j0, jb, rows_pack, n_blk, lane, T);
+    diag_follow<1>(S, T, lane);
+  } else if (w == 2) {
+    DiagRows<2> T;
+    diag_load<2, UPDATE>(S, Wm, ld, j0, jb, rows_pack, n_blk, lane, T);
+    diag_follow<2>(S, T, lane);
+  } else {
+    DiagRows<3> T;
+    diag_load<3, UPDATE>(S, Wm, ld, j0, jb, rows_pack, n_blk, lane, T);
+    diag_follow<3>(S, T, lane);
+  }
+  // L to the matrix, eight rows of 128 B per store, and its tiles off the
+  // diagonal, packed, to pack: nine tiles per wavefront
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    const int rb = q <= w ? w : NT - 1 - w, t = q <= w ? q : q - w - 1;
+    const double *src = S.tile + diag_at(rb, t);
+    if (t < rb) put_tile(pack + diag_at(rb, t), lane, get_tile(src, lane));
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r = 8 * h + (lane >> 3), c = 2 * (lane & 7), i = rb * RB + r, j = t * RB + c;
+      double2 o;
+      if (t < rb) {
+        o = make_double2(src[packed_at(r, c)], src[packed_at(r, c + 1)]);
+      } else {
+        o = *reinterpret_cast<const double2 *>(src + diag_row(r, c));
+      }
+      // a pair may reach one column past the diagonal or the block: that entry
+      // of the row is above the diagonal and never read
+      if (i < jb && j <= i) *reinterpret_cast<double2 *>(Wm + (j0 + i) * ld + j0 + j) = o;
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void k_diag(double *__restrict__ Wm, int64_t ld, int64_t j0, int jb,
+                                              double *__restrict__ pack, int *__restrict__ flag) {
+  __shared__ __attribute__((aligned(16))) DiagLds S;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  diag_block<false>(S, Wm, ld, j0, jb, nullptr, 1, w, lane, pack, flag);
+}
+
+// Panel solve X = B L^-T of the rows below a diagonal block: 64 rows per
+// workgroup, 16 per wavefront, forward substitution over the eight column
+// blocks entirely in registers.  The packed diagonal block (72 KB) and the rows
+// themselves (1 KB per row and load, 16 KB per wavefront) are copied straight
+// into LDS, the 16-byte chunk c of row r at slot c ^ r, from where the tiles
+// are read free of bank conflicts; X goes back the same way.  X goes to the
+// matrix and, packed, to rows_pack for the trailing update.
+//
+// Bound at up to 256 workgroups by its start: launch, 136 KB into each CU's LDS
+// and one wavefront's 144 products (4 us): 10 us at 800 rows, 12 at 4500 (15.8
+// with 8-byte gathers of 16 rows a load).
+__global__ __launch_bounds__(256) void k_solve(double *__restrict__ Wm, int64_t ld, int64_t j0, int jb, int64_t rows,
+                                               const double *__restrict__ pack, double *__restrict__ rows_pack) {
+  __shared__ __attribute__((aligned(16))) double lp[PACK_DIAG];
+  __shared__ __attribute__((aligned(16))) double lb[4 * RB * NB];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, g = lane >> 4;
+  const int64_t blk = (int64_t)blockIdx.x * 4 + w;  // 16-row block below the diagonal block
+  const int64_t i0 = j0 + jb + blk * RB;
+  double *B = Wm + i0 * ld + j0, *sb = lb + w * RB * NB;
+  // rows past the matrix read as zero: the descriptor ends at the last one
+  const int64_t nr = min((int64_t)RB, rows - i0);
+  const __amdgpu_buffer_rsrc_t rb =
+      __builtin_amdgcn_make_buffer_rsrc((void *)B, 0, nr > 0 ? (int)(((nr - 1) * ld + min((int64_t)NB, ld - j0)) * 8) : 0, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void *)pack, 0, PACK_DIAG * 8, 0x00020000);
+#pragma unroll
+  for (int q = 0; q < RB; ++q)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (__attribute__((address_space(3))) void *)(sb + q * NB), 16,
+                                             (uint32_t)(q * ld * 8 + 16 * (lane ^ q)), 0, 0, 0);
+#pragma unroll
+  for (int q = 0; q < PACK_DIAG / 512; ++q)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rp, (__attribute__((address_space(3))) void *)(lp + (q * 4 + w) * 128),
+                                             16, (uint32_t)(((q * 4 + w) * 128 + 2 * lane) * 8), 0, 0, 0);
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's copies into LDS
   __syncthreads();
-  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-  f64x4 acc[2][2];
+  f64x4 T[NT];
+  const int at = r * NB + (g & 1);
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int kk = 0; kk < NB; kk += 4) {
-    const int kc = kk + (lane >> 4);
-    double a[2], b[2];
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-      a[blk] = B[wr + blk * 16 + (lane & 15)][kc];
-      b[blk] = Li[wc + blk * 16 + (lane & 15)][kc];  // (L^-T)[k][j] = Linv[j][k]
+    for (int v = 0; v < 4; ++v) {
+      const double x = sb[at + 2 * ((8 * t + 2 * v + (g >> 1)) ^ r)];
+      T[t][v] = t * RB + g + 4 * v < jb ? x : 0.0;
     }
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+  for (int j = 0; j < NT; ++j) {
+    T[j] = tile_fma(get_tile(lp + diag_at(j, j), lane), T[j], f64x4{0.0, 0.0, 0.0, 0.0});
 #pragma unroll
-      for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x], b[y], acc[x][y], 0, 0, 0);
+    for (int t = j + 1; t < NT; ++t) T[t] = tile_fms(get_tile(lp + diag_at(t, j), lane), T[j], T[t]);
   }
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+  for (int t = 0; t < NT; ++t) {
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
+    for (int v = 0; v < 4; ++v) sb[at + 2 * ((8 * t + 2 * v + (g >> 1)) ^ r)] = T[t][v];
+    if (rows_pack) put_tile(rows_pack + blk * PACK_ROW + t * TILE, lane, T[t]);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  // an odd jb lets a pair reach one column past the block: the corner entry of
+  // the bordered matrix, which nothing reads
+#pragma unroll
+  for (int q = 0; q < RB; ++q)
+    if (q < nr && 2 * lane < jb)
+      *reinterpret_cast<double2 *>(B + q * ld + 2 * lane) = *reinterpret_cast<const double2 *>(sb + q * NB + 2 * (lane ^ q));
+}
+
+// Trailing update W[i][j] -= sum_k X[i][k] X[j][k] over one solved panel (k = 128)
+// for i in [r0, rows), j in [r0, c1), i >= j, from the packed X: a workgroup
+// takes a tile of 32 S rows and columns (four wavefronts, each S x S tiles of
+// 16), operands straight from the L2 into registers (every load of a wavefront
+// is 1 KB, half a 16-deep step ahead), no LDS and no barrier.  Workgroup 0
+// instead updates the next panel's diagonal block and factors it, so that the
+// factorisation's serial chain runs beside the update.
+//
+// Up to about 3000 rows workgroup 0 sets the time (31 us: 13 for its update,
+// 17 for the factorisation); beyond, the reads and writes of W, 16 bytes per
+// 256 flops, and the matrix cores about equally.
+template <int S>
+__global__ __launch_bounds__(256, 2) void k_trail(double *__restrict__ Wm, int64_t ld, int64_t r0, int64_t rows,
+                                                  int64_t c1, const double *__restrict__ rows_pack, int64_t n_blk,
+                                                  int64_t tcols, double *__restrict__ pack, int *__restrict__ flag) {
+  __shared__ __attribute__((aligned(16))) DiagLds D;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 15, g = lane >> 4;
+  if (blockIdx.x == 0) {
+    diag_block<true>(D, Wm, ld, r0, (int)min((int64_t)NB, c1 - r0), rows_pack, n_blk, w, lane, pack, flag);
+    return;
+  }
+  // tile (ti, tj) of 2 S x 2 S 16-blocks on the lower triangle, tj < tcols
+  const int64_t q = blockIdx.x - 1;
+  int64_t ti, tj;
+  const int64_t tri = tcols * (tcols + 1) / 2;
+  if (q < tri) {
+    ti = (int64_t)((sqrt(8.0 * (double)q + 1.0) - 1.0) * 0.5);
+    while ((ti + 1) * (ti + 2) / 2 <= q) ++ti;
+    while (ti * (ti + 1) / 2 > q) --ti;
+    tj = q - ti * (ti + 1) / 2;
+  } else {
+    ti = tcols + (q - tri) / tcols;
+    tj = (q - tri) % tcols;
+  }
+  const int64_t ib = ti * 2 * S + (w >> 1) * S, jb0 = tj * 2 * S + (w & 1) * S;  // first 16-blocks
+  const int64_t ilim = (rows - r0 + RB - 1) / RB, jlim = (c1 - r0 + RB - 1) / RB;
+  const int64_t own = min((int64_t)NB, c1 - r0);  // rows of the next diagonal block (workgroup 0's)
+  // whole wavefront outside the matrix, above the diagonal, or inside the
+  // next diagonal block
+  if (ib >= ilim || jb0 >= jlim || jb0 > ib + S - 1 || (ib + S) * RB <= own) return;
+  const double *pa[S], *pb[S];
+#pragma unroll
+  for (int x = 0; x < S; ++x) {
+    pa[x] = rows_pack + min(ib + x, n_blk - 1) * PACK_ROW + 2 * lane;
+    pb[x] = rows_pack + min(jb0 + x, n_blk - 1) * PACK_ROW + 2 * lane;
+  }
+  // accumulator of rows x columns: element v of lane l is row g + 4 v, column
+  // l % 16
+  f64x4 acc[S][S];
+#pragma unroll
+  for (int x = 0; x < S; ++x)
+#pragma unroll
+    for (int y = 0; y < S; ++y)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int i = wr + x * 16 + (lane >> 4) + 4 * v;
-        const int c = wc + y * 16 + (lane & 15);
-        if (rb + i < r1 && c < jb) Wm[(rb + i) * ld + j0 + c] = acc[x][y][v];
+        const int64_t i = min(r0 + (ib + x) * RB + g + 4 * v, rows - 1);
+        const int64_t j = min(r0 + (jb0 + y) * RB + r, c1 - 1);
+        acc[x][y][v] = Wm[i * ld + min(i, j)];
+      }
+  double2 a[2][S], b[2][S];
+  auto load = [&](int h, int st) {  // half step st: two of the four products of a 16-deep step
+#pragma unroll
+    for (int x = 0; x < S; ++x) {
+      a[h][x] = *reinterpret_cast<const double2 *>(pa[x] + st * 128);
+      b[h][x] = *reinterpret_cast<const double2 *>(pb[x] + st * 128);
+    }
+  };
+  auto mul = [&](int h) {
+#pragma unroll
+    for (int x = 0; x < S; ++x)
+#pragma unroll
+      for (int y = 0; y < S; ++y)
+        acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[h][x].x, b[h][y].x, acc[x][y], 0, 0, 0);
+#pragma unroll
+    for (int x = 0; x < S; ++x)
+#pragma unroll
+      for (int y = 0; y < S; ++y)
+        acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[h][x].y, b[h][y].y, acc[x][y], 0, 0, 0);
+  };
+  load(0, 0);
+#pragma unroll
+  for (int st = 0; st < 2 * NT; st += 2) {
+    load(1, st + 1);
+    mul(0);
+    if (st + 2 < 2 * NT) load(0, st + 2);
+    mul(1);
+  }
+#pragma unroll
+  for (int x = 0; x < S; ++x)
+#pragma unroll
+    for (int y = 0; y < S; ++y)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t i = r0 + (ib + x) * RB + g + 4 * v;
+        const int64_t j = r0 + (jb0 + y) * RB + r;
+        if (i < rows && j < c1 && i >= j && i - r0 >= own) Wm[i * ld + j] = acc[x][y][v];
       }
 }
 
-// Factor columns [0, n) of M (n + 1 rows).  scratch: the 64 x 64 inverse of
-// the current diagonal block, then the split-k buffer of the panel updates.
-// The pivot flag is checked by the caller after synchronisation.
+// The trailing update of rows [r0, rows), columns [r0, c1) with the panel just
+// solved, and the factorisation of the next diagonal block.
+static void launch_trail(double *Wm, int64_t ld, int64_t r0, int64_t rows, int64_t c1, const double *rows_pack,
+                         int64_t n_blk, double *pack, int *flag, hipStream_t s, KernelProbe *probe) {
+  const bool timed = probe && probe->ev && probe->count < probe->cap;
+  if (probe) {
+    const double cols = (double)(c1 - r0);
+    probe->flops += 2.0 * NB * (cols * (double)rows - (double)(r0 + c1 - 1) * cols / 2.0);  // entries with i >= j
+    ++probe->launches;
+  }
+  if (timed) (void)hipEventRecord(probe->ev[2 * probe->count], s);
+  auto tiles_of = [&](int64_t t) {
+    const int64_t tc = (c1 - r0 + t - 1) / t, tr = (rows - r0 + t - 1) / t;
+    return tc * (tc + 1) / 2 + (tr - tc) * tc;
+  };
+  // 64 x 64 tiles until 128 x 128 ones fill the chip one and a half times over
+  // (two workgroups per CU): n = 4550 2.05 ms, from 256 tiles on 2.13
+  if (tiles_of(128) >= 768)
+    hipLaunchKernelGGL(k_trail<4>, dim3((unsigned)(1 + tiles_of(128))), dim3(256), 0, s, Wm, ld, r0, rows, c1,
+                       rows_pack, n_blk, (c1 - r0 + 127) / 128, pack, flag);
+  else
+    hipLaunchKernelGGL(k_trail<2>, dim3((unsigned)(1 + tiles_of(64))), dim3(256), 0, s, Wm, ld, r0, rows, c1,
+                       rows_pack, n_blk, (c1 - r0 + 63) / 64, pack, flag);
+  if (timed) (void)hipEventRecord(probe->ev[2 * probe->count++ + 1], s);
+}
+
+// Factor columns [0, n) of M (n + 1 rows).  scratch: the packed diagonal block,
+// then the packed rows of the current panel, which share their space with the
+// split-k buffer of the long panel updates.  The pivot flag is checked by the
+// caller after synchronisation.
 int chol_factor(double *Wm, int64_t n, int64_t ld, double *scratch, int *flag, hipStream_t s,
                 KernelProbe *probe) {
   const int64_t rows = n + 1;
-  double *Linv = scratch;
-  double *part = scratch + NB * NB;
-  for (int64_t J0 = 0; J0 < n; J0 += NB_OUT) {
-    const int64_t Jend = std::min<int64_t>(J0 + NB_OUT, n);
+  double *pack = scratch;
+  double *part = scratch + PACK_DIAG;
+  const int64_t part_rows = (int64_t)(chol_scratch_bytes(n) / 8 - PACK_DIAG) / NB_OUT;
+  const int64_t outer = n <= RIGHT_MAX ? n : NB_OUT;
+  for (int64_t J0 = 0; J0 < n; J0 += outer) {
+    const int64_t Jend = std::min<int64_t>(J0 + outer, n);
     // everything left of the panel, in one product over k = [0, J0)
-    launch_update2(Wm, ld, J0, rows, Jend, 0, J0, part, chol_part_rows(n), s, probe);
+    launch_update2(Wm, ld, J0, rows, Jend, 0, J0, part, part_rows, s, probe);
     for (int64_t j0 = J0; j0 < Jend; j0 += NB) {
       const int jb = (int)std::min<int64_t>(NB, Jend - j0);
-      hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, s, Wm, ld, j0, jb, Linv, flag);
-      const int64_t r0 = j0 + jb;
-      if (r0 < rows) {
-        const int64_t nblk = (rows - r0 + NB - 1) / NB;
-        hipLaunchKernelGGL(k_trsm, dim3((unsigned)nblk), dim3(256), 0, s, Wm, ld, j0, jb, r0, rows, Linv);
-      }
-      // the rest of this panel with the freshly solved columns
-      launch_update2(Wm, ld, j0 + jb, rows, Jend, j0, j0 + jb, nullptr, 0, s, probe);
+      if (j0 == J0) hipLaunchKernelGGL(k_diag, dim3(1), dim3(256), 0, s, Wm, ld, j0, jb, pack, flag);
+      const int64_t r0 = j0 + jb;  // first row below
+      const bool more = r0 < Jend;
+      const int64_t nblk = (rows - r0 + 63) / 64;
+      hipLaunchKernelGGL(k_solve, dim3((unsigned)nblk), dim3(256), 0, s, Wm, ld, j0, jb, rows, pack,
+                         more ? part : (double *)nullptr);
+      if (more) launch_trail(Wm, ld, r0, rows, Jend, part, 4 * nblk, pack, flag, s, probe);
     }
   }
   return 0;
@@ -261,8 +716,12 @@ int chol_factor(double *Wm, int64_t n, int64_t ld, double *scratch, int *flag, h
 // have k ranges below n, so they take at most update2_max_slices(n) slices
 // of at most n + 1 rows each; small matrices reserve little.  The reserve
 // never binds the split choice below PART_ROWS, so it does not change it.
-int64_t chol_part_rows(int64_t n) { return std::min<int64_t>(PART_ROWS, update2_max_slices(n) * (n + 1)); }
-size_t chol_scratch_bytes(int64_t n) { return (size_t)NB * NB * 8 + (size_t)chol_part_rows(n) * NB_OUT * 8; }
+static int64_t chol_part_rows(int64_t n) { return std::min<int64_t>(PART_ROWS, update2_max_slices(n) * (n + 1)); }
+size_t chol_scratch_bytes(int64_t n) {
+  const size_t split = (size_t)64 * 64 * 8 + (size_t)chol_part_rows(n) * NB_OUT * 8;
+  const size_t packed = (size_t)PACK_DIAG * 8 + (n > NB ? (size_t)(n + 64) * NB * 8 : 0);
+  return std::max(split, packed);
+}
 
 // ------------------------------------------------------------- y^T y
 __global__ void k_sumsq_row(const double *__restrict__ Wm, int64_t n, int64_t ld, double *__restrict__ out) {
