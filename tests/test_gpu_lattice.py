@@ -90,3 +90,31 @@ def test_euclid5_triangles_continuum(counts):
         assert abs(tris[q] / cont - 1.0) < CONT_TOL, (i, j, k, tris[q], cont)
         checked += 1
     assert checked >= 11
+
+
+# (n_ell, ell_min, ell_max, f_sky): radii of a few rows (one workgroup, mostly
+# outside the bins), just past one workgroup's 64 x 256 rows, and past 16000
+# (64-bit intermediates), where only the bins that the oracle can count pair by
+# pair are compared
+@pytest.mark.parametrize("shape", [(3, 10.0, 40.0, 0.02), (4, 10.0, 200.0, 0.36), (5, 20.0, 420.0, 0.37),
+                                   (6, 20.0, 60000.0, 0.36)], ids=lambda s: "%d-%g" % (s[0], s[2]))
+def test_lattice_row_pairs(shape):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_1812_07437_amd import wlcov as wl
+    n_ell, lo, hi, f_sky = shape
+    _say("case lattice row pairs %s" % (shape,))
+    t = synth.make_tables("tiny", n_ell=n_ell, ell_min=lo, ell_max=hi, n_chi=4, n_m=4, f_sky=f_sky)
+    prob = wl.Problem(t.cfg, t.arrays(), precision="fp64")
+    modes, tris = (x.cpu().tolist() for x in prob.lattice_counts())
+    prob.close()
+    o = oracle.Oracle(t)
+    thr = oracle.lattice_thresholds(o.edges, f_sky)
+    checked = 0
+    for q, (i, j, k, _) in enumerate(o.tris):
+        if modes[i] * modes[j] > 2e8:
+            continue
+        assert tris[q] == oracle.lattice_triangles(thr, i, j, k), (i, j, k)
+        checked += 1
+    assert checked >= 2
