@@ -292,10 +292,11 @@ int wlc_snr2_lmax(wlc_plan plan, const void *C, const int32_t *row_exp2, const d
  * observables D^_a = S_a . d (eq. NewObs), their (S/N)^2_a = D^_a^2 /
  * lambda_a (eq. SNperEign) and the cumulative curve (eq. CumulSN).
  * The eigenvalues span tens of decades, so they come from one-sided Jacobi
- * on the graded Cholesky factor (C_true = G^T G, G = L^T 2^-t with L the
- * FP64 Cholesky factor of the scaled C), which keeps relative accuracy; the
- * rotations run in blocks of 32 columns on FP64 MFMA until no pair of
- * columns has |cos| above 8 sqrt(n_pad) eps, at most 40 sweeps.
+ * on the graded Cholesky factor (C_true = W W^T, W = 2^-t L with L the FP64
+ * Cholesky factor of the scaled C, its rows taken in decreasing order of the
+ * diagonal of C_true), which keeps relative accuracy; the rotations run in
+ * blocks of 32 columns on FP64 MFMA until no pair of columns has |cos| above
+ * 8 sqrt(n_pad) eps, at most 40 sweeps.
  * Inputs as wlc_snr2 (DEVICE C, row_exp2, d).  Outputs (HOST, n_data each):
  *   lambda     eigenvalues of C_true, ascending;
  *   snr2_mode  (S/N)^2 of each mode, in the order of lambda;

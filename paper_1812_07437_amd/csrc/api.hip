@@ -153,21 +153,16 @@ size_t snr_ws_bytes(const Plan &p) {
          align_up((size_t)n * 4, 256) + 3 * align_up((size_t)p.n_ell * 8, 256);
 }
 
-// PCA workspace: the S/N workspace (bordered Cholesky), then X and V
+// PCA workspace: the S/N workspace (bordered Cholesky), then X
 // [n_pad][n_pad], y [n_pad], per-mode arrays and the convergence word.
 static int64_t pca_pad(const Plan &p) { return round_up(p.n_out, 64); }
-// Jacobi sweeps on each pair's 64 x 64 Gram matrix per round: one sweep
-// measured as fast in outer sweeps as full diagonalisation, at a third of
-// the cost.
-constexpr int PCA_INNER = 1;
-
 size_t pca_ws_bytes(const Plan &p) {
   const int64_t np = pca_pad(p), n = p.n_out;
   if (np > 65535) return 0;
   const size_t pairs = (size_t)np / 64;
-  return align_up(snr_ws_bytes(p), 256) + 2 * align_up((size_t)np * np * 8, 256) + align_up((size_t)np * 8, 256) +
+  return align_up(snr_ws_bytes(p), 256) + align_up((size_t)np * np * 8, 256) + align_up((size_t)np * 8, 256) +
          5 * align_up((size_t)n * 8, 256) + 2 * align_up((size_t)n * 4, 256) + 256 +
-         align_up(pairs * pca_slices(np) * 64 * 64 * 8, 256) + align_up(pairs * 64 * 64 * 8, 256) +
+         align_up(pairs * pca_slices(np) * PCA_PART * 8, 256) + align_up(pairs * 64 * 64 * 8, 256) +
          align_up(pairs * 4, 256);
 }
 
@@ -556,7 +551,8 @@ int run_enqueue(const Plan &p, const wlc_tables &tb, void *ws, double *d, double
 }
 
 int snr_enqueue(const Plan &p, const void *C, const int32_t *row_exp2, const double *d, void *ws, hipStream_t s,
-                PhaseHooks *hooks, KernelProbe *probe, int32_t **flag_dev, double **out_dev, bool lmax) {
+                PhaseHooks *hooks, KernelProbe *probe, int32_t **flag_dev, double **out_dev, bool lmax,
+                int32_t **by_diag) {
   const int64_t n = p.n_out, ld = snr_ld(n);
   char *base = static_cast<char *>(ws);
   double *Wm = reinterpret_cast<double *>(base);
@@ -583,7 +579,11 @@ int snr_enqueue(const Plan &p, const void *C, const int32_t *row_exp2, const dou
   }
   if (hooks) hooks->begin(WLC_PHASE_SNR_PREP);
   launch_fill_i32(flag, 1, 0, s);
-  launch_chol_prep(C, !prec_f64(p.cfg.precision), row_exp2, d, n, ld, Wm, s, lmax ? perm : nullptr);
+  if (by_diag) {
+    launch_pca_order(C, !prec_f64(p.cfg.precision), row_exp2, n, perm, s);
+    *by_diag = perm;
+  }
+  launch_chol_prep(C, !prec_f64(p.cfg.precision), row_exp2, d, n, ld, Wm, s, lmax || by_diag ? perm : nullptr);
   if (hooks) hooks->end(WLC_PHASE_SNR_PREP);
   if (hooks) hooks->begin(WLC_PHASE_CHOL);
   chol_factor(Wm, n, ld, scratch, flag, s, probe);
@@ -1055,7 +1055,6 @@ int wlc_pca(wlc_plan plan, const void *C, const int32_t *row_exp2, const double 
     return q;
   };
   double *X = reinterpret_cast<double *>(take((size_t)np * np * 8));
-  double *V = reinterpret_cast<double *>(take((size_t)np * np * 8));
   double *y = reinterpret_cast<double *>(take((size_t)np * 8));
   double *lam = reinterpret_cast<double *>(take((size_t)n * 8));
   double *snr = reinterpret_cast<double *>(take((size_t)n * 8));
@@ -1066,28 +1065,28 @@ int wlc_pca(wlc_plan plan, const void *C, const int32_t *row_exp2, const double 
   int32_t *rank_snr = reinterpret_cast<int32_t *>(take((size_t)n * 4));
   double *conv = reinterpret_cast<double *>(take(256));
   const size_t pairs = (size_t)np / 64;
-  double *part = reinterpret_cast<double *>(take(pairs * pca_slices(np) * 64 * 64 * 8));
+  double *part = reinterpret_cast<double *>(take(pairs * pca_slices(np) * PCA_PART * 8));
   double *Qg = reinterpret_cast<double *>(take(pairs * 64 * 64 * 8));
   int32_t *rot = reinterpret_cast<int32_t *>(take(pairs * 4));
-  // the bordered Cholesky: L of the scaled C and y = L^-1 2^t d
-  int32_t *flag = nullptr;
+  // the bordered Cholesky, rows by decreasing diagonal: L of the scaled C and
+  // y = L^-1 2^t d
+  int32_t *flag = nullptr, *perm = nullptr;
   double *unused = nullptr;
-  int rc = snr_enqueue(p, C, row_exp2, d, ws, s, nullptr, nullptr, &flag, &unused);
+  int rc = snr_enqueue(p, C, row_exp2, d, ws, s, nullptr, nullptr, &flag, &unused, false, &perm);
   if (rc) return rc;
   int32_t hflag = 0;
   rc = hip_check(hipMemcpyAsync(&hflag, flag, 4, hipMemcpyDeviceToHost, s), "pca copy");
   if (!rc) rc = hip_check(hipStreamSynchronize(s), "pca sync");
   if (rc) return rc;
   if (hflag) return fail(WLC_ENOTPD, "covariance is not positive definite");
-  double *Vr = S ? V : nullptr;
-  launch_pca_init(reinterpret_cast<const double *>(ws), ld, row_exp2, n, np, X, Vr, y, s);
+  launch_pca_init(reinterpret_cast<const double *>(ws), ld, row_exp2, perm, n, np, X, y, s);
   const double tol = 8.0 * std::sqrt((double)np) * 2.220446049250313e-16;
   const int n_blk = (int)(np / 32);
   int used = 0;
   bool converged = false;
   for (int sweep = 0; sweep < 40 && !converged; ++sweep) {
     launch_fill_i32(reinterpret_cast<int32_t *>(conv), 2, 0, s);
-    for (int r = 0; r < n_blk - 1; ++r) launch_pca_round(X, Vr, np, r, tol, PCA_INNER, conv, part, Qg, rot, s);
+    for (int r = 0; r < n_blk - 1; ++r) launch_pca_round(X, y, np, r, tol, conv, part, Qg, rot, s);
     double hconv = 0.0;
     rc = hip_check(hipMemcpyAsync(&hconv, conv, 8, hipMemcpyDeviceToHost, s), "pca copy");
     if (!rc) rc = hip_check(hipStreamSynchronize(s), "pca sync");
@@ -1097,7 +1096,7 @@ int wlc_pca(wlc_plan plan, const void *C, const int32_t *row_exp2, const double 
   }
   if (sweeps) *sweeps = used;
   if (!converged) return fail(WLC_ENOCONV, "the PCA Jacobi sweeps did not converge");
-  launch_pca_finish(X, y, Vr, n, np, lam, snr, rank_lam, rank_snr, lam_out, snr_out, desc, S, s);
+  launch_pca_finish(X, y, perm, n, np, lam, snr, rank_lam, rank_snr, lam_out, snr_out, desc, S, s);
   rc = hip_check(hipMemcpyAsync(lambda, lam_out, (size_t)n * 8, hipMemcpyDeviceToHost, s), "pca copy");
   if (!rc) rc = hip_check(hipMemcpyAsync(snr2_mode, snr_out, (size_t)n * 8, hipMemcpyDeviceToHost, s), "pca copy");
   if (!rc) rc = hip_check(hipMemcpyAsync(cum_desc, desc, (size_t)n * 8, hipMemcpyDeviceToHost, s), "pca copy");

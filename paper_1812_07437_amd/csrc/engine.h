@@ -51,7 +51,8 @@ int run_enqueue_gram_reduce(const Plan &p, void *ws, hipStream_t s);
 // With lmax, the rows are taken in ell_max order and *out_dev holds the
 // (S/N)^2 of every ell_max cut, one per used ell-bin (wlc_snr2_lmax).
 int snr_enqueue(const Plan &p, const void *C, const int32_t *row_exp2, const double *d, void *ws, hipStream_t s,
-                PhaseHooks *hooks, KernelProbe *probe, int32_t **flag_dev, double **out_dev, bool lmax = false);
+                PhaseHooks *hooks, KernelProbe *probe, int32_t **flag_dev, double **out_dev, bool lmax = false,
+                int32_t **by_diag = nullptr);
 
 // The same (S/N)^2 through the distinct rows, from the run workspace of a
 // completed wlc_run (PAPER tomography only): the bordered Cholesky of

@@ -6,22 +6,29 @@
 // The eigenvalues span tens of decades.  A tridiagonal eigensolver resolves
 // only those above about 1e-16 of the largest, so this path uses one-sided
 // (Hestenes) Jacobi, which keeps relative accuracy on graded matrices
-// (Demmel and Veselic 1992): with C = Delta C^ Delta (Delta = 2^-t, the
-// row scaling of the covariance) and C^ = L L^T from the bordered Cholesky,
-// C = G^T G for G = L^T Delta.  Column rotations G -> G Q make the columns
-// w_a of G Q orthogonal; then lambda_a = |w_a|^2, the eigenvectors are the
-// columns of the accumulated Q, and since d = G^T y (y = L^-1 2^t d, the
-// Cholesky's own forward substitution), D^_a = w_a . y.
+// (Demmel and Veselic 1992): with C = Delta C^ Delta (Delta = 2^-t, the row
+// scaling of the covariance) and C^ = L L^T from the bordered Cholesky,
+// C = W W^T for W = Delta L.  Column rotations W -> W V make the columns w_a
+// orthogonal; then lambda_a = |w_a|^2 and the eigenvectors are w_a / |w_a|, with
+// no rotation accumulated beside W.  Since d = W y (y = L^-1 2^t d, the
+// Cholesky's own forward substitution), D^_a / sqrt(lambda_a) is component a of
+// V^T y: y is rotated along.  The rows are taken in decreasing order of the
+// diagonal of C before the factorisation, so that the columns of W come graded
+// and the rotations start small (Veselic and Hari 1989): 818 rows of the paper's
+// binning converge in 7 sweeps of a plain cyclic Jacobi instead of 11 on the
+// rows of Delta L, with the same accuracy (327 rows against 80-bit arithmetic:
+// 3.3e-13 on the worst of 17 decades of eigenvalues, 3.1e-13 on the rows).
 //
-// Storage: the columns of G are the rows of X (row j = 2^-t_j times row j of
-// L, zero-padded to n_pad), and the columns of Q the rows of V, so every
-// vector the method touches is a contiguous row.  Rows are grouped in blocks
-// of 32; each round pairs all blocks (a round-robin tournament over n_blk =
+// Storage: the columns of W are the rows of X (zero-padded to n_pad), so every
+// vector the method touches is a contiguous row.  Rows are grouped in blocks of
+// 32; each round pairs all blocks (a round-robin tournament over n_blk =
 // n_pad / 32 blocks, n_blk - 1 rounds per sweep); for each pair (p, q) the
 // 64 x 64 Gram matrix of its rows is formed on FP64 MFMA, rotated towards
 // diagonal form by cyclic two-sided Jacobi in LDS (relative accuracy again:
-// rotations are driven by |M_jl| / sqrt(M_jj M_ll)), and the 64 x 64
-// rotation is applied to its rows of X and V on FP64 MFMA.  Sweeps repeat
+// rotations are driven by |M_jl| / sqrt(M_jj M_ll)), and the 64 x 64 rotation is
+// applied to its rows of X on FP64 MFMA.  The first round of a sweep rotates
+// every pair of a 64-row pair of blocks, the others those across the two
+// blocks, so that a sweep rotates every pair of columns once.  Sweeps repeat
 // until no pair has a scaled off-diagonal entry above tol.
 #include <hip/hip_runtime.h>
 
@@ -36,17 +43,58 @@ constexpr int PLD = PR + 1;   // padded LDS row
 // Round-robin tournament: position 0 is fixed, the others rotate by r.
 __device__ __forceinline__ int rr_at(int pos, int r, int n) { return pos == 0 ? 0 : 1 + (pos - 1 + r) % (n - 1); }
 
-// X from the bordered factor Wm (rows 0..n-1: L in the lower triangle, row n:
-// y): X[j][k] = 2^-t_j Wm[j][k] for k <= j < n, else 0; y_pad = row n of Wm;
-// V = I when given.  One block row per blockIdx.y.
-__global__ void k_pca_init(const double *__restrict__ Wm, int64_t ld, const int32_t *__restrict__ t, int64_t n,
-                           int64_t n_pad, double *__restrict__ X, double *__restrict__ V, double *__restrict__ y) {
-  const int64_t j = blockIdx.y;
-  const double sc = j < n ? ldexp(1.0, -t[j]) : 0.0;
-  for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n_pad; k += (int64_t)gridDim.x * blockDim.x) {
-    X[j * n_pad + k] = (j < n && k <= j) ? sc * Wm[j * ld + k] : 0.0;
-    if (V) V[j * n_pad + k] = j == k ? 1.0 : 0.0;
-    if (j == 0) y[k] = k < n ? Wm[n * ld + k] : 0.0;
+// Where a diagonal entry C 2^-2t of C_true stands: its exponent and mantissa,
+// compared one after the other, so that no scale rounds or overflows; entries
+// that are not positive (or no number: the factorisation refuses them later)
+// come last, infinite ones first.
+__device__ __forceinline__ void diag_key(double c, int t, int &e, double &f) {
+  f = frexp(c, &e);
+  e -= 2 * t;
+  if (!(c > 0.0)) { e = INT32_MIN; f = 0.0; }
+  if (c == __builtin_inf()) { e = INT32_MAX; f = 0.0; }
+}
+
+// One wavefront per row: the rank of the row in decreasing order of the
+// diagonal of C_true (ties by index), as the permutation that puts the rows in
+// that order.
+template <typename InT>
+__global__ void k_pca_order(const InT *__restrict__ C, const int32_t *__restrict__ t, int64_t n,
+                            int32_t *__restrict__ perm) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  const int64_t a = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
+  if (a >= n) return;
+  int ea, eb;
+  double fa, fb;
+  diag_key((double)C[a * n + a], t[a], ea, fa);
+  int rank = 0;
+  for (int64_t b = lane; b < n; b += WAVE) {
+    diag_key((double)C[b * n + b], t[b], eb, fb);
+    rank += eb > ea || (eb == ea && (fb > fa || (fb == fa && b < a)));
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) rank += __shfl_xor(rank, o, WAVE);
+  if (lane == 0) perm[rank] = (int32_t)a;
+}
+
+// X from the bordered factor Wm of the ordered rows (rows 0..n-1: L in the lower
+// triangle, row n: y): X[j][k] = 2^-t_k Wm[k][j] for j <= k < n, else 0;
+// y_pad = row n of Wm.  A 64 x 64 block per workgroup, transposed through LDS.
+__global__ __launch_bounds__(256) void k_pca_init(const double *__restrict__ Wm, int64_t ld,
+                                                  const int32_t *__restrict__ t, const int32_t *__restrict__ perm,
+                                                  int64_t n, int64_t n_pad, double *__restrict__ X,
+                                                  double *__restrict__ y) {
+  __shared__ double tile[64][65];
+  const int64_t j0 = (int64_t)blockIdx.y * 64, k0 = (int64_t)blockIdx.x * 64;
+  const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
+  for (int r = r0; r < 64; r += 4) {
+    const int64_t k = k0 + r, j = j0 + c;
+    tile[r][c] = k < n && j <= k ? ldexp(Wm[k * ld + j], -t[perm[k]]) : 0.0;
+  }
+  __syncthreads();
+  for (int r = r0; r < 64; r += 4) X[(j0 + r) * n_pad + k0 + c] = tile[c][r];
+  if (blockIdx.x == 0 && threadIdx.x < 64) {
+    const int64_t j = j0 + threadIdx.x;
+    y[j] = j < n ? Wm[n * ld + j] : 0.0;
   }
 }
 
@@ -56,35 +104,41 @@ __device__ __forceinline__ void atomic_max_nonneg(double *addr, double v) {
 }
 
 // A round is three launches.  (a) k_pca_gram: partial 64 x 64 Gram matrices
-// of each block pair over KS column slices (FP64 MFMA); (b) k_pca_rot, one
+// of each block pair over column slices (FP64 MFMA); (b) k_pca_rot, one
 // workgroup per pair: sum the slices in fixed order, measure the largest
-// scaled off-diagonal entry, and unless it is below tol run Jacobi sweeps on
-// M in LDS and store Q (reordering the rotated columns by norm, as in
-// de Rijk's sorting, was measured to break the convergence of the cyclic
-// tournament here);
-// (c) k_pca_apply: rows of X (and V) <- Q^T rows, 64 columns per workgroup,
-// skipped for pairs that did not rotate.
+// scaled off-diagonal entry, and unless it is below tol rotate M in LDS, store
+// Q and rotate the pair's components of y (reordering the rotated columns by
+// norm, as in de Rijk's sorting, was measured to break the convergence of the
+// cyclic tournament here); (c) k_pca_apply: rows of X <- Q^T rows, skipped for
+// pairs that did not rotate.
 __device__ __forceinline__ int64_t pair_row(int bp, int bq, int j) {
   return j < PB ? (int64_t)bp * PB + j : (int64_t)bq * PB + (j - PB);
 }
 
-// Gram of a pair, with the pair's 64 rows
-// are copied one 64-column chunk ahead into two LDS buffers of [64 rows][64
+constexpr int PART = PCA_PART;
+
+// Gram of a pair.  The pair's 64 rows are copied one 64-column chunk ahead into two LDS buffers of [64 rows][64
 // doubles], unpadded, with the 16-byte chunk s of row l at slot s ^ (l & 15),
 // so the 16 consecutive rows one MFMA operand read touches at one column
 // fall on 16 distinct bank groups.  A wavefront copy fills two rows.
+//
+// Bound at few pairs by the chain of a slice's chunks, at many by reading X: 8 us
+// a round at 832 columns, 16 at 2432 (47 MB); 10.6 and 21 us with the full
+// 64 x 64 square, one quadrant per wavefront.
 __device__ __forceinline__ int gram_slot(int l, int k) { return l * PR + 2 * ((k >> 1) ^ (l & 15)) + (k & 1); }
 
 __global__ __launch_bounds__(256) void k_pca_gram(const double *__restrict__ X, int64_t n_pad, int n_blk, int r,
-                                                    int64_t cols, double *__restrict__ part) {
-  __shared__ __attribute__((aligned(16))) double st0[PR * PR];
-  __shared__ __attribute__((aligned(16))) double st1[PR * PR];
+                                                    double *__restrict__ part) {
+  __shared__ __attribute__((aligned(16))) double st0[2 * PART];
+  __shared__ __attribute__((aligned(16))) double st1[2 * PART];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int pi = blockIdx.x, ks = blockIdx.y;
   const int bp = rr_at(pi, r, n_blk), bq = rr_at(n_blk - 1 - pi, r, n_blk);
   const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-  const int64_t c0 = (int64_t)ks * cols;
-  const int nch = (int)(cols / PR);
+  // this slice's 64-column chunks
+  const int all = (int)(n_pad / PR), first = (int)((int64_t)all * ks / gridDim.y);
+  const int64_t c0 = (int64_t)first * PR;
+  const int nch = (int)((int64_t)all * (ks + 1) / gridDim.y) - first;
   // copy i of this wavefront: rows l0 = 2 (4 i + w) and l0 + 1 of the pair
   // (one 32-row block, so consecutive rows of X), one descriptor per copy
   const double *rows[8];
@@ -104,25 +158,24 @@ __global__ __launch_bounds__(256) void k_pca_gram(const double *__restrict__ X, 
           (int)((c0 + (int64_t)ci * PR) * 8), 0, 0);
     __builtin_amdgcn_sched_barrier(0);
   };
-  f64x4 acc[2][2];
+  // each wavefront sums the ten 16 x 16 tiles of the lower triangle over a
+  // quarter of the chunk's columns: one read per row block and step serves
+  // as both operands
+  f64x4 acc[10];
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
-#pragma unroll
-    for (int z = 0; z < 2; ++z) acc[x][z] = f64x4{0.0, 0.0, 0.0, 0.0};
+  for (int x = 0; x < 10; ++x) acc[x] = f64x4{0.0, 0.0, 0.0, 0.0};
   auto compute = [&](const double *buf) {
 #pragma unroll
-    for (int kk = 0; kk < PR; kk += 4) {
-      const int k = kk + (lane >> 4);
-      double a[2], b[2];
+    for (int kk = 0; kk < PR / 4; kk += 4) {
+      const int k = wave * (PR / 4) + kk + (lane >> 4);
+      double a[4];
 #pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        a[x] = buf[gram_slot(wr + x * 16 + (lane & 15), k)];
-        b[x] = buf[gram_slot(wc + x * 16 + (lane & 15), k)];
-      }
+      for (int x = 0; x < 4; ++x) a[x] = buf[gram_slot(x * 16 + (lane & 15), k)];
 #pragma unroll
-      for (int x = 0; x < 2; ++x)
+      for (int x = 0; x < 4; ++x)
 #pragma unroll
-        for (int z = 0; z < 2; ++z) acc[x][z] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x], b[z], acc[x][z], 0, 0, 0);
+        for (int z = 0; z <= x; ++z)
+          acc[x * (x + 1) / 2 + z] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x], a[z], acc[x * (x + 1) / 2 + z], 0, 0, 0);
     }
   };
   if (nch > 0) issue(0, st0);
@@ -145,172 +198,240 @@ __global__ __launch_bounds__(256) void k_pca_gram(const double *__restrict__ X, 
     __syncthreads();
     compute(st0);
   }
-  // accumulator value v of lane l: row l / 16 + 4 v, column l % 16
-  double *P = part + ((int64_t)pi * gridDim.y + ks) * PR * PR;
+  // the wavefronts' sums in order, through LDS; tile x (x + 1) / 2 + z of the
+  // result is 64 lanes of four values (row l / 16 + 4 v, column l % 16)
+  __syncthreads();
+  double *P = part + ((int64_t)pi * gridDim.y + ks) * PART;
+  double *sum = wave < 2 ? st0 : st1;  // 20 KB per wavefront
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+  for (int x = 0; x < 10; ++x)
 #pragma unroll
-    for (int z = 0; z < 2; ++z)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        P[(wr + x * 16 + (lane >> 4) + 4 * v) * PR + wc + z * 16 + (lane & 15)] = acc[x][z][v];
+    for (int v = 0; v < 4; v += 2)
+      *reinterpret_cast<double2 *>(&sum[(wave & 1) * PART + x * 256 + v * 64 + 2 * lane]) =
+          make_double2(acc[x][v], acc[x][v + 1]);
+  __syncthreads();
+  for (int e = 2 * tid; e < PART; e += 512) {
+    double2 o = *reinterpret_cast<const double2 *>(&st0[e]);
+    const double2 o1 = *reinterpret_cast<const double2 *>(&st0[PART + e]);
+    const double2 o2 = *reinterpret_cast<const double2 *>(&st1[e]), o3 = *reinterpret_cast<const double2 *>(&st1[PART + e]);
+    o.x = ((o.x + o1.x) + o2.x) + o3.x;
+    o.y = ((o.y + o1.y) + o2.y) + o3.y;
+    *reinterpret_cast<double2 *>(&P[e]) = o;
+  }
 }
 
-constexpr int RT = 1024;  // threads of the rotation kernel: one 2 x 2 block each per inner step
+constexpr int RT = 512;       // threads of the rotation kernel
+constexpr int QLD = PR + 2;   // padded row of Q^T (16-byte aligned)
 
-__global__ __launch_bounds__(RT) void k_pca_rot(const double *__restrict__ part, int n_ks, double tol, int max_inner,
-                                                 double *__restrict__ Qg, int32_t *__restrict__ rot,
-                                                 double *__restrict__ conv) {
+// 1 / sqrt(x) for x in the normal range: estimate and one third-order step
+__device__ __forceinline__ double rsqrt_near(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// The rotation that zeroes m = M_jl between a = M_jj and b = M_ll:
+// x_j' = c x_j - s x_l, x_l' = s x_j + c x_l, |angle| <= pi / 4, t = s / c.  With
+// h = sqrt((b - a)^2 + 4 m^2): cos 2 theta = |b - a| / h, c = sqrt((1 + cos) / 2),
+// s = m / (h c), signed.  The exponents are taken out first, so neither squares
+// nor h leave the range, and (c, s) is brought back to unit length to rounding.
+__device__ __forceinline__ void jacobi_angle(double a, double b, double m, double &c, double &s, double &t) {
+  const double d0 = b - a;
+  const int em = __builtin_amdgcn_frexp_exp(m) + 1;
+  const int e = d0 == 0.0 ? em : max(__builtin_amdgcn_frexp_exp(d0), em);
+  const double d = ldexp(d0, -e), m2 = ldexp(m, 1 - e);
+  const double rh = rsqrt_near(fma(d, d, m2 * m2));
+  const double u = fma(0.5 * fabs(d), rh, 0.5);
+  const double ru = rsqrt_near(u);
+  const double sg = d0 >= 0.0 ? 0.5 : -0.5;
+  c = u * ru;
+  s = sg * m2 * rh * ru;
+  const double f = 0.5 * fma(-s, s, fma(-c, c, 1.0));
+  c = fma(c, f, c);
+  s = fma(s, f, s);
+  t = sg * m2 * rh * ru * ru;
+}
+
+// One workgroup per pair.  M is kept in its lower triangle (row >= column); a
+// step rotates 32 disjoint pairs of indices: 32 threads find the angles and
+// update their own 2 x 2 block, then every thread updates one of the 496 blocks
+// between two pairs, and its share of Q (stored transposed, so that a thread
+// takes four rows of both columns at once).  Steps: FULL rotates all 2016 pairs
+// in 63 steps (round-robin), otherwise the 1024 across the two blocks in 32
+// steps, index i with 32 + (i + step) mod 32.
+//
+// Bound by the chain of a step: an angle (two reciprocal square roots), a
+// barrier, the blocks' reads and writes in LDS, a barrier: 25 us for 32 steps
+// with six slices to sum, 65 for 63.  1024 threads, two divisions and two square
+// roots per angle and all 63 steps in every round took 100 us (a barrier over
+// 16 wavefronts takes 265 ns, one over eight a fraction of it).
+template <bool FULL>
+__global__ __launch_bounds__(RT) void k_pca_rot(const double *__restrict__ part, int n_ks, double tol, int n_blk, int r,
+                                                double *__restrict__ y, double *__restrict__ Qg,
+                                                int32_t *__restrict__ rot, double *__restrict__ conv) {
   __shared__ double M[PR * PLD];
-  __shared__ double Q[PR * PLD];
-  __shared__ double cs_c[PR], cs_s[PR], cs_t[PR];
-    __shared__ double red[RT];
+  __shared__ __attribute__((aligned(16))) double QT[PR * QLD];
+  __shared__ __attribute__((aligned(16))) double2 cs[PR / 2];
+  __shared__ double diag[PR], red[RT / WAVE], ys[PR];
+  constexpr int NV = (PART / 2 + RT - 1) / RT;
   const int tid = threadIdx.x, pi = blockIdx.x;
-  for (int e = tid; e < PR * PR; e += RT) {
-    const double *P = part + (int64_t)pi * n_ks * PR * PR + e;
-    double v = 0.0;
-    for (int k = 0; k < n_ks; ++k) v += P[(int64_t)k * PR * PR];
-    M[(e / PR) * PLD + e % PR] = v;
-    Q[(e / PR) * PLD + e % PR] = (e / PR == e % PR) ? 1.0 : 0.0;
+  const double *P = part + (int64_t)pi * n_ks * PART;
+  double2 v[NV];
+  int row[NV], col[NV];  // of v.x; v.y is four rows below
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    const int e = 2 * min(tid + RT * q, PART / 2 - 1);
+    const int tile = e >> 8, l = (e & 127) >> 1;
+    const int x = (tile >= 1) + (tile >= 3) + (tile >= 6);
+    row[q] = 16 * x + (l >> 4) + 8 * ((e >> 7) & 1);
+    col[q] = 16 * (tile - x * (x + 1) / 2) + (l & 15);
+    v[q] = *reinterpret_cast<const double2 *>(P + e);
   }
-  __syncthreads();
-  // symmetrise from the lower triangle and measure the largest scaled
-  // off-diagonal entry
-  double off = 0.0;
-  for (int e = tid; e < PR * PR; e += RT) {
-    const int j = e / PR, l = e % PR;
-    if (l < j) {
-      const double mjl = M[j * PLD + l];
-      M[l * PLD + j] = mjl;
-      const double den = sqrt(M[j * PLD + j] * M[l * PLD + l]);
-      if (den > 0.0) off = fmax(off, fabs(mjl) / den);
+  for (int k = 1; k < n_ks; ++k)
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const double2 w = *reinterpret_cast<const double2 *>(P + (int64_t)k * PART + 2 * min(tid + RT * q, PART / 2 - 1));
+      v[q].x += w.x;
+      v[q].y += w.y;
     }
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    if (row[q] >= col[q]) M[row[q] * PLD + col[q]] = v[q].x;
+    if (row[q] + 4 >= col[q]) M[(row[q] + 4) * PLD + col[q]] = v[q].y;
+    if (row[q] == col[q]) diag[row[q]] = v[q].x;
+    if (row[q] + 4 == col[q]) diag[col[q]] = v[q].y;
   }
-  red[tid] = off;
+#pragma unroll
+  for (int q = 0; q < PR * PR / 2 / RT; ++q) {
+    const int e = 2 * (tid + RT * q), a = e / PR, b = e % PR;
+    *reinterpret_cast<double2 *>(&QT[a * QLD + b]) = make_double2(a == b ? 1.0 : 0.0, a == b + 1 ? 1.0 : 0.0);
+  }
   __syncthreads();
-  for (int w = RT / 2; w > 0; w >>= 1) {
-    if (tid < w) red[tid] = fmax(red[tid], red[tid + w]);
-    __syncthreads();
+  // the largest scaled off-diagonal entry
+  double off = 0.0;
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    const double dc = diag[col[q]], d0 = diag[row[q]] * dc, d1 = diag[row[q] + 4] * dc;
+    if (col[q] < row[q] && d0 > 0.0) off = fmax(off, fabs(v[q].x) / sqrt(d0));
+    if (col[q] < row[q] + 4 && d1 > 0.0) off = fmax(off, fabs(v[q].y) / sqrt(d1));
   }
-  const double off0 = red[0];
+  off = wave_max(off);
+  if ((tid & 63) == 0) red[tid / WAVE] = off;
+  __syncthreads();
+  double off0 = red[0];
+#pragma unroll
+  for (int q = 1; q < RT / WAVE; ++q) off0 = fmax(off0, red[q]);
   if (tid == 0) {
     atomic_max_nonneg(conv, off0);
     rot[pi] = off0 > tol ? 1 : 0;
   }
   if (!(off0 > tol)) return;  // this pair is already orthogonal
-  __syncthreads();
 
-  // cyclic two-sided Jacobi on M (in place), Q accumulates the rotations
-  for (int sweep = 0; sweep < max_inner; ++sweep) {
-    double inner = 0.0;
-    for (int ir = 0; ir < PR - 1; ++ir) {
-      if (tid < PR / 2) {
-        const int j = rr_at(tid, ir, PR), l = rr_at(PR - 1 - tid, ir, PR);
-        const double mjj = M[j * PLD + j], mll = M[l * PLD + l], mjl = M[j * PLD + l];
-        const double den = sqrt(mjj * mll);
-        double c = 1.0, sn = 0.0, tt = 0.0;
-        if (den > 0.0 && fabs(mjl) > tol * den) {
-          inner = fmax(inner, fabs(mjl) / den);
-          const double th = (mll - mjj) / (2.0 * mjl);
-          tt = (th >= 0.0 ? 1.0 : -1.0) / (fabs(th) + sqrt(1.0 + th * th));
-          c = 1.0 / sqrt(1.0 + tt * tt);
-          sn = c * tt;
-        }
-        // x_j' = c x_j - s x_l, x_l' = s x_j + c x_l
-        cs_c[j] = c; cs_s[j] = -sn; cs_t[j] = -tt;
-        cs_c[l] = c; cs_s[l] = sn;  cs_t[l] = tt;
+  // block between pairs bi > bk for threads below 496
+  int bi = 1, bk = tid;
+  while (bk >= bi) {
+    bk -= bi;
+    ++bi;
+  }
+  const bool block = bi < PR / 2;
+  const int qp = tid >> 4, q0 = 4 * (tid & 15);  // Q: pair, first of four rows
+  const double tol2 = tol * tol;
+  auto lower = [](int i, int k) { return max(i, k) * PLD + min(i, k); };
+#pragma unroll 1
+  for (int ir = 0; ir < (FULL ? PR - 1 : PR / 2); ++ir) {
+    auto first = [&](int q) { return FULL ? rr_at(q, ir, PR) : q; };
+    auto second = [&](int q) { return FULL ? rr_at(PR - 1 - q, ir, PR) : PR / 2 + ((q + ir) & (PR / 2 - 1)); };
+    if (tid < PR / 2) {
+      const int j = first(tid), l = second(tid), jl = FULL ? lower(j, l) : l * PLD + j;
+      const double mjj = M[j * PLD + j], mll = M[l * PLD + l], mjl = M[jl];
+      double c = 1.0, sn = 0.0;
+      if (mjl * mjl > tol2 * (mjj * mll) && mjj > 0.0 && mll > 0.0) {
+        double tt;
+        jacobi_angle(mjj, mll, mjl, c, sn, tt);
+        M[j * PLD + j] = fma(-tt, mjl, mjj);
+        M[l * PLD + l] = fma(tt, mjl, mll);
+        M[jl] = 0.0;
       }
-      __syncthreads();
-      // 2 x 2 blocks (pair of i) x (pair of k), one per thread and step
-      for (int bidx = tid; bidx < (PR / 2) * (PR / 2); bidx += RT) {
-        const int qi = bidx / (PR / 2), qk = bidx % (PR / 2);
-        const int i0 = rr_at(qi, ir, PR), i1 = rr_at(PR - 1 - qi, ir, PR);
-        const int k0 = rr_at(qk, ir, PR), k1 = rr_at(PR - 1 - qk, ir, PR);
-        if (qi == qk) {
-          // the pair's own block: exact diagonal update, zero off-diagonal
-          const double m01 = M[i0 * PLD + i1];
-          if (cs_s[i0] != 0.0) {
-            M[i0 * PLD + i0] += cs_t[i0] * m01;  // M_jj - t M_jl
-            M[i1 * PLD + i1] += cs_t[i1] * m01;  // M_ll + t M_jl
-            M[i0 * PLD + i1] = 0.0;
-            M[i1 * PLD + i0] = 0.0;
-          }
-        } else {
-          const double a00 = M[i0 * PLD + k0], a01 = M[i0 * PLD + k1], a10 = M[i1 * PLD + k0],
-                       a11 = M[i1 * PLD + k1];
-          // x_i' = c_i x_i + s_i x_(partner of i), on both sides
-          const double ci0 = cs_c[i0], si0 = cs_s[i0], ci1 = cs_c[i1], si1 = cs_s[i1];
-          const double ck0 = cs_c[k0], sk0 = cs_s[k0], ck1 = cs_c[k1], sk1 = cs_s[k1];
-          const double r00 = ci0 * a00 + si0 * a10, r01 = ci0 * a01 + si0 * a11;
-          const double r10 = ci1 * a10 + si1 * a00, r11 = ci1 * a11 + si1 * a01;
-          M[i0 * PLD + k0] = ck0 * r00 + sk0 * r01;
-          M[i0 * PLD + k1] = ck1 * r01 + sk1 * r00;
-          M[i1 * PLD + k0] = ck0 * r10 + sk0 * r11;
-          M[i1 * PLD + k1] = ck1 * r11 + sk1 * r10;
-        }
-      }
-      // Q <- Q J: the two columns of each pair, row by row
-      for (int e = tid; e < PR * (PR / 2); e += RT) {
-        const int row = e / (PR / 2), qi = e % (PR / 2);
-        const int i0 = rr_at(qi, ir, PR), i1 = rr_at(PR - 1 - qi, ir, PR);
-        if (cs_s[i0] == 0.0) continue;
-        const double q0 = Q[row * PLD + i0], q1 = Q[row * PLD + i1];
-        Q[row * PLD + i0] = cs_c[i0] * q0 + cs_s[i0] * q1;
-        Q[row * PLD + i1] = cs_c[i1] * q1 + cs_s[i1] * q0;
-      }
-      __syncthreads();
-    }
-    if (tid < PR / 2) red[tid] = inner;
-    __syncthreads();
-    if (tid == 0) {
-      double m = 0.0;
-      for (int q = 0; q < PR / 2; ++q) m = fmax(m, red[q]);
-      red[0] = m;
+      cs[tid] = make_double2(c, sn);
     }
     __syncthreads();
-    const bool done = !(red[0] > tol);
+    if (block) {
+      const int i0 = first(bi), i1 = second(bi), k0 = first(bk), k1 = second(bk);
+      const int p00 = FULL ? lower(i0, k0) : i0 * PLD + k0, p01 = FULL ? lower(i0, k1) : k1 * PLD + i0,
+                p10 = FULL ? lower(i1, k0) : i1 * PLD + k0, p11 = lower(i1, k1);
+      const double2 ci = cs[bi], ck = cs[bk];
+      const double a00 = M[p00], a01 = M[p01], a10 = M[p10], a11 = M[p11];
+      const double r00 = ci.x * a00 - ci.y * a10, r10 = ci.y * a00 + ci.x * a10;
+      const double r01 = ci.x * a01 - ci.y * a11, r11 = ci.y * a01 + ci.x * a11;
+      M[p00] = ck.x * r00 - ck.y * r01;
+      M[p01] = ck.y * r00 + ck.x * r01;
+      M[p10] = ck.x * r10 - ck.y * r11;
+      M[p11] = ck.y * r10 + ck.x * r11;
+    }
+    const double2 cq = cs[qp];
+    if (cq.y != 0.0) {
+      double *a = &QT[first(qp) * QLD + q0], *b = &QT[second(qp) * QLD + q0];
+      const double2 x0 = *reinterpret_cast<double2 *>(a), x1 = *reinterpret_cast<double2 *>(a + 2);
+      const double2 z0 = *reinterpret_cast<double2 *>(b), z1 = *reinterpret_cast<double2 *>(b + 2);
+      *reinterpret_cast<double2 *>(a) = make_double2(cq.x * x0.x - cq.y * z0.x, cq.x * x0.y - cq.y * z0.y);
+      *reinterpret_cast<double2 *>(a + 2) = make_double2(cq.x * x1.x - cq.y * z1.x, cq.x * x1.y - cq.y * z1.y);
+      *reinterpret_cast<double2 *>(b) = make_double2(cq.y * x0.x + cq.x * z0.x, cq.y * x0.y + cq.x * z0.y);
+      *reinterpret_cast<double2 *>(b + 2) = make_double2(cq.y * x1.x + cq.x * z1.x, cq.y * x1.y + cq.x * z1.y);
+    }
     __syncthreads();
-    if (done) break;
   }
   double *out = Qg + (int64_t)pi * PR * PR;
-  for (int e = tid; e < PR * PR; e += RT) out[e] = Q[(e / PR) * PLD + e % PR];
+  for (int e = tid; e < PR * PR; e += RT) out[e] = QT[(e % PR) * QLD + e / PR];
+  // y of the pair <- Q^T y
+  const int bp = rr_at(pi, r, n_blk), bq = rr_at(n_blk - 1 - pi, r, n_blk);
+  if (tid < PR) ys[tid] = y[pair_row(bp, bq, tid)];
+  __syncthreads();
+  if (tid < PR) {
+    double o = 0.0;
+    for (int l = 0; l < PR; ++l) o += QT[tid * QLD + l] * ys[l];
+    y[pair_row(bp, bq, tid)] = o;
+  }
 }
 
-// Per mode a < n: lambda_a = |x_a|^2 and (S/N)^2_a = (x_a . y)^2 / lambda_a.
+// Per mode a < n: lambda_a = |x_a|^2 and (S/N)^2_a = y_a^2.
 __global__ void k_pca_modes(const double *__restrict__ X, const double *__restrict__ y, int64_t n, int64_t n_pad,
                             double *__restrict__ lam, double *__restrict__ snr2) {
   const int lane = threadIdx.x & (WAVE - 1);
   const int64_t a = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
   if (a >= n) return;
   const double *x = X + a * n_pad;
-  double nn = 0.0, dy = 0.0;
-  for (int64_t k = lane; k < n_pad; k += WAVE) {
-    nn += x[k] * x[k];
-    dy += x[k] * y[k];
-  }
+  double nn = 0.0;
+  for (int64_t k = lane; k < n_pad; k += WAVE) nn += x[k] * x[k];
   nn = wave_sum(nn);
-  dy = wave_sum(dy);
   if (lane == 0) {
     lam[a] = nn;
-    snr2[a] = nn > 0.0 ? dy * dy / nn : 0.0;
+    snr2[a] = nn > 0.0 ? y[a] * y[a] : 0.0;
   }
 }
 
 // Rank of each mode by ascending lambda (ties by index) and by descending
-// (S/N)^2; outputs in those orders.
+// (S/N)^2, one wavefront per mode.
 __global__ void k_pca_rank(const double *__restrict__ lam, const double *__restrict__ snr2, int64_t n,
                            int32_t *__restrict__ rank_lam, int32_t *__restrict__ rank_snr) {
-  const int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int lane = threadIdx.x & (WAVE - 1);
+  const int64_t a = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
   if (a >= n) return;
   const double la = lam[a], sa = snr2[a];
-  int64_t rl = 0, rs = 0;
-  for (int64_t b = 0; b < n; ++b) {
+  int rl = 0, rs = 0;
+  for (int64_t b = lane; b < n; b += WAVE) {
     const double lb = lam[b], sb = snr2[b];
     rl += (lb < la) || (lb == la && b < a);
     rs += (sb > sa) || (sb == sa && b < a);
   }
-  rank_lam[a] = (int32_t)rl;
-  rank_snr[a] = (int32_t)rs;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    rl += __shfl_xor(rl, o, WAVE);
+    rs += __shfl_xor(rs, o, WAVE);
+  }
+  if (lane == 0) {
+    rank_lam[a] = rl;
+    rank_snr[a] = rs;
+  }
 }
 
 __global__ void k_pca_scatter(const double *__restrict__ lam, const double *__restrict__ snr2,
@@ -324,30 +445,45 @@ __global__ void k_pca_scatter(const double *__restrict__ lam, const double *__re
   desc[rank_snr[a]] = snr2[a];
 }
 
-// Cumulative sum in place, in order, by one thread (n is at most a few 1e5).
+// Cumulative sum in place by one wavefront, 64 values at a time.
 __global__ void k_pca_cumsum(double *__restrict__ v, int64_t n) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  const int lane = threadIdx.x;
   double s = 0.0;
-  for (int64_t a = 0; a < n; ++a) {
-    s += v[a];
-    v[a] = s;
+  double next = lane < n ? v[lane] : 0.0;
+  for (int64_t b = 0; b < n; b += WAVE) {
+    double x = next;
+    next = b + WAVE + lane < n ? v[b + WAVE + lane] : 0.0;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+      const double u = __shfl_up(x, o, WAVE);
+      if (lane >= o) x += u;
+    }
+    x += s;
+    if (b + lane < n) v[b + lane] = x;
+    s = __shfl(x, WAVE - 1, WAVE);
   }
 }
 
-// Eigenvector rows in ascending-lambda order, first n entries, with the
-// sign that makes the largest entry in magnitude positive.
-__global__ void k_pca_vectors(const double *__restrict__ Vr, const int32_t *__restrict__ rank_lam, int64_t n,
+// Eigenvector rows w_a / |w_a| in ascending-lambda order, back in the data
+// vector's order, with the sign that makes the largest entry in magnitude
+// positive (the first of them in the data vector's order).
+__global__ void k_pca_vectors(const double *__restrict__ X, const double *__restrict__ lam,
+                              const int32_t *__restrict__ rank_lam, const int32_t *__restrict__ perm, int64_t n,
                               int64_t n_pad, double *__restrict__ S) {
   __shared__ double bv[256];
   __shared__ int64_t bi[256];
+  __shared__ int64_t bk[256];
   const int64_t a = blockIdx.x;
-  const double *v = Vr + a * n_pad;
+  const double *v = X + a * n_pad;
   double best = -1.0;
-  int64_t at = 0;
-  for (int64_t k = threadIdx.x; k < n; k += blockDim.x)
-    if (fabs(v[k]) > best) { best = fabs(v[k]); at = k; }
+  int64_t at = n, bat = 0;
+  for (int64_t k = threadIdx.x; k < n; k += blockDim.x) {
+    const double m = fabs(v[k]);
+    if (m > best || (m == best && perm[k] < at)) { best = m; at = perm[k]; bat = k; }
+  }
   bv[threadIdx.x] = best;
   bi[threadIdx.x] = at;
+  bk[threadIdx.x] = bat;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) {
@@ -356,19 +492,29 @@ __global__ void k_pca_vectors(const double *__restrict__ Vr, const int32_t *__re
       if (o > bv[threadIdx.x] || (o == bv[threadIdx.x] && oi < bi[threadIdx.x])) {
         bv[threadIdx.x] = o;
         bi[threadIdx.x] = oi;
+        bk[threadIdx.x] = bk[threadIdx.x + w];
       }
     }
     __syncthreads();
   }
-  const double sg = v[bi[0]] < 0.0 ? -1.0 : 1.0;
+  const double nrm = lam[a] > 0.0 ? 1.0 / sqrt(lam[a]) : 0.0;
+  const double sg = v[bk[0]] < 0.0 ? -nrm : nrm;
   double *out = S + (int64_t)rank_lam[a] * n;
-  for (int64_t k = threadIdx.x; k < n; k += blockDim.x) out[k] = sg * v[k];
+  for (int64_t k = threadIdx.x; k < n; k += blockDim.x) out[perm[k]] = sg * v[k];
 }
 
-void launch_pca_init(const double *Wm, int64_t ld, const int32_t *t, int64_t n, int64_t n_pad, double *X, double *V,
-                     double *y, hipStream_t s) {
-  const dim3 grid((unsigned)std::min<int64_t>((n_pad + 255) / 256, 64), (unsigned)n_pad);
-  hipLaunchKernelGGL(k_pca_init, grid, dim3(256), 0, s, Wm, ld, t, n, n_pad, X, V, y);
+void launch_pca_order(const void *C, int c_f32, const int32_t *t, int64_t n, int32_t *perm, hipStream_t s) {
+  const dim3 grid((unsigned)((n + 3) / 4));
+  if (c_f32)
+    hipLaunchKernelGGL(k_pca_order<float>, grid, dim3(256), 0, s, (const float *)C, t, n, perm);
+  else
+    hipLaunchKernelGGL(k_pca_order<double>, grid, dim3(256), 0, s, (const double *)C, t, n, perm);
+}
+
+void launch_pca_init(const double *Wm, int64_t ld, const int32_t *t, const int32_t *perm, int64_t n, int64_t n_pad,
+                     double *X, double *y, hipStream_t s) {
+  const dim3 grid((unsigned)(n_pad / 64), (unsigned)(n_pad / 64));
+  hipLaunchKernelGGL(k_pca_init, grid, dim3(256), 0, s, Wm, ld, t, perm, n, n_pad, X, y);
 }
 
 // Rotation of a pair's rows.  Q's fragments stay in
@@ -378,13 +524,11 @@ void launch_pca_init(const double *Wm, int64_t ld, const int32_t *t, int64_t n, 
 // buffers of [64 rows][64 doubles], unpadded, with the 16-byte chunk s of
 // row l at slot s ^ (8 (l & 1)): the four rows one MFMA operand read touches
 // fall on alternate halves of the banks.  A wavefront copy fills two rows.
-constexpr int ACD = 8;  // 64-column chunks per workgroup
-
 __device__ __forceinline__ int apply_slot(int l, int col) { return l * PR + 2 * ((col >> 1) ^ (8 * (l & 1))) + (col & 1); }
 
-__global__ __launch_bounds__(256) void k_pca_apply(double *__restrict__ X, double *__restrict__ V, int64_t n_pad,
-                                                     int n_blk, int r, const double *__restrict__ Qg,
-                                                     const int32_t *__restrict__ rot) {
+// `per` chunks per workgroup.
+__global__ __launch_bounds__(256) void k_pca_apply(double *__restrict__ Y, int64_t n_pad, int per, int n_blk, int r,
+                                                     const double *__restrict__ Qg, const int32_t *__restrict__ rot) {
   __shared__ __attribute__((aligned(16))) double st0[PR * PR];
   __shared__ __attribute__((aligned(16))) double st1[PR * PR];
   const int pi = blockIdx.x;
@@ -392,7 +536,6 @@ __global__ __launch_bounds__(256) void k_pca_apply(double *__restrict__ X, doubl
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int bp = rr_at(pi, r, n_blk), bq = rr_at(n_blk - 1 - pi, r, n_blk);
   const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-  double *Y = blockIdx.z == 0 ? X : V;
   // Q fragments: step kk, block x: Q[kk + lane / 16][wr + 16 x + lane % 16]
   const double *q = Qg + (int64_t)pi * PR * PR;
   double qa[PR / 4][2];
@@ -411,8 +554,8 @@ __global__ __launch_bounds__(256) void k_pca_apply(double *__restrict__ X, doubl
     rows[i] = Y + pair_row(bp, bq, l0) * n_pad;
     off[i] = (uint32_t)(((lane >> 5) * n_pad + 2 * ((lane & 31) ^ (8 * (l & 1)))) * 8);
   }
-  const int64_t cbase = (int64_t)blockIdx.y * ACD * PR;
-  const int nch = (int)min((int64_t)ACD, (n_pad - cbase) / PR);
+  const int64_t cbase = (int64_t)blockIdx.y * per * PR;
+  const int nch = (int)min((int64_t)per, (n_pad - cbase) / PR);
   auto issue = [&](int ci, double *buf) {
 #pragma unroll
     for (int i = 0; i < 8; ++i)
@@ -475,36 +618,43 @@ __global__ __launch_bounds__(256) void k_pca_apply(double *__restrict__ X, doubl
   }
 }
 
-// Column slices of the Gram: enough workgroups to cover the chip, each
-// slice a multiple of 64 columns.
+// Column slices of the Gram.  A slice costs its share of the chunks (1.1 us
+// each, on one workgroup) and 20 KB for the rotation kernel to read back on one
+// CU (0.35 us): about sqrt(3 chunks) slices, as long as the workgroups fit
+// the chip four times.
 int pca_slices(int64_t n_pad) {
-  const int pairs = (int)(n_pad / PB) / 2;
+  const int pairs = (int)(n_pad / PR), chunks = (int)(n_pad / PR);
   int ks = 1;
-  while (pairs * ks * 2 <= 1024 && n_pad % ((int64_t)ks * 2 * PR) == 0 && n_pad / (ks * 2) >= 256) ks *= 2;
+  while ((ks + 1) * (ks + 1) <= 3 * chunks && ks + 1 <= chunks && pairs * (ks + 1) <= 1024) ++ks;
   return ks;
 }
 
-void launch_pca_round(double *X, double *V, int64_t n_pad, int r, double tol, int max_inner, double *conv,
-                      double *part, double *Qg, int32_t *rot, hipStream_t s) {
-  const int n_blk = (int)(n_pad / PB), pairs = n_blk / 2, ks = pca_slices(n_pad);
-  // slices are multiples of 64 columns
-  hipLaunchKernelGGL(k_pca_gram, dim3((unsigned)pairs, (unsigned)ks), dim3(256), 0, s, X, n_pad, n_blk, r,
-                     n_pad / ks, part);
-  hipLaunchKernelGGL(k_pca_rot, dim3((unsigned)pairs), dim3(RT), 0, s, part, ks, tol, max_inner, Qg, rot, conv);
-  hipLaunchKernelGGL(k_pca_apply, dim3((unsigned)pairs, (unsigned)((n_pad / PR + ACD - 1) / ACD), V ? 2u : 1u),
-                     dim3(256), 0, s, X, V, n_pad, n_blk, r, Qg, rot);
+void launch_pca_round(double *X, double *y, int64_t n_pad, int r, double tol, double *conv, double *part, double *Qg,
+                      int32_t *rot, hipStream_t s) {
+  const int n_blk = (int)(n_pad / PB), pairs = n_blk / 2, ks = pca_slices(n_pad), chunks = (int)(n_pad / PR);
+  hipLaunchKernelGGL(k_pca_gram, dim3((unsigned)pairs, (unsigned)ks), dim3(256), 0, s, X, n_pad, n_blk, r, part);
+  if (r == 0)
+    hipLaunchKernelGGL(k_pca_rot<true>, dim3((unsigned)pairs), dim3(RT), 0, s, part, ks, tol, n_blk, r, y, Qg, rot, conv);
+  else
+    hipLaunchKernelGGL(k_pca_rot<false>, dim3((unsigned)pairs), dim3(RT), 0, s, part, ks, tol, n_blk, r, y, Qg, rot,
+                       conv);
+  // chunks per workgroup: eight amortise the 32 KB of Q, fewer while the chip
+  // is not filled twice
+  int per = (int)std::min<int64_t>(8, std::max<int64_t>(1, (int64_t)pairs * chunks / 512));
+  hipLaunchKernelGGL(k_pca_apply, dim3((unsigned)pairs, (unsigned)((chunks + per - 1) / per)), dim3(256), 0, s, X,
+                     n_pad, per, n_blk, r, Qg, rot);
 }
 
-void launch_pca_finish(const double *X, const double *y, const double *Vr, int64_t n, int64_t n_pad, double *lam,
+void launch_pca_finish(const double *X, const double *y, const int32_t *perm, int64_t n, int64_t n_pad, double *lam,
                        double *snr2, int32_t *rank_lam, int32_t *rank_snr, double *lam_out, double *snr2_out,
                        double *desc, double *S, hipStream_t s) {
-  hipLaunchKernelGGL(k_pca_modes, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, X, y, n, n_pad, lam, snr2);
-  const unsigned g = (unsigned)((n + 255) / 256);
-  hipLaunchKernelGGL(k_pca_rank, dim3(g), dim3(256), 0, s, lam, snr2, n, rank_lam, rank_snr);
-  hipLaunchKernelGGL(k_pca_scatter, dim3(g), dim3(256), 0, s, lam, snr2, rank_lam, rank_snr, n, lam_out, snr2_out,
-                     desc);
+  const dim3 waves((unsigned)((n + 3) / 4));
+  hipLaunchKernelGGL(k_pca_modes, waves, dim3(256), 0, s, X, y, n, n_pad, lam, snr2);
+  hipLaunchKernelGGL(k_pca_rank, waves, dim3(256), 0, s, lam, snr2, n, rank_lam, rank_snr);
+  hipLaunchKernelGGL(k_pca_scatter, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, lam, snr2, rank_lam, rank_snr,
+                     n, lam_out, snr2_out, desc);
   hipLaunchKernelGGL(k_pca_cumsum, dim3(1), dim3(64), 0, s, desc, n);
-  if (S && Vr) hipLaunchKernelGGL(k_pca_vectors, dim3((unsigned)n), dim3(256), 0, s, Vr, rank_lam, n, n_pad, S);
+  if (S) hipLaunchKernelGGL(k_pca_vectors, dim3((unsigned)n), dim3(256), 0, s, X, lam, rank_lam, perm, n, n_pad, S);
 }
 
 }  // namespace wlc

@@ -132,3 +132,51 @@ def test_pca_paper_binning(wl, n_z):
     near = np.min(np.abs(cum0[max(0, k0 - 2):k0 + 1] - thr)) < 1e-8 * cum0[-1]
     assert k == k0 or near
     prob.close()
+
+
+# (n_data, n_z, n_ell, ell_min, ell_max): less than one block of 32, one pair of
+# blocks exactly and not, one row more than a pair, odd and even numbers of
+# 64-column chunks, and one column slice against several
+@pytest.mark.parametrize("shape", [(2, 1, 1, 10.0, 500.0), (17, 1, 4, 50.0, 500.0), (64, 2, 4, 10.0, 500.0),
+                                   (65, 2, 3, 200.0, 500.0), (128, 1, 8, 400.0, 500.0), (143, 2, 5, 50.0, 500.0),
+                                   (383, 2, 9, 10.0, 500.0)], ids=lambda s: str(s[0]))
+def test_pca_block_edges(wl, shape):
+    """A graded covariance Delta M Delta, M = 1.5 I + V V^T with four columns in
+    V and Delta over 20 decades, in no order: Jacobi on the Cholesky factor
+    finds every eigenvalue to a modest multiple of n eps kappa(M) (Demmel and
+    Veselic 1992, theorem 3.1 and section 4), here 40 n eps kappa(M); the
+    cumulative curve ends at d^T C^-1 d, a 4 x 4 solve."""
+    n, n_z, n_ell, lo, hi = shape
+    _say("case pca block edges n = %d" % n)
+    cfg = dict(synth.PRESETS["tiny"], **synth.SURVEY_DEFAULTS, rho_mean=8.3e10)
+    cfg.update(n_z=n_z, n_ell=n_ell, ell_min=lo, ell_max=hi, n_chi=8, n_m=4)
+    prob = wl.Problem(cfg, synth.make_tables("tiny").arrays(), precision="fp64")
+    assert prob.sizes.n_data == n
+    rng = np.random.default_rng(n)
+    V = rng.standard_normal((n, 4)) / np.sqrt(n)
+    M = V @ V.T + 1.5 * np.eye(n)
+    kappa = 1.0 + np.linalg.norm(V, 2) ** 2 / 1.5
+    e = rng.integers(-33, 34, n).astype(np.int32)  # C_true = 2^-e M 2^-e
+    z = rng.standard_normal(n)
+    d = np.ldexp(z, -e)
+    prob.C.copy_(torch.from_numpy(M))
+    prob.row_exp2.copy_(torch.from_numpy(e))
+    prob.d.copy_(torch.from_numpy(d))
+    lam, snr, cum, sweeps, S = prob.pca()
+    lam0, snr0, cum0, S0 = oracle.Oracle.pca(np.ldexp(M, -(e[:, None] + e[None, :])), d)
+    tol = 40 * n * np.finfo(float).eps * kappa
+    assert np.max(np.abs(lam / lam0 - 1.0)) < 2 * tol  # both sides
+    want = float(z @ z / 1.5 - (z @ V) @ np.linalg.solve(np.eye(4) + V.T @ V / 1.5, V.T @ z) / 2.25)
+    assert abs(cum[-1] / want - 1.0) < tol
+    Sg = S.cpu().numpy()
+    assert np.max(np.abs(Sg @ Sg.T - np.eye(n))) < tol
+    assert np.all(Sg[np.arange(n), np.argmax(np.abs(Sg), axis=1)] > 0)
+    # a diagonal that is not a number has no place in the order of the rows:
+    # refused, like any matrix that is not positive definite
+    for bad in (float("nan"), 0.0, -1.0):
+        prob.C.copy_(torch.from_numpy(M))
+        prob.C[n // 2, n // 2] = bad
+        with pytest.raises(wl.WlcError) as ex:
+            prob.pca(vectors=False)
+        assert ex.value.code == wl.WLC_ENOTPD
+    prob.close()
