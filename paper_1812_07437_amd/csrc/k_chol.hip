@@ -10,15 +10,16 @@
 // panel's update while one workgroup of the same launch already updates and
 // factors the next diagonal block (k_trail), so that the serial chain runs
 // beside the update.  Up to RIGHT_MAX columns the trailing update covers the
-// whole remaining matrix.  Beyond it the matrix is read and written too often
-// that way, and blocks of 256 columns first receive the update from every
-// column to their left in one long-k MFMA product (k_update.hip); the panels'
-// own updates then stay within the block.
+// whole remaining matrix, for eight panels at once while the matrix is large.
+// Beyond it the matrix is read and written too often that way, and blocks of 256
+// columns first receive the update from every column to their left in one
+// long-k MFMA product (k_update.hip); the panels' own updates then stay within
+// the block.
 //
 // Measured, one factorisation (before: 64-wide diagonal blocks in launches of
 // their own, left-looking over 256 columns at every size): n = 818
-// 0.99 -> 0.35 ms, 2420 3.1 -> 0.96 ms, 4550 6.0 -> 2.05 ms, 10000
-// 15.1 -> 10.4 ms, 25044 106 -> 94 ms.
+// 0.99 -> 0.35 ms, 2420 3.1 -> 0.96 ms, 4550 6.0 -> 2.03 ms, 10000
+// 15.1 -> 8.7 ms, 17059 42.5 -> 32 ms, 25044 106 -> 94 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -30,12 +31,20 @@ namespace wlc {
 
 constexpr int NB = 128;      // panel width
 constexpr int NB_OUT = 256;  // columns that take one long-k update together
-// Up to this size every panel's update goes to the whole trailing matrix.
-// Measured with and without: n = 6550 4.0 against 5.8 ms, 10000 10.4 against
-// 10.4 ms, 12768 19.6 against 17.1 ms (the trailing matrix is then read and
-// written once per 128 columns, which the long-k product does not need).
-constexpr int64_t RIGHT_MAX = 10000;
-constexpr int64_t PART_ROWS = 524288;  // split-k scratch: slices x rows of 256 doubles
+// Up to this size the update goes to the whole trailing matrix.  Measured with
+// and against the long-k product: n = 10000 8.7 and 10.4 ms, 17059 32.8 and
+// 34.6, 25044 94.7 and 94.2, 33165 214 and 204 (its 256 columns at a time are
+// summed over one long k, and the trailing matrix is far beyond the caches).
+constexpr int64_t RIGHT_MAX = 20000;
+// While this many columns remain, the panels of a group of eight update only the
+// group's own columns one by one, and the rest of the matrix together, so that
+// it is read and written once per 1024 columns.  n = 10000 10.4 ms without
+// groups, 9.5 with groups of two, 9.1 of four and of eight (8.7 with the inner
+// loop unrolled over a panel); 12768 19.6, 17.1, 16.0, 15.7; 6550 4.0, 4.0, 4.0,
+// 3.9 (3.7): there the group's own small updates cost what the traffic saves.
+constexpr int64_t GROUP_MIN = 5000;
+constexpr int GROUP = 8;
+constexpr int64_t PART_ROWS = 524288;  // split-k scratch of the long-k product: slices x rows of 256 doubles
 
 // ------------------------------------------------------------- prepare
 // Lower triangle of M from the scaled covariance (f32 or f64) and d: one
@@ -307,13 +316,21 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// Solved panels whose update is due: the packed rows of panel p from the
+// update's first row on are at rows + p stride, n_blk row blocks.
+struct Panels {
+  const double *rows;
+  int64_t stride;
+  int n;
+  int64_t n_blk;
+};
+
 // A wavefront's row blocks of the diagonal block at r0, less (UPDATE) X X^T over
-// the first 128 rows of the panel just solved, a 16-deep step's tiles read from
-// the L2 while the one before is multiplied.
+// the first 128 rows of the solved panels, a 16-deep step's tiles read from the
+// L2 while the one before is multiplied.
 template <int W, bool UPDATE>
 __device__ __forceinline__ void diag_load(DiagLds &S, const double *__restrict__ Wm, int64_t ld, int64_t r0, int jb,
-                                          const double *__restrict__ rows_pack, int64_t n_blk, int lane,
-                                          DiagRows<W> &T) {
+                                          const Panels &X, int lane, DiagRows<W> &T) {
   constexpr int R0 = DiagRows<W>::R0, R1 = DiagRows<W>::R1;
 #pragma unroll
   for (int t = 0; t <= R0; ++t) T.a[t] = f64x4{0.0, 0.0, 0.0, 0.0};
@@ -321,9 +338,12 @@ __device__ __forceinline__ void diag_load(DiagLds &S, const double *__restrict__
   for (int t = 0; t <= R1; ++t) T.b[t] = f64x4{0.0, 0.0, 0.0, 0.0};
   if constexpr (UPDATE) {
     f64x4 x[2][R0 + 1];
-    auto read = [&](f64x4(&d)[R0 + 1], int s) {
+    uint32_t at[R0 + 1];  // row block t in a panel's packed rows
 #pragma unroll
-      for (int t = 0; t <= R0; ++t) d[t] = get_tile(rows_pack + min((int64_t)t, n_blk - 1) * PACK_ROW + s * TILE, lane);
+    for (int t = 0; t <= R0; ++t) at[t] = (uint32_t)min((int64_t)t, X.n_blk - 1) * PACK_ROW;
+    auto read = [&](f64x4(&d)[R0 + 1], const double *p) {
+#pragma unroll
+      for (int t = 0; t <= R0; ++t) d[t] = get_tile(p + at[t], lane);
     };
     auto mul = [&](const f64x4(&d)[R0 + 1]) {
 #pragma unroll
@@ -331,15 +351,21 @@ __device__ __forceinline__ void diag_load(DiagLds &S, const double *__restrict__
 #pragma unroll
       for (int t = 0; t <= R1; ++t) T.b[t] = tile_fms(d[t], d[R1], T.b[t]);
     };
-    read(x[0], 0);
+    const double *p = X.rows;
+    read(x[0], p);
     diag_copy<R0>(S, Wm, ld, r0, jb, lane);
     diag_copy<R1>(S, Wm, ld, r0, jb, lane);
 #pragma unroll 1
-    for (int s = 0; s < NT; s += 2) {
-      read(x[1], s + 1);
-      mul(x[0]);
-      read(x[0], min(s + 2, NT - 1));
-      mul(x[1]);
+    for (int left = X.n; left > 0; --left) {
+      const double *next = left > 1 ? p + X.stride : p;
+#pragma unroll 1
+      for (int s = 0; s < NT; s += 2) {
+        read(x[1], p + TILE);
+        mul(x[0]);
+        p = s + 2 < NT ? p + 2 * TILE : next;
+        read(x[0], p);
+        mul(x[1]);
+      }
     }
   } else {
     diag_copy<R0>(S, Wm, ld, r0, jb, lane);
@@ -441,23 +467,23 @@ __device__ __forceinline__ void diag_follow(DiagLds &S, DiagRows<W> &T, int lane
 
 template <bool UPDATE>
 __device__ __forceinline__ void diag_block(DiagLds &S, double *__restrict__ Wm, int64_t ld, int64_t j0, int jb,
-                                           const double *__restrict__ rows_pack, int64_t n_blk, int w, int lane,
-                                           double *__restrict__ pack, int *__restrict__ flag) {
+                                           const Panels &X, int w, int lane, double *__restrict__ pack,
+                                           int *__restrict__ flag) {
   if (w == 0) {
     DiagRows<0> T;
-    diag_load<0, UPDATE>(S, Wm, ld, j0, jb, rows_pack, n_blk, lane, T);
+    diag_load<0, UPDATE>(S, Wm, ld, j0, jb, X, lane, T);
     diag_walk(S, T, lane, pack, flag);
   } else if (w == 1) {
     DiagRows<1> T;
-    diag_load<1, UPDATE>(S, Wm, ld, j0, jb, rows_pack, n_blk, lane, T);
+    diag_load<1, UPDATE>(S, Wm, ld, j0, jb, X, lane, T);
     diag_follow<1>(S, T, lane);
   } else if (w == 2) {
     DiagRows<2> T;
-    diag_load<2, UPDATE>(S, Wm, ld, j0, jb, rows_pack, n_blk, lane, T);
+    diag_load<2, UPDATE>(S, Wm, ld, j0, jb, X, lane, T);
     diag_follow<2>(S, T, lane);
   } else {
     DiagRows<3> T;
-    diag_load<3, UPDATE>(S, Wm, ld, j0, jb, rows_pack, n_blk, lane, T);
+    diag_load<3, UPDATE>(S, Wm, ld, j0, jb, X, lane, T);
     diag_follow<3>(S, T, lane);
   }
   // L to the matrix, eight rows of 128 B per store, and its tiles off the
@@ -487,7 +513,7 @@ __global__ __launch_bounds__(256) void k_diag(double *__restrict__ Wm, int64_t l
                                               double *__restrict__ pack, int *__restrict__ flag) {
   __shared__ __attribute__((aligned(16))) DiagLds S;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  diag_block<false>(S, Wm, ld, j0, jb, nullptr, 1, w, lane, pack, flag);
+  diag_block<false>(S, Wm, ld, j0, jb, Panels{}, w, lane, pack, flag);
 }
 
 // Panel solve X = B L^-T of the rows below a diagonal block: 64 rows per
@@ -570,13 +596,13 @@ __global__ __launch_bounds__(256) void k_solve(double *__restrict__ Wm, int64_t 
 // 256 flops, and the matrix cores about equally.
 template <int S>
 __global__ __launch_bounds__(256, 2) void k_trail(double *__restrict__ Wm, int64_t ld, int64_t r0, int64_t rows,
-                                                  int64_t c1, const double *__restrict__ rows_pack, int64_t n_blk,
-                                                  int64_t tcols, double *__restrict__ pack, int *__restrict__ flag) {
+                                                  int64_t c1, Panels X, int64_t tcols, double *__restrict__ pack,
+                                                  int *__restrict__ flag) {
   __shared__ __attribute__((aligned(16))) DiagLds D;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, g = lane >> 4;
   if (blockIdx.x == 0) {
-    diag_block<true>(D, Wm, ld, r0, (int)min((int64_t)NB, c1 - r0), rows_pack, n_blk, w, lane, pack, flag);
+    diag_block<true>(D, Wm, ld, r0, (int)min((int64_t)NB, c1 - r0), X, w, lane, pack, flag);
     return;
   }
   // tile (ti, tj) of 2 S x 2 S 16-blocks on the lower triangle, tj < tcols
@@ -598,11 +624,11 @@ __global__ __launch_bounds__(256, 2) void k_trail(double *__restrict__ Wm, int64
   // whole wavefront outside the matrix, above the diagonal, or inside the
   // next diagonal block
   if (ib >= ilim || jb0 >= jlim || jb0 > ib + S - 1 || (ib + S) * RB <= own) return;
-  const double *pa[S], *pb[S];
+  uint32_t pa[S], pb[S];  // row blocks in a panel's packed rows (below 2^32 doubles)
 #pragma unroll
   for (int x = 0; x < S; ++x) {
-    pa[x] = rows_pack + min(ib + x, n_blk - 1) * PACK_ROW + 2 * lane;
-    pb[x] = rows_pack + min(jb0 + x, n_blk - 1) * PACK_ROW + 2 * lane;
+    pa[x] = (uint32_t)min(ib + x, X.n_blk - 1) * PACK_ROW + 2 * lane;
+    pb[x] = (uint32_t)min(jb0 + x, X.n_blk - 1) * PACK_ROW + 2 * lane;
   }
   // accumulator of rows x columns: element v of lane l is row g + 4 v, column
   // l % 16
@@ -618,11 +644,12 @@ __global__ __launch_bounds__(256, 2) void k_trail(double *__restrict__ Wm, int64
         acc[x][y][v] = Wm[i * ld + min(i, j)];
       }
   double2 a[2][S], b[2][S];
-  auto load = [&](int h, int st) {  // half step st: two of the four products of a 16-deep step
+  // half step st of the panel at p: two of the four products of a 16-deep step
+  auto load = [&](int h, const double *p, int st) {
 #pragma unroll
     for (int x = 0; x < S; ++x) {
-      a[h][x] = *reinterpret_cast<const double2 *>(pa[x] + st * 128);
-      b[h][x] = *reinterpret_cast<const double2 *>(pb[x] + st * 128);
+      a[h][x] = *reinterpret_cast<const double2 *>(p + st * 128 + pa[x]);
+      b[h][x] = *reinterpret_cast<const double2 *>(p + st * 128 + pb[x]);
     }
   };
   auto mul = [&](int h) {
@@ -637,13 +664,19 @@ __global__ __launch_bounds__(256, 2) void k_trail(double *__restrict__ Wm, int64
       for (int y = 0; y < S; ++y)
         acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[h][x].y, b[h][y].y, acc[x][y], 0, 0, 0);
   };
-  load(0, 0);
+  const double *p = X.rows;
+  load(0, p, 0);
+#pragma unroll 1
+  for (int left = X.n; left > 0; --left) {
+    const double *next = left > 1 ? p + X.stride : p;
 #pragma unroll
-  for (int st = 0; st < 2 * NT; st += 2) {
-    load(1, st + 1);
-    mul(0);
-    if (st + 2 < 2 * NT) load(0, st + 2);
-    mul(1);
+    for (int st = 0; st < 2 * NT; st += 2) {
+      load(1, p, st + 1);
+      mul(0);
+      load(0, st + 2 < 2 * NT ? p : next, (st + 2) % (2 * NT));
+      mul(1);
+    }
+    p = next;
   }
 #pragma unroll
   for (int x = 0; x < S; ++x)
@@ -657,14 +690,15 @@ __global__ __launch_bounds__(256, 2) void k_trail(double *__restrict__ Wm, int64
       }
 }
 
-// The trailing update of rows [r0, rows), columns [r0, c1) with the panel just
-// solved, and the factorisation of the next diagonal block.
-static void launch_trail(double *Wm, int64_t ld, int64_t r0, int64_t rows, int64_t c1, const double *rows_pack,
-                         int64_t n_blk, double *pack, int *flag, hipStream_t s, KernelProbe *probe) {
+// The trailing update of rows [r0, rows), columns [r0, c1) with the solved panels
+// X, and the factorisation of the next diagonal block.
+static void launch_trail(double *Wm, int64_t ld, int64_t r0, int64_t rows, int64_t c1, const Panels &X, double *pack,
+                         int *flag, hipStream_t s, KernelProbe *probe) {
   const bool timed = probe && probe->ev && probe->count < probe->cap;
   if (probe) {
     const double cols = (double)(c1 - r0);
-    probe->flops += 2.0 * NB * (cols * (double)rows - (double)(r0 + c1 - 1) * cols / 2.0);  // entries with i >= j
+    // entries with i >= j
+    probe->flops += 2.0 * NB * X.n * (cols * (double)rows - (double)(r0 + c1 - 1) * cols / 2.0);
     ++probe->launches;
   }
   if (timed) (void)hipEventRecord(probe->ev[2 * probe->count], s);
@@ -675,38 +709,56 @@ static void launch_trail(double *Wm, int64_t ld, int64_t r0, int64_t rows, int64
   // 64 x 64 tiles until 128 x 128 ones fill the chip one and a half times over
   // (two workgroups per CU): n = 4550 2.05 ms, from 256 tiles on 2.13
   if (tiles_of(128) >= 768)
-    hipLaunchKernelGGL(k_trail<4>, dim3((unsigned)(1 + tiles_of(128))), dim3(256), 0, s, Wm, ld, r0, rows, c1,
-                       rows_pack, n_blk, (c1 - r0 + 127) / 128, pack, flag);
+    hipLaunchKernelGGL(k_trail<4>, dim3((unsigned)(1 + tiles_of(128))), dim3(256), 0, s, Wm, ld, r0, rows, c1, X,
+                       (c1 - r0 + 127) / 128, pack, flag);
   else
-    hipLaunchKernelGGL(k_trail<2>, dim3((unsigned)(1 + tiles_of(64))), dim3(256), 0, s, Wm, ld, r0, rows, c1,
-                       rows_pack, n_blk, (c1 - r0 + 63) / 64, pack, flag);
+    hipLaunchKernelGGL(k_trail<2>, dim3((unsigned)(1 + tiles_of(64))), dim3(256), 0, s, Wm, ld, r0, rows, c1, X,
+                       (c1 - r0 + 63) / 64, pack, flag);
   if (timed) (void)hipEventRecord(probe->ev[2 * probe->count++ + 1], s);
 }
 
 // Factor columns [0, n) of M (n + 1 rows).  scratch: the packed diagonal block,
-// then the packed rows of the current panel, which share their space with the
-// split-k buffer of the long panel updates.  The pivot flag is checked by the
-// caller after synchronisation.
+// then the packed rows of the panels whose update is due, which share their
+// space with the split-k buffer of the long panel updates.  The pivot flag is
+// checked by the caller after synchronisation.
 int chol_factor(double *Wm, int64_t n, int64_t ld, double *scratch, int *flag, hipStream_t s,
                 KernelProbe *probe) {
   const int64_t rows = n + 1;
   double *pack = scratch;
   double *part = scratch + PACK_DIAG;
-  const int64_t part_rows = (int64_t)(chol_scratch_bytes(n) / 8 - PACK_DIAG) / NB_OUT;
+  const int64_t part_doubles = (int64_t)(chol_scratch_bytes(n) / 8) - PACK_DIAG;
+  const int64_t pack_rows = (n + 64) * NB;  // a panel's packed rows
   const int64_t outer = n <= RIGHT_MAX ? n : NB_OUT;
   for (int64_t J0 = 0; J0 < n; J0 += outer) {
     const int64_t Jend = std::min<int64_t>(J0 + outer, n);
     // everything left of the panel, in one product over k = [0, J0)
-    launch_update2(Wm, ld, J0, rows, Jend, 0, J0, part, part_rows, s, probe);
-    for (int64_t j0 = J0; j0 < Jend; j0 += NB) {
-      const int jb = (int)std::min<int64_t>(NB, Jend - j0);
-      if (j0 == J0) hipLaunchKernelGGL(k_diag, dim3(1), dim3(256), 0, s, Wm, ld, j0, jb, pack, flag);
-      const int64_t r0 = j0 + jb;  // first row below
-      const bool more = r0 < Jend;
-      const int64_t nblk = (rows - r0 + 63) / 64;
-      hipLaunchKernelGGL(k_solve, dim3((unsigned)nblk), dim3(256), 0, s, Wm, ld, j0, jb, rows, pack,
-                         more ? part : (double *)nullptr);
-      if (more) launch_trail(Wm, ld, r0, rows, Jend, part, 4 * nblk, pack, flag, s, probe);
+    launch_update2(Wm, ld, J0, rows, Jend, 0, J0, part, part_doubles / NB_OUT, s, probe);
+    hipLaunchKernelGGL(k_diag, dim3(1), dim3(256), 0, s, Wm, ld, J0, (int)std::min<int64_t>(NB, Jend - J0), pack, flag);
+    for (int64_t j0 = J0; j0 < Jend;) {
+      // the panels of a group update the group's columns one by one, the rest of
+      // the matrix together
+      int group = Jend - j0 >= GROUP_MIN ? GROUP : 1;
+      if (group * pack_rows > part_doubles) group = 1;
+      const int64_t gend = j0 + group * NB;
+      for (int q = 0; q < group; ++q, j0 += NB) {
+        const int jb = (int)std::min<int64_t>(NB, Jend - j0);
+        const int64_t r0 = j0 + jb;  // first row below
+        const int64_t nblk = (rows - r0 + 63) / 64;
+        hipLaunchKernelGGL(k_solve, dim3((unsigned)nblk), dim3(256), 0, s, Wm, ld, j0, jb, rows, pack,
+                           r0 < Jend ? part + q * pack_rows : (double *)nullptr);
+        if (r0 >= Jend) continue;
+        Panels X{};
+        X.n_blk = 4 * nblk;
+        if (r0 < gend) {  // this panel alone
+          X.n = 1;
+          X.rows = part + q * pack_rows;
+        } else {  // panel p lies 128 (group - 1 - p) rows higher than the last one
+          X.n = group;
+          X.rows = part + (int64_t)(group - 1) * NT * PACK_ROW;
+          X.stride = pack_rows - NT * PACK_ROW;
+        }
+        launch_trail(Wm, ld, r0, rows, std::min(r0 < gend ? gend : Jend, Jend), X, pack, flag, s, probe);
+      }
     }
   }
   return 0;
