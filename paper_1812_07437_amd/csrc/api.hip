@@ -52,7 +52,7 @@ constexpr int64_t K_ALIGN = 64;
 
 enum Buf {
   B_ROWR, B_ROWO, B_CFGT, B_CENT, B_NMODES, B_NTRI, B_THR, B_TRI, B_FLAGS,
-  B_U, B_PK, B_NE, B_X, B_R, B_DR, B_RR, B_PS, B_G, B_GMAX, B_TS, B_SEXP,
+  B_U, B_LEG, B_CHIF, B_LAST, B_X, B_R, B_DR, B_RR, B_PS, B_G, B_GMAX, B_TS, B_SEXP,
   B_A0, B_A1, B_GM, B_PART, B_H, B_G2, B_H2, B_TS2, B_T2, B_SW, B_SOFF, B_SLEG, B_SWT, B_SQ, B_GD, B_FP,
   B_AROW, B_POS, B_EXT, B_GP, NBUF
 };
@@ -92,7 +92,9 @@ static Layout run_layout(const Plan &p) {
   sz[B_TRI] = (size_t)std::max(1, p.n_tri) * 12;
   sz[B_FLAGS] = 64 * 4;
   sz[B_U] = n_ls * c.n_chi * c.n_m * 8;
-  sz[B_PK] = sz[B_NE] = n_ls * c.n_chi * 8;
+  sz[B_LEG] = n_ls * c.n_chi * sizeof(LegTerm);
+  sz[B_CHIF] = (size_t)c.n_chi * 4 * 8;
+  sz[B_LAST] = (size_t)p.n_R * 4;
   sz[B_X] = sz[B_R] = (size_t)n_cfg * c.n_chi * 8;
   sz[B_DR] = sz[B_RR] = (size_t)p.n_R * 8;
   sz[B_PS] = (size_t)nl * c.n_z * c.n_z * 8;
@@ -387,7 +389,8 @@ int run_enqueue_front(const Plan &p, const wlc_tables &tb, void *ws, hipStream_t
   const int n_cfg = (int)p.cfgs.size();
   const int32_t *cfgT = at<int32_t>(ws, L, B_CFGT);
   const int32_t *rowR = at<int32_t>(ws, L, B_ROWR);
-  double *U = at<double>(ws, L, B_U), *Pk = at<double>(ws, L, B_PK), *Ne = at<double>(ws, L, B_NE);
+  double *U = at<double>(ws, L, B_U), *F = at<double>(ws, L, B_CHIF);
+  LegTerm *legs = at<LegTerm>(ws, L, B_LEG);
   double *X = at<double>(ws, L, B_X), *R = at<double>(ws, L, B_R);
   double *dR = at<double>(ws, L, B_DR), *rR = at<double>(ws, L, B_RR);
   double *Ps = at<double>(ws, L, B_PS);
@@ -396,24 +399,22 @@ int run_enqueue_front(const Plan &p, const wlc_tables &tb, void *ws, hipStream_t
 
   if (hooks) hooks->begin(WLC_PHASE_TABLES);
   const SubList sl{at<int32_t>(ws, L, B_SOFF), at<int32_t>(ws, L, B_SLEG), at<double>(ws, L, B_SWT)};
-  launch_stage(T, cent, p.n_ell * p.n_sub, U, Pk, Ne, s);
-  launch_spectra(T, cfgT, n_cfg, sl, U, Pk, Ne, cent, X, R, s);
-  launch_project(T, rowR, cfgT, p.n_R, X, R, dR, rR, s);
-  launch_ps(dR, Ps, p.n_ell, c.n_z, p.noise, s);
+  launch_stage(T, cent, p.n_ell * p.n_sub, U, legs, F, s);
   const bool ssc_chi = (c.flags & WLC_FLAG_SSC_CHI) != 0;
   const int n_mg = g_cols(c);
   double *sw = ssc_chi ? at<double>(ws, L, B_SW) : nullptr;
   if (ssc_chi) launch_sigma_w2(T, theta_sky(p), sw, s);
-  launch_gfactor(T, cfgT, n_cfg, sl, U, R, sw, std::sqrt(p.omega), n_mg, G, Gmax, s);
-  launch_tfactor(T, rowR, cfgT, p.n_R, Gmax, Ts, sexp, s);
+  const bool auto_split = c.precision == WLC_BF16_AUTO;
+  double *Gsq = auto_split ? at<double>(ws, L, B_SQ) : nullptr, *gd = auto_split ? at<double>(ws, L, B_GD) : nullptr;
+  double *panel_f = auto_split ? at<double>(ws, L, B_FP) : nullptr;
+  int32_t *last = at<int32_t>(ws, L, B_LAST);
+  launch_spectra(T, cfgT, n_cfg, sl, U, legs, cent, sw, std::sqrt(p.omega), n_mg, X, R, G, Gmax, Gsq, s);
+  launch_rows(T, rowR, cfgT, p.n_R, F, X, R, Gmax, Gsq, p.noise, dR, rR, Ps, Ts, sexp, last, gd, s);
   const bool arows = !p.arow.empty();  // the flattened products run on A-rows in their own order
   const int32_t *arow = arows ? at<int32_t>(ws, L, B_AROW) : nullptr;
-  const int32_t *pos = arows ? at<int32_t>(ws, L, B_POS) : nullptr;
   int32_t *ext = arows ? at<int32_t>(ws, L, B_EXT) : nullptr;
-  if (arows) launch_panel_ext(Ts, arow, p.r_pad, c.n_chi, n_mg, p.k_pad, ext, s);
-  if (c.precision == WLC_BF16_AUTO)
-    launch_split_plan(asm_args(p, ws, L), rowR, Ts, G, p.n_R, n_cfg, c.n_chi, n_mg, at<double>(ws, L, B_SQ),
-                      at<double>(ws, L, B_GD), at<double>(ws, L, B_FP), (int)(p.r_pad / GRAM_TILE), s, pos);
+  if (arows) launch_panel_ext(last, arow, p.r_pad, n_mg, p.k_pad, ext, panel_f, s);
+  if (auto_split) launch_split_share(asm_args(p, ws, L), gd, panel_f, at<int32_t>(ws, L, B_POS), s);
   if (c.flags & WLC_FLAG_NGINS) {
     // the projected one-halo trispectrum of two legs per triangle (the P.T
     // term), in FP64 through the factorisation along chi
@@ -429,10 +430,8 @@ int run_enqueue_front(const Plan &p, const wlc_tables &tb, void *ws, hipStream_t
   if (hooks) hooks->begin(WLC_PHASE_ABUILD);
   if (c.precision != WLC_FP64_CHI) {
     const int fmt = c.precision == WLC_FP64 ? 0 : c.precision == WLC_BF16 ? 1 : c.precision == WLC_FP32 ? 3 : 2;
-    const bool auto_split = c.precision == WLC_BF16_AUTO;
     launch_abuild(fmt, rowR, Ts, G, p.n_R, p.r_pad, c.n_chi, n_mg, p.k_pad, p.k_pad, at<void>(ws, L, B_A0),
-                  at<void>(ws, L, B_A1), s, auto_split ? at<double>(ws, L, B_FP) : nullptr,
-                  auto_split ? split_lim(p) : 0.0, arow, ext);
+                  at<void>(ws, L, B_A1), s, panel_f, auto_split ? split_lim(p) : 0.0, arow, ext);
   }
   if (hooks) hooks->end(WLC_PHASE_ABUILD);
   return hip_check(hipGetLastError(), "run launch");

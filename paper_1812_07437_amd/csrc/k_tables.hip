@@ -72,229 +72,88 @@ void launch_validate(const DevTables &T, const double *centres, int n_ell, doubl
 }
 
 // ------------------------------------------------------------- staging
-// U[b][n][m] = u(m, c_b / chi_n) (0 above k_max); Pk, Ne [b][n] = P and its
-// logarithmic slope at c_b / chi_n.
-__global__ void k_stage_u(DevTables T, const double *centres, int n_ell, double *U) {
-  const int64_t total = (int64_t)n_ell * T.n_chi * T.n_m_pts;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int mi = (int)(i % T.n_m_pts);
-    const int64_t bn = i / T.n_m_pts;
-    const int n = (int)(bn % T.n_chi), b = (int)(bn / T.n_chi);
-    const double kk = centres[b] / T.chi[n];
-    double v = 0.0;
-    int j; double t;
-    if (kk <= T.k_max && bracket_lnk(T.k, T.n_k, kk, j, t)) {
-      const double *row = T.u + (int64_t)mi * T.n_k;
-      v = exp((1.0 - t) * log(row[j]) + t * log(row[j + 1]));
-    }
-    U[i] = v;
+// One wavefront per (staged ell value l, chi node n): the k interval of
+// l / chi_n is found once for the node (two or three rounds of 64 probes), lanes stride
+// over the masses of U[l][n][m] = u(m, l / chi_n), and the same pass sums
+// I_1^1 over them.  Lanes 0 to 3 hold the four table nodes that P and its
+// logarithmic slope take.  Everything is 0 above k_max.
+// The wavefronts past the last node fill the chi factors that the rows of
+// either kind share, F[4][n_chi]: w chi^-2 and w chi^-4 of the projections
+// (p = 2, 3 legs), sqrt(w) chi^-3 and sqrt(w) chi^-5 of the Gram factor.
+//
+// Bound by the latency of its loads and logarithms: at 30 sub-bins, 256 chi
+// nodes and 128 masses 22 us (with an interval search for every mass 26, and
+// 9 for P and the slope).
+
+// The last j <= nk - 2 with kg[j] <= kk, for kg[0] <= kk <= kg[nk - 1], by a
+// wavefront.
+__device__ __forceinline__ int wave_bracket(const double *kg, int nk, double kk, int lane) {
+  int lo = 0, hi = nk - 1;
+  while (hi - lo > 1) {
+    const int step = (hi - lo + WAVE - 1) / WAVE;
+    const int q = lo + lane * step;
+    const bool below = q < hi && kg[q] <= kk;
+    lo += (max(__popcll(__ballot(below)), 1) - 1) * step;
+    hi = min(hi, lo + step);
   }
+  return min(lo, nk - 2);
 }
 
-__device__ __forceinline__ double node_slope(const double *kg, const double *row, int nk, int j) {
-  const int a = j > 0 ? j - 1 : 0, b = j < nk - 1 ? j + 1 : nk - 1;
-  return (log(row[b]) - log(row[a])) / (log(kg[b]) - log(kg[a]));
-}
-
-__global__ void k_stage_p(DevTables T, const double *centres, int n_ell, double *Pk, double *Ne) {
-  const int64_t total = (int64_t)n_ell * T.n_chi;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int n = (int)(i % T.n_chi), b = (int)(i / T.n_chi);
-    const double kk = centres[b] / T.chi[n];
-    double pv = 0.0, nv = 0.0;
-    int j; double t;
-    if (kk <= T.k_max && bracket_lnk(T.k, T.n_k, kk, j, t)) {
-      const double *row = T.P + (int64_t)n * T.n_k;
-      pv = exp((1.0 - t) * log(row[j]) + t * log(row[j + 1]));
-      nv = (1.0 - t) * node_slope(T.k, row, T.n_k, j) + t * node_slope(T.k, row, T.n_k, j + 1);
-    }
-    Pk[i] = pv;
-    Ne[i] = nv;
-  }
-}
-
-void launch_stage(const DevTables &T, const double *centres, int n_ell, double *U, double *Pk, double *Ne,
-                  hipStream_t s) {
-  const int64_t tu = (int64_t)n_ell * T.n_chi * T.n_m_pts;
-  const int gu = (int)std::min<int64_t>((tu + 255) / 256, 65536);
-  hipLaunchKernelGGL(k_stage_u, dim3(gu), dim3(256), 0, s, T, centres, n_ell, U);
-  const int64_t tp = (int64_t)n_ell * T.n_chi;
-  const int gp = (int)std::min<int64_t>((tp + 255) / 256, 65536);
-  hipLaunchKernelGGL(k_stage_p, dim3(gp), dim3(256), 0, s, T, centres, n_ell, Pk, Ne);
-}
-
-// ------------------------------------------------------------- 3-D spectra
-// One wavefront per (configuration, chi node): for each entry of the
-// configuration's averaging list (its bin centres, or its sub-bins), lanes
-// stride over the mass nodes, a wavefront reduction gives every mass
-// integral, and lane 0 adds the entry's weighted X and R.
-__device__ __forceinline__ double cosine3(double ki, double kj, double kl) {
-  return (kl * kl - ki * ki - kj * kj) / (2.0 * ki * kj);
-}
-
-// X and R at one ell-triple (kind 3) or ell (kind 2) and chi node; valid on
-// lane 0.  l0, l1, l2 index the staged ell values.
-__device__ void spectrum_at(const DevTables &T, int kind, int l0, int l1, int l2, int n, const double *U,
-                            const double *Pk, const double *Ne, const double *centres, int lane, double &X,
-                            double &R) {
-  const double chi = T.chi[n];
-  double lmax = centres[l0];
-  if (kind == 3) lmax = fmax(lmax, fmax(centres[l1], centres[l2]));
-  X = R = 0.0;
-  if (lmax / chi > T.k_max) return;
+__global__ __launch_bounds__(256) void k_stage(DevTables T, const double *__restrict__ centres, int n_ls, double *U,
+                                               LegTerm *legs, double *F) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * (256 / WAVE) + threadIdx.x / WAVE);
   const int nm = T.n_m_pts;
-  const double inv_rho = 1.0 / T.rho;
-  if (kind == 2) {
-    const double *Ub = U + ((size_t)l0 * T.n_chi + n) * nm;
-    double I11 = 0.0, I20 = 0.0, I21 = 0.0;
-    for (int mi = lane; mi < nm; mi += WAVE) {
-      const double x = T.m[mi] * inv_rho;
-      const double wn = T.w_m[mi] * T.n_m[mi];
-      const double b1 = T.b1 ? T.b1[mi] : 1.0;
-      const double uu = Ub[mi];
-      I11 += wn * b1 * x * uu;
-      I20 += wn * x * x * uu * uu;
-      I21 += wn * b1 * x * x * uu * uu;
-    }
-    I11 = wave_sum(I11); I20 = wave_sum(I20); I21 = wave_sum(I21);
-    if (lane == 0) {
-      const double P = Pk[(size_t)l0 * T.n_chi + n], ne = Ne[(size_t)l0 * T.n_chi + n];
-      const double Rlin = 47.0 / 21.0 * P - ne * P / 3.0;
-      X = I20 + I11 * I11 * P;
-      R = I11 * I11 * Rlin + I21;
+  if (item >= n_ls * T.n_chi) {
+    const int q = (item - n_ls * T.n_chi) * WAVE + lane;
+    if (q < 4 * T.n_chi) {
+      const int f = q / T.n_chi, n = q % T.n_chi;
+      const double w = T.w_chi[n];
+      F[q] = f < 2 ? w * pow(T.chi[n], f == 0 ? -2.0 : -4.0) : sqrt(w) * pow(T.chi[n], f == 2 ? -3.0 : -5.0);
     }
     return;
   }
-  const int lg[3] = {l0, l1, l2};
-  const double *Ua = U + ((size_t)l0 * T.n_chi + n) * nm;
-  const double *Ub = U + ((size_t)l1 * T.n_chi + n) * nm;
-  const double *Uc = U + ((size_t)l2 * T.n_chi + n) * nm;
-  double I11[3] = {0, 0, 0}, I21[3] = {0, 0, 0}, I22[3] = {0, 0, 0}, I30 = 0.0, I31 = 0.0;
-  for (int mi = lane; mi < nm; mi += WAVE) {
-    const double x = T.m[mi] * inv_rho;
-    const double wn = T.w_m[mi] * T.n_m[mi];
-    const double b1 = T.b1 ? T.b1[mi] : 1.0;
-    const double b2 = T.b2 ? T.b2[mi] : 0.0;
-    const double u[3] = {Ua[mi], Ub[mi], Uc[mi]};
-    const double w1 = wn * x, w2 = wn * x * x, w3 = wn * x * x * x;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const double ubc = u[(a + 1) % 3] * u[(a + 2) % 3];
-      I11[a] += w1 * b1 * u[a];
-      I21[a] += w2 * b1 * ubc;
-      I22[a] += w2 * b2 * ubc;
+  const int l = item / T.n_chi, n = item % T.n_chi;
+  const double kk = centres[l] / T.chi[n];
+  double *Uo = U + (size_t)item * nm;
+  LegTerm leg = {0.0, 0.0, 0.0, 0.0, 0.0};
+  if (kk <= T.k_max && kk >= T.k[0] && kk <= T.k[T.n_k - 1]) {
+    const int j = wave_bracket(T.k, T.n_k, kk, lane);
+    // nodes j - 1 .. j + 2, the end nodes twice at the ends of the table
+    const int jn = min(max(j - 1 + (lane & 3), 0), T.n_k - 1);
+    const double lk = log(T.k[jn]), lp = log(T.P[(size_t)n * T.n_k + jn]);
+    const double k0 = __shfl(lk, 0), k1 = __shfl(lk, 1), k2 = __shfl(lk, 2), k3 = __shfl(lk, 3);
+    const double p0 = __shfl(lp, 0), p1 = __shfl(lp, 1), p2 = __shfl(lp, 2), p3 = __shfl(lp, 3);
+    const double t = (log(kk) - k1) / (k2 - k1);
+    double i1 = 0.0;
+    for (int mi = lane; mi < nm; mi += WAVE) {
+      const double *row = T.u + (size_t)mi * T.n_k + j;
+      const double u = exp((1.0 - t) * log(row[0]) + t * log(row[1]));
+      Uo[mi] = u;
+      i1 += T.w_m[mi] * T.n_m[mi] * (T.b1 ? T.b1[mi] : 1.0) * (T.m[mi] / T.rho) * u;
     }
-    const double u3 = u[0] * u[1] * u[2];
-    I30 += w3 * u3;
-    I31 += w3 * b1 * u3;
+    leg.i1 = wave_sum(i1);
+    leg.p = exp((1.0 - t) * p1 + t * p2);
+    leg.ne = (1.0 - t) * ((p2 - p0) / (k2 - k0)) + t * ((p3 - p1) / (k3 - k1));
+    leg.lin = leg.i1 * leg.p;
+    leg.resp = leg.i1 * (47.0 / 21.0 * leg.p - leg.ne * leg.p / 3.0);
+  } else {
+    for (int mi = lane; mi < nm; mi += WAVE) Uo[mi] = 0.0;
   }
-#pragma unroll
-  for (int a = 0; a < 3; ++a) { I11[a] = wave_sum(I11[a]); I21[a] = wave_sum(I21[a]); I22[a] = wave_sum(I22[a]); }
-  I30 = wave_sum(I30);
-  I31 = wave_sum(I31);
-  if (lane == 0) {
-    double P[3], ne[3], kv[3], Rlin[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      P[a] = Pk[(size_t)lg[a] * T.n_chi + n];
-      ne[a] = Ne[(size_t)lg[a] * T.n_chi + n];
-      kv[a] = centres[lg[a]] / chi;
-      Rlin[a] = 47.0 / 21.0 * P[a] - ne[a] * P[a] / 3.0;
-    }
-    double two_halo = 0.0, resp_cyc = 0.0, Bpt = 0.0, Bg2 = 0.0, dil = 0.0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      two_halo += I11[a] * I21[a] * P[a];
-      resp_cyc += I11[a] * I22[a] * P[a] + I11[a] * I21[a] * Rlin[a];
-      const int i = a, j = (a + 1) % 3, l = (a + 2) % 3;
-      const double mu = cosine3(kv[i], kv[j], kv[l]);
-      const double F = 5.0 / 7.0 + 0.5 * mu * (kv[i] / kv[j] + kv[j] / kv[i]) + 2.0 / 7.0 * mu * mu;
-      Bpt += 2.0 * F * P[i] * P[j];
-      Bg2 += 2.0 * (mu * mu - 1.0) * P[i] * P[j];
-      dil += 2.0 * F * P[i] * P[j] * (ne[i] + ne[j]);
-    }
-    const double I111 = I11[0] * I11[1] * I11[2];
-    X = I30 + two_halo + I111 * Bpt;
-    R = I111 * (433.0 / 126.0 * Bpt + 5.0 / 126.0 * Bg2 - dil / 3.0) + resp_cyc + I31;
-  }
+  if (lane == 0) legs[item] = leg;
 }
 
-__global__ void k_spectra(DevTables T, const int32_t *cfgT, int n_cfg, SubList sl, const double *U,
-                          const double *Pk, const double *Ne, const double *centres, double *X, double *R) {
-  const int lane = threadIdx.x & (WAVE - 1);
-  const int64_t item = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
-  if (item >= (int64_t)n_cfg * T.n_chi) return;
-  const int c = (int)(item / T.n_chi), n = (int)(item % T.n_chi);
-  const int kind = cfgT[4 * c];
-  double xs = 0.0, rs = 0.0;
-  for (int e = sl.off[c]; e < sl.off[c + 1]; ++e) {
-    double xe, re;
-    spectrum_at(T, kind, sl.leg[4 * e], sl.leg[4 * e + 1], sl.leg[4 * e + 2], n, U, Pk, Ne, centres, lane, xe,
-                re);
-    xs += sl.w[e] * xe;
-    rs += sl.w[e] * re;
-  }
-  if (lane == 0) {
-    X[item] = xs;
-    R[item] = rs;
-  }
+void launch_stage(const DevTables &T, const double *centres, int n_ls, double *U, LegTerm *legs, double *F,
+                  hipStream_t s) {
+  const int64_t waves = (int64_t)n_ls * T.n_chi + (4 * T.n_chi + WAVE - 1) / WAVE;
+  hipLaunchKernelGGL(k_stage, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, T, centres, n_ls, U, legs, F);
 }
 
-void launch_spectra(const DevTables &T, const int32_t *cfgT, int n_cfg, const SubList &sl, const double *U,
-                    const double *Pk, const double *Ne, const double *centres, double *X, double *R, hipStream_t s) {
-  const int64_t items = (int64_t)n_cfg * T.n_chi;
-  const int g = (int)((items + 3) / 4);
-  hipLaunchKernelGGL(k_spectra, dim3(g), dim3(256), 0, s, T, cfgT, n_cfg, sl, U, Pk, Ne, centres, X, R);
-}
-
-// ------------------------------------------------------------- projection
-// One wavefront per distinct row: lanes stride over chi, then reduce.
-__global__ void k_project(DevTables T, const int32_t *rowR, const int32_t *cfgT, int64_t n_R, const double *X,
-                          const double *R, double *dR, double *rR) {
-  const int lane = threadIdx.x & (WAVE - 1);
-  const int64_t row = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
-  if (row >= n_R) return;
-  const int c = rowR[4 * row];
-  const int p = cfgT[4 * c];
-  int z[3] = {rowR[4 * row + 1], rowR[4 * row + 2], rowR[4 * row + 3]};
-  double sd = 0.0, sr = 0.0;
-  for (int n = lane; n < T.n_chi; n += WAVE) {
-    const double chi = T.chi[n];
-    double tw = T.w_chi[n] * pow(chi, 2.0 - 2.0 * p);
-    for (int q = 0; q < p; ++q) tw *= T.W[(size_t)z[q] * T.n_chi + n];
-    sd += tw * X[(size_t)c * T.n_chi + n];
-    sr += tw * R[(size_t)c * T.n_chi + n];
-  }
-  sd = wave_sum(sd);
-  sr = wave_sum(sr);
-  if (lane == 0) { dR[row] = sd; rR[row] = sr; }
-}
-
-void launch_project(const DevTables &T, const int32_t *rowR, const int32_t *cfgT, int64_t n_R, const double *X,
-                    const double *R, double *dR, double *rR, hipStream_t s) {
-  const int g = (int)((n_R + 3) / 4);
-  hipLaunchKernelGGL(k_project, dim3(g), dim3(256), 0, s, T, rowR, cfgT, n_R, X, R, dR, rR);
-}
-
-// Shot-noise power P^s_ij(l_b) = P_ij(l_b) + delta_ij sigma_eps^2 / n_i
-// (eq. ShotNoise); the power-spectrum rows lead the distinct rows.
-__global__ void k_ps(const double *dR, double *Ps, int n_ell, int n_z, double noise) {
-  const int total = n_ell * n_z * n_z;
-  const int npair = n_z * (n_z + 1) / 2;
-  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < total; q += gridDim.x * blockDim.x) {
-    const int j = q % n_z, i = (q / n_z) % n_z, b = q / (n_z * n_z);
-    const int lo = i < j ? i : j, hi = i < j ? j : i;
-    const int rank = lo * n_z - lo * (lo - 1) / 2 + (hi - lo);
-    Ps[q] = dR[(size_t)b * npair + rank] + (i == j ? noise : 0.0);
-  }
-}
-
-void launch_ps(const double *dR, double *Ps, int n_ell, int n_z, double noise, hipStream_t s) {
-  const int total = n_ell * n_z * n_z;
-  hipLaunchKernelGGL(k_ps, dim3((total + 255) / 256), dim3(256), 0, s, dR, Ps, n_ell, n_z, noise);
-}
-
-// ------------------------------------------------------------- Gram factor
+// ------------------------------------------------------------- 3-D spectra
+// One wavefront per (configuration, chi node) gives the spectrum X, its
+// response R and the Gram factor G, all averaged over the configuration's
+// list of ell-triples (its bin centres, or its sub-bins, with weights w_e).
+//
 // The one-halo (p_a + p_b)-point function factorises over the legs of each
 // row (eq. General1h), so
 //   A[row][(n, m)] = sqrt(w_n) chi_n^-(2p-1) prod_i W_i(chi_n)        (= T[row][n])
@@ -304,81 +163,217 @@ void launch_ps(const double *dR, double *Ps, int n_ell, int n_z, double noise, h
 // WLSSCflatskyLimber resolved along chi,
 //   sum_n w_n sigma_W^2(chi_n) chi_n^(2-2p) prod W R_cfg(chi_n) (same for b),
 // as G[cfg][n][n_m] = sqrt(Omega) chi_n sqrt(sigma_W^2(chi_n)) R[cfg][n].
-__global__ void k_gfactor(DevTables T, const int32_t *cfgT, int n_cfg, SubList sl, const double *U,
-                          const double *R, const double *sw, double sq_omega, int n_mg, double *G, double *Gmax) {
+//
+// Every mass integral of X and R is linear in products of u over legs, with
+// factors (I_1^1 P and I_1^1 P_response of the other leg) that do not depend on the
+// mass, so the list is summed first, for each mass, and one reduction over the
+// masses serves the whole list:
+//   t = sum_e w_e u0 u1 u2,  h = sum_e w_e sum_a (I11 P)_a u_b u_c,  r alike with the
+//   response factor;  X = sum_m w_m n_m x^2 (x t + b1 h) + tree terms,
+//   R = sum_m w_m n_m x^2 (b2 h + b1 r + b1 x t) + tree terms.
+// Entries that share their first two legs are consecutive, and only the third
+// one's u is read for each.  The tree terms take one entry per lane.
+//
+// At 74 configurations of up to 27 sub-bin triples, 256 chi nodes and 128
+// masses 87 us, where a reduction over the masses for every integral of every
+// entry and a second pass for G took 560 + 119; bound by the loads of u and
+// FP64 arithmetic.
+__device__ __forceinline__ double cosine3(double ki, double kj, double kl) {
+  return (kl * kl - ki * ki - kj * kj) / (2.0 * ki * kj);
+}
+
+__global__ __launch_bounds__(256) void k_spectra(DevTables T, const int32_t *__restrict__ cfgT, int n_cfg,
+                                                 SubList sl, const double *__restrict__ U,
+                                                 const LegTerm *__restrict__ legs,
+                                                 const double *__restrict__ centres, const double *__restrict__ sw,
+                                                 double sq_omega, int n_mg, double *X, double *R, double *G,
+                                                 double *Gmax, double *Gsq) {
   const int lane = threadIdx.x & (WAVE - 1);
-  const int64_t item = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
-  if (item >= (int64_t)n_cfg * T.n_chi) return;
-  const int c = (int)(item / T.n_chi), n = (int)(item % T.n_chi);
-  const int kind = cfgT[4 * c];
-  const int nm = T.n_m_pts;
-  const double inv_rho = 1.0 / T.rho;
+  const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * (256 / WAVE) + threadIdx.x / WAVE);
+  if (item >= n_cfg * T.n_chi) return;
+  const int c = item / T.n_chi, n = item % T.n_chi, nm = T.n_m_pts;
+  const bool tri = cfgT[4 * c] == 3;
   const int e0 = sl.off[c], e1 = sl.off[c + 1];
-  double mx = 0.0;
-  double *Gout = G + (size_t)item * n_mg;
-  for (int mi = lane; mi < nm; mi += WAVE) {
-    const double x = T.m[mi] * inv_rho;
-    double g = 0.0;
-    // the average over the configuration's entries (one entry of weight 1
-    // at the bin centres)
-    for (int e = e0; e < e1; ++e) {
-      const double *U0 = U + ((size_t)sl.leg[4 * e] * T.n_chi + n) * nm;
-      const double *U1 = kind == 3 ? U + ((size_t)sl.leg[4 * e + 1] * T.n_chi + n) * nm : U0;
-      double ge = sqrt(T.w_m[mi] * T.n_m[mi]) * x * x * U0[mi] * U1[mi];
-      if (kind == 3) ge *= x * U[((size_t)sl.leg[4 * e + 2] * T.n_chi + n) * nm + mi];
-      g += sl.w[e] * ge;
+  const int4 *lists = (const int4 *)sl.leg;
+  const double chi = T.chi[n];
+  double xs = 0.0, rs = 0.0, mx = 0.0, sq = 0.0;
+  // the terms without a mass integral over more than one leg
+  for (int e = e0 + lane; e < e1; e += WAVE) {
+    const int4 q = lists[e];
+    const double w = sl.w[e];
+    const LegTerm a = legs[(size_t)q.x * T.n_chi + n];
+    if (!tri) {
+      xs += w * a.i1 * a.i1 * a.p;
+      rs += w * a.i1 * a.resp;
+      continue;
     }
-    Gout[mi] = g;
-    mx = fmax(mx, fabs(g));
+    const LegTerm b = legs[(size_t)q.y * T.n_chi + n], d = legs[(size_t)q.z * T.n_chi + n];
+    const double P[3] = {a.p, b.p, d.p}, ne[3] = {a.ne, b.ne, d.ne};
+    const double kv[3] = {centres[q.x] / chi, centres[q.y] / chi, centres[q.z] / chi};
+    double Bpt = 0.0, Bg2 = 0.0, dil = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const int j = (i + 1) % 3, l = (i + 2) % 3;
+      const double mu = cosine3(kv[i], kv[j], kv[l]);
+      const double Fk = 5.0 / 7.0 + 0.5 * mu * (kv[i] / kv[j] + kv[j] / kv[i]) + 2.0 / 7.0 * mu * mu;
+      Bpt += 2.0 * Fk * P[i] * P[j];
+      Bg2 += 2.0 * (mu * mu - 1.0) * P[i] * P[j];
+      dil += 2.0 * Fk * P[i] * P[j] * (ne[i] + ne[j]);
+    }
+    const double I111 = w * a.i1 * b.i1 * d.i1;
+    xs += I111 * Bpt;
+    rs += I111 * (433.0 / 126.0 * Bpt + 5.0 / 126.0 * Bg2 - dil / 3.0);
   }
-  if (sw && lane == 0) {
-    const double g = sq_omega * T.chi[n] * sqrt(sw[n]) * R[item];
-    Gout[nm] = g;
+  double *Go = G + (size_t)item * n_mg;
+  const size_t at = (size_t)n * nm, step = (size_t)T.n_chi * nm;
+  for (int m0 = 0; m0 < nm; m0 += 2 * WAVE) {
+    const bool in0 = m0 + lane < nm, in1 = m0 + WAVE + lane < nm;
+    const int mi[2] = {in0 ? m0 + lane : nm - 1, in1 ? m0 + WAVE + lane : nm - 1};
+    double t[2] = {0.0, 0.0}, h[2] = {0.0, 0.0}, r[2] = {0.0, 0.0};
+    int4 q = lists[e0];
+    for (int e = e0; e < e1;) {
+      const int l0 = q.x, l1 = tri ? q.y : q.x;
+      const double *U0 = U + l0 * step + at, *U1 = U + l1 * step + at;
+      const double u0[2] = {U0[mi[0]], U0[mi[1]]}, u1[2] = {U1[mi[0]], U1[mi[1]]};
+      if (!tri) {
+        const double w = sl.w[e];
+        t[0] += w * (u0[0] * u1[0]);
+        t[1] += w * (u0[1] * u1[1]);
+        if (++e < e1) q = lists[e];
+        continue;
+      }
+      const LegTerm &a0 = legs[(size_t)l0 * T.n_chi + n], &a1 = legs[(size_t)l1 * T.n_chi + n];
+      double v[2] = {0.0, 0.0}, lin = 0.0, resp = 0.0;
+      do {
+        const double w = sl.w[e];
+        const double *U2 = U + q.z * step + at;
+        const LegTerm &a2 = legs[(size_t)q.z * T.n_chi + n];
+        v[0] += w * U2[mi[0]];
+        v[1] += w * U2[mi[1]];
+        lin += w * a2.lin;
+        resp += w * a2.resp;
+        if (++e == e1) break;
+        q = lists[e];
+      } while (q.x == l0 && q.y == l1);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const double u01 = u0[j] * u1[j];
+        t[j] += u01 * v[j];
+        h[j] += (a0.lin * u1[j] + a1.lin * u0[j]) * v[j] + u01 * lin;
+        r[j] += (a0.resp * u1[j] + a1.resp * u0[j]) * v[j] + u01 * resp;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      if (!(j == 0 ? in0 : in1)) continue;
+      const double x = T.m[mi[j]] / T.rho, wn = T.w_m[mi[j]] * T.n_m[mi[j]];
+      const double b1 = T.b1 ? T.b1[mi[j]] : 1.0, b2 = T.b2 ? T.b2[mi[j]] : 0.0;
+      const double f = tri ? x * t[j] : t[j];
+      xs += wn * x * x * (f + b1 * h[j]);
+      rs += wn * x * x * (b2 * h[j] + b1 * (r[j] + f));
+      const double g = sqrt(wn) * x * x * f;
+      Go[mi[j]] = g;
+      mx = fmax(mx, fabs(g));
+      sq += g * g;
+    }
+  }
+  xs = wave_sum(xs);
+  rs = wave_sum(rs);
+  if (sw) {
+    const double g = sq_omega * chi * sqrt(sw[n]) * rs;
+    if (lane == 0) {
+      Go[nm] = g;
+      sq += g * g;
+    }
     mx = fmax(mx, fabs(g));
   }
   mx = wave_max(mx);
-  if (lane == 0) Gmax[item] = mx;
+  if (Gsq) sq = wave_sum(sq);
+  if (lane == 0) {
+    X[item] = xs;
+    R[item] = rs;
+    Gmax[item] = mx;
+    if (Gsq) Gsq[item] = sq;
+  }
 }
 
-void launch_gfactor(const DevTables &T, const int32_t *cfgT, int n_cfg, const SubList &sl, const double *U,
-                    const double *R, const double *sw, double sq_omega, int n_mg, double *G, double *Gmax,
-                    hipStream_t s) {
+void launch_spectra(const DevTables &T, const int32_t *cfgT, int n_cfg, const SubList &sl, const double *U,
+                    const LegTerm *legs, const double *centres, const double *sw, double sq_omega, int n_mg, double *X,
+                    double *R, double *G, double *Gmax, double *Gsq, hipStream_t s) {
   const int64_t items = (int64_t)n_cfg * T.n_chi;
-  hipLaunchKernelGGL(k_gfactor, dim3((int)((items + 3) / 4)), dim3(256), 0, s, T, cfgT, n_cfg, sl, U, R, sw,
-                     sq_omega, n_mg, G, Gmax);
+  hipLaunchKernelGGL(k_spectra, dim3((unsigned)((items + 3) / 4)), dim3(256), 0, s, T, cfgT, n_cfg, sl, U, legs,
+                     centres, sw, sq_omega, n_mg, X, R, G, Gmax, Gsq);
 }
 
-// Per distinct row: T[n] and the row exponent s = -e with
-// max_k |A[row][k]| = f 2^e, f in [0.5, 1); Ts[row][n] = 2^s T[n].
-__global__ void k_tfactor(DevTables T, const int32_t *rowR, const int32_t *cfgT, int64_t n_R, const double *Gmax,
-                          double *Ts, int32_t *sexp) {
+// ------------------------------------------------------------- rows
+// One wavefront per distinct row, lanes over chi: the projections d and r,
+// the row's factor T[n] with the exponent s = -e, max_k |A[row][k]| = f 2^e,
+// f in [0.5, 1), Ts[row][n] = 2^s T[n], the last chi node with a nonzero Ts
+// (-1: none) and, with Gsq (sum_m G^2), the row's Gram diagonal
+// sum_n Ts^2 Gsq.  The power-spectrum rows lead, and also give the shot-noise power
+// P^s_ij(l_b) = P_ij(l_b) + delta_ij sigma_eps^2 / n_i (eq. ShotNoise).
+// Bound by the write of Ts: 33165 rows of 512 nodes take 113 us (1.3 TB/s), against
+// 133 + 285 for projection and factor with powers of chi for every row.
+__global__ __launch_bounds__(256) void k_rows(DevTables T, const int32_t *__restrict__ rowR,
+                                              const int32_t *__restrict__ cfgT, int64_t n_R,
+                                              const double *__restrict__ F, const double *__restrict__ X,
+                                              const double *__restrict__ R, const double *__restrict__ Gmax,
+                                              const double *__restrict__ Gsq, double noise, double *dR, double *rR,
+                                              double *Ps, double *Ts, int32_t *sexp, int32_t *last, double *gd) {
   const int lane = threadIdx.x & (WAVE - 1);
-  const int64_t row = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
+  const int64_t row = (int64_t)blockIdx.x * (256 / WAVE) + threadIdx.x / WAVE;
   if (row >= n_R) return;
-  const int c = rowR[4 * row];
-  const int p = cfgT[4 * c];
-  const int z[3] = {rowR[4 * row + 1], rowR[4 * row + 2], rowR[4 * row + 3]};
-  double mx = 0.0;
-  for (int n = lane; n < T.n_chi; n += WAVE) {
-    const double chi = T.chi[n];
-    double t = sqrt(T.w_chi[n]) * pow(chi, 1.0 - 2.0 * p);
-    for (int q = 0; q < p; ++q) t *= T.W[(size_t)z[q] * T.n_chi + n];
-    mx = fmax(mx, fabs(t) * Gmax[(size_t)c * T.n_chi + n]);
+  const int4 rc = ((const int4 *)rowR)[row];
+  const int c = rc.x, nc = T.n_chi;
+  const bool tri = cfgT[4 * c] == 3;
+  const double *W0 = T.W + (size_t)rc.y * nc, *W1 = T.W + (size_t)rc.z * nc;
+  const double *W2 = tri ? T.W + (size_t)rc.w * nc : nullptr;
+  const double *Fp = F + (tri ? nc : 0), *Ft = Fp + 2 * nc;
+  const double *Xc = X + (size_t)c * nc, *Rc = R + (size_t)c * nc, *gm = Gmax + (size_t)c * nc;
+  double sd = 0.0, sr = 0.0, mx = 0.0;
+  for (int n = lane; n < nc; n += WAVE) {
+    double w = W0[n] * W1[n];
+    if (tri) w *= W2[n];
+    const double pw = Fp[n] * w;
+    sd += pw * Xc[n];
+    sr += pw * Rc[n];
+    mx = fmax(mx, fabs(Ft[n] * w) * gm[n]);
   }
   mx = wave_max(mx);
   const int s = -exp2_of(mx);
-  for (int n = lane; n < T.n_chi; n += WAVE) {
-    const double chi = T.chi[n];
-    double t = sqrt(T.w_chi[n]) * pow(chi, 1.0 - 2.0 * p);
-    for (int q = 0; q < p; ++q) t *= T.W[(size_t)z[q] * T.n_chi + n];
-    Ts[(size_t)row * T.n_chi + n] = ldexp(t, s);
+  double dg = 0.0;
+  int top = -1;
+  for (int n = lane; n < nc; n += WAVE) {
+    double w = W0[n] * W1[n];
+    if (tri) w *= W2[n];
+    const double t = ldexp(Ft[n] * w, s);
+    Ts[(size_t)row * nc + n] = t;
+    if (t != 0.0) top = n;
+    if (Gsq) dg += t * t * Gsq[(size_t)c * nc + n];
   }
-  if (lane == 0) sexp[row] = s;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, WAVE));
+  sd = wave_sum(sd);
+  sr = wave_sum(sr);
+  if (Gsq) dg = wave_sum(dg);
+  if (lane == 0) {
+    dR[row] = sd;
+    rR[row] = sr;
+    sexp[row] = s;
+    last[row] = top;
+    if (Gsq) gd[row] = dg;
+    if (!tri) {  // configuration c of kind 2 is ell-bin c
+      double *P = Ps + (size_t)c * T.n_z * T.n_z;
+      P[rc.y * T.n_z + rc.z] = P[rc.z * T.n_z + rc.y] = sd + (rc.y == rc.z ? noise : 0.0);
+    }
+  }
 }
 
-void launch_tfactor(const DevTables &T, const int32_t *rowR, const int32_t *cfgT, int64_t n_R, const double *Gmax,
-                    double *Ts, int32_t *sexp, hipStream_t s) {
-  hipLaunchKernelGGL(k_tfactor, dim3((int)((n_R + 3) / 4)), dim3(256), 0, s, T, rowR, cfgT, n_R, Gmax, Ts, sexp);
+void launch_rows(const DevTables &T, const int32_t *rowR, const int32_t *cfgT, int64_t n_R, const double *F,
+                 const double *X, const double *R, const double *Gmax, const double *Gsq, double noise, double *dR,
+                 double *rR, double *Ps, double *Ts, int32_t *sexp, int32_t *last, double *gd, hipStream_t s) {
+  hipLaunchKernelGGL(k_rows, dim3((unsigned)((n_R + 3) / 4)), dim3(256), 0, s, T, rowR, cfgT, n_R, F, X, R, Gmax,
+                     Gsq, noise, dR, rR, Ps, Ts, sexp, last, gd);
 }
 
 // ------------------------------------------------------------- two-leg factors
@@ -696,33 +691,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FMT == 1 ? 
   }
 }
 
-// One workgroup per 256-row panel of A-rows: each thread scans its row's T
-// back from the last chi node to the last nonzero one; the panel keeps the
-// largest count of k-blocks (the k of node n are n N_M .. n N_M + N_M - 1).
-__global__ __launch_bounds__(256) void k_panel_ext(const double *__restrict__ Ts, const int32_t *__restrict__ arow,
-                                                  int n_chi, int n_mg, int64_t k_pad, int32_t *__restrict__ ext) {
+// One workgroup per 256-row panel of A-rows: the panel keeps the largest count
+// of k-blocks (the k of node n are n N_M .. n N_M + N_M - 1).
+__global__ __launch_bounds__(256) void k_panel_ext(const int32_t *__restrict__ last, const int32_t *__restrict__ arow,
+                                                  int n_mg, int64_t k_pad, int32_t *__restrict__ ext,
+                                                  double *__restrict__ panel_f) {
   __shared__ int32_t best;
   if (threadIdx.x == 0) best = 0;
   __syncthreads();
   const int e = arow[(int64_t)blockIdx.x * 256 + threadIdx.x];
-  int last = -1;
-  if (e >= 0) {
-    const double *t = Ts + (size_t)e * n_chi;
-    for (int n = n_chi - 1; n >= 0; --n)
-      if (t[n] != 0.0) {
-        last = n;
-        break;
-      }
-  }
-  const int64_t kb = min(((int64_t)(last + 1) * n_mg + GRAM_KB - 1) / GRAM_KB, k_pad / GRAM_KB);
+  const int top = e >= 0 ? last[e] : -1;
+  const int64_t kb = min(((int64_t)(top + 1) * n_mg + GRAM_KB - 1) / GRAM_KB, k_pad / GRAM_KB);
   if (kb > 0) atomicMax(&best, (int32_t)kb);
   __syncthreads();
-  if (threadIdx.x == 0) ext[blockIdx.x] = best;
+  if (threadIdx.x == 0) {
+    ext[blockIdx.x] = best;
+    if (panel_f) {
+      panel_f[blockIdx.x] = 0.0;
+      if (blockIdx.x == 0) panel_f[gridDim.x] = 0.0;
+    }
+  }
 }
 
-void launch_panel_ext(const double *Ts, const int32_t *arow, int64_t r_pad, int n_chi, int n_mg, int64_t k_pad,
-                      int32_t *ext, hipStream_t s) {
-  hipLaunchKernelGGL(k_panel_ext, dim3((unsigned)(r_pad / 256)), dim3(256), 0, s, Ts, arow, n_chi, n_mg, k_pad, ext);
+void launch_panel_ext(const int32_t *last, const int32_t *arow, int64_t r_pad, int n_mg, int64_t k_pad, int32_t *ext,
+                      double *panel_f, hipStream_t s) {
+  hipLaunchKernelGGL(k_panel_ext, dim3((unsigned)(r_pad / 256)), dim3(256), 0, s, last, arow, n_mg, k_pad, ext,
+                     panel_f);
 }
 
 void launch_abuild(int fmt, const int32_t *rowR, const double *Ts, const double *G, int64_t n_R, int64_t r_pad,

@@ -25,38 +25,53 @@ constexpr double PI_D = 3.14159265358979323846;
 //   2 <= x < 25  Bessel's integral J1(x) = (1/pi) int_0^pi cos(t - x sin t) dt
 //                (9.1.21) by the trapezoid rule on 32 intervals; for this
 //                periodic analytic integrand the rule is exact up to
-//                J_65(x) - J_63(x), below 1e-18 here, and the two end terms
-//                cancel (cos 0 + cos pi = 0);
+//                J_65(x) - J_63(x), below 1e-18 here, the two end terms
+//                cancel (cos 0 + cos pi = 0), and those at t and pi - t add to
+//                cos(t - x sin t) - cos(t + x sin t) = 2 sin t sin(x sin t);
 //   x >= 25      Hankel's expansion (9.2.5, 9.2.9, 9.2.10) with mu = 4:
 //                J1 = sqrt(2 / (pi x)) (P cos w - Q sin w), w = x - 3 pi / 4,
 //                rewritten through sin x and cos x (exactly reduced by the
 //                math library) as (P (sin x - cos x) + Q (sin x + cos x)) /
 //                sqrt(pi x); the terms t_k = t_(k-1) (mu - (2k - 1)^2) / (8 k x)
 //                fall for every k < 2x and are summed down to 1e-17.
-// s_sin[j] = sin(j pi / 32).
-__device__ double bessel_j1(double x, const double *s_sin) {
+// tab[0 .. 15] = sin(j pi / 32), tab[16 + k] = (4 - (2k - 1)^2) / (8 k) with the
+// signs of P and Q, tab[47 + m] = -1 / (4 m (m + 1)).
+constexpr int J1_TERMS = 30, J1_SERIES = 14;
+constexpr int J1_TAB = 16 + J1_TERMS + 1 + J1_SERIES + 1;
+
+__device__ __forceinline__ double bessel_tab(int i) {
+  if (i < 16) return sin(i * (PI_D / 32.0));
+  if (i > 16 + J1_TERMS) {
+    const int m = i - 17 - J1_TERMS;
+    return m == 0 ? 0.0 : -0.25 / (double)(m * (m + 1));
+  }
+  const int k = i - 16;
+  // k = 1, 2, 3, 4, ... contributes +Q, -P, -Q, +P, ...: a sign change at every even k
+  return k == 0 ? 0.0 : (double)(4 - (2 * k - 1) * (2 * k - 1)) / (8.0 * k) * ((k & 1) ? 1.0 : -1.0);
+}
+
+__device__ __forceinline__ double bessel_j1(double x, const double *tab) {
   if (x < 2.0) {
-    const double q = -0.25 * x * x;
+    const double q = x * x;
     double t = 0.5 * x, s = t;
-    for (int m = 1; m <= 14; ++m) {
-      t *= q / (double)(m * (m + 1));
+    for (int m = 1; m <= J1_SERIES; ++m) {
+      t *= q * tab[17 + J1_TERMS + m];
       s += t;
     }
     return s;
   }
   if (x < 25.0) {
     double s = 0.0;
-    for (int j = 1; j < 32; ++j) s += cos(j * (PI_D / 32.0) - x * s_sin[j]);
-    return s * (1.0 / 32.0);
+    for (int j = 1; j < 16; ++j) s += tab[j] * sin(x * tab[j]);
+    return (2.0 * s + sin(x)) * (1.0 / 32.0);
   }
   double P = 1.0, Q = 0.0, t = 1.0;
-  const double inv8x = 0.125 / x;
-  for (int k = 1; k <= 30; ++k) {
-    const double f = (double)((2 * k - 1) * (2 * k - 1));
-    t *= (4.0 - f) * inv8x / (double)k;
-    // k = 1, 2, 3, 4, ... contributes +Q, -P, -Q, +P, ...
-    const double sg = (((k + 1) >> 1) & 1) ? 1.0 : -1.0;
-    if (k & 1) Q += sg * t; else P -= sg * t;
+  const double inv = 1.0 / x;
+  for (int k = 1; k < J1_TERMS; k += 2) {
+    t *= tab[16 + k] * inv;
+    Q += t;
+    t *= tab[17 + k] * inv;
+    P += t;
     if (fabs(t) < 1e-17) break;
   }
   double sx, cx;
@@ -64,42 +79,66 @@ __device__ double bessel_j1(double x, const double *s_sin) {
   return (P * (sx - cx) + Q * (sx + cx)) / sqrt(PI_D * x);
 }
 
-// One block per chi node: threads stride over the window nodes, then a block
-// reduction of the trapezoid sum.
-__global__ __launch_bounds__(256) void k_sigma_w2(DevTables T, double theta, double *sw) {
-  __shared__ double s_sin[32];
-  __shared__ double part[256 / WAVE];
-  if (threadIdx.x < 32) s_sin[threadIdx.x] = sin(threadIdx.x * (PI_D / 32.0));
+// One workgroup per chi node: threads stride over the window nodes, then a
+// block reduction of the trapezoid sum.  STAGED: ln k and ln P of the node's
+// table row are taken once, into LDS (tables of up to SIG_NK nodes, its 64 KB;
+// longer ones are read and their logarithms taken for every window node).  A
+// node's eps^2 P is one exponential of its ln eps.
+//
+// Bound by FP64 arithmetic (two exponentials, a sine and cosine, a square root
+// and two divisions for every node): 256 chi nodes 87 us, against 284 with the
+// interval, four logarithms of the table and twice the sines found for every node.
+constexpr int SIG_THREADS = 512;
+constexpr int SIG_NK = 4000;
+template <bool STAGED>
+__global__ __launch_bounds__(SIG_THREADS) void k_sigma_w2(DevTables T, double theta, double *sw) {
+  extern __shared__ double lds[];  // ln k, ln P [n_k] each
+  __shared__ double tab[J1_TAB];
+  __shared__ double part[SIG_THREADS / WAVE];
+  const int n = blockIdx.x, nk = T.n_k;
+  double *lk = lds, *lp = lds + nk;
+  for (int i = threadIdx.x; i < J1_TAB; i += SIG_THREADS) tab[i] = bessel_tab(i);
+  if constexpr (STAGED)
+    for (int i = threadIdx.x; i < nk; i += SIG_THREADS) {
+      lk[i] = log(T.k[i]);
+      lp[i] = log(T.P[(size_t)n * nk + i]);
+    }
   __syncthreads();
-  const int n = blockIdx.x;
-  const double chi = T.chi[n];
-  const double *row = T.P + (size_t)n * T.n_k;
-  const double l0 = log(T.k[0]), l1 = log(T.k[T.n_k - 1]);
+  auto ln_k = [&](int i) { return STAGED ? lk[i] : log(T.k[i]); };
+  auto ln_p = [&](int i) { return STAGED ? lp[i] : log(T.P[(size_t)n * nk + i]); };
+  const double scale = T.chi[n] * theta;
+  const double l0 = ln_k(0), l1 = ln_k(nk - 1);
   const double h = (l1 - l0) / (WINDOW_NODES - 1);
   double s = 0.0;
-  for (int j = threadIdx.x; j < WINDOW_NODES; j += blockDim.x) {
-    const double eps = j == 0 ? T.k[0] : (j == WINDOW_NODES - 1 ? T.k[T.n_k - 1] : exp(l0 + j * h));
-    const double x = eps * chi * theta;
-    const double win = bessel_j1(x, s_sin) / x;
-    int jj;
-    double t;
-    if (!bracket_lnk(T.k, T.n_k, eps, jj, t)) continue;  // every node lies on the table
-    const double P = exp((1.0 - t) * log(row[jj]) + t * log(row[jj + 1]));
+  for (int j = threadIdx.x; j < WINDOW_NODES; j += SIG_THREADS) {
+    const double le = j == WINDOW_NODES - 1 ? l1 : l0 + j * h;
+    const double eps = exp(le), x = eps * scale;
+    int lo = 0, hi = nk - 1;  // the last lo <= n_k - 2 at or below the node
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (STAGED ? lk[mid] <= le : T.k[mid] <= eps) lo = mid; else hi = mid;
+    }
+    const double k0 = ln_k(lo), t = (le - k0) / (ln_k(lo + 1) - k0);
+    const double win = bessel_j1(x, tab) / x;
     const double w = (j == 0 || j == WINDOW_NODES - 1) ? 0.5 * h : h;
-    s += w * eps * eps * win * win * P;
+    s += w * win * win * exp(2.0 * le + ((1.0 - t) * ln_p(lo) + t * ln_p(lo + 1)));
   }
   s = wave_sum(s);
   if ((threadIdx.x & (WAVE - 1)) == 0) part[threadIdx.x / WAVE] = s;
   __syncthreads();
   if (threadIdx.x == 0) {
     double tot = 0.0;
-    for (int w = 0; w < 256 / WAVE; ++w) tot += part[w];
+    for (int w = 0; w < SIG_THREADS / WAVE; ++w) tot += part[w];
     sw[n] = 2.0 / PI_D * tot;
   }
 }
 
 void launch_sigma_w2(const DevTables &T, double theta, double *sw, hipStream_t s) {
-  hipLaunchKernelGGL(k_sigma_w2, dim3((unsigned)T.n_chi), dim3(256), 0, s, T, theta, sw);
+  if (T.n_k <= SIG_NK)
+    hipLaunchKernelGGL(k_sigma_w2<true>, dim3((unsigned)T.n_chi), dim3(SIG_THREADS), (size_t)T.n_k * 16, s, T, theta,
+                       sw);
+  else
+    hipLaunchKernelGGL(k_sigma_w2<false>, dim3((unsigned)T.n_chi), dim3(SIG_THREADS), 0, s, T, theta, sw);
 }
 
 }  // namespace wlc

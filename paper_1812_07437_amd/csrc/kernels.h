@@ -18,21 +18,26 @@ struct SubList {
   const double *w;
 };
 void launch_validate(const DevTables &T, const double *centres, int n_ell, double theta, int *flags, hipStream_t s);
-void launch_stage(const DevTables &T, const double *centres, int n_ell, double *U, double *Pk, double *Ne,
+// One staged ell value at one chi node: I_1^1, P, the slope of ln P, and the
+// factors I_1^1 P and I_1^1 (47/21 - n_e/3) P of the two-halo terms.
+struct LegTerm {
+  double i1, p, ne, lin, resp;
+};
+// U [n_ls][n_chi][n_m], legs [n_ls][n_chi], F [4][n_chi] (the rows' chi factors)
+void launch_stage(const DevTables &T, const double *centres, int n_ls, double *U, LegTerm *legs, double *F,
                   hipStream_t s);
-void launch_spectra(const DevTables &T, const int32_t *cfgT, int n_cfg, const SubList &sl, const double *U,
-                    const double *Pk, const double *Ne, const double *centres, double *X, double *R, hipStream_t s);
-void launch_project(const DevTables &T, const int32_t *rowR, const int32_t *cfgT, int64_t n_R, const double *X,
-                    const double *R, double *dR, double *rR, hipStream_t s);
-void launch_ps(const double *dR, double *Ps, int n_ell, int n_z, double noise, hipStream_t s);
+// X, R, Gmax (largest |G|) and, where not nullptr, Gsq (sum of G^2): [n_cfg][n_chi].
 // G [n_cfg][n_chi][n_mg]: n_mg = n_m, or n_m + 1 when sw != NULL, the last
 // column then holding sqrt(Omega) chi_n sqrt(sigma_W^2(chi_n)) R[cfg][n] (the
 // super-sample term resolved along chi as one more Gram column).
-void launch_gfactor(const DevTables &T, const int32_t *cfgT, int n_cfg, const SubList &sl, const double *U,
-                    const double *R, const double *sw, double sq_omega, int n_mg, double *G, double *Gmax,
-                    hipStream_t s);
-void launch_tfactor(const DevTables &T, const int32_t *rowR, const int32_t *cfgT, int64_t n_R, const double *Gmax,
-                    double *Ts, int32_t *sexp, hipStream_t s);
+void launch_spectra(const DevTables &T, const int32_t *cfgT, int n_cfg, const SubList &sl, const double *U,
+                    const LegTerm *legs, const double *centres, const double *sw, double sq_omega, int n_mg, double *X,
+                    double *R, double *G, double *Gmax, double *Gsq, hipStream_t s);
+// last [n_R]: the last chi node where a row's Ts is not zero (-1: none); gd
+// (with Gsq): the diagonal of the Gram product.
+void launch_rows(const DevTables &T, const int32_t *rowR, const int32_t *cfgT, int64_t n_R, const double *F,
+                 const double *X, const double *R, const double *Gmax, const double *Gsq, double noise, double *dR,
+                 double *rR, double *Ps, double *Ts, int32_t *sexp, int32_t *last, double *gd, hipStream_t s);
 // fmt: 0 = f64, 1 = bf16 (hi only), 2 = bf16 hi + lo, 3 = f32.  f64 and f32
 // are row-major with row pitch lda; bf16 operands are k-blocked: element
 // (r, k) at ((k / GRAM_KB) r_pad + r) GRAM_KB + k % GRAM_KB, so that the
@@ -50,10 +55,11 @@ void launch_abuild(int fmt, const int32_t *rowR, const double *Ts, const double 
                    const double *panel_f = nullptr, double lim = 0.0, const int32_t *arow = nullptr,
                    const int32_t *ext = nullptr);
 // Per 256-row panel of A-rows, ext[P] = the 32-column k-blocks up to the last
-// chi node where T (Ts [n_R][n_chi]) of one of its rows is nonzero: the
-// factor of a row is zero beyond it (T carries the lensing kernels).
-void launch_panel_ext(const double *Ts, const int32_t *arow, int64_t r_pad, int n_chi, int n_mg, int64_t k_pad,
-                      int32_t *ext, hipStream_t s);
+// chi node where T of one of its rows is nonzero (last [n_R]): the factor of a
+// row is zero beyond it (T carries the lensing kernels).  With panel_f, its
+// r_pad / 256 + 1 values are cleared.
+void launch_panel_ext(const int32_t *last, const int32_t *arow, int64_t r_pad, int n_mg, int64_t k_pad, int32_t *ext,
+                      double *panel_f, hipStream_t s);
 
 // Two-leg factors of the projected one-halo trispectrum (P.T term): G2
 // [n2][n_chi][n_m] and Ts2 [rows][n_chi] for the n2 = n_ell (n_ell + 1) / 2
@@ -145,14 +151,11 @@ struct AsmArgs {
 void launch_rowexp(const AsmArgs &a, int32_t *row_exp2, double *d, double *r, hipStream_t s);
 // WLC_BF16_AUTO: the largest one-halo share f_a = C1h_aa / C_aa of the data
 // rows of every 256-row panel of distinct rows, into F [n_panels], and the
-// largest of all into F[n_panels], from the
-// Gram factors in FP64 before the product: S [n_cfg][n_chi] and gd [n_R]
-// are scratch.  C_aa leaves out the in-survey terms (positive on the
-// diagonal), so F errs on the large side.
+// largest of all into F[n_panels] (cleared by launch_panel_ext), from the Gram
+// diagonal gd of launch_rows, before the product.  C_aa leaves out the
+// in-survey terms (positive on the diagonal), so F errs on the large side.
 // pos (nullptr: identity) maps a distinct row to its A-row, whose panel F holds.
-void launch_split_plan(const AsmArgs &a, const int32_t *rowR, const double *Ts, const double *G, int64_t n_R,
-                       int n_cfg, int n_chi, int n_mg, double *S, double *gd, double *F, int n_panels, hipStream_t s,
-                       const int32_t *pos = nullptr);
+void launch_split_share(const AsmArgs &a, const double *gd, double *F, const int32_t *pos, hipStream_t s);
 // C in the type of the one-halo block Gm: FP32 when gm_f32, else FP64.
 void launch_assemble(const AsmArgs &a, const int32_t *row_exp2, void *C, hipStream_t s);
 
