@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -51,10 +52,12 @@ constexpr int64_t GRAM_TILE = 256;  // rows of A padded to the bf16 Gram tile
 constexpr int64_t K_ALIGN = 64;
 
 enum Buf {
-  B_ROWR, B_ROWO, B_CFGT, B_CENT, B_NMODES, B_NTRI, B_THR, B_TRI, B_FLAGS,
+  // the plan's index tables, in one piece with the cleared flags
+  B_ROWR, B_ROWO, B_CFGT, B_CENT, B_SOFF, B_SLEG, B_SWT, B_NMODES, B_NTRI, B_THR, B_TRI, B_AROW, B_POS, B_FLAGS,
+  B_INDEX_END,
   B_U, B_LEG, B_CHIF, B_LAST, B_X, B_R, B_DR, B_RR, B_PS, B_G, B_GMAX, B_TS, B_SEXP,
-  B_A0, B_A1, B_GM, B_PART, B_H, B_G2, B_H2, B_TS2, B_T2, B_SW, B_SOFF, B_SLEG, B_SWT, B_SQ, B_GD, B_FP,
-  B_AROW, B_POS, B_EXT, B_GP, NBUF
+  B_A0, B_A1, B_GM, B_PART, B_H, B_G2, B_H2, B_TS2, B_T2, B_SW, B_SQ, B_GD, B_FP,
+  B_EXT, B_GP, NBUF
 };
 
 // Columns per chi node of the configuration factor G: the mass nodes, and
@@ -202,6 +205,8 @@ static void order_arows(Plan &p) {
   }
 }
 
+static void pack_index(Plan &p);
+
 static void finish_sizes(Plan &p) {
   p.k_len = (int64_t)p.cfg.n_chi * g_cols(p.cfg);
   p.k_pad = round_up(p.k_len, K_ALIGN);
@@ -209,6 +214,7 @@ static void finish_sizes(Plan &p) {
   order_arows(p);
   p.ws_run = run_ws_bytes(p);
   p.ws_snr = snr_ws_bytes(p);
+  pack_index(p);
 }
 
 int snr_structured_enqueue(const Plan &p, const void *ws_run, void *ws, hipStream_t s, PhaseHooks *hooks,
@@ -302,38 +308,56 @@ static T *at(void *ws, const Layout &L, Buf b) {
   return reinterpret_cast<T *>(static_cast<char *>(ws) + L.off[b]);
 }
 
-struct Upload { Buf b; const void *src; size_t bytes; };
+// The plan's index tables as they lie in the workspace, in one host block
+// that is copied whole (table by table, and again after the check of the
+// tables, the copies took 110 of the 450 us of a run of 143 rows and its S/N).
+static void pack_index(Plan &p) {
+  const Layout L = run_layout(p);
+  p.index.assign(L.off[B_INDEX_END], 0);
+  auto put = [&](Buf b, const void *src, size_t bytes) {
+    if (bytes) std::memcpy(p.index.data() + L.off[b], src, bytes);
+  };
+  put(B_ROWR, p.rowR.data(), p.rowR.size() * 4);
+  put(B_ROWO, p.rowO.data(), p.rowO.size() * 4);
+  put(B_CFGT, p.cfgT.data(), p.cfgT.size() * 4);
+  put(B_CENT, p.sub_centres.data(), p.sub_centres.size() * 8);
+  put(B_SOFF, p.sub_off.data(), p.sub_off.size() * 4);
+  put(B_SLEG, p.sub_leg.data(), p.sub_leg.size() * 4);
+  put(B_SWT, p.sub_w.data(), p.sub_w.size() * 8);
+  put(B_NMODES, p.n_modes.data(), p.n_modes.size() * 8);
+  put(B_NTRI, p.n_tri_closed.data(), p.n_tri_closed.size() * 8);
+  put(B_THR, p.lattice_thr.data(), p.lattice_thr.size() * 8);
+  put(B_TRI, p.triT.data(), p.triT.size() * 4);
+  put(B_AROW, p.arow.data(), p.arow.size() * 4);
+  put(B_POS, p.pos.data(), p.pos.size() * 4);
+  p.lmax_index = p.lmax_perm;
+  p.lmax_index.resize(align_up((size_t)p.n_out * 4, 256) / 4, 0);
+  p.lmax_index.insert(p.lmax_index.end(), p.lmax_ends.begin(), p.lmax_ends.end());
+}
 
-static int upload(const Upload *ups, size_t n, void *ws, const Layout &L, hipStream_t s) {
-  for (size_t i = 0; i < n; ++i) {
-    const Upload &u = ups[i];
-    if (!u.bytes) continue;
-    int rc = hip_check(hipMemcpyAsync(at<char>(ws, L, u.b), u.src, u.bytes, hipMemcpyHostToDevice, s),
-                       "index upload");
-    if (rc) return rc;
-  }
+// n values at out and the pivot flag before them (at most a few hundred bytes
+// apart) in one transfer; waits for the stream.
+static int fetch_snr(const int32_t *flag, const double *out, size_t n, double *host, hipStream_t s) {
+  const size_t gap = (size_t)((const char *)out - (const char *)flag);
+  std::unique_ptr<double[]> h(new (std::nothrow) double[gap / 8 + n]);
+  if (!h) return fail(WLC_ENOMEM, "host allocation failed");
+  int rc = hip_check(hipMemcpyAsync(h.get(), flag, gap + n * 8, hipMemcpyDeviceToHost, s), "snr copy");
+  if (!rc) rc = hip_check(hipStreamSynchronize(s), "snr sync");
+  if (rc) return rc;
+  int32_t bad = 0;
+  std::memcpy(&bad, h.get(), 4);
+  if (bad) return fail(WLC_ENOTPD, "covariance is not positive definite");
+  std::memcpy(host, h.get() + gap / 8, n * 8);
   return WLC_OK;
 }
 
-// Copy the plan's index tables into the workspace (the sources live in the
-// plan, which outlives every run using it).
-static int upload_index(const Plan &p, void *ws, const Layout &L, hipStream_t s) {
-  const Upload ups[] = {
-      {B_ROWR, p.rowR.data(), p.rowR.size() * 4},
-      {B_ROWO, p.rowO.data(), p.rowO.size() * 4},
-      {B_CFGT, p.cfgT.data(), p.cfgT.size() * 4},
-      {B_CENT, p.sub_centres.data(), p.sub_centres.size() * 8},
-      {B_SOFF, p.sub_off.data(), p.sub_off.size() * 4},
-      {B_SLEG, p.sub_leg.data(), p.sub_leg.size() * 4},
-      {B_SWT, p.sub_w.data(), p.sub_w.size() * 8},
-      {B_NMODES, p.n_modes.data(), p.n_modes.size() * 8},
-      {B_NTRI, p.n_tri_closed.data(), p.n_tri_closed.size() * 8},
-      {B_THR, p.lattice_thr.data(), p.lattice_thr.size() * 8},
-      {B_TRI, p.triT.data(), p.triT.size() * 4},
-      {B_AROW, p.arow.data(), p.arow.size() * 4},
-      {B_POS, p.pos.data(), p.pos.size() * 4},
-  };
-  return upload(ups, sizeof(ups) / sizeof(ups[0]), ws, L, s);
+// Copy the index tables (and clear the flags) in the workspace, or the buffers
+// first .. last - 1 of them.  The source lies in the plan, which outlives
+// every run using it.
+static int upload_index(const Plan &p, void *ws, const Layout &L, hipStream_t s, Buf first = B_ROWR,
+                        Buf last = B_INDEX_END) {
+  return hip_check(hipMemcpyAsync(at<char>(ws, L, first), p.index.data() + L.off[first], L.off[last] - L.off[first],
+                                  hipMemcpyHostToDevice, s), "index upload");
 }
 
 static DevTables dev_tables(const Plan &p, const wlc_tables &tb, double rho = 0.0) {
@@ -356,7 +380,6 @@ int validate_tables(const Plan &p, const wlc_tables &tb, void *ws, hipStream_t s
   if (rc) return rc;
   const DevTables T = dev_tables(p, tb);
   int32_t *flags = at<int32_t>(ws, L, B_FLAGS);
-  launch_fill_i32(flags, 64, 0, s);
   launch_validate(T, at<double>(ws, L, B_CENT), p.n_ell * p.n_sub, (p.cfg.flags & WLC_FLAG_SSC_CHI) ? theta_sky(p) : 0.0,
                   flags, s);
   int32_t hf[3] = {0, 0, 0};
@@ -372,12 +395,13 @@ int validate_tables(const Plan &p, const wlc_tables &tb, void *ws, hipStream_t s
 static AsmArgs asm_args(const Plan &p, void *ws, const Layout &L);
 static double split_lim(const Plan &p);
 
-int run_enqueue_front(const Plan &p, const wlc_tables &tb, void *ws, hipStream_t s, PhaseHooks *hooks, double rho) {
+int run_enqueue_front(const Plan &p, const wlc_tables &tb, void *ws, hipStream_t s, PhaseHooks *hooks, double rho,
+                      bool uploaded) {
   int rc = check_tables_present(tb);
   if (rc) return rc;
   const wlc_config &c = p.cfg;
   const Layout L = run_layout(p);
-  rc = upload_index(p, ws, L, s);
+  if (!uploaded) rc = upload_index(p, ws, L, s);
   if (rc) return rc;
   if (tb.n_tri && p.n_tri > 0) {  // the workspace keeps the counts this run used
     rc = hip_check(hipMemcpyAsync(at<double>(ws, L, B_NTRI), tb.n_tri, (size_t)p.n_tri * 8, hipMemcpyDeviceToDevice,
@@ -542,8 +566,8 @@ int run_enqueue_back(const Plan &p, const wlc_tables &tb, void *ws, double *d, d
 }
 
 int run_enqueue(const Plan &p, const wlc_tables &tb, void *ws, double *d, double *r, void *C, int32_t *row_exp2,
-                hipStream_t s, PhaseHooks *hooks, double rho) {
-  int rc = run_enqueue_front(p, tb, ws, s, hooks, rho);
+                hipStream_t s, PhaseHooks *hooks, double rho, bool uploaded) {
+  int rc = run_enqueue_front(p, tb, ws, s, hooks, rho, uploaded);
   if (!rc) rc = run_enqueue_gram(p, ws, s, hooks);
   if (!rc) rc = run_enqueue_back(p, tb, ws, d, r, C, row_exp2, s, hooks);
   return rc;
@@ -562,18 +586,16 @@ int snr_enqueue(const Plan &p, const void *C, const int32_t *row_exp2, const dou
   o += 256;
   double *out = reinterpret_cast<double *>(base + o);
   o += 256;
+  double *curve = reinterpret_cast<double *>(base + o);
+  o += align_up((size_t)p.n_ell * 8, 256);
   int32_t *perm = reinterpret_cast<int32_t *>(base + o);
   o += align_up((size_t)n * 4, 256);
   int32_t *ends = reinterpret_cast<int32_t *>(base + o);
   o += align_up((size_t)p.n_ell * 8, 256);
   double *part = reinterpret_cast<double *>(base + o);
-  o += align_up((size_t)p.n_ell * 8, 256);
-  double *curve = reinterpret_cast<double *>(base + o);
-  if (lmax) {
-    int rc = hip_check(hipMemcpyAsync(perm, p.lmax_perm.data(), (size_t)n * 4, hipMemcpyHostToDevice, s), "perm upload");
-    if (!rc)
-      rc = hip_check(hipMemcpyAsync(ends, p.lmax_ends.data(), (size_t)p.n_ell * 4, hipMemcpyHostToDevice, s),
-                     "ends upload");
+  if (lmax) {  // the order, then the group ends
+    int rc = hip_check(hipMemcpyAsync(perm, p.lmax_index.data(), p.lmax_index.size() * 4, hipMemcpyHostToDevice, s),
+                       "order upload");
     if (rc) return rc;
   }
   if (hooks) hooks->begin(WLC_PHASE_SNR_PREP);
@@ -812,9 +834,7 @@ int wlc_lattice_counts(wlc_plan plan, void *ws, uint64_t *modes, uint64_t *tris,
   const Layout L = run_layout(p);
   // only the thresholds and the triangle legs: the workspace may hold the
   // triangle counts of a completed run, which a later structured S/N reads
-  const Upload ups[] = {{B_THR, p.lattice_thr.data(), p.lattice_thr.size() * 8},
-                        {B_TRI, p.triT.data(), p.triT.size() * 4}};
-  int rc = upload(ups, 2, ws, L, s);
+  int rc = upload_index(p, ws, L, s, B_THR, B_AROW);
   if (rc) return rc;
   const int64_t thr_max = p.lattice_thr[p.n_ell];
   launch_lattice(at<int64_t>(ws, L, B_THR), thr_max, p.n_ell, at<int32_t>(ws, L, B_TRI), p.n_tri, modes, tris, s);
@@ -827,14 +847,15 @@ int wlc_run(wlc_plan plan, const wlc_tables *tb, void *ws, double *d, double *r,
   if (((uintptr_t)ws & 255) != 0) return fail(WLC_EINVAL, "workspace must be 256-byte aligned");
   const Plan &p = plan->p;
   hipStream_t s = (hipStream_t)stream;
-  if (!(p.cfg.flags & WLC_FLAG_NOCHECK)) {
+  const bool check = !(p.cfg.flags & WLC_FLAG_NOCHECK);
+  if (check) {
     int rc = validate_tables(p, *tb, ws, s);
     if (rc) return rc;
   }
   for (int ph = WLC_PHASE_TABLES; ph <= WLC_PHASE_ASSEMBLE; ++ph) plan->recorded[ph] = false;
   PlanTimer tm(plan, s);
   const bool timed = plan->timing && plan->events_ready;
-  return run_enqueue(p, *tb, ws, d, r, C, row_exp2, s, timed ? &tm : nullptr);
+  return run_enqueue(p, *tb, ws, d, r, C, row_exp2, s, timed ? &tm : nullptr, 0.0, check);
 }
 
 int wlc_sigma_w2(wlc_plan plan, const wlc_tables *tb, double *sw, void *stream) {
@@ -865,14 +886,7 @@ int wlc_snr2(wlc_plan plan, const void *C, const int32_t *row_exp2, const double
   double *out = nullptr;
   int rc = snr_enqueue(p, C, row_exp2, d, ws, s, timed ? &tm : nullptr, probe, &flag, &out);
   if (rc) return rc;
-  struct { int32_t flag; int32_t pad; double v; } h{};
-  rc = hip_check(hipMemcpyAsync(&h.flag, flag, 4, hipMemcpyDeviceToHost, s), "snr copy");
-  if (!rc) rc = hip_check(hipMemcpyAsync(&h.v, out, 8, hipMemcpyDeviceToHost, s), "snr copy");
-  if (!rc) rc = hip_check(hipStreamSynchronize(s), "snr sync");
-  if (rc) return rc;
-  if (h.flag) return fail(WLC_ENOTPD, "covariance is not positive definite");
-  *snr2_host = h.v;
-  return WLC_OK;
+  return fetch_snr(flag, out, 1, snr2_host, s);
 }
 
 int wlc_gram_split_tiles(wlc_plan plan, const void *ws_run, int64_t *split, int64_t *tiles) {
@@ -1028,13 +1042,7 @@ int wlc_snr2_lmax(wlc_plan plan, const void *C, const int32_t *row_exp2, const d
   double *out = nullptr;
   int rc = snr_enqueue(p, C, row_exp2, d, ws, s, timed ? &tm : nullptr, nullptr, &flag, &out, true);
   if (rc) return rc;
-  int32_t hflag = 0;
-  rc = hip_check(hipMemcpyAsync(&hflag, flag, 4, hipMemcpyDeviceToHost, s), "snr copy");
-  if (!rc) rc = hip_check(hipMemcpyAsync(snr2_host, out, (size_t)p.n_ell * 8, hipMemcpyDeviceToHost, s), "snr copy");
-  if (!rc) rc = hip_check(hipStreamSynchronize(s), "snr sync");
-  if (rc) return rc;
-  if (hflag) return fail(WLC_ENOTPD, "covariance is not positive definite");
-  return WLC_OK;
+  return fetch_snr(flag, out, (size_t)p.n_ell, snr2_host, s);
 }
 
 int wlc_pca(wlc_plan plan, const void *C, const int32_t *row_exp2, const double *d, void *ws, double *lambda,
@@ -1124,14 +1132,7 @@ int wlc_snr2_structured(wlc_plan plan, const void *ws_run, void *ws, double *snr
   double *out = nullptr;
   int rc = snr_structured_enqueue(p, ws_run, ws, s, timed ? &tm : nullptr, probe, &flag, &out);
   if (rc) return rc;
-  struct { int32_t flag; int32_t pad; double v; } h{};
-  rc = hip_check(hipMemcpyAsync(&h.flag, flag, 4, hipMemcpyDeviceToHost, s), "snr copy");
-  if (!rc) rc = hip_check(hipMemcpyAsync(&h.v, out, 8, hipMemcpyDeviceToHost, s), "snr copy");
-  if (!rc) rc = hip_check(hipStreamSynchronize(s), "snr sync");
-  if (rc) return rc;
-  if (h.flag) return fail(WLC_ENOTPD, "covariance is not positive definite");
-  *snr2_host = h.v;
-  return WLC_OK;
+  return fetch_snr(flag, out, 1, snr2_host, s);
 }
 
 }  // extern "C"

@@ -26,16 +26,17 @@ int validate_tables(const Plan &p, const wlc_tables &tb, void *ws, hipStream_t s
 
 // Enqueue the hot path (no synchronisation): index upload, staging,
 // quadrature, projection, A-build, Gram product, assembly.
-// rho > 0 replaces the plan's mean matter density.
+// rho > 0 replaces the plan's mean matter density; uploaded: validate_tables
+// has put the index tables into this workspace on this stream.
 int run_enqueue(const Plan &p, const wlc_tables &tb, void *ws, double *d, double *r, void *C, int32_t *row_exp2,
-                hipStream_t s, PhaseHooks *hooks, double rho = 0.0);
+                hipStream_t s, PhaseHooks *hooks, double rho = 0.0, bool uploaded = false);
 
 // The same path in three parts, so that the Gram products of several runs
 // can share one batched launch (the request server): front = index upload,
 // staging, quadrature, projection and A-build; gram = the one-halo product
 // with its split-K reduction; back = mirror, row exponents and assembly.
 int run_enqueue_front(const Plan &p, const wlc_tables &tb, void *ws, hipStream_t s, PhaseHooks *hooks,
-                      double rho = 0.0);
+                      double rho = 0.0, bool uploaded = false);
 int run_enqueue_gram(const Plan &p, void *ws, hipStream_t s, PhaseHooks *hooks);
 int run_enqueue_back(const Plan &p, const wlc_tables &tb, void *ws, double *d, double *r, void *C, int32_t *row_exp2,
                      hipStream_t s, PhaseHooks *hooks);

@@ -43,6 +43,8 @@ struct Plan {
   // per used bin b, the number of rows whose largest bin is <= b
   std::vector<int32_t> lmax_perm;
   std::vector<int32_t> lmax_ends;
+  std::vector<int32_t> lmax_index;          // both, as they lie in the S/N workspace
+  std::vector<uint8_t> index;               // the index tables, as they lie in the run workspace
   double omega = 0.0;                       // 4 pi f_sky
   double noise = 0.0;                       // sigma_eps^2 / n_i
   // Flattened Gram products (every precision but FP64_CHI): the rows of A in
