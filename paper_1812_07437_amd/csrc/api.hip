@@ -461,7 +461,7 @@ int run_enqueue_front(const Plan &p, const wlc_tables &tb, void *ws, hipStream_t
   return hip_check(hipGetLastError(), "run launch");
 }
 
-static GramShape gram_shape(const Plan &p) { return GramShape{p.r_pad, p.k_pad, p.r_pad, p.k_pad}; }
+static GramShape gram_shape(const Plan &p) { return GramShape{p.r_pad, p.k_pad, p.r_pad, p.k_pad, p.n_R}; }
 
 // WLC_BF16_AUTO: tile (I, J) takes the split product iff
 // (2u + u^2 + K 2^-24) sqrt(F_I F_J) > tol, i.e. F_I F_J > lim, with
@@ -554,10 +554,8 @@ int run_enqueue_back(const Plan &p, const wlc_tables &tb, void *ws, double *d, d
   if (hooks) hooks->begin(WLC_PHASE_ASSEMBLE);
   if (p.arow.empty()) {
     launch_gram_mirror(a.gm_f32, Gm, p.n_R, p.r_pad, s);
-  } else {  // the product of the A-rows, made symmetric, back in the distinct-row order
-    void *GP = at<void>(ws, L, B_GP);
-    launch_gram_mirror(a.gm_f32, GP, p.r_pad, p.r_pad, s);
-    launch_gram_unpermute(a.gm_f32, GP, at<int32_t>(ws, L, B_POS), p.n_R, p.r_pad, Gm, s);
+  } else {  // the product of the A-rows, made symmetric in the distinct-row order
+    launch_gram_unpermute(a.gm_f32, at<void>(ws, L, B_GP), at<int32_t>(ws, L, B_POS), p.n_R, p.r_pad, Gm, s);
   }
   launch_rowexp(a, row_exp2, d, r, s);
   launch_assemble(a, row_exp2, C, s);
@@ -1007,7 +1005,7 @@ int wlc_gram_work(wlc_plan plan, const void *ws_run, double *flops, double *mfma
   *mfma_flops = m;
   if (factor_bytes) {
     double b = 0.0;
-    if (ext.empty() || prec == WLC_FP64) {  // the FP64 factor is written over all of K
+    if (ext.empty() || prec == WLC_FP64) {  // the FP64 factor is counted over all of K
       b = (double)p.n_R * (double)p.k_len * (prec == WLC_FP64 ? 8.0 : prec == WLC_FP32 ? 4.0 : 2.0);
     } else {  // the distinct rows lead the A-row order; a panel's rows end at its extent
       for (int64_t P = 0; P < np; ++P) {

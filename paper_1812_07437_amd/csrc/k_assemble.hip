@@ -11,6 +11,8 @@
 // is evaluated once and written to both halves, so C~ is exactly symmetric.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace wlc {
@@ -26,19 +28,18 @@ __device__ __forceinline__ double gauss_entry(const AsmArgs &A, const int32_t *r
     return (P[ra[2] * nz + rb[2]] * P[ra[3] * nz + rb[3]] + P[ra[2] * nz + rb[3]] * P[ra[3] * nz + rb[2]]) /
            A.nmodes[b];
   }
-  const int perm[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
-  double s = 0.0;
+  // M[a][b] = P^s of leg a and primed leg b where their ell-bins agree (else 0),
+  // all nine loads at once; the six maps are the terms of its permanent
+  double M[3][3];
 #pragma unroll
-  for (int p = 0; p < 6; ++p) {
-    double term = 1.0;
+  for (int a = 0; a < 3; ++a)
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const int sa = perm[p][a];
-      if (ra[5 + a] != rb[5 + sa]) { term = 0.0; break; }
-      term *= Ps[((size_t)ra[5 + a] * nz + ra[2 + a]) * nz + rb[2 + sa]];
+    for (int b = 0; b < 3; ++b) {
+      const double v = Ps[((size_t)ra[5 + a] * nz + ra[2 + a]) * nz + rb[2 + b]];
+      M[a][b] = ra[5 + a] == rb[5 + b] ? v : 0.0;
     }
-    s += term;
-  }
+  const double s = M[0][0] * M[1][1] * M[2][2] + M[0][0] * M[1][2] * M[2][1] + M[0][1] * M[1][0] * M[2][2] +
+                   M[0][1] * M[1][2] * M[2][0] + M[0][2] * M[1][0] * M[2][1] + M[0][2] * M[1][1] * M[2][0];
   return A.omega / A.ntri[ra[0] - A.n_ell] * s;
 }
 
@@ -158,10 +159,16 @@ void launch_rowexp(const AsmArgs &a, int32_t *row_exp2, double *d, double *r, hi
 // (gd) comes with the rows' factors.
 constexpr int SPLIT_PANEL = 256;  // rows per panel: the bf16 Gram tile
 
-// The share only ever grows, so a lane's atomic is left out where the value
-// there is as large already (a stale one is smaller and costs an atomic more).
-__global__ void k_split_share(AsmArgs A, const double *__restrict__ gd, double *F, const int32_t *__restrict__ pos) {
+// A workgroup's largest shares are found in LDS first (best [n_panels]; 0 panels:
+// straight in global memory): 4550 rows 5 us, with every lane's atomic on a
+// handful of addresses 27.
+__global__ void k_split_share(AsmArgs A, const double *__restrict__ gd, double *F, const int32_t *__restrict__ pos,
+                              int n_panels) {
+  extern __shared__ unsigned long long best[];
+  for (int i = threadIdx.x; i < n_panels; i += blockDim.x) best[i] = 0;
+  __syncthreads();
   const int64_t a = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  unsigned long long *Fb = (unsigned long long *)F, *to = n_panels ? best : Fb;
   double f = 0.0;
   if (a < A.n) {
     const int32_t *ra = A.rowO + 8 * a;
@@ -171,18 +178,21 @@ __global__ void k_split_share(AsmArgs A, const double *__restrict__ gd, double *
     const double c = c1h + gauss_entry(A, ra, ra) + A.sigma_b2 * rr * rr;
     // a share of 1 (no other term) for a row whose diagonal is not positive
     f = c > 0.0 && isfinite(c) ? c1h / c : 1.0;
-    // non-negative doubles order like their bit patterns
-    double *Fp = &F[(pos ? pos[e] : e) / SPLIT_PANEL];  // the panel of its A-row
-    if (f > *(volatile double *)Fp)
-      atomicMax((unsigned long long *)Fp, (unsigned long long)__double_as_longlong(f));
+    // non-negative doubles order like their bit patterns; the panel of the row's A-row
+    atomicMax(&to[(pos ? pos[e] : e) / SPLIT_PANEL], (unsigned long long)__double_as_longlong(f));
   }
   f = wave_max(f);
   if ((threadIdx.x & (WAVE - 1)) == 0)
-    atomicMax((unsigned long long *)&F[A.ld_g / SPLIT_PANEL], (unsigned long long)__double_as_longlong(f));
+    atomicMax(&Fb[A.ld_g / SPLIT_PANEL], (unsigned long long)__double_as_longlong(f));
+  __syncthreads();
+  for (int i = threadIdx.x; i < n_panels; i += blockDim.x)
+    if (best[i]) atomicMax(&Fb[i], best[i]);
 }
 
 void launch_split_share(const AsmArgs &a, const double *gd, double *F, const int32_t *pos, hipStream_t s) {
-  hipLaunchKernelGGL(k_split_share, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, a, gd, F, pos);
+  const int64_t panels = a.ld_g / SPLIT_PANEL;
+  const int n = panels <= 4096 ? (int)panels : 0;  // 32 KB of LDS: a million rows
+  hipLaunchKernelGGL(k_split_share, dim3((unsigned)((a.n + 255) / 256)), dim3(256), (size_t)n * 8, s, a, gd, F, pos, n);
 }
 
 // 64 x 64 output tiles (I >= J); each thread computes 16 entries of one
@@ -196,9 +206,11 @@ void launch_split_share(const AsmArgs &a, const double *gd, double *F, const int
 // responses, so a workgroup waits on global memory twice before it writes.
 constexpr int AT = 64;
 constexpr int ASM_XCD = 8;
+constexpr int64_t ASM_WIDE = 6000;
 
-template <typename OutT>
-__global__ __launch_bounds__(256) void k_assemble(AsmArgs A, const int32_t *__restrict__ row_exp2,
+// Q entries for each thread (4096 / Q threads).
+template <typename OutT, int Q>
+__global__ __launch_bounds__(AT * AT / Q) void k_assemble(AsmArgs A, const int32_t *__restrict__ row_exp2,
                                                   OutT *__restrict__ C, int64_t n_tiles) {
   __shared__ OutT tileT[AT][AT + 1];
   __shared__ int32_t rowA[AT][8], rowB[AT][8];
@@ -213,7 +225,7 @@ __global__ __launch_bounds__(256) void k_assemble(AsmArgs A, const int32_t *__re
   const int64_t I = i, J = t - i * (i + 1) / 2;
   const int64_t a0 = I * AT, b0 = J * AT;
   const int tid = threadIdx.x;
-  for (int q = tid; q < AT * 8; q += 256) {
+  for (int q = tid; q < AT * 8; q += AT * AT / Q) {
     const int r = q / 8, c = q % 8;
     rowA[r][c] = a0 + r < A.n ? A.rowO[(a0 + r) * 8 + c] : 0;
     rowB[r][c] = b0 + r < A.n ? A.rowO[(b0 + r) * 8 + c] : 0;
@@ -225,17 +237,17 @@ __global__ __launch_bounds__(256) void k_assemble(AsmArgs A, const int32_t *__re
   }
   __syncthreads();
   const int cb = tid & 63;          // column within the tile
-  const int rbase = (tid >> 6) * 16;
+  const int rbase = (tid >> 6) * Q;
   const int64_t b = b0 + cb;
-  // the 16 one-halo values, all loads in flight together with those of the
+  // the Q one-halo values, all loads in flight together with those of the
   // exponents and responses (padding rows map to distinct row 0, so every
   // index is valid)
   // (the one-halo block has the output's type: FP32 for the mixed modes)
-  OutT gv[16];
+  OutT gv[Q];
   const int64_t eb = rowB[cb][1];
   const OutT *G = (const OutT *)A.Gm;
 #pragma unroll
-  for (int q = 0; q < 16; ++q) gv[q] = G[rowA[rbase + q][1] * A.ld_g + eb];
+  for (int q = 0; q < Q; ++q) gv[q] = G[rowA[rbase + q][1] * A.ld_g + eb];
   if (tid < AT) {
     const bool live = a0 + tid < A.n;
     sA[tid] = live ? A.sexp[rowA[tid][1]] : 0;
@@ -248,7 +260,7 @@ __global__ __launch_bounds__(256) void k_assemble(AsmArgs A, const int32_t *__re
   }
   __syncthreads();
 #pragma unroll 4
-  for (int q = 0; q < 16; ++q) {
+  for (int q = 0; q < Q; ++q) {
     const int ra = rbase + q;
     const int64_t a = a0 + ra;
     OutT v = 0;
@@ -268,7 +280,7 @@ __global__ __launch_bounds__(256) void k_assemble(AsmArgs A, const int32_t *__re
   // with non-temporal stores (measured 1 ms faster at N = 82575; both halves
   // non-temporal was 2 ms slower)
 #pragma unroll 4
-  for (int q = 0; q < 16; ++q) {
+  for (int q = 0; q < Q; ++q) {
     const int rb = rbase + q;  // row of the transposed tile (b index)
     const int ca = cb;         // column (a index)
     const int64_t bb = b0 + rb, aa = a0 + ca;
@@ -280,10 +292,16 @@ void launch_assemble(const AsmArgs &a, const int32_t *row_exp2, void *C, hipStre
   const int64_t nt = (a.n + AT - 1) / AT;
   const int64_t tiles = nt * (nt + 1) / 2;
   const dim3 grid((unsigned)((tiles + ASM_XCD - 1) / ASM_XCD * ASM_XCD));
+  auto run = [&](auto out, auto wide) {
+    using T = decltype(out);
+    constexpr int Q = decltype(wide)::value ? 4 : 16;
+    hipLaunchKernelGGL((k_assemble<T, Q>), grid, dim3(AT * AT / Q), 0, s, a, row_exp2, (T *)C, tiles);
+  };
+  const bool wide = a.n <= ASM_WIDE;
   if (a.gm_f32)
-    hipLaunchKernelGGL(k_assemble<float>, grid, dim3(256), 0, s, a, row_exp2, (float *)C, tiles);
+    wide ? run(0.0f, std::true_type{}) : run(0.0f, std::false_type{});
   else
-    hipLaunchKernelGGL(k_assemble<double>, grid, dim3(256), 0, s, a, row_exp2, (double *)C, tiles);
+    wide ? run(0.0, std::true_type{}) : run(0.0, std::false_type{});
 }
 
 }  // namespace wlc

@@ -631,7 +631,9 @@ __global__ __launch_bounds__(256) void k_gram_x4(const T *__restrict__ A, int64_
 // 16 h .. 16 h + 15 of the 128 x 128 lower-triangle tile t, a thread one
 // column of every other row, so that the launch has eight workgroups per
 // tile (with one per tile, at the Euclid-like shape in FP64, 210 workgroups
-// took 0.50 ms for 210 MB of partials).
+// took 0.50 ms for 210 MB of partials).  A thread's rows are summed side by side,
+// so that the loads of a slice are in flight together: with 32 slices of one
+// 256-row panel 11 us, row after row 69.
 constexpr int RED_ROWS = 16;
 template <typename T>
 __global__ __launch_bounds__(256) void k_gram_reduce(const T *__restrict__ part, int n_split, int64_t part_stride,
@@ -640,13 +642,20 @@ __global__ __launch_bounds__(256) void k_gram_reduce(const T *__restrict__ part,
   tri_tile(blockIdx.x, I, J);
   const int64_t row0 = (int64_t)I * TILE + blockIdx.y * RED_ROWS + (threadIdx.x >> 7);
   const int64_t col = (int64_t)J * TILE + (threadIdx.x & 127);
+  const int64_t off = row0 * ld + col;
+  T s[RED_ROWS / 2];
 #pragma unroll
-  for (int q = 0; q < RED_ROWS / 2; ++q) {
-    const int64_t off = (row0 + 2 * q) * ld + col;
-    T s = out[off];  // slice 0
-    for (int p = 1; p < n_split; ++p) s += part[(p - 1) * part_stride + off];
-    out[off] = s;
+  for (int q = 0; q < RED_ROWS / 2; ++q) s[q] = out[off + 2 * q * ld];  // slice 0
+#pragma unroll 2
+  for (int p = 1; p < n_split; ++p) {
+    T v[RED_ROWS / 2];
+#pragma unroll
+    for (int q = 0; q < RED_ROWS / 2; ++q) v[q] = part[(p - 1) * part_stride + off + 2 * q * ld];
+#pragma unroll
+    for (int q = 0; q < RED_ROWS / 2; ++q) s[q] += v[q];
   }
+#pragma unroll
+  for (int q = 0; q < RED_ROWS / 2; ++q) out[off + 2 * q * ld] = s[q];
 }
 
 // FP64 Gram on 128 x 256 tiles with the tile product of f64tile.h: tile
@@ -672,7 +681,7 @@ __device__ __forceinline__ void f64_gram_tile(int64_t t, int &I, int &J) {
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gram_f64(
     const double *__restrict__ A, int64_t k_pad, int64_t lda, int64_t k_split, int n_split, int64_t n_work,
     double *__restrict__ out, double *__restrict__ partial, int64_t ld, int64_t part_stride,
-    const int32_t *__restrict__ panel_ext) {
+    const int32_t *__restrict__ panel_ext, int64_t n) {
   // items dealt to the XCDs in chunks of GRAM_XC (one per resident
   // workgroup), as gram_work<GRAM_XC> deals them: with panel extents the
   // items of the later panels are longer, and contiguous runs per XCD left
@@ -698,6 +707,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int b = 0; b < 4; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
   f64_tile_product(A + row0 * lda, A + col0 * lda, lda, FT_R, FT_S, kb, (ke - kb) / FT_K, acc);
+  if (row0 + wr >= n || col0 + wc >= n) return;  // padding only
   double *dst = gram_dst(out, partial, split, part_stride);
 #pragma unroll
   for (int x = 0; x < 4; ++x)
@@ -742,37 +752,59 @@ void launch_gram_mirror(int f32, void *G, int64_t n, int64_t ld, hipStream_t s) 
     hipLaunchKernelGGL(k_gram_mirror<double>, dim3(tiles), dim3(256), 0, s, (double *)G, ld);
 }
 
-// G in the order of the distinct rows from the product of the A-rows (GP,
-// symmetric): G[e][f] = GP[pos[e]][pos[f]], in 64 x 64 tiles of G.  Within a
-// configuration the rows of one lowest bin are consecutive in both orders,
-// so a wavefront's 64 reads of one GP row fall in a few contiguous runs.
+// G in the order of the distinct rows, both triangles, from the lower triangle
+// of the product of the A-rows: G[e][f] = GP[max][min] of pos[e], pos[f], in pairs
+// of 64 x 64 tiles of G, (I, J) and its mirror image.  Within a configuration the
+// rows of one lowest bin are consecutive in both orders, so a wavefront's
+// reads of one GP row fall in a few contiguous runs: entries with pos[e] >= pos[f] are
+// taken with f along the lanes, the others (they lie in GP's row pos[f]) with e
+// along the lanes, and meet in LDS.  Bound by HBM: 33165 rows in FP32 (2.2 GB read,
+// 4.4 written) 1.57 ms, where a mirrored GP took 0.85 + 2.30.
 template <typename T>
 __global__ __launch_bounds__(256) void k_gram_unpermute(const T *__restrict__ GP, const int32_t *__restrict__ pos,
                                                        int64_t n, int64_t ld, T *__restrict__ G) {
-  __shared__ int32_t prow[64];
-  const int64_t nt = (n + 63) / 64;
-  const int64_t I = blockIdx.x / nt, J = blockIdx.x % nt;
+  __shared__ T tile[64][65];
+  __shared__ int32_t prow[64], pcol[64];
+  int I, J;
+  tri_tile(blockIdx.x, I, J);
+  const int64_t i0 = (int64_t)I * 64, j0 = (int64_t)J * 64;
   const int c = threadIdx.x & 63, rb = (threadIdx.x >> 6) * 16;
-  if (threadIdx.x < 64) prow[threadIdx.x] = I * 64 + threadIdx.x < n ? pos[I * 64 + threadIdx.x] : 0;
+  if (threadIdx.x < 64)
+    prow[threadIdx.x] = i0 + threadIdx.x < n ? pos[i0 + threadIdx.x] : -1;
+  else if (threadIdx.x < 128)
+    pcol[c] = j0 + c < n ? pos[j0 + c] : -1;
   __syncthreads();
-  const int64_t f = J * 64 + c;
-  if (f >= n) return;
-  const int64_t pf = pos[f];
-#pragma unroll 4
+  const int32_t pe = prow[c], pf = pcol[c];
+  T v[16], w[16];
+#pragma unroll
   for (int q = 0; q < 16; ++q) {
-    const int64_t e = I * 64 + rb + q;
-    if (e < n) G[e * ld + f] = GP[(int64_t)prow[rb + q] * ld + pf];
+    const int32_t pr = prow[rb + q], pc = pcol[rb + q];
+    v[q] = w[q] = 0;
+    if (pf >= 0 && pr >= pf) v[q] = GP[(int64_t)pr * ld + pf];
+    if (pe >= 0 && pc > pe) w[q] = GP[(int64_t)pc * ld + pe];
+  }
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    if (prow[rb + q] >= pf) tile[rb + q][c] = v[q];
+    if (pcol[rb + q] > pe) tile[c][rb + q] = w[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int r = rb + q;
+    if (i0 + r < n && j0 + c < n) G[(i0 + r) * ld + j0 + c] = tile[r][c];
+    if (I != J && j0 + r < n && i0 + c < n) __builtin_nontemporal_store(tile[c][r], &G[(j0 + r) * ld + i0 + c]);
   }
 }
 
 void launch_gram_unpermute(int f32, const void *GP, const int32_t *pos, int64_t n, int64_t ld, void *G,
                            hipStream_t s) {
-  const int64_t nt = (n + 63) / 64;
+  const int64_t nt = (n + 63) / 64, tiles = nt * (nt + 1) / 2;
   if (f32)
-    hipLaunchKernelGGL(k_gram_unpermute<float>, dim3((unsigned)(nt * nt)), dim3(256), 0, s, (const float *)GP, pos,
+    hipLaunchKernelGGL(k_gram_unpermute<float>, dim3((unsigned)tiles), dim3(256), 0, s, (const float *)GP, pos,
                        n, ld, (float *)G);
   else
-    hipLaunchKernelGGL(k_gram_unpermute<double>, dim3((unsigned)(nt * nt)), dim3(256), 0, s, (const double *)GP, pos,
+    hipLaunchKernelGGL(k_gram_unpermute<double>, dim3((unsigned)tiles), dim3(256), 0, s, (const double *)GP, pos,
                        n, ld, (double *)G);
 }
 
@@ -816,6 +848,7 @@ static int gram_bk(int prec) { return prec == WLC_FP64 ? 16 : (prec == WLC_FP32 
 static bool f64_tiles(int prec, const GramShape &g) {
   return prec == WLC_FP64 && g.lda % 2 == 0 && (int64_t)FT_S * g.lda * 8 < ((int64_t)1 << 31) && g.r_pad % FT_S == 0;
 }
+static int64_t gram_rows(const GramShape &g) { return g.n > 0 ? g.n : g.r_pad; }
 bool gram_f64_tiles(const GramShape &g) { return f64_tiles(WLC_FP64, g); }
 static int64_t gram_tile_count(int prec, const GramShape &g) {
   if (f64_tiles(prec, g)) {
@@ -917,7 +950,7 @@ void launch_gram_reduce(int prec, const GramShape &g, void *out, void *partial, 
   if (q.ns <= 1) return;
   // the reduction walks the lower triangle in 128 x 128 tiles, which the
   // 256 x 256 tiles cover exactly
-  const int64_t nr = g.r_pad / TILE;
+  const int64_t nr = (gram_rows(g) + TILE - 1) / TILE;
   const unsigned rt = (unsigned)(nr * (nr + 1) / 2);
   const dim3 grid(rt, TILE / RED_ROWS);
   if (prec == WLC_FP64)
@@ -959,7 +992,7 @@ void launch_gram(int prec, const GramShape &g, const void *A0, const void *A1, v
     default:
       if (f64_tiles(prec, g)) {
         hipLaunchKernelGGL(k_gram_f64, grid, dim3(512), 0, s, (const double *)A0, g.k_pad, g.lda, ksplit, ns, n_work,
-                           (double *)out, (double *)partial, g.ld_out, pstride, panel_ext);
+                           (double *)out, (double *)partial, g.ld_out, pstride, panel_ext, gram_rows(g));
         break;
       }
       hipLaunchKernelGGL(k_gram_x4<double>, grid, dim3(256), 0, s, (const double *)A0, g.k_pad, g.lda, ksplit, ns, nti,

@@ -448,17 +448,23 @@ void launch_twoleg(const DevTables &T, int n_ell, const double *U, double *G2, d
 //
 // Row-major f64 / f32 ([r_pad][lda]): consecutive rows mostly share their
 // configuration, so each block holds 8 consecutive k of G_cfg per thread in
-// registers and writes them, times T_row, for AB_ROWS consecutive rows,
+// registers and writes them, times T_row, for `rows` consecutive rows,
 // reloading G only where the configuration changes.  With arow, row r of A
-// is the distinct row arow[r] (zero where it is negative); every k is
-// written.
+// is the distinct row arow[r] (zero where it is negative), and with ext a
+// 256-row panel is written up to its last k-block (no product reads it there).
+// rows is AB_ROWS, or as many fewer as it takes for 1024 workgroups: a row is a
+// chain of loads, and a small product is over sooner with more of them side by side (256
+// rows of 2048 k in FP64: 8 us, with 16 rows to each of 16 workgroups 26).
 constexpr int AB_ROWS = 16;
 
 template <int FMT>
 __global__ __launch_bounds__(256) void k_abuild(const int32_t *__restrict__ rowR, const double *__restrict__ Ts,
                                                const double *__restrict__ G, int64_t n_R, int n_chi, int n_m,
                                                int64_t k_pad, int64_t lda, void *A0, void *A1,
-                                               const int32_t *__restrict__ arow) {
+                                               const int32_t *__restrict__ arow,
+                                               const int32_t *__restrict__ ext, int rows) {
+  const int64_t r0 = (int64_t)blockIdx.y * rows;  // rows divides 256: one panel
+  if (ext) k_pad = min(k_pad, (int64_t)ext[r0 / 256] * GRAM_KB);
   const int64_t k0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 8;
   if (k0 >= k_pad) return;
   const int64_t k_len = (int64_t)n_chi * n_m;
@@ -473,8 +479,7 @@ __global__ __launch_bounds__(256) void k_abuild(const int32_t *__restrict__ rowR
   }
   double g[8];
   int cc = -1;
-  const int64_t r0 = (int64_t)blockIdx.y * AB_ROWS;
-  for (int rr = 0; rr < AB_ROWS; ++rr) {
+  for (int rr = 0; rr < rows; ++rr) {
     const int64_t row = r0 + rr;
     const int64_t e = arow ? (int64_t)arow[row] : (row < n_R ? row : -1);  // its distinct row
     double v[8];
@@ -735,11 +740,16 @@ void launch_abuild(int fmt, const int32_t *rowR, const double *Ts, const double 
     return;
   }
   // r_pad is a multiple of AB_ROWS (rows are padded to the Gram tile)
-  const dim3 grid((unsigned)((k_pad / 8 + 255) / 256), (unsigned)((r_pad + AB_ROWS - 1) / AB_ROWS));
+  const int64_t gx = (k_pad / 8 + 255) / 256;
+  int rows = AB_ROWS;
+  while (rows > 1 && gx * (r_pad / rows) < 1024) rows /= 2;
+  const dim3 grid((unsigned)gx, (unsigned)(r_pad / rows));
   if (fmt == 0)
-    hipLaunchKernelGGL(k_abuild<0>, grid, dim3(256), 0, s, rowR, Ts, G, n_R, n_chi, n_m, k_pad, lda, A0, A1, arow);
+    hipLaunchKernelGGL(k_abuild<0>, grid, dim3(256), 0, s, rowR, Ts, G, n_R, n_chi, n_m, k_pad, lda, A0, A1, arow, ext,
+                       rows);
   else
-    hipLaunchKernelGGL(k_abuild<3>, grid, dim3(256), 0, s, rowR, Ts, G, n_R, n_chi, n_m, k_pad, lda, A0, A1, arow);
+    hipLaunchKernelGGL(k_abuild<3>, grid, dim3(256), 0, s, rowR, Ts, G, n_R, n_chi, n_m, k_pad, lda, A0, A1, arow, ext,
+                       rows);
 }
 
 }  // namespace wlc

@@ -47,9 +47,8 @@ constexpr int GRAM_KB = 32;
 // panel_f, lim (fmt 2 only): write the lo half only for panels that can
 // take the split product (WLC_BF16_AUTO); nullptr writes it everywhere.
 // arow: the distinct row of each A-row (-1 past the distinct rows); ext
-// (bf16 formats): the k-blocks each 256-row panel of A-rows needs (see
-// launch_panel_ext), written only that far (the FP32 and FP64 formats write
-// every k-block).  nullptr: A-row = distinct row, every k-block.
+// the k-blocks each 256-row panel of A-rows needs (see launch_panel_ext),
+// written only that far.  nullptr: A-row = distinct row, every k-block.
 void launch_abuild(int fmt, const int32_t *rowR, const double *Ts, const double *G, int64_t n_R, int64_t r_pad,
                    int n_chi, int n_m, int64_t k_pad, int64_t lda, void *A0, void *A1, hipStream_t s,
                    const double *panel_f = nullptr, double lim = 0.0, const int32_t *arow = nullptr,
@@ -77,6 +76,7 @@ struct GramShape {
   int64_t k_pad;   // padded contraction length
   int64_t ld_out;  // leading dimension of the output
   int64_t lda;     // row pitch of A in elements (>= k_pad); bf16 operands are k-blocked instead
+  int64_t n = 0;   // rows whose products are wanted (0: all r_pad)
 };
 size_t gram_partial_bytes(int prec, const GramShape &g);
 // panel_f, split_lim: WLC_BF16_AUTO only (see k_gram.hip); ignored otherwise.
@@ -120,8 +120,8 @@ void launch_chifact(const double *Ts, const double *G, double *H, int n_cfg, int
 // f32 or f64) onto the upper one, so that G is exactly symmetric.
 void launch_gram_mirror(int f32, void *G, int64_t n, int64_t ld, hipStream_t s);
 // G[e][f] = GP[pos[e]][pos[f]] for e, f < n (both triangles, f32 or f64,
-// pitch ld): the product of the A-rows (GP, made symmetric first) back in the
-// order of the distinct rows.
+// pitch ld), from the lower triangle of GP: the product of the A-rows back in
+// the order of the distinct rows, exactly symmetric.
 void launch_gram_unpermute(int f32, const void *GP, const int32_t *pos, int64_t n, int64_t ld, void *G,
                            hipStream_t s);
 // Whether the FP64 product of this shape runs on 128 x 256 tiles (else on
