@@ -355,8 +355,9 @@ __device__ __forceinline__ void diag_load(DiagLds &S, const double *__restrict__
     read(x[0], p);
     diag_copy<R0>(S, Wm, ld, r0, jb, lane);
     diag_copy<R1>(S, Wm, ld, r0, jb, lane);
+    // (nothing to sum where both row blocks lie past a narrow last panel)
 #pragma unroll 1
-    for (int left = X.n; left > 0; --left) {
+    for (int left = R1 * RB < jb ? X.n : 0; left > 0; --left) {
       const double *next = left > 1 ? p + X.stride : p;
 #pragma unroll 1
       for (int s = 0; s < NT; s += 2) {
@@ -388,8 +389,10 @@ __device__ __forceinline__ void diag_load(DiagLds &S, const double *__restrict__
 // and the eight hand-overs between tiles (1600 cycles each): 17 us, where a
 // workgroup-wide 64 x 64 factorisation with one barrier per column took 28 us
 // and had to run twice.  Its loop is not unrolled, so that one copy of the code,
-// still in the instruction cache, runs all eight columns.
-__device__ __forceinline__ void diag_walk(DiagLds &S, const DiagRows<0> &T, int lane, double *__restrict__ pack,
+// still in the instruction cache, runs all eight columns.  A narrow last panel
+// stops after its last tile: 15 columns take
+// 3 us, and the whole launch 10 instead of 32.
+__device__ __forceinline__ void diag_walk(DiagLds &S, const DiagRows<0> &T, int jb, int lane, double *__restrict__ pack,
                                           int *__restrict__ flag) {
   const int r = lane & 15, g = lane >> 4;
   const f64x4 z = f64x4{0.0, 0.0, 0.0, 0.0};
@@ -398,7 +401,7 @@ __device__ __forceinline__ void diag_walk(DiagLds &S, const DiagRows<0> &T, int 
   put_tile(S.tile + diag_at(1, 1), lane, T.a[1]);
   f64x4 next = T.b[0];
 #pragma unroll 1
-  for (int j = 0; j < NT; ++j) {
+  for (int j = 0; j * RB < jb; ++j) {
     double row[RB];
     const f64x4 inv = factor_tile(next, S.row, lane, row, bad);
     put_tile(S.inv, lane, inv);
@@ -427,11 +430,12 @@ __device__ __forceinline__ void diag_walk(DiagLds &S, const DiagRows<0> &T, int 
 }
 
 template <int W>
-__device__ __forceinline__ void diag_follow(DiagLds &S, DiagRows<W> &T, int lane) {
+__device__ __forceinline__ void diag_follow(DiagLds &S, DiagRows<W> &T, int jb, int lane) {
   constexpr int R0 = DiagRows<W>::R0, R1 = DiagRows<W>::R1;  // R0 > R1
   const f64x4 z = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
+    if (j * RB >= jb) break;
     if (j > 0) {
       // column j - 1, but for tile (j, j), which wavefront 0 has
 #pragma unroll
@@ -472,19 +476,19 @@ __device__ __forceinline__ void diag_block(DiagLds &S, double *__restrict__ Wm, 
   if (w == 0) {
     DiagRows<0> T;
     diag_load<0, UPDATE>(S, Wm, ld, j0, jb, X, lane, T);
-    diag_walk(S, T, lane, pack, flag);
+    diag_walk(S, T, jb, lane, pack, flag);
   } else if (w == 1) {
     DiagRows<1> T;
     diag_load<1, UPDATE>(S, Wm, ld, j0, jb, X, lane, T);
-    diag_follow<1>(S, T, lane);
+    diag_follow<1>(S, T, jb, lane);
   } else if (w == 2) {
     DiagRows<2> T;
     diag_load<2, UPDATE>(S, Wm, ld, j0, jb, X, lane, T);
-    diag_follow<2>(S, T, lane);
+    diag_follow<2>(S, T, jb, lane);
   } else {
     DiagRows<3> T;
     diag_load<3, UPDATE>(S, Wm, ld, j0, jb, X, lane, T);
-    diag_follow<3>(S, T, lane);
+    diag_follow<3>(S, T, jb, lane);
   }
   // L to the matrix, eight rows of 128 B per store, and its tiles off the
   // diagonal, packed, to pack: nine tiles per wavefront
@@ -562,6 +566,7 @@ __global__ __launch_bounds__(256) void k_solve(double *__restrict__ Wm, int64_t 
     }
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
+    if (j * RB >= jb) break;
     T[j] = tile_fma(get_tile(lp + diag_at(j, j), lane), T[j], f64x4{0.0, 0.0, 0.0, 0.0});
 #pragma unroll
     for (int t = j + 1; t < NT; ++t) T[t] = tile_fms(get_tile(lp + diag_at(t, j), lane), T[j], T[t]);
