@@ -159,16 +159,16 @@ void launch_rowexp(const AsmArgs &a, int32_t *row_exp2, double *d, double *r, hi
 // (gd) comes with the rows' factors.
 constexpr int SPLIT_PANEL = 256;  // rows per panel: the bf16 Gram tile
 
-// A workgroup's largest shares are found in LDS first (best [n_panels]; 0 panels:
-// straight in global memory): 4550 rows 5 us, with every lane's atomic on a
-// handful of addresses 27.
+// A workgroup's largest shares are found in LDS first (best [n_panels], 8 bytes
+// for each 256 rows of the product): 4550 rows 5 us, with every lane's atomic on
+// a handful of global addresses 27.
 __global__ void k_split_share(AsmArgs A, const double *__restrict__ gd, double *F, const int32_t *__restrict__ pos,
                               int n_panels) {
   extern __shared__ unsigned long long best[];
   for (int i = threadIdx.x; i < n_panels; i += blockDim.x) best[i] = 0;
   __syncthreads();
   const int64_t a = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  unsigned long long *Fb = (unsigned long long *)F, *to = n_panels ? best : Fb;
+  unsigned long long *Fb = (unsigned long long *)F;
   double f = 0.0;
   if (a < A.n) {
     const int32_t *ra = A.rowO + 8 * a;
@@ -179,7 +179,7 @@ __global__ void k_split_share(AsmArgs A, const double *__restrict__ gd, double *
     // a share of 1 (no other term) for a row whose diagonal is not positive
     f = c > 0.0 && isfinite(c) ? c1h / c : 1.0;
     // non-negative doubles order like their bit patterns; the panel of the row's A-row
-    atomicMax(&to[(pos ? pos[e] : e) / SPLIT_PANEL], (unsigned long long)__double_as_longlong(f));
+    atomicMax(&best[(pos ? pos[e] : e) / SPLIT_PANEL], (unsigned long long)__double_as_longlong(f));
   }
   f = wave_max(f);
   if ((threadIdx.x & (WAVE - 1)) == 0)
@@ -190,8 +190,7 @@ __global__ void k_split_share(AsmArgs A, const double *__restrict__ gd, double *
 }
 
 void launch_split_share(const AsmArgs &a, const double *gd, double *F, const int32_t *pos, hipStream_t s) {
-  const int64_t panels = a.ld_g / SPLIT_PANEL;
-  const int n = panels <= 4096 ? (int)panels : 0;  // 32 KB of LDS: a million rows
+  const int n = (int)(a.ld_g / SPLIT_PANEL);
   hipLaunchKernelGGL(k_split_share, dim3((unsigned)((a.n + 255) / 256)), dim3(256), (size_t)n * 8, s, a, gd, F, pos, n);
 }
 
@@ -206,7 +205,10 @@ void launch_split_share(const AsmArgs &a, const double *gd, double *F, const int
 // responses, so a workgroup waits on global memory twice before it writes.
 constexpr int AT = 64;
 constexpr int ASM_XCD = 8;
-constexpr int64_t ASM_WIDE = 6000;
+// Up to here four entries per thread: a workgroup is a chain of loads, and the
+// few of a small matrix are over sooner (818 rows 24.5 us for the phase
+// against 34.6 with sixteen, 3750 rows 54 and 56, 7625 rows 146 and 107)
+constexpr int64_t ASM_WIDE = 4000;
 
 // Q entries for each thread (4096 / Q threads).
 template <typename OutT, int Q>
