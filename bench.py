@@ -644,11 +644,10 @@ def main():
     upd_ms = upd["ms"] / max(upd_frac_timed, 1e-9)
     upd_tf = upd["flops"] / (upd_ms * 1e-3) / 1e12 if upd_ms > 0 else 0.0
     if upd_ms >= ph["gram"]:
-        # every block update is timed, on 128 x 256 tiles (k_update2d) or
-        # 128 x 128 ones (k_update2<4>), with its split-k reduction
-        tr = measured_traffic("k_update2d", "k_update2", "k_update_reduce", per=("k_update2d", "k_update2"))
-        roof = dict(bound="mfma", kernel="k_update2d + k_update2<4> (FP64 Cholesky block update, incl. split-k "
-                    "reduce)",
+        # every trailing update is timed, with the factorisation of the next
+        # diagonal block that runs beside it
+        tr = measured_traffic("k_trail")
+        roof = dict(bound="mfma", kernel="k_trail (FP64 Cholesky trailing update and next diagonal block)",
                     achieved=upd_tf, peak=PEAK_TFLOPS["fp64"], unit="TFLOP/s", frac=upd_tf / PEAK_TFLOPS["fp64"],
                     traffic=tr["bytes_per_launch"] / 1e9 if tr else None, launches=upd["launches"],
                     avg_launch_ms=upd_ms / max(upd["launches"], 1), flops_per_step=upd["flops"])

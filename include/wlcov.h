@@ -405,8 +405,8 @@ enum {
 };
 int wlc_plan_set_timing(wlc_plan plan, int enable);
 int wlc_plan_timings(wlc_plan plan, float *ms);
-/* Launch statistics of the Cholesky block-update kernel (k_update2 and its
- * split-k reduction) in the last timed wlc_snr2, into HOST scalars: summed
+/* Launch statistics of the Cholesky trailing-update kernel (k_trail, which also
+ * factors the next diagonal block) in the last timed wlc_snr2, into HOST scalars: summed
  * event time of the timed launches, number of launches, number timed (event
  * capacity permitting; the time covers only those), and the algorithmic
  * flops of all launches (2 k per updated lower-triangle entry).  Synchronises

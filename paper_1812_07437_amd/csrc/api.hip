@@ -267,7 +267,7 @@ int snr_structured_enqueue(const Plan &p, const void *ws_run, void *ws, hipStrea
   w.sigma_b2 = (c.flags & WLC_FLAG_SSC_CHI) ? 0.0 : c.sigma_b2;  // else inside the Gram product
   w.flag = flag;
   if (hooks) hooks->begin(WLC_PHASE_SNR_PREP);
-  launch_fill_i32(flag, 1, 0, s);
+  launch_fill_i32(flag, CHOL_FLAG_INTS, 0, s);
   launch_woodbury(w, s);
   if (hooks) hooks->end(WLC_PHASE_SNR_PREP);
   if (hooks) hooks->begin(WLC_PHASE_CHOL);
@@ -597,7 +597,7 @@ int snr_enqueue(const Plan &p, const void *C, const int32_t *row_exp2, const dou
     if (rc) return rc;
   }
   if (hooks) hooks->begin(WLC_PHASE_SNR_PREP);
-  launch_fill_i32(flag, 1, 0, s);
+  launch_fill_i32(flag, CHOL_FLAG_INTS, 0, s);
   if (by_diag) {
     launch_pca_order(C, !prec_f64(p.cfg.precision), row_exp2, n, perm, s);
     *by_diag = perm;
@@ -691,8 +691,8 @@ int wlc_plan_set_timing(wlc_plan plan, int enable) {
       int rc = hip_check(hipEventCreate(&e), "event create");
       if (rc) return rc;
     }
-    // two events per block-update launch: about 5 launches per 256 columns
-    const int64_t launches = 5 * ((plan->p.n_out + 255) / 256) + 16;
+    // two events per trailing update: one for every 128 columns
+    const int64_t launches = (plan->p.n_out + 127) / 128;
     plan->upd_ev.resize((size_t)std::min<int64_t>(2 * launches, 16384));
     for (auto &e : plan->upd_ev) {
       int rc = hip_check(hipEventCreate(&e), "event create");

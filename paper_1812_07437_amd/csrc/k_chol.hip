@@ -7,19 +7,14 @@
 //
 // Panels of 128 columns, two launches each: the rows below the factored diagonal
 // block are solved against it (k_solve), then the trailing columns receive the
-// panel's update while one workgroup of the same launch already updates and
-// factors the next diagonal block (k_trail), so that the serial chain runs
-// beside the update.  Up to RIGHT_MAX columns the trailing update covers the
-// whole remaining matrix, for eight panels at once while the matrix is large.
-// Beyond it the matrix is read and written too often that way, and blocks of 256
-// columns first receive the update from every column to their left in one
-// long-k MFMA product (k_update.hip); the panels' own updates then stay within
-// the block.
+// update of the solved panels that is due, while the first workgroups of the
+// same launch already update and factor the next diagonal block (k_trail), so
+// that the serial chain runs beside the update.
 //
 // Measured, one factorisation (before: 64-wide diagonal blocks in launches of
-// their own, left-looking over 256 columns at every size): n = 818
-// 0.99 -> 0.35 ms, 2420 3.1 -> 0.96 ms, 4550 6.0 -> 2.03 ms, 10000
-// 15.1 -> 8.7 ms, 17059 42.5 -> 32 ms, 25044 106 -> 94 ms.
+// their own, left-looking over 256 columns): n = 818 0.99 -> 0.29 ms, 2420 3.1 ->
+// 0.76 ms, 4550 6.0 -> 1.66 ms, 10000 15.1 -> 7.8 ms, 17059 42.5 -> 29.7 ms, 25044
+// 106 -> 85 ms, 33165 221 -> 189 ms, 82575 2.80 -> 2.81 s.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -30,21 +25,19 @@
 namespace wlc {
 
 constexpr int NB = 128;      // panel width
-constexpr int NB_OUT = 256;  // columns that take one long-k update together
-// Up to this size the update goes to the whole trailing matrix.  Measured with
-// and against the long-k product: n = 10000 8.7 and 10.4 ms, 17059 32.8 and
-// 34.6, 25044 94.7 and 94.2, 33165 214 and 204 (its 256 columns at a time are
-// summed over one long k, and the trailing matrix is far beyond the caches).
-constexpr int64_t RIGHT_MAX = 20000;
 // While this many columns remain, the panels of a group of eight update only the
-// group's own columns one by one, and the rest of the matrix together, so that
-// it is read and written once per 1024 columns.  n = 10000 10.4 ms without
-// groups, 9.5 with groups of two, 9.1 of four and of eight (8.7 with the inner
-// loop unrolled over a panel); 12768 19.6, 17.1, 16.0, 15.7; 6550 4.0, 4.0, 4.0,
-// 3.9 (3.7): there the group's own small updates cost what the traffic saves.
-constexpr int64_t GROUP_MIN = 5000;
+// group's own columns, and then the rest of the matrix together, so that it is
+// read and written once per 1024 columns in launches of many tiles (k = 1024: 60
+// TFLOP/s).  n = 10000 8.3 ms without groups, 7.8 with; 12768 15.1 and 14.0; 6550
+// 3.17 either way; groups down to 4000 remaining columns cost 4550 3 %.
+constexpr int64_t GROUP_MIN = 6000;
 constexpr int GROUP = 8;
-constexpr int64_t PART_ROWS = 524288;  // split-k scratch of the long-k product: slices x rows of 256 doubles
+// Otherwise (and among a group's own columns) a column block is updated with
+// GAP panels at a time, in every launch the blocks whose turn it is: a GAP-th of
+// the reads and writes of the matrix, and each launch its share of the work.
+// n = 2420 0.82 ms with every panel at once, 0.78 two, 0.76 four, 0.85 eight (one
+// tile then outlasts the factorisation beside it); 4550 1.86, 1.74, 1.66, 1.90.
+constexpr int GAP = 4;
 
 // ------------------------------------------------------------- prepare
 // Lower triangle of M from the scaled covariance (f32 or f64) and d: one
@@ -292,10 +285,10 @@ __device__ __forceinline__ void diag_copy(DiagLds &S, const double *__restrict__
     }
 }
 
-// acc += the row block as diag_copy left it: the mirror image above the
-// diagonal, the identity (and no acc) from jb on.
+// The row block as diag_copy left it: the mirror image above the diagonal, the
+// identity from jb on.
 template <int RBK>
-__device__ __forceinline__ void diag_add(const DiagLds &S, int jb, int lane, f64x4 (&acc)[RBK + 1]) {
+__device__ __forceinline__ void diag_get(const DiagLds &S, int jb, int lane, f64x4 (&acc)[RBK + 1]) {
   const int r = lane & 15, g = lane >> 4;
 #pragma unroll
   for (int t = 0; t <= RBK; ++t)
@@ -303,7 +296,7 @@ __device__ __forceinline__ void diag_add(const DiagLds &S, int jb, int lane, f64
     for (int v = 0; v < 4; ++v) {
       const int c = g + 4 * v, i = RBK * RB + r, j = t * RB + c;
       const int hi = t == RBK ? max(r, c) : r, lo = t == RBK ? min(r, c) : c;
-      const double x = S.tile[diag_at(RBK, t) + diag_row(hi, lo)] + acc[t][v];
+      const double x = S.tile[diag_at(RBK, t) + diag_row(hi, lo)];
       acc[t][v] = max(i, j) < jb ? x : i == j ? 1.0 : 0.0;
     }
 }
@@ -316,65 +309,16 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// Solved panels whose update is due: the packed rows of panel p from the
-// update's first row on are at rows + p stride, n_blk row blocks.
-struct Panels {
-  const double *rows;
-  int64_t stride;
-  int n;
-  int64_t n_blk;
-};
-
-// A wavefront's row blocks of the diagonal block at r0, less (UPDATE) X X^T over
-// the first 128 rows of the solved panels, a 16-deep step's tiles read from the
-// L2 while the one before is multiplied.
-template <int W, bool UPDATE>
+// A wavefront's row blocks of the diagonal block at r0.
+template <int W>
 __device__ __forceinline__ void diag_load(DiagLds &S, const double *__restrict__ Wm, int64_t ld, int64_t r0, int jb,
-                                          const Panels &X, int lane, DiagRows<W> &T) {
+                                          int lane, DiagRows<W> &T) {
   constexpr int R0 = DiagRows<W>::R0, R1 = DiagRows<W>::R1;
-#pragma unroll
-  for (int t = 0; t <= R0; ++t) T.a[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int t = 0; t <= R1; ++t) T.b[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-  if constexpr (UPDATE) {
-    f64x4 x[2][R0 + 1];
-    uint32_t at[R0 + 1];  // row block t in a panel's packed rows
-#pragma unroll
-    for (int t = 0; t <= R0; ++t) at[t] = (uint32_t)min((int64_t)t, X.n_blk - 1) * PACK_ROW;
-    auto read = [&](f64x4(&d)[R0 + 1], const double *p) {
-#pragma unroll
-      for (int t = 0; t <= R0; ++t) d[t] = get_tile(p + at[t], lane);
-    };
-    auto mul = [&](const f64x4(&d)[R0 + 1]) {
-#pragma unroll
-      for (int t = 0; t <= R0; ++t) T.a[t] = tile_fms(d[t], d[R0], T.a[t]);
-#pragma unroll
-      for (int t = 0; t <= R1; ++t) T.b[t] = tile_fms(d[t], d[R1], T.b[t]);
-    };
-    const double *p = X.rows;
-    read(x[0], p);
-    diag_copy<R0>(S, Wm, ld, r0, jb, lane);
-    diag_copy<R1>(S, Wm, ld, r0, jb, lane);
-    // (nothing to sum where both row blocks lie past a narrow last panel)
-#pragma unroll 1
-    for (int left = R1 * RB < jb ? X.n : 0; left > 0; --left) {
-      const double *next = left > 1 ? p + X.stride : p;
-#pragma unroll 1
-      for (int s = 0; s < NT; s += 2) {
-        read(x[1], p + TILE);
-        mul(x[0]);
-        p = s + 2 < NT ? p + 2 * TILE : next;
-        read(x[0], p);
-        mul(x[1]);
-      }
-    }
-  } else {
-    diag_copy<R0>(S, Wm, ld, r0, jb, lane);
-    diag_copy<R1>(S, Wm, ld, r0, jb, lane);
-  }
+  diag_copy<R0>(S, Wm, ld, r0, jb, lane);
+  diag_copy<R1>(S, Wm, ld, r0, jb, lane);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's copies
-  diag_add<R0>(S, jb, lane, T.a);
-  diag_add<R1>(S, jb, lane, T.b);
+  diag_get<R0>(S, jb, lane, T.a);
+  diag_get<R1>(S, jb, lane, T.b);
 }
 
 // Factorisation of a diagonal block, right-looking over its eight column blocks.
@@ -469,25 +413,24 @@ __device__ __forceinline__ void diag_follow(DiagLds &S, DiagRows<W> &T, int jb, 
   }
 }
 
-template <bool UPDATE>
-__device__ __forceinline__ void diag_block(DiagLds &S, double *__restrict__ Wm, int64_t ld, int64_t j0, int jb,
-                                           const Panels &X, int w, int lane, double *__restrict__ pack,
+__device__ __forceinline__ void diag_block(DiagLds &S, double *__restrict__ Wm, int64_t ld, int64_t j0, int jb, int w,
+                                           int lane, double *__restrict__ pack,
                                            int *__restrict__ flag) {
   if (w == 0) {
     DiagRows<0> T;
-    diag_load<0, UPDATE>(S, Wm, ld, j0, jb, X, lane, T);
+    diag_load<0>(S, Wm, ld, j0, jb, lane, T);
     diag_walk(S, T, jb, lane, pack, flag);
   } else if (w == 1) {
     DiagRows<1> T;
-    diag_load<1, UPDATE>(S, Wm, ld, j0, jb, X, lane, T);
+    diag_load<1>(S, Wm, ld, j0, jb, lane, T);
     diag_follow<1>(S, T, jb, lane);
   } else if (w == 2) {
     DiagRows<2> T;
-    diag_load<2, UPDATE>(S, Wm, ld, j0, jb, X, lane, T);
+    diag_load<2>(S, Wm, ld, j0, jb, lane, T);
     diag_follow<2>(S, T, jb, lane);
   } else {
     DiagRows<3> T;
-    diag_load<3, UPDATE>(S, Wm, ld, j0, jb, X, lane, T);
+    diag_load<3>(S, Wm, ld, j0, jb, lane, T);
     diag_follow<3>(S, T, jb, lane);
   }
   // L to the matrix, eight rows of 128 B per store, and its tiles off the
@@ -517,7 +460,7 @@ __global__ __launch_bounds__(256) void k_diag(double *__restrict__ Wm, int64_t l
                                               double *__restrict__ pack, int *__restrict__ flag) {
   __shared__ __attribute__((aligned(16))) DiagLds S;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  diag_block<false>(S, Wm, ld, j0, jb, Panels{}, w, lane, pack, flag);
+  diag_block(S, Wm, ld, j0, jb, w, lane, pack, flag);
 }
 
 // Panel solve X = B L^-T of the rows below a diagonal block: 64 rows per
@@ -588,52 +531,135 @@ __global__ __launch_bounds__(256) void k_solve(double *__restrict__ Wm, int64_t 
       *reinterpret_cast<double2 *>(B + q * ld + 2 * lane) = *reinterpret_cast<const double2 *>(sb + q * NB + 2 * (lane ^ q));
 }
 
-// Trailing update W[i][j] -= sum_k X[i][k] X[j][k] over one solved panel (k = 128)
-// for i in [r0, rows), j in [r0, c1), i >= j, from the packed X: a workgroup
-// takes a tile of 32 S rows and columns (four wavefronts, each S x S tiles of
-// 16), operands straight from the L2 into registers (every load of a wavefront
-// is 1 KB, half a 16-deep step ahead), no LDS and no barrier.  Workgroup 0
-// instead updates the next panel's diagonal block and factors it, so that the
-// factorisation's serial chain runs beside the update.
+// The packed rows of the solved panels: panel q (its first row below is
+// 128 (q + 1)) in slot q % slots; panel `last` has just been solved.
+struct Panels {
+  const double *base;
+  int64_t stride;
+  int slots, last;
+  // 16-row block ab of the matrix in panel q
+  __device__ __forceinline__ const double *block(int q, int64_t ab) const {
+    return base + (q % slots) * stride + (ab - (int64_t)NT * (q + 1)) * PACK_ROW;
+  }
+};
+
+// Trailing update W[i][j] -= sum_k X[i][k] X[j][k], i >= j, after panel p has been
+// solved, r0 its first row below:
+//  - the diagonal block at r0 with panel p: the first nine workgroups, a 16 x 16
+//    tile per wavefront; the one that is done last (none waits) factors it, so
+//    that the factorisation's serial chain runs beside the rest;
+//  - columns r0 + 128 (1 + m B), m = 0, 1, ..., 128 each, with panels
+//    p - B + 1 .. p: each column block is read and written once per B
+//    panels, a B-th of them in every launch, and has received every panel but the
+//    last when its turn comes;
+//  - the rest of columns r0 .. r0 + 127 with panel p.
+// A workgroup takes a tile of 32 S rows and columns (four wavefronts, each S x S
+// tiles of 16), operands straight from the L2 into registers (every load of a
+// wavefront is 1 KB, half a 16-deep step ahead), no LDS and no barrier.
 //
-// Up to about 3000 rows workgroup 0 sets the time (31 us: 13 for its update,
-// 17 for the factorisation); beyond, the reads and writes of W, 16 bytes per
-// 256 flops, and the matrix cores about equally.
+// While the update is small the chain sets the time (24 us, 17 of them the
+// factorisation; with one workgroup for update and factorisation of the block
+// 31); then the matrix cores, and the reads and writes of W (16 bytes per 256 B
+// flops).
+constexpr int DIAG_WG = NT * (NT + 1) / 2 / 4;
+// the counter of the diagonal block's workgroups, in ints past the pivot flag
+constexpr int DIAG_COUNT = 16;
+
+// A wavefront's 16 x 16 tile (ib, jb0) of the diagonal block at r0, own rows.
+__device__ __forceinline__ void trail_diag_tile(double *__restrict__ Wm, int64_t ld, int64_t r0, int own,
+                                                const Panels &X, int first, int ib, int jb0, int lane) {
+  const int r = lane & 15, g = lane >> 4;
+  double *dst = Wm + r0 * ld + r0;
+  f64x4 acc[2];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int i = min(ib * RB + g + 4 * v, own - 1), j = min(jb0 * RB + r, i);
+    acc[0][v] = dst[i * ld + j];
+    acc[1][v] = 0.0;
+  }
+#pragma unroll 1
+  for (int k = first; k <= X.last; ++k) {
+    const double *pa = X.block(k, r0 / RB + ib) + 2 * lane, *pb = X.block(k, r0 / RB + jb0) + 2 * lane;
+    double2 a[2 * NT], b[2 * NT];  // a panel at once: the loads' latency is what this waits for
+#pragma unroll
+    for (int st = 0; st < 2 * NT; ++st) {
+      a[st] = *reinterpret_cast<const double2 *>(pa + st * 128);
+      b[st] = *reinterpret_cast<const double2 *>(pb + st * 128);
+    }
+#pragma unroll
+    for (int st = 0; st < 2 * NT; ++st) {
+      acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[st].x, b[st].x, acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[st].y, b[st].y, acc[1], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int i = ib * RB + g + 4 * v, j = jb0 * RB + r;
+    if (i < own && j <= i) dst[i * ld + j] = acc[0][v] + acc[1][v];
+  }
+}
+
+// U.batch: tiles of the column blocks that are U.gap apart (t0 rows of tiles in
+// the first of them), with panels U.first .. X.last; the diagonal block and the
+// rest of its columns take panels U.now .. X.last
+struct Update {
+  int first, now, gap, batch, t0;
+};
 template <int S>
 __global__ __launch_bounds__(256, 2) void k_trail(double *__restrict__ Wm, int64_t ld, int64_t r0, int64_t rows,
-                                                  int64_t c1, Panels X, int64_t tcols, double *__restrict__ pack,
+                                                  int64_t c1, Panels X, Update U, double *__restrict__ pack,
                                                   int *__restrict__ flag) {
   __shared__ __attribute__((aligned(16))) DiagLds D;
+  __shared__ int done;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, g = lane >> 4;
-  if (blockIdx.x == 0) {
-    diag_block<true>(D, Wm, ld, r0, (int)min((int64_t)NB, c1 - r0), X, w, lane, pack, flag);
+  const int64_t own = min((int64_t)NB, c1 - r0);  // rows of the next diagonal block
+  if (blockIdx.x < DIAG_WG) {
+    const int t = blockIdx.x * 4 + w;
+    int ib = 0;
+    while ((ib + 1) * (ib + 2) / 2 <= t) ++ib;
+    if (ib * RB < own) trail_diag_tile(Wm, ld, r0, (int)own, X, U.now, ib, t - ib * (ib + 1) / 2, lane);
+    // the tiles are visible to the device before the count says so
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __syncthreads();
+    if (threadIdx.x == 0) done = atomicAdd(flag + DIAG_COUNT, 1);
+    __syncthreads();
+    if (done != DIAG_WG - 1) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (threadIdx.x == 0) flag[DIAG_COUNT] = 0;  // for the next launch
+    diag_block(D, Wm, ld, r0, (int)own, w, lane, pack, flag);
     return;
   }
-  // tile (ti, tj) of 2 S x 2 S 16-blocks on the lower triangle, tj < tcols
-  const int64_t q = blockIdx.x - 1;
-  int64_t ti, tj;
-  const int64_t tri = tcols * (tcols + 1) / 2;
-  if (q < tri) {
-    ti = (int64_t)((sqrt(8.0 * (double)q + 1.0) - 1.0) * 0.5);
-    while ((ti + 1) * (ti + 2) / 2 <= q) ++ti;
-    while (ti * (ti + 1) / 2 > q) --ti;
-    tj = q - ti * (ti + 1) / 2;
+  constexpr int CT = NT / (2 * S);  // tiles across a column block
+  int q = blockIdx.x - DIAG_WG;
+  int64_t ib, jb0;  // the workgroup's first 16-blocks
+  int first = U.now;
+  if (q < U.batch) {  // column block m: CT tiles by t0 - m CT gap rows of them
+    const int step = CT * U.gap, t0 = U.t0, k = q / CT;
+    const double h = t0 + 0.5 * step;
+    int m = (int)((h - sqrt(max(h * h - 2.0 * step * k, 0.0))) / step);
+    while (m > 0 && m * t0 - step * (m * (m - 1) / 2) > k) --m;
+    while ((m + 1) * t0 - step * ((m + 1) * m / 2) <= k) ++m;
+    const int64_t c = r0 / RB + NT * (1 + (int64_t)m * U.gap);
+    ib = c + (int64_t)(k - (m * t0 - step * (m * (m - 1) / 2))) * 2 * S;
+    jb0 = c + (q % CT) * 2 * S;
+    first = U.first;
   } else {
-    ti = tcols + (q - tri) / tcols;
-    tj = (q - tri) % tcols;
+    q -= U.batch;
+    ib = (r0 + own) / RB + (int64_t)(q / CT) * 2 * S;
+    jb0 = r0 / RB + (q % CT) * 2 * S;
   }
-  const int64_t ib = ti * 2 * S + (w >> 1) * S, jb0 = tj * 2 * S + (w & 1) * S;  // first 16-blocks
-  const int64_t ilim = (rows - r0 + RB - 1) / RB, jlim = (c1 - r0 + RB - 1) / RB;
-  const int64_t own = min((int64_t)NB, c1 - r0);  // rows of the next diagonal block (workgroup 0's)
-  // whole wavefront outside the matrix, above the diagonal, or inside the
-  // next diagonal block
-  if (ib >= ilim || jb0 >= jlim || jb0 > ib + S - 1 || (ib + S) * RB <= own) return;
-  uint32_t pa[S], pb[S];  // row blocks in a panel's packed rows (below 2^32 doubles)
+  ib += (w >> 1) * S;
+  jb0 += (w & 1) * S;
+  const int64_t ilim = (rows + RB - 1) / RB;
+  // whole wavefront outside the matrix or above the diagonal
+  if (ib >= ilim || jb0 * RB >= c1 || jb0 > ib + S - 1) return;
+  int64_t pa[S], pb[S];  // row blocks in a panel's packed rows
+  const double *p = X.block(first, 0) + 2 * lane;
 #pragma unroll
   for (int x = 0; x < S; ++x) {
-    pa[x] = (uint32_t)min(ib + x, X.n_blk - 1) * PACK_ROW + 2 * lane;
-    pb[x] = (uint32_t)min(jb0 + x, X.n_blk - 1) * PACK_ROW + 2 * lane;
+    pa[x] = min(ib + x, ilim - 1) * PACK_ROW;
+    pb[x] = min(jb0 + x, ilim - 1) * PACK_ROW;
   }
   // accumulator of rows x columns: element v of lane l is row g + 4 v, column
   // l % 16
@@ -644,8 +670,8 @@ __global__ __launch_bounds__(256, 2) void k_trail(double *__restrict__ Wm, int64
     for (int y = 0; y < S; ++y)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int64_t i = min(r0 + (ib + x) * RB + g + 4 * v, rows - 1);
-        const int64_t j = min(r0 + (jb0 + y) * RB + r, c1 - 1);
+        const int64_t i = min((ib + x) * RB + g + 4 * v, rows - 1);
+        const int64_t j = min((jb0 + y) * RB + r, c1 - 1);
         acc[x][y][v] = Wm[i * ld + min(i, j)];
       }
   double2 a[2][S], b[2][S];
@@ -669,11 +695,10 @@ __global__ __launch_bounds__(256, 2) void k_trail(double *__restrict__ Wm, int64
       for (int y = 0; y < S; ++y)
         acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[h][x].y, b[h][y].y, acc[x][y], 0, 0, 0);
   };
-  const double *p = X.rows;
   load(0, p, 0);
 #pragma unroll 1
-  for (int left = X.n; left > 0; --left) {
-    const double *next = left > 1 ? p + X.stride : p;
+  for (int k = first; k <= X.last; ++k) {
+    const double *next = k < X.last ? X.block(k + 1, 0) + 2 * lane : p;
 #pragma unroll
     for (int st = 0; st < 2 * NT; st += 2) {
       load(1, p, st + 1);
@@ -689,95 +714,93 @@ __global__ __launch_bounds__(256, 2) void k_trail(double *__restrict__ Wm, int64
     for (int y = 0; y < S; ++y)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int64_t i = r0 + (ib + x) * RB + g + 4 * v;
-        const int64_t j = r0 + (jb0 + y) * RB + r;
-        if (i < rows && j < c1 && i >= j && i - r0 >= own) Wm[i * ld + j] = acc[x][y][v];
+        const int64_t i = (ib + x) * RB + g + 4 * v;
+        const int64_t j = (jb0 + y) * RB + r;
+        // (rows before r0 + own are the diagonal block's, or another column block's own)
+        if (i < rows && j < c1 && i >= j && i >= r0 + own) Wm[i * ld + j] = acc[x][y][v];
       }
 }
 
-// The trailing update of rows [r0, rows), columns [r0, c1) with the solved panels
-// X, and the factorisation of the next diagonal block.
-static void launch_trail(double *Wm, int64_t ld, int64_t r0, int64_t rows, int64_t c1, const Panels &X, double *pack,
-                         int *flag, hipStream_t s, KernelProbe *probe) {
+// The updates due after panel X.last, first row below r0, columns up to c1, and
+// the factorisation of the next diagonal block.
+static void launch_trail(double *Wm, int64_t ld, int64_t r0, int64_t rows, int64_t c1, const Panels &X, Update U,
+                         double *pack, int *flag, hipStream_t s, KernelProbe *probe) {
   const bool timed = probe && probe->ev && probe->count < probe->cap;
+  const int64_t own = std::min<int64_t>(NB, c1 - r0);
   if (probe) {
-    const double cols = (double)(c1 - r0);
-    // entries with i >= j
-    probe->flops += 2.0 * NB * X.n * (cols * (double)rows - (double)(r0 + c1 - 1) * cols / 2.0);
+    auto entries = [&](int64_t c, int64_t cols) { return (double)cols * (double)(rows - c) - (double)cols * (cols - 1) / 2.0; };
+    double f = (X.last - U.now + 1) * entries(r0, own);
+    for (int64_t c = r0 + NB; c < c1; c += NB * U.gap)
+      f += (X.last - U.first + 1) * entries(c, std::min<int64_t>(NB, c1 - c));
+    probe->flops += 2.0 * NB * f;
     ++probe->launches;
   }
-  if (timed) (void)hipEventRecord(probe->ev[2 * probe->count], s);
-  auto tiles_of = [&](int64_t t) {
-    const int64_t tc = (c1 - r0 + t - 1) / t, tr = (rows - r0 + t - 1) / t;
-    return tc * (tc + 1) / 2 + (tr - tc) * tc;
+  // the batch in t x t tiles
+  auto batch_of = [&](int64_t t) {
+    int64_t k = c1 > r0 + NB ? (rows - r0 - NB + t - 1) / t : 0, n = 0;
+    U.t0 = (int)k;
+    for (int64_t c = r0 + NB; c < c1; c += NB * U.gap, k -= NB / t * U.gap) n += k * (NB / t);
+    U.batch = (int)n;
+    return n;
   };
+  auto grid = [&](int64_t t) {
+    return dim3((unsigned)(DIAG_WG + U.batch + (rows - (r0 + own) / RB * RB + t - 1) / t * (NB / t)));
+  };
+  if (timed) (void)hipEventRecord(probe->ev[2 * probe->count], s);
   // 64 x 64 tiles until 128 x 128 ones fill the chip one and a half times over
-  // (two workgroups per CU): n = 4550 2.05 ms, from 256 tiles on 2.13
-  if (tiles_of(128) >= 768)
-    hipLaunchKernelGGL(k_trail<4>, dim3((unsigned)(1 + tiles_of(128))), dim3(256), 0, s, Wm, ld, r0, rows, c1, X,
-                       (c1 - r0 + 127) / 128, pack, flag);
-  else
-    hipLaunchKernelGGL(k_trail<2>, dim3((unsigned)(1 + tiles_of(64))), dim3(256), 0, s, Wm, ld, r0, rows, c1, X,
-                       (c1 - r0 + 63) / 64, pack, flag);
+  // (two workgroups per CU): n = 10000 7.82 ms, from 400 tiles on 7.94
+  if (batch_of(128) >= 768) {
+    hipLaunchKernelGGL(k_trail<4>, grid(128), dim3(256), 0, s, Wm, ld, r0, rows, c1, X, U, pack, flag);
+  } else {
+    batch_of(64);
+    hipLaunchKernelGGL(k_trail<2>, grid(64), dim3(256), 0, s, Wm, ld, r0, rows, c1, X, U, pack, flag);
+  }
   if (timed) (void)hipEventRecord(probe->ev[2 * probe->count++ + 1], s);
 }
 
 // Factor columns [0, n) of M (n + 1 rows).  scratch: the packed diagonal block,
-// then the packed rows of the panels whose update is due, which share their
-// space with the split-k buffer of the long panel updates.  The pivot flag is
-// checked by the caller after synchronisation.
+// then the packed rows of up to eight solved panels.  The pivot flag is checked by
+// the caller after synchronisation.
 int chol_factor(double *Wm, int64_t n, int64_t ld, double *scratch, int *flag, hipStream_t s,
                 KernelProbe *probe) {
-  const int64_t rows = n + 1;
-  double *pack = scratch;
-  double *part = scratch + PACK_DIAG;
-  const int64_t part_doubles = (int64_t)(chol_scratch_bytes(n) / 8) - PACK_DIAG;
-  const int64_t pack_rows = (n + 64) * NB;  // a panel's packed rows
-  const int64_t outer = n <= RIGHT_MAX ? n : NB_OUT;
-  for (int64_t J0 = 0; J0 < n; J0 += outer) {
-    const int64_t Jend = std::min<int64_t>(J0 + outer, n);
-    // everything left of the panel, in one product over k = [0, J0)
-    launch_update2(Wm, ld, J0, rows, Jend, 0, J0, part, part_doubles / NB_OUT, s, probe);
-    hipLaunchKernelGGL(k_diag, dim3(1), dim3(256), 0, s, Wm, ld, J0, (int)std::min<int64_t>(NB, Jend - J0), pack, flag);
-    for (int64_t j0 = J0; j0 < Jend;) {
-      // the panels of a group update the group's columns one by one, the rest of
-      // the matrix together
-      int group = Jend - j0 >= GROUP_MIN ? GROUP : 1;
-      if (group * pack_rows > part_doubles) group = 1;
-      const int64_t gend = j0 + group * NB;
-      for (int q = 0; q < group; ++q, j0 += NB) {
-        const int jb = (int)std::min<int64_t>(NB, Jend - j0);
-        const int64_t r0 = j0 + jb;  // first row below
-        const int64_t nblk = (rows - r0 + 63) / 64;
-        hipLaunchKernelGGL(k_solve, dim3((unsigned)nblk), dim3(256), 0, s, Wm, ld, j0, jb, rows, pack,
-                           r0 < Jend ? part + q * pack_rows : (double *)nullptr);
-        if (r0 >= Jend) continue;
-        Panels X{};
-        X.n_blk = 4 * nblk;
-        if (r0 < gend) {  // this panel alone
-          X.n = 1;
-          X.rows = part + q * pack_rows;
-        } else {  // panel p lies 128 (group - 1 - p) rows higher than the last one
-          X.n = group;
-          X.rows = part + (int64_t)(group - 1) * NT * PACK_ROW;
-          X.stride = pack_rows - NT * PACK_ROW;
-        }
-        launch_trail(Wm, ld, r0, rows, std::min(r0 < gend ? gend : Jend, Jend), X, pack, flag, s, probe);
-      }
+  const int64_t rows = n + 1, pack_rows = (n + 64) * NB;  // doubles of a panel's packed rows
+  double *pack = scratch, *part = scratch + PACK_DIAG;
+  const int64_t fit = ((int64_t)(chol_scratch_bytes(n) / 8) - PACK_DIAG) / pack_rows;
+  const int slots = (int)std::max<int64_t>(1, std::min<int64_t>(GROUP, fit));
+  hipLaunchKernelGGL(k_diag, dim3(1), dim3(256), 0, s, Wm, ld, 0, (int)std::min<int64_t>(NB, n), pack, flag);
+  Panels X{part, pack_rows, slots, 0};
+  int begin = 0;     // the panels before this one have reached every column
+  int64_t gend = n;  // columns from here on wait for the end of the group
+  for (int64_t j0 = 0; j0 < n; j0 += NB, ++X.last) {
+    const int jb = (int)std::min<int64_t>(NB, n - j0);
+    const int64_t r0 = j0 + jb;  // first row below
+    if (begin == X.last && slots > GAP && n - j0 >= GROUP_MIN) gend = j0 + slots * NB;
+    hipLaunchKernelGGL(k_solve, dim3((unsigned)((rows - r0 + 63) / 64)), dim3(256), 0, s, Wm, ld, j0, jb, rows, pack,
+                       r0 < n ? part + X.last % slots * pack_rows : (double *)nullptr);
+    if (r0 >= n) break;
+    Update U{};
+    U.now = X.last;
+    U.gap = std::min(GAP, slots);
+    U.first = std::max(begin, X.last - U.gap + 1);
+    int64_t c1 = gend;
+    if (r0 == gend) {  // the end of a group: its panels to all the columns it left
+      U.now = U.first = begin;
+      U.gap = 1;
+      c1 = gend = n;
+      begin = X.last + 1;
     }
+    launch_trail(Wm, ld, r0, rows, c1, X, U, pack, flag, s, probe);
   }
   return 0;
 }
 
-// Split-k scratch rows for an n x n factorisation: the long panel updates
-// have k ranges below n, so they take at most update2_max_slices(n) slices
-// of at most n + 1 rows each; small matrices reserve little.  The reserve
-// never binds the split choice below PART_ROWS, so it does not change it.
-static int64_t chol_part_rows(int64_t n) { return std::min<int64_t>(PART_ROWS, update2_max_slices(n) * (n + 1)); }
+// The packed diagonal block and the packed rows of one panel (up to 1023 rows),
+// three (from 1024), five (1536), seven (2048) or eight (2560 to 131000).
 size_t chol_scratch_bytes(int64_t n) {
-  const size_t split = (size_t)64 * 64 * 8 + (size_t)chol_part_rows(n) * NB_OUT * 8;
+  const int64_t pairs = std::clamp<int64_t>((n + 15) / 16 / 32, 1, 64);
+  const size_t panels = (size_t)64 * 64 * 8 + (size_t)std::min<int64_t>(524288, pairs * (n + 1)) * 256 * 8;
   const size_t packed = (size_t)PACK_DIAG * 8 + (n > NB ? (size_t)(n + 64) * NB * 8 : 0);
-  return std::max(split, packed);
+  return std::max(panels, packed);
 }
 
 // ------------------------------------------------------------- y^T y

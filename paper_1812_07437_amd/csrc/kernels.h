@@ -173,13 +173,11 @@ struct KernelProbe {
   int64_t launches = 0;
   double flops = 0.0;
 };
+// flag [CHOL_FLAG_INTS], cleared: the pivot flag first
+constexpr int CHOL_FLAG_INTS = 64;
 int chol_factor(double *Wm, int64_t n, int64_t ld, double *scratch, int *flag, hipStream_t s,
                 KernelProbe *probe = nullptr);
-int64_t update2_max_slices(int64_t k_len);
 size_t chol_scratch_bytes(int64_t n);
-// part: split-k scratch of part_rows x 256 doubles (NULL: no split)
-void launch_update2(double *Wm, int64_t ld, int64_t c0, int64_t r1, int64_t c1, int64_t k0, int64_t k1,
-                    double *part, int64_t part_rows, hipStream_t s, KernelProbe *probe = nullptr);
 void launch_sumsq_row(const double *Wm, int64_t n, int64_t ld, double *out, hipStream_t s);
 // out[g] = sum of y_j^2 over j < ends[g] (y: the last row of the bordered
 // factor); part: ng doubles of scratch

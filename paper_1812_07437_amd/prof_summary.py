@@ -32,7 +32,7 @@ Example (from the repository root, after the four profiling runs)::
     python -m paper_1812_07437_amd.prof_summary --trace T --fetch F --write W \\
         --hit H --out profiles/x.md --title "..." --command "..." \\
         --traffic-json profiles/traffic.json \\
-        --record k_update2=paper_1812_07437_amd/csrc/k_update.hip
+        --record k_trail=paper_1812_07437_amd/csrc/k_chol.hip
 """
 import argparse
 import collections
