@@ -646,7 +646,7 @@ __global__ __launch_bounds__(256) void k_gram_reduce(const T *__restrict__ part,
   T s[RED_ROWS / 2];
 #pragma unroll
   for (int q = 0; q < RED_ROWS / 2; ++q) s[q] = out[off + 2 * q * ld];  // slice 0
-#pragma unroll 2
+#pragma unroll 4
   for (int p = 1; p < n_split; ++p) {
     T v[RED_ROWS / 2];
 #pragma unroll
@@ -693,6 +693,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   int I, J;
   f64_gram_tile(w / n_split, I, J);
   const int64_t row0 = (int64_t)I * FT_R, col0 = (int64_t)J * FT_S;
+  if (row0 >= n) return;  // padding only
   if (panel_ext) {
     k_pad = min(k_pad, (int64_t)max(min(panel_ext[I >> 1], panel_ext[J]), 0) * GRAM_KB);
     k_split = (k_pad / FT_K + n_split - 1) / n_split * FT_K;

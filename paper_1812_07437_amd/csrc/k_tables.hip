@@ -521,7 +521,9 @@ __global__ __launch_bounds__(256) void k_abuild(const int32_t *__restrict__ rowR
 }
 
 // k-blocked bf16 (fmt 1: hi only; fmt 2: hi and lo; see launch_abuild): a 256-thread
-// block covers 64 rows and AB_KB consecutive 32-column k-blocks.  Each
+// block covers 64 rows and kb_wg consecutive 32-column k-blocks: AB_KB, or as many
+// fewer (four, one pass, at least) as it takes for 512 blocks (512 rows of 4608
+// k with lo: 12 us, with 32 k-blocks to each of 40 blocks 30).  Each
 // wavefront takes every fourth k-block of the block; in one, lane l converts
 // 8 consecutive k (chunk l % 4) of the rows l / 4 + 16 j, j < AB_RW, so that
 // each of its stores writes 16 whole rows of the k-block, 1 KB contiguous
@@ -562,7 +564,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FMT == 1 ? 
                                                    int64_t k_pad, int64_t r_pad, uint16_t *__restrict__ A0,
                                                    uint16_t *__restrict__ A1, const double *__restrict__ panel_f,
                                                    double lim, const int32_t *__restrict__ arow,
-                                                   const int32_t *__restrict__ ext) {
+                                                   const int32_t *__restrict__ ext, int kb_wg) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int chunk = lane & 3;
   const int64_t row0 = (int64_t)blockIdx.y * 64 + (lane >> 2);  // A-rows row0 + 16 j
@@ -570,7 +572,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FMT == 1 ? 
   // are zero from k-block ext[panel] on, and no product reads them there
   const int panel = blockIdx.y / 4;
   const int n_kb =
-      (int)min((int64_t)AB_KB, (ext ? (int64_t)ext[panel] : k_pad / GRAM_KB) - (int64_t)blockIdx.x * AB_KB);
+      (int)min((int64_t)kb_wg, (ext ? (int64_t)ext[panel] : k_pad / GRAM_KB) - (int64_t)blockIdx.x * kb_wg);
   if (n_kb <= 0) return;  // workgroup-uniform, before any barrier
   const bool need_lo = FMT == 2 && (panel_f == nullptr || panel_f[panel] * panel_f[r_pad / 256] > lim);
   const int64_t k_len = (int64_t)n_chi * n_m;
@@ -590,7 +592,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FMT == 1 ? 
   // from 16 rows n_chi apart at every node change)
   __shared__ double Tl[64][AB_TN + 1];
   __shared__ int c_rng[2];  // smallest and largest configuration of the workgroup's rows
-  const int64_t kbeg = (int64_t)blockIdx.x * AB_KB * GRAM_KB;
+  const int64_t kbeg = (int64_t)blockIdx.x * kb_wg * GRAM_KB;
   const int n_lo = kbeg < k_len ? (int)(kbeg / n_m) : 0;
   const int n_hi = kbeg < k_len ? (int)((min(kbeg + (int64_t)n_kb * GRAM_KB, k_len) - 1) / n_m) : 0;
   const int nodes = n_hi - n_lo + 1;
@@ -636,7 +638,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FMT == 1 ? 
       __syncthreads();
     }
     if (q >= n_kb) continue;  // past the panel's k-blocks (later passes' barriers still to come: no break)
-    const int64_t kblk = (int64_t)blockIdx.x * AB_KB + q;
+    const int64_t kblk = (int64_t)blockIdx.x * kb_wg + q;
     const int64_t k0 = kblk * GRAM_KB + 8 * chunk;
     const int n = k0 < k_len ? (int)(k0 / n_m) : 0;
     double g[8];
@@ -730,13 +732,15 @@ void launch_abuild(int fmt, const int32_t *rowR, const double *Ts, const double 
   if (fmt == 1 || fmt == 2) {
     // r_pad is a multiple of 64 and k_pad of GRAM_KB (rows are padded to the
     // Gram tile, columns to 64)
-    const dim3 grid((unsigned)((k_pad / GRAM_KB + AB_KB - 1) / AB_KB), (unsigned)(r_pad / 64));
+    int kb = AB_KB;
+    while (kb > 4 && (k_pad / GRAM_KB + kb - 1) / kb * (r_pad / 64) < 512) kb /= 2;
+    const dim3 grid((unsigned)((k_pad / GRAM_KB + kb - 1) / kb), (unsigned)(r_pad / 64));
     if (fmt == 1)
       hipLaunchKernelGGL(k_abuild_blk<1>, grid, dim3(256), 0, s, rowR, Ts, G, n_R, n_chi, n_m, k_pad, r_pad,
-                         (uint16_t *)A0, (uint16_t *)A1, nullptr, 0.0, arow, ext);
+                         (uint16_t *)A0, (uint16_t *)A1, nullptr, 0.0, arow, ext, kb);
     else
       hipLaunchKernelGGL(k_abuild_blk<2>, grid, dim3(256), 0, s, rowR, Ts, G, n_R, n_chi, n_m, k_pad, r_pad,
-                         (uint16_t *)A0, (uint16_t *)A1, panel_f, lim, arow, ext);
+                         (uint16_t *)A0, (uint16_t *)A1, panel_f, lim, arow, ext, kb);
     return;
   }
   // r_pad is a multiple of AB_ROWS (rows are padded to the Gram tile)
