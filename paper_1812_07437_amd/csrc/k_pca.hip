@@ -104,8 +104,8 @@ __device__ __forceinline__ void atomic_max_nonneg(double *addr, double v) {
 }
 
 // A round is three launches.  (a) k_pca_gram: partial 64 x 64 Gram matrices
-// of each block pair over column slices (FP64 MFMA); (b) k_pca_rot, one
-// workgroup per pair: sum the slices in fixed order, measure the largest
+// of each block pair over column slices (FP64 MFMA); (b) k_pca_rot or
+// k_pca_cross, one workgroup per pair: sum the slices in fixed order, measure the largest
 // scaled off-diagonal entry, and unless it is below tol rotate M in LDS, store
 // Q and rotate the pair's components of y (reordering the rotated columns by
 // norm, as in de Rijk's sorting, was measured to break the convergence of the
@@ -252,45 +252,33 @@ __device__ __forceinline__ void jacobi_angle(double a, double b, double m, doubl
   t = sg * m2 * rh * ru * ru;
 }
 
-// One workgroup per pair.  M is kept in its lower triangle (row >= column); a
-// step rotates 32 disjoint pairs of indices: 32 threads find the angles and
-// update their own 2 x 2 block, then every thread updates one of the 496 blocks
-// between two pairs, and its share of Q (stored transposed, so that a thread
-// takes four rows of both columns at once).  Steps: FULL rotates all 2016 pairs
-// in 63 steps (round-robin), otherwise the 1024 across the two blocks in 32
-// steps, index i with 32 + (i + step) mod 32.
-//
-// Bound by the chain of a step: an angle (two reciprocal square roots), a
-// barrier, the blocks' reads and writes in LDS, a barrier: 25 us for 32 steps
-// with six slices to sum, 65 for 63.  1024 threads, two divisions and two square
-// roots per angle and all 63 steps in every round took 100 us (a barrier over
-// 16 wavefronts takes 265 ns, one over eight a fraction of it).
-template <bool FULL>
-__global__ __launch_bounds__(RT) void k_pca_rot(const double *__restrict__ part, int n_ks, double tol, int n_blk, int r,
-                                                double *__restrict__ y, double *__restrict__ Qg,
-                                                int32_t *__restrict__ rot, double *__restrict__ conv) {
-  __shared__ double M[PR * PLD];
-  __shared__ __attribute__((aligned(16))) double QT[PR * QLD];
-  __shared__ __attribute__((aligned(16))) double2 cs[PR / 2];
-  __shared__ double diag[PR], red[RT / WAVE], ys[PR];
-  constexpr int NV = (PART / 2 + RT - 1) / RT;
-  const int tid = threadIdx.x, pi = blockIdx.x;
+// What both rotation kernels begin with, on T threads: M (lower triangle, row >=
+// column) from the slices, in order, and the pair's largest scaled off-diagonal
+// entry; whether it is above tol (else the pair is orthogonal).
+template <int T>
+__device__ __forceinline__ bool rot_begin(const double *__restrict__ part, int n_ks, double tol, int pi,
+                                          double *__restrict__ M, double *__restrict__ diag, double *__restrict__ red,
+                                          int32_t *__restrict__ rot, double *__restrict__ conv) {
+  constexpr int NV = (PART / 2 + T - 1) / T;
+  const int tid = threadIdx.x;
   const double *P = part + (int64_t)pi * n_ks * PART;
   double2 v[NV];
-  int row[NV], col[NV];  // of v.x; v.y is four rows below
+  int row[NV], col[NV], at[NV];  // of v.x; v.y is four rows below
 #pragma unroll
   for (int q = 0; q < NV; ++q) {
-    const int e = 2 * min(tid + RT * q, PART / 2 - 1);
+    const int e = 2 * min(tid + T * q, PART / 2 - 1);
     const int tile = e >> 8, l = (e & 127) >> 1;
     const int x = (tile >= 1) + (tile >= 3) + (tile >= 6);
     row[q] = 16 * x + (l >> 4) + 8 * ((e >> 7) & 1);
     col[q] = 16 * (tile - x * (x + 1) / 2) + (l & 15);
+    at[q] = e;
     v[q] = *reinterpret_cast<const double2 *>(P + e);
   }
+#pragma unroll 2
   for (int k = 1; k < n_ks; ++k)
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
-      const double2 w = *reinterpret_cast<const double2 *>(P + (int64_t)k * PART + 2 * min(tid + RT * q, PART / 2 - 1));
+      const double2 w = *reinterpret_cast<const double2 *>(P + (int64_t)k * PART + at[q]);
       v[q].x += w.x;
       v[q].y += w.y;
     }
@@ -301,13 +289,7 @@ __global__ __launch_bounds__(RT) void k_pca_rot(const double *__restrict__ part,
     if (row[q] == col[q]) diag[row[q]] = v[q].x;
     if (row[q] + 4 == col[q]) diag[col[q]] = v[q].y;
   }
-#pragma unroll
-  for (int q = 0; q < PR * PR / 2 / RT; ++q) {
-    const int e = 2 * (tid + RT * q), a = e / PR, b = e % PR;
-    *reinterpret_cast<double2 *>(&QT[a * QLD + b]) = make_double2(a == b ? 1.0 : 0.0, a == b + 1 ? 1.0 : 0.0);
-  }
   __syncthreads();
-  // the largest scaled off-diagonal entry
   double off = 0.0;
 #pragma unroll
   for (int q = 0; q < NV; ++q) {
@@ -320,29 +302,51 @@ __global__ __launch_bounds__(RT) void k_pca_rot(const double *__restrict__ part,
   __syncthreads();
   double off0 = red[0];
 #pragma unroll
-  for (int q = 1; q < RT / WAVE; ++q) off0 = fmax(off0, red[q]);
+  for (int q = 1; q < T / WAVE; ++q) off0 = fmax(off0, red[q]);
   if (tid == 0) {
     atomic_max_nonneg(conv, off0);
     rot[pi] = off0 > tol ? 1 : 0;
   }
-  if (!(off0 > tol)) return;  // this pair is already orthogonal
+  return off0 > tol;
+}
 
-  // block between pairs bi > bk for threads below 496
-  int bi = 1, bk = tid;
+// block between pairs bi > bk, numbered e < 496 (else bi is past the last pair)
+__device__ __forceinline__ void rot_block(int e, int &bi, int &bk) {
+  bi = 1;
+  bk = e;
   while (bk >= bi) {
     bk -= bi;
     ++bi;
   }
-  const bool block = bi < PR / 2;
+}
+
+// All 2016 pairs of a pair of blocks (the first round of a sweep), one workgroup
+// for each, in 63 round-robin steps.  A step rotates 32 disjoint pairs of indices: 32
+// threads find the angles and update their own 2 x 2 block, then every thread
+// updates one of the 496 blocks between two pairs, and its share of Q (stored
+// transposed, so that a thread takes four rows of both columns at once).  65 us:
+// bound by the chain of a step, as the kernel below.
+__global__ __launch_bounds__(RT) void k_pca_rot(const double *__restrict__ part, int n_ks, double tol, int n_blk, int r,
+                                                double *__restrict__ y, double *__restrict__ Qg,
+                                                int32_t *__restrict__ rot, double *__restrict__ conv) {
+  __shared__ double M[PR * PLD];
+  __shared__ __attribute__((aligned(16))) double QT[PR * QLD];
+  __shared__ __attribute__((aligned(16))) double2 cs[PR / 2];
+  __shared__ double diag[PR], red[RT / WAVE], ys[PR];
+  const int tid = threadIdx.x, pi = blockIdx.x;
+  if (!rot_begin<RT>(part, n_ks, tol, pi, M, diag, red, rot, conv)) return;
+  for (int e = tid; e < PR * PR; e += RT) QT[e / PR * QLD + e % PR] = e / PR == e % PR ? 1.0 : 0.0;
+  int bi, bk;
+  rot_block(tid, bi, bk);
   const int qp = tid >> 4, q0 = 4 * (tid & 15);  // Q: pair, first of four rows
   const double tol2 = tol * tol;
   auto lower = [](int i, int k) { return max(i, k) * PLD + min(i, k); };
 #pragma unroll 1
-  for (int ir = 0; ir < (FULL ? PR - 1 : PR / 2); ++ir) {
-    auto first = [&](int q) { return FULL ? rr_at(q, ir, PR) : q; };
-    auto second = [&](int q) { return FULL ? rr_at(PR - 1 - q, ir, PR) : PR / 2 + ((q + ir) & (PR / 2 - 1)); };
+  for (int ir = 0; ir < PR - 1; ++ir) {
+    auto first = [&](int q) { return rr_at(q, ir, PR); };
+    auto second = [&](int q) { return rr_at(PR - 1 - q, ir, PR); };
     if (tid < PR / 2) {
-      const int j = first(tid), l = second(tid), jl = FULL ? lower(j, l) : l * PLD + j;
+      const int j = first(tid), l = second(tid), jl = lower(j, l);
       const double mjj = M[j * PLD + j], mll = M[l * PLD + l], mjl = M[jl];
       double c = 1.0, sn = 0.0;
       if (mjl * mjl > tol2 * (mjj * mll) && mjj > 0.0 && mll > 0.0) {
@@ -355,10 +359,9 @@ __global__ __launch_bounds__(RT) void k_pca_rot(const double *__restrict__ part,
       cs[tid] = make_double2(c, sn);
     }
     __syncthreads();
-    if (block) {
+    if (bi < PR / 2) {
       const int i0 = first(bi), i1 = second(bi), k0 = first(bk), k1 = second(bk);
-      const int p00 = FULL ? lower(i0, k0) : i0 * PLD + k0, p01 = FULL ? lower(i0, k1) : k1 * PLD + i0,
-                p10 = FULL ? lower(i1, k0) : i1 * PLD + k0, p11 = lower(i1, k1);
+      const int p00 = lower(i0, k0), p01 = lower(i0, k1), p10 = lower(i1, k0), p11 = lower(i1, k1);
       const double2 ci = cs[bi], ck = cs[bk];
       const double a00 = M[p00], a01 = M[p01], a10 = M[p10], a11 = M[p11];
       const double r00 = ci.x * a00 - ci.y * a10, r10 = ci.y * a00 + ci.x * a10;
@@ -388,7 +391,153 @@ __global__ __launch_bounds__(RT) void k_pca_rot(const double *__restrict__ part,
   __syncthreads();
   if (tid < PR) {
     double o = 0.0;
+#pragma unroll 8
     for (int l = 0; l < PR; ++l) o += QT[tid * QLD + l] * ys[l];
+    y[pair_row(bp, bq, tid)] = o;
+  }
+}
+
+// The 1024 pairs across the two blocks (the other rounds) in 32 steps, step k
+// rotating j < 32 with 32 + (j + k) mod 32.  M is kept twice, a step reading the
+// one and writing the other, so that while eight wavefronts apply step k (as
+// above, but for the pairs' own 2 x 2 blocks) the first one already finds the
+// angles of step k + 1: lane j holds M_jj and, of its partner, M_ll; the partner's
+// neighbour hands over the next M_ll, and the next M_jl is one entry of the block
+// between the two pairs.  One barrier per step.  Q is in registers: a thread has
+// two rows of columns j and j + 16 and of their partners, and the partners' columns
+// move one pair on after every step.
+//
+// Bound by the chain of a step (four reads of LDS, an angle with two reciprocal
+// square roots, a barrier) and LDS about equally: 18.5 us with six slices to sum, 21.7
+// with Q in LDS, 25.4 with angles and updates one after the other; 1024 threads, two divisions and two square roots per
+// angle and all 63 steps in every round took 100 (a barrier over 16 wavefronts
+// takes 265 ns, one over eight a fraction of it).
+constexpr int CT = RT + WAVE;
+// the next lane's value among 16 (the last one's: the first one's)
+__device__ __forceinline__ double next_of_16(double x) {
+  const int64_t b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x12F, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x12F, 0xf, 0xf, true);
+  return __longlong_as_double(((int64_t)hi << 32) | (uint32_t)lo);
+}
+// the next lane's value (the last lane: the first one's)
+__device__ __forceinline__ double next_lane(double x) {
+  const int64_t b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x134, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x134, 0xf, 0xf, true);
+  return __longlong_as_double(((int64_t)hi << 32) | (uint32_t)lo);
+}
+__global__ __launch_bounds__(CT) void k_pca_cross(const double *__restrict__ part, int n_ks, double tol, int n_blk,
+                                                  int r, double *__restrict__ y, double *__restrict__ Qg,
+                                                  int32_t *__restrict__ rot, double *__restrict__ conv) {
+  constexpr int H = PR / 2;
+  __shared__ double M0[2 * PR * PLD];
+  __shared__ __attribute__((aligned(16))) double2 cs[2][H];
+  __shared__ double diag[PR], red[CT / WAVE], ys[H][PR + 1];
+  const int tid = threadIdx.x, pi = blockIdx.x;
+  if (!rot_begin<CT>(part, n_ks, tol, pi, M0, diag, red, rot, conv)) return;
+  auto lower = [](int i, int k) { return max(i, k) * PLD + min(i, k); };
+  const int bp = rr_at(pi, r, n_blk), bq = rr_at(n_blk - 1 - pi, r, n_blk);
+  if (tid < WAVE) {
+    const int j = tid & (H - 1), jn = (j + 1) & (H - 1);  // both halves alike
+    const double tol2 = tol * tol;
+    double mjj = M0[j * PLD + j], mll = M0[(H + j) * PLD + H + j], mjl = M0[(H + j) * PLD + j];
+    double c, s, t;
+    bool on;
+    auto angle = [&]() {
+      on = mjl * mjl > tol2 * (mjj * mll) && mjj > 0.0 && mll > 0.0;
+      jacobi_angle(mjj, mll, mjl, c, s, t);  // no number where both are zero
+      c = on ? c : 1.0;
+      s = on ? s : 0.0;
+      t = on ? t : 0.0;
+    };
+    __builtin_amdgcn_s_setprio(3);  // the others wait for this wavefront
+    angle();
+    cs[0][j] = make_double2(c, s);
+    double cn = next_lane(c), sn = next_lane(s), next = next_lane(fma(t, mjl, mll));
+    __syncthreads();
+#pragma unroll 1
+    for (int k = 0; k < H; ++k) {
+      const double *M = M0 + (k & 1) * PR * PLD;
+      double *out = M0 + ((k + 1) & 1) * PR * PLD;
+      const int l = H + ((j + k) & (H - 1)), ln = H + ((j + k + 1) & (H - 1));
+      const double a00 = M[lower(j, jn)], a10 = M[l * PLD + jn], a01 = M[ln * PLD + j], a11 = M[lower(l, ln)];
+      out[l * PLD + j] = on ? 0.0 : mjl;
+      mjj = fma(-t, mjl, mjj);
+      mll = next;
+      mjl = sn * (c * a00 - s * a10) + cn * (c * a01 - s * a11);
+      angle();
+      cs[(k + 1) & 1][j] = make_double2(c, s);
+      cn = next_lane(c);
+      sn = next_lane(s);
+      next = next_lane(fma(t, mjl, mll));
+      __syncthreads();
+    }
+  } else {
+    const int e = tid - WAVE;
+    int bi, bk;
+    rot_block(e, bi, bk);
+    // rows row and row + 1 of Q, columns j + 16 p and their partners
+    const int j = e & 15, row = 2 * (e >> 4);
+    double x[2][2], z[2][2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        x[p][i] = row + i == j + 16 * p ? 1.0 : 0.0;
+        z[p][i] = row + i == H + j + 16 * p ? 1.0 : 0.0;
+      }
+    const double y0 = y[pair_row(bp, bq, row)], y1 = y[pair_row(bp, bq, row + 1)];
+    __syncthreads();
+#pragma unroll 1
+    for (int k = 0; k < H; ++k) {
+      const double *M = M0 + (k & 1) * PR * PLD;
+      double *out = M0 + ((k + 1) & 1) * PR * PLD;
+      const double2 *cur = cs[k & 1];
+      if (bi < H) {
+        const int li = H + ((bi + k) & (H - 1)), lk = H + ((bk + k) & (H - 1));
+        const int p00 = bi * PLD + bk, p01 = lk * PLD + bi, p10 = li * PLD + bk, p11 = lower(li, lk);
+        const double2 ci = cur[bi], ck = cur[bk];
+        const double a00 = M[p00], a01 = M[p01], a10 = M[p10], a11 = M[p11];
+        const double r00 = ci.x * a00 - ci.y * a10, r10 = ci.y * a00 + ci.x * a10;
+        const double r01 = ci.x * a01 - ci.y * a11, r11 = ci.y * a01 + ci.x * a11;
+        out[p00] = ck.x * r00 - ck.y * r01;
+        out[p01] = ck.y * r00 + ck.x * r01;
+        out[p10] = ck.x * r10 - ck.y * r11;
+        out[p11] = ck.y * r10 + ck.x * r11;
+      }
+      const double2 c0 = cur[j], c1 = cur[j + 16];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const double u = x[0][i], v = x[1][i];
+        x[0][i] = c0.x * u - c0.y * z[0][i];
+        x[1][i] = c1.x * v - c1.y * z[1][i];
+        // the partners' columns go to the pairs before: lane j + 1's, and
+        // across the ends of the 16 lanes
+        const double n0 = next_of_16(c0.y * u + c0.x * z[0][i]), n1 = next_of_16(c1.y * v + c1.x * z[1][i]);
+        z[0][i] = j == 15 ? n1 : n0;
+        z[1][i] = j == 15 ? n0 : n1;
+      }
+      __syncthreads();
+    }
+    double *out = Qg + (int64_t)pi * PR * PR + row * PR + j;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        out[i * PR + 16 * p] = x[p][i];
+        out[i * PR + 16 * p + H] = z[p][i];
+      }
+      ys[e >> 4][j + 16 * p] = x[p][0] * y0 + x[p][1] * y1;
+      ys[e >> 4][j + 16 * p + H] = z[p][0] * y0 + z[p][1] * y1;
+    }
+  }
+  __syncthreads();
+  // y of the pair <- Q^T y
+  if (tid < PR) {
+    double o = 0.0;
+#pragma unroll 8
+    for (int l = 0; l < H; ++l) o += ys[l][tid];
     y[pair_row(bp, bq, tid)] = o;
   }
 }
@@ -634,10 +783,9 @@ void launch_pca_round(double *X, double *y, int64_t n_pad, int r, double tol, do
   const int n_blk = (int)(n_pad / PB), pairs = n_blk / 2, ks = pca_slices(n_pad), chunks = (int)(n_pad / PR);
   hipLaunchKernelGGL(k_pca_gram, dim3((unsigned)pairs, (unsigned)ks), dim3(256), 0, s, X, n_pad, n_blk, r, part);
   if (r == 0)
-    hipLaunchKernelGGL(k_pca_rot<true>, dim3((unsigned)pairs), dim3(RT), 0, s, part, ks, tol, n_blk, r, y, Qg, rot, conv);
+    hipLaunchKernelGGL(k_pca_rot, dim3((unsigned)pairs), dim3(RT), 0, s, part, ks, tol, n_blk, r, y, Qg, rot, conv);
   else
-    hipLaunchKernelGGL(k_pca_rot<false>, dim3((unsigned)pairs), dim3(RT), 0, s, part, ks, tol, n_blk, r, y, Qg, rot,
-                       conv);
+    hipLaunchKernelGGL(k_pca_cross, dim3((unsigned)pairs), dim3(CT), 0, s, part, ks, tol, n_blk, r, y, Qg, rot, conv);
   // chunks per workgroup: eight amortise the 32 KB of Q, fewer while the chip
   // is not filled twice
   int per = (int)std::min<int64_t>(8, std::max<int64_t>(1, (int64_t)pairs * chunks / 512));
