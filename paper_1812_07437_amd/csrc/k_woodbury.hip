@@ -38,49 +38,50 @@ namespace wlc {
 // ------------------------------------------------------------------ Q
 constexpr int QMAX = WOOD_NZ_MAX;
 
-// Q_b = (P^s_b)^-1 for every ell-bin, one thread per bin (n_z <= QMAX).
-__global__ void k_qinv(const double *__restrict__ Ps, int n_ell, int nz, double *__restrict__ Q,
-                       int *__restrict__ flag) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= n_ell) return;
-  double L[QMAX][QMAX];
+// Q_b = (P^s_b)^-1 for every ell-bin (n_z <= QMAX), one wavefront each, lane i
+// with row i of the Cholesky factor and column i of its inverse, in LDS (ten bins
+// 5 us; one thread for each ell-bin, its matrix in scratch memory, 20).
+__global__ __launch_bounds__(WAVE) void k_qinv(const double *__restrict__ Ps, int nz, double *__restrict__ Q,
+                                               int *__restrict__ flag) {
+  __shared__ double L[QMAX][QMAX + 1], X[QMAX][QMAX + 1];
+  const int b = blockIdx.x, i = threadIdx.x;
   const double *P = Ps + (size_t)b * nz * nz;
+  for (int e = i; e < nz * nz; e += WAVE) L[e / nz][e % nz] = P[e];
+  __syncthreads();
   bool bad = false;
-  for (int j = 0; j < nz; ++j) {
-    double s = P[j * nz + j];
-    for (int k = 0; k < j; ++k) s -= L[j][k] * L[j][k];
-    if (!(s > 0.0)) {
+  for (int k = 0; k < nz; ++k) {
+    double v = L[k][k];
+    if (!(v > 0.0)) {
       bad = true;
-      s = 1.0;
+      v = 1.0;
     }
-    L[j][j] = sqrt(s);
-    for (int i = j + 1; i < nz; ++i) {
-      double t = P[i * nz + j];
-      for (int k = 0; k < j; ++k) t -= L[i][k] * L[j][k];
-      L[i][j] = t / L[j][j];
-    }
+    const double d = sqrt(v);
+    const double l = i > k && i < nz ? L[i][k] / d : 0.0;
+    __syncthreads();
+    if (i == k) L[k][k] = d;
+    if (i > k && i < nz) L[i][k] = l;
+    __syncthreads();
+    if (i > k && i < nz)
+      for (int j = k + 1; j <= i; ++j) L[i][j] -= l * L[j][k];
+    __syncthreads();
   }
-  // X = L^-1 in the upper part of L (X[i][j] for i >= j stored at L[j][i])
-  for (int j = 0; j < nz; ++j) {
-    L[j][j] = 1.0 / L[j][j];
-    for (int i = j + 1; i < nz; ++i) {
+  if (i < nz) {  // column i of X = L^-1
+    X[i][i] = 1.0 / L[i][i];
+    for (int r = i + 1; r < nz; ++r) {
       double t = 0.0;
-      for (int k = j; k < i; ++k) t -= L[i][k] * (k == j ? L[j][j] : L[j][k]);
-      L[j][i] = t / L[i][i];
+      for (int k = i; k < r; ++k) t -= L[r][k] * X[k][i];
+      X[r][i] = t / L[r][r];
     }
   }
+  __syncthreads();
   // Q = X^T X
-  for (int i = 0; i < nz; ++i)
-    for (int j = 0; j < nz; ++j) {
-      double t = 0.0;
-      for (int k = (i > j ? i : j); k < nz; ++k) {
-        const double xi = k == i ? L[i][i] : L[i][k];  // X[k][i]
-        const double xj = k == j ? L[j][j] : L[j][k];
-        t += xi * xj;
-      }
-      Q[((size_t)b * nz + i) * nz + j] = t;
-    }
-  if (bad) atomicOr(flag, 1);
+  for (int e = i; e < nz * nz; e += WAVE) {
+    const int r = e / nz, c = e % nz;
+    double t = 0.0;
+    for (int k = max(r, c); k < nz; ++k) t += X[k][r] * X[k][c];
+    Q[(size_t)b * nz * nz + e] = t;
+  }
+  if (bad && i == 0) atomicOr(flag, 1);
 }
 
 // ------------------------------------------------------------------ G
@@ -117,40 +118,19 @@ __device__ __forceinline__ double s2(const Qv &q, int b, int i, int j, int k, in
   return q(b, i, k) * q(b, j, l) + q(b, i, l) * q(b, j, k);
 }
 
-// distinct orderings of a sorted triple; returns their number
-__device__ __forceinline__ int orderings(const int m[3], int out[6][3]) {
-  const int perm[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
-  int n = 0;
-  for (int p = 0; p < 6; ++p) {
-    const int a = m[perm[p][0]], b = m[perm[p][1]], c = m[perm[p][2]];
-    bool dup = false;
-    for (int q = 0; q < n; ++q) dup |= (out[q][0] == a && out[q][1] == b && out[q][2] == c);
-    if (!dup) {
-      out[n][0] = a;
-      out[n][1] = b;
-      out[n][2] = c;
-      ++n;
-    }
-  }
-  return n;
+// number of distinct orderings of a sorted triple
+__device__ __forceinline__ int orderings(const int m[3]) {
+  return m[0] == m[2] ? 1 : m[0] == m[1] || m[1] == m[2] ? 3 : 6;
 }
 
-// For a triangle with two equal legs, the data-vector rows of multiset m:
-// the bin on the odd leg is one of the distinct values of m and the other two
-// are sorted.  Returns the count; odd[q] is the odd leg's bin, (lo, hi) the pair.
-__device__ __forceinline__ int odd_leg_rows(const int m[3], int odd[3], int lo[3], int hi[3]) {
-  int n = 0;
-  for (int q = 0; q < 3; ++q) {
-    if (q > 0 && m[q] == m[q - 1]) continue;
-    const int a = q == 0 ? m[1] : m[0], b = q == 2 ? m[1] : m[2];
-    odd[n] = m[q];
-    lo[n] = a;
-    hi[n] = b;
-    ++n;
-  }
-  return n;
-}
-
+// On a triangle's rows the entry of G is
+//   sum over the distinct orderings a of m and b of m' of Q_1(a_1, b_1) Q_2(a_2, b_2) Q_3(a_3, b_3),
+// halved for two equal legs and a sixth of it for three: a row of an (i <= j, k) or
+// (i <= j <= k) block stands for nu or mu orderings, and in the sum over all of
+// them the two terms of S2 (the six of S3) are the same.  The orderings are taken
+// as all 36 pairs of permutations, n n' / 36 of their sum, from 27 values that
+// are loaded together (64 triangles of 35 rows 7 us; the distinct orderings, listed in
+// scratch memory, 37).
 __global__ void k_gblock(BlockMap B, const int32_t *__restrict__ cfgT, Qv q, const double *__restrict__ nmodes,
                          const double *__restrict__ ntri, double omega, double *__restrict__ Gb) {
   const int c = blockIdx.y;
@@ -173,28 +153,23 @@ __global__ void k_gblock(BlockMap B, const int32_t *__restrict__ cfgT, Qv q, con
       int m[3], mp[3];
       decode_trip(mi, nz, m[0], m[1], m[2]);
       decode_trip(mj, nz, mp[0], mp[1], mp[2]);
-      if (l1 == l2 && l2 == l3) {
-        int oa[6][3], ob[6][3];
-        const int na = orderings(m, oa), nb = orderings(mp, ob);
-        double t = 0.0;
-        for (int p = 0; p < nb; ++p) t += q(l1, m[0], ob[p][0]) * q(l1, m[1], ob[p][1]) * q(l1, m[2], ob[p][2]);
-        // the six leg permutations visit each distinct ordering 6 / nb times
-        v = (double)(na * nb) / 36.0 * (6.0 / nb) * t;
-      } else if (l1 == l2 || l2 == l3) {
-        int oa[3], la[3], ha[3], ob[3], lb[3], hb[3];
-        const int na = odd_leg_rows(m, oa, la, ha), nb = odd_leg_rows(mp, ob, lb, hb);
-        const int lp = l1 == l2 ? l1 : l2, lodd = l1 == l2 ? l3 : l1;
-        for (int x = 0; x < na; ++x)
-          for (int y = 0; y < nb; ++y) {
-            const double nu = (la[x] == ha[x] ? 1.0 : 2.0) * (lb[y] == hb[y] ? 1.0 : 2.0);
-            v += nu * 0.25 * s2(q, lp, la[x], ha[x], lb[y], hb[y]) * q(lodd, oa[x], ob[y]);
-          }
-      } else {
-        int oa[6][3], ob[6][3];
-        const int na = orderings(m, oa), nb = orderings(mp, ob);
-        for (int x = 0; x < na; ++x)
-          for (int y = 0; y < nb; ++y) v += q(l1, oa[x][0], ob[y][0]) * q(l2, oa[x][1], ob[y][1]) * q(l3, oa[x][2], ob[y][2]);
-      }
+      double a[3][3], b[3][3], d[3][3];
+#pragma unroll
+      for (int x = 0; x < 3; ++x)
+#pragma unroll
+        for (int y = 0; y < 3; ++y) {
+          a[x][y] = q(l1, m[x], mp[y]);
+          b[x][y] = q(l2, m[x], mp[y]);
+          d[x][y] = q(l3, m[x], mp[y]);
+        }
+#pragma unroll
+      for (int x = 0; x < 3; ++x)
+#pragma unroll
+        for (int y = 0; y < 3; ++y) {
+          const int x1 = (x + 1) % 3, x2 = (x + 2) % 3, y1 = (y + 1) % 3, y2 = (y + 2) % 3;
+          v += a[x][y] * (b[x1][y1] * d[x2][y2] + b[x1][y2] * d[x2][y1] + b[x2][y1] * d[x1][y2] + b[x2][y2] * d[x1][y1]);
+        }
+      v *= (double)(orderings(m) * orderings(mp)) / (l1 == l3 ? 216.0 : l1 == l2 || l2 == l3 ? 72.0 : 36.0);
       v *= ntri[c - B.nl] / omega;
     }
     G[(int64_t)mi * s + mj] = v;
@@ -205,20 +180,28 @@ __global__ void k_gblock(BlockMap B, const int32_t *__restrict__ cfgT, Qv q, con
 // Per block (one workgroup): row scales tau with G_ee 2^(2 tau) in [1, 4),
 // the scaled block factored in place (lower), u = L^T D^-1 d_R into the
 // border row, and r scaled by D^-1.
+//
+// LDS: the block lies in LDS (up to GCHOL_MAX rows), else it stays in global
+// memory.  Bound by the chain of its columns, one barrier each: column k is
+// scaled while column k + 1 is eliminated with, and an elimination divides by the
+// pivot instead (blocks of 35 rows 27 us, of 84 115; in global memory with three
+// barriers 42 and 320).
+constexpr int GCHOL_MAX = 138;  // 138 139 8 bytes, and vectors, in 160 KB
+
+template <bool LDS>
 __global__ __launch_bounds__(256) void k_gchol(BlockMap B, double *__restrict__ Gb, const double *__restrict__ dR,
                                                const double *__restrict__ rR, int32_t *__restrict__ tau,
                                                double *__restrict__ rhat, double *__restrict__ urow,
                                                int *__restrict__ flag) {
-  __shared__ double piv;
-  __shared__ int bad;
+  extern __shared__ double lds[];
   const int c = blockIdx.x;
   const int s = B.size(c);
   const int64_t b0 = B.start(c);
-  double *A = Gb + B.off(c);
-  const int tid = threadIdx.x;
-  if (tid == 0) bad = 0;
+  double *G = Gb + B.off(c), *A = LDS ? lds : G;
+  const int ld = LDS ? s | 1 : s;
+  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   for (int e = tid; e < s; e += 256) {
-    const double g = A[(int64_t)e * s + e];
+    const double g = G[(int64_t)e * s + e];
     int t = 0;
     if (g > 0.0 && isfinite(g)) {
       const int q = exp2_of(g) - 1;
@@ -228,39 +211,46 @@ __global__ __launch_bounds__(256) void k_gchol(BlockMap B, double *__restrict__ 
     rhat[b0 + e] = ldexp(rR[b0 + e], -t);
   }
   __syncthreads();
-  for (int64_t e = tid; e < (int64_t)s * s; e += 256) {
-    const int i = (int)(e / s), j = (int)(e % s);
-    if (j <= i) A[e] = ldexp(A[e], tau[b0 + i] + tau[b0 + j]);
+  for (int i = ty; i < s; i += 16)
+    for (int j = tx; j <= i; j += 16)
+      A[(int64_t)i * ld + j] = ldexp(G[(int64_t)i * s + j], tau[b0 + i] + tau[b0 + j]);
+  __syncthreads();
+  bool bad = false;
+  double rp = 1.0;  // of the column before
+  for (int k = 0; k < s; ++k) {
+    double v = A[(int64_t)k * ld + k];
+    if (!(v > 0.0)) {
+      bad = true;
+      v = 1.0;
+    }
+    const double rv = 1.0 / v;
+    // column k - 1, no longer needed as it was
+    if (k > 0)
+      for (int i = k + tid; i < s; i += 256) A[(int64_t)i * ld + k - 1] *= rp;
+    for (int i = k + 1 + ty; i < s; i += 16) {
+      const double f = A[(int64_t)i * ld + k] * rv;
+      for (int j = k + 1 + tx; j <= i; j += 16) A[(int64_t)i * ld + j] -= f * A[(int64_t)j * ld + k];
+    }
+    rp = 1.0 / sqrt(v);
+    __syncthreads();
+    if (tid == 0) A[(int64_t)k * ld + k] = sqrt(v);  // read by no later step
   }
   __syncthreads();
-  for (int k = 0; k < s; ++k) {
-    if (tid == 0) {
-      const double v = A[(int64_t)k * s + k];
-      if (!(v > 0.0)) bad = 1;
-      piv = sqrt(v > 0.0 ? v : 1.0);
-      A[(int64_t)k * s + k] = piv;
-    }
-    __syncthreads();
-    const double rp = 1.0 / piv;
-    for (int i = k + 1 + tid; i < s; i += 256) A[(int64_t)i * s + k] *= rp;
-    __syncthreads();
-    const int m = s - 1 - k;
-    for (int e = tid; e < m * m; e += 256) {
-      const int i = k + 1 + e / m, j = k + 1 + e % m;
-      if (j <= i) A[(int64_t)i * s + j] -= A[(int64_t)i * s + k] * A[(int64_t)j * s + k];
-    }
-    __syncthreads();
-  }
+  if (LDS)
+    for (int i = ty; i < s; i += 16)
+      for (int j = tx; j <= i; j += 16) G[(int64_t)i * s + j] = A[(int64_t)i * ld + j];
   for (int e = tid; e < s; e += 256) {
     double u = 0.0;
-    for (int f = e; f < s; ++f) u += A[(int64_t)f * s + e] * ldexp(dR[b0 + f], -tau[b0 + f]);
+    for (int f = e; f < s; ++f) u += A[(int64_t)f * ld + e] * ldexp(dR[b0 + f], -tau[b0 + f]);
     urow[b0 + e] = u;
   }
   if (tid == 0 && bad) atomicOr(flag, 1);
 }
 
 // ------------------------------------------------------------------ products
-// MODE 0:  T[e][g] = sum_{h in block(e), h >= e} L[h][e] Mhat[g][h]   (all tiles)
+// MODE 0:  T[e][g] = sum_{h in block(e), h >= e} L[h][e] Mhat[g][h]   (tiles with
+//          columns up to the end of the last block of their rows: no entry of W
+//          takes more)
 // MODE 1:  W[e][f] = delta_ef + sum_{g in block(f), g >= f} T[e][g] L[g][f]   (e >= f)
 // with Mhat[g][h] = 2^-(s_g + s_h + tau_g + tau_h) Gm[g][h] / Omega
 //                  + sigma_b^2 rhat_g rhat_h,
@@ -268,6 +258,10 @@ __global__ __launch_bounds__(256) void k_gchol(BlockMap B, double *__restrict__ 
 // v_mfma_f64_16x16x4 (four wavefronts of 32 x 32); the contraction runs over
 // the configuration blocks that the tile's rows (MODE 0) or columns (MODE 1)
 // touch, in LDS stages of 16.
+//
+// Bound by the loads of a stage: 2390 rows 43 + 24 us, 12768 rows 1.24 + 0.76 ms
+// (with every tile of T, and each stage's loads waited for before the products
+// of the one before, 60 + 25 us and 2.06 + 0.78 ms).
 struct WbArgs {
   BlockMap B;
   const double *Gb;        // factored blocks
@@ -305,6 +299,10 @@ __global__ __launch_bounds__(256) void k_wb_prod(WbArgs a) {
     tj = t - i * (i + 1) / 2;
   }
   const int64_t e0 = ti * 64, f0 = tj * 64;
+  if (MODE == 0) {  // past the blocks of the tile's rows: no W takes it
+    const int cl = a.B.blk(min(nR, e0 + 64) - 1);
+    if (f0 >= a.B.start(cl) + a.B.size(cl)) return;
+  }
   // contraction range: the blocks spanned by the rows (MODE 0) or columns (MODE 1)
   const int64_t s0 = MODE == 0 ? e0 : f0;
   const int64_t s1 = min(nR, s0 + 64) - 1;
@@ -321,7 +319,6 @@ __global__ __launch_bounds__(256) void k_wb_prod(WbArgs a) {
   // fixed, so the block facts of the L row (e in MODE 0, f in MODE 1) and
   // the scale of the Mhat row f (MODE 0) are taken once here, and the k
   // loop does no index division.
-  double pa[4], pb[4];
   int64_t lb0[4], lb1[4], lbase[4];  // block [lb0, lb1) holding the L row, Gb index of L[lb0][row]
   int lsz[4];
   double fscale[4], frh[4];          // MODE 0: 2^-(s_f + tau_f) / Omega and sigma_b^2 rhat_f
@@ -345,22 +342,21 @@ __global__ __launch_bounds__(256) void k_wb_prod(WbArgs a) {
       frh[j] = a.sigma_b2 * a.rhat[f];
     }
   }
+  double lw[4], gw[4], rk = 0.0;
+  float gf[4];
+  int sk = 0;
   auto gload = [&](int64_t kq) {
     // every element of this thread sits in column k = kq + tid % WK of the
     // stage, so the column's Mhat factors are loaded once.  All loads are
-    // unconditional, from indices clamped into range, and masked afterwards
-    // by multiplication (the values are finite), so they are in flight
-    // together instead of one branch and wait each.
+    // unconditional, from indices clamped into range, and masked by
+    // multiplication when they are put into LDS (the values are finite), so they are in
+    // flight together, under the products of the stage before.
     const int64_t k = kq + tid % WK;
-    const bool kin = k < k1;
-    const int64_t kc = kin ? k : k1 - 1;
-    int sk = 0;
-    double rk = 0.0;
+    const int64_t kc = k < k1 ? k : k1 - 1;
     if (MODE == 0) {
       sk = a.sexp[kc] + a.tau[kc];
       rk = a.rhat[kc];
     }
-    double lw[4], gw[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int64_t lr = (MODE == 0 ? e0 : f0) + (tid + 256 * j) / WK;
@@ -371,12 +367,9 @@ __global__ __launch_bounds__(256) void k_wb_prod(WbArgs a) {
     }
     if (MODE == 0) {
       if (a.gm_f32) {
-        float gf[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
           gf[j] = ((const float *)a.Gm)[min(f0 + (tid + 256 * j) / WK, nR - 1) * a.ld_g + kc];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) gw[j] = (double)gf[j];
       } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j) gw[j] = ((const double *)a.Gm)[min(f0 + (tid + 256 * j) / WK, nR - 1) * a.ld_g + kc];
@@ -385,31 +378,33 @@ __global__ __launch_bounds__(256) void k_wb_prod(WbArgs a) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) gw[j] = a.T[min(e0 + (tid + 256 * j) / WK, nR - 1) * a.ld_t + kc];
     }
+  };
+  auto lstore = [&](int64_t kq) {
+    const int64_t k = kq + tid % WK;
+    const bool kin = k < k1;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int r = (tid + 256 * j) / WK;
+      const int q = tid + 256 * j, r = q / WK;
       const int64_t e = e0 + r, f = f0 + r;
       const int64_t lr = MODE == 0 ? e : f;
-      const double lv = lw[j] * ((k >= lr && k < lb1[j]) ? 1.0 : 0.0);
-      const double in = kin ? 1.0 : 0.0;
+      const double lv = lw[j] * ((k >= lr && k < lb1[j] && kin) ? 1.0 : 0.0);
+      double pa, pb;
       if (MODE == 0) {
-        pa[j] = lv * in;
-        pb[j] = (ldexp(gw[j] * fscale[j], -sk) + frh[j] * rk) * ((f < nR && kin) ? 1.0 : 0.0);
+        const double g = a.gm_f32 ? (double)gf[j] : gw[j];
+        pa = lv;
+        pb = (ldexp(g * fscale[j], -sk) + frh[j] * rk) * ((f < nR && kin) ? 1.0 : 0.0);
       } else {
-        pa[j] = gw[j] * ((e < nR && kin) ? 1.0 : 0.0);
-        pb[j] = lv * in;
+        pa = gw[j] * ((e < nR && kin) ? 1.0 : 0.0);
+        pb = lv;
       }
+      lds[0][r * WLD + q % WK] = pa;
+      lds[1][r * WLD + q % WK] = pb;
     }
   };
   gload(k0);
   for (int64_t kq = k0; kq < k1; kq += WK) {
     __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int q = tid + 256 * j;
-      lds[0][(q / WK) * WLD + q % WK] = pa[j];
-      lds[1][(q / WK) * WLD + q % WK] = pb[j];
-    }
+    lstore(kq);
     __syncthreads();
     if (kq + WK < k1) gload(kq + WK);
 #pragma unroll
@@ -447,13 +442,17 @@ __global__ __launch_bounds__(256) void k_wb_prod(WbArgs a) {
 void launch_woodbury(const WoodArgs &w, hipStream_t s) {
   const BlockMap &B = w.B;
   const int n_cfg = B.nl + B.n_tri;
-  hipLaunchKernelGGL(k_qinv, dim3((w.n_ell + 63) / 64), dim3(64), 0, s, w.Ps, w.n_ell, w.nz, w.Q, w.flag);
+  hipLaunchKernelGGL(k_qinv, dim3((unsigned)w.n_ell), dim3(WAVE), 0, s, w.Ps, w.nz, w.Q, w.flag);
   const int smax = B.sb > B.sp ? B.sb : B.sp;
   const unsigned gx = (unsigned)((smax * smax + 255) / 256);
   hipLaunchKernelGGL(k_gblock, dim3(gx, (unsigned)n_cfg), dim3(256), 0, s, B, w.cfgT, Qv{w.Q, w.nz}, w.nmodes,
                      w.ntri, w.omega, w.Gb);
-  hipLaunchKernelGGL(k_gchol, dim3((unsigned)n_cfg), dim3(256), 0, s, B, w.Gb, w.dR, w.rR, w.tau, w.rhat,
-                     w.W + B.n_R * w.ld_w, w.flag);
+  if (smax <= GCHOL_MAX)
+    hipLaunchKernelGGL(k_gchol<true>, dim3((unsigned)n_cfg), dim3(256), (size_t)smax * (smax | 1) * 8, s, B, w.Gb, w.dR,
+                       w.rR, w.tau, w.rhat, w.W + B.n_R * w.ld_w, w.flag);
+  else
+    hipLaunchKernelGGL(k_gchol<false>, dim3((unsigned)n_cfg), dim3(256), 0, s, B, w.Gb, w.dR, w.rR, w.tau, w.rhat,
+                       w.W + B.n_R * w.ld_w, w.flag);
   WbArgs a{B, w.Gb, w.Gm, w.gm_f32, w.ld_g, w.sexp, w.tau, w.rhat, 1.0 / w.omega, w.sigma_b2, w.T, w.ld_t, w.W,
            w.ld_w};
   const int64_t nt = (B.n_R + 63) / 64;
