@@ -472,8 +472,13 @@ __global__ __launch_bounds__(256) void k_diag(double *__restrict__ Wm, int64_t l
 // matrix and, packed, to rows_pack for the trailing update.
 //
 // Bound at up to 256 workgroups by its start: launch, 136 KB into each CU's LDS
-// and one wavefront's 144 products (4 us): 10 us at 800 rows, 12 at 4500 (15.8
-// with 8-byte gathers of 16 rows a load).
+// and one wavefront's 144 products (4 us): 9.2 us at 800 rows, 9.6 at 4500 (15.8
+// with 8-byte gathers of 16 rows a load; 10.1 and 10.9 with each column's tiles
+// read when their turn comes and X's rows read one by one).  Tiles straight from
+// the L2, eight ahead, took 10.8 and 11.3.
+// FULL: the panel has all its 128 columns, and a column of tiles is read while
+// the one before is multiplied.
+template <bool FULL>
 __global__ __launch_bounds__(256) void k_solve(double *__restrict__ Wm, int64_t ld, int64_t j0, int jb, int64_t rows,
                                                const double *__restrict__ pack, double *__restrict__ rows_pack) {
   __shared__ __attribute__((aligned(16))) double lp[PACK_DIAG];
@@ -505,14 +510,25 @@ __global__ __launch_bounds__(256) void k_solve(double *__restrict__ Wm, int64_t 
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const double x = sb[at + 2 * ((8 * t + 2 * v + (g >> 1)) ^ r)];
-      T[t][v] = t * RB + g + 4 * v < jb ? x : 0.0;
+      T[t][v] = FULL || t * RB + g + 4 * v < jb ? x : 0.0;
     }
+  f64x4 L[2][NT];
+  auto fetch = [&](int j) {
+#pragma unroll
+    for (int t = j; t < NT; ++t) L[j & 1][t] = get_tile(lp + diag_at(t, j), lane);
+  };
+  fetch(0);
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
-    if (j * RB >= jb) break;
-    T[j] = tile_fma(get_tile(lp + diag_at(j, j), lane), T[j], f64x4{0.0, 0.0, 0.0, 0.0});
+    if (!FULL && j * RB >= jb) break;
+    if (j + 1 < NT) fetch(j + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    T[j] = tile_fma(L[j & 1][j], T[j], f64x4{0.0, 0.0, 0.0, 0.0});
 #pragma unroll
-    for (int t = j + 1; t < NT; ++t) T[t] = tile_fms(get_tile(lp + diag_at(t, j), lane), T[j], T[t]);
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int t = j + 1; t < NT; ++t)
+        T[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-L[j & 1][t][v], T[j][v], T[t], 0, 0, 0);
   }
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
@@ -525,10 +541,18 @@ __global__ __launch_bounds__(256) void k_solve(double *__restrict__ Wm, int64_t 
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   // an odd jb lets a pair reach one column past the block: the corner entry of
   // the bordered matrix, which nothing reads
+  auto row = [&](int q) { return *reinterpret_cast<const double2 *>(sb + q * NB + 2 * (lane ^ q)); };
+  if (FULL && nr == RB) {  // all reads in flight together
+    double2 out[RB];
 #pragma unroll
-  for (int q = 0; q < RB; ++q)
-    if (q < nr && 2 * lane < jb)
-      *reinterpret_cast<double2 *>(B + q * ld + 2 * lane) = *reinterpret_cast<const double2 *>(sb + q * NB + 2 * (lane ^ q));
+    for (int q = 0; q < RB; ++q) out[q] = row(q);
+#pragma unroll
+    for (int q = 0; q < RB; ++q) *reinterpret_cast<double2 *>(B + q * ld + 2 * lane) = out[q];
+  } else {
+#pragma unroll
+    for (int q = 0; q < RB; ++q)
+      if (q < nr && 2 * lane < jb) *reinterpret_cast<double2 *>(B + q * ld + 2 * lane) = row(q);
+  }
 }
 
 // The packed rows of the solved panels: panel q (its first row below is
@@ -775,8 +799,12 @@ int chol_factor(double *Wm, int64_t n, int64_t ld, double *scratch, int *flag, h
     const int jb = (int)std::min<int64_t>(NB, n - j0);
     const int64_t r0 = j0 + jb;  // first row below
     if (begin == X.last && slots > GAP && n - j0 >= GROUP_MIN) gend = j0 + slots * NB;
-    hipLaunchKernelGGL(k_solve, dim3((unsigned)((rows - r0 + 63) / 64)), dim3(256), 0, s, Wm, ld, j0, jb, rows, pack,
-                       r0 < n ? part + X.last % slots * pack_rows : (double *)nullptr);
+    const dim3 grid((unsigned)((rows - r0 + 63) / 64));
+    double *solved = r0 < n ? part + X.last % slots * pack_rows : nullptr;
+    if (jb == NB)
+      hipLaunchKernelGGL(k_solve<true>, grid, dim3(256), 0, s, Wm, ld, j0, jb, rows, pack, solved);
+    else
+      hipLaunchKernelGGL(k_solve<false>, grid, dim3(256), 0, s, Wm, ld, j0, jb, rows, pack, solved);
     if (r0 >= n) break;
     Update U{};
     U.now = X.last;
