@@ -432,7 +432,7 @@ int run_enqueue_front(const Plan &p, const wlc_tables &tb, void *ws, hipStream_t
   double *Gsq = auto_split ? at<double>(ws, L, B_SQ) : nullptr, *gd = auto_split ? at<double>(ws, L, B_GD) : nullptr;
   double *panel_f = auto_split ? at<double>(ws, L, B_FP) : nullptr;
   int32_t *last = at<int32_t>(ws, L, B_LAST);
-  launch_spectra(T, cfgT, n_cfg, sl, U, legs, cent, sw, std::sqrt(p.omega), n_mg, X, R, G, Gmax, Gsq, s);
+  launch_spectra(T, cfgT, n_cfg, sl, U, legs, cent, sw, std::sqrt(p.omega), n_mg, p.n_sub, X, R, G, Gmax, Gsq, s);
   launch_rows(T, rowR, cfgT, p.n_R, F, X, R, Gmax, Gsq, p.noise, dR, rR, Ps, Ts, sexp, last, gd, s);
   const bool arows = !p.arow.empty();  // the flattened products run on A-rows in their own order
   const int32_t *arow = arows ? at<int32_t>(ws, L, B_AROW) : nullptr;

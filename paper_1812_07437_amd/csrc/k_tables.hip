@@ -175,32 +175,50 @@ void launch_stage(const DevTables &T, const double *centres, int n_ls, double *U
 // one's u is read for each.  The tree terms take one entry per lane.
 //
 // At 74 configurations of up to 27 sub-bin triples, 256 chi nodes and 128
-// masses 87 us, where a reduction over the masses for every integral of every
-// entry and a second pass for G took 560 + 119; bound by the loads of u and
-// FP64 arithmetic.
+// masses 74 us, where a reduction over the masses for every integral of every
+// entry and a second pass for G took 560 + 119; bound by FP64 arithmetic at the
+// four wavefronts a SIMD that the rows in LDS leave.
+// the value that lane i (the same for all) holds
+__device__ __forceinline__ double lane_value(double x, int i) {
+  const int64_t b = __double_as_longlong(x);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)b, i), hi = __builtin_amdgcn_readlane((int)(b >> 32), i);
+  return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
+}
+
 __device__ __forceinline__ double cosine3(double ki, double kj, double kl) {
   return (kl * kl - ki * ki - kj * kj) / (2.0 * ki * kj);
 }
 
+// SUB: with S sub-bins to a bin the 3 S rows of u that a configuration's entries
+// take again and again lie in LDS, one wavefront's beside the other's, and the
+// entries and their legs come from one lane each instead of a chain of loads
+// for every entry (at the sizes above 74 us; from memory, a load each, 84).  Bin
+// centres have one entry and take each row once: they stay with memory and loads
+// (3276 configurations of 64 nodes: 120 us, with lanes 146).  Rows past LDS_U
+// bytes, two workgroups to a CU, do too.
+constexpr int64_t LDS_U = 64 * 1024;
+template <bool SUB>
 __global__ __launch_bounds__(256) void k_spectra(DevTables T, const int32_t *__restrict__ cfgT, int n_cfg,
-                                                 SubList sl, const double *__restrict__ U,
+                                                 const int32_t *__restrict__ first,
+                                                 const int4 *__restrict__ lists,
+                                                 const double *__restrict__ weights, const double *__restrict__ U,
                                                  const LegTerm *__restrict__ legs,
                                                  const double *__restrict__ centres, const double *__restrict__ sw,
-                                                 double sq_omega, int n_mg, double *X, double *R, double *G,
+                                                 double sq_omega, int n_mg, int S, double *X, double *R, double *G,
                                                  double *Gmax, double *Gsq) {
-  const int lane = threadIdx.x & (WAVE - 1);
-  const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * (256 / WAVE) + threadIdx.x / WAVE);
+  extern __shared__ double lds[];
+  const int lane = threadIdx.x & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * (256 / WAVE) + wave);
   if (item >= n_cfg * T.n_chi) return;
   const int c = item / T.n_chi, n = item % T.n_chi, nm = T.n_m_pts;
   const bool tri = cfgT[4 * c] == 3;
-  const int e0 = sl.off[c], e1 = sl.off[c + 1];
-  const int4 *lists = (const int4 *)sl.leg;
+  const int e0 = first[c], e1 = first[c + 1];
   const double chi = T.chi[n];
   double xs = 0.0, rs = 0.0, mx = 0.0, sq = 0.0;
   // the terms without a mass integral over more than one leg
   for (int e = e0 + lane; e < e1; e += WAVE) {
     const int4 q = lists[e];
-    const double w = sl.w[e];
+    const double w = weights[e];
     const LegTerm a = legs[(size_t)q.x * T.n_chi + n];
     if (!tri) {
       xs += w * a.i1 * a.i1 * a.p;
@@ -226,41 +244,125 @@ __global__ __launch_bounds__(256) void k_spectra(DevTables T, const int32_t *__r
   }
   double *Go = G + (size_t)item * n_mg;
   const size_t at = (size_t)n * nm, step = (size_t)T.n_chi * nm;
+  const int bin[3] = {cfgT[4 * c + 1], cfgT[4 * c + 2], cfgT[4 * c + 3]};
+  double *rows = lds + (size_t)wave * 3 * S * nm;
+  if constexpr (SUB) {
+    for (int a = 0; a < (tri ? 3 : 1); ++a) {
+      const double *Ua = U + (size_t)bin[a] * S * step + at;
+      double *dst = rows + a * S * nm;
+      int mi = lane % nm, q = lane / nm;
+#pragma unroll 6
+      for (int e = lane; e < S * nm; e += WAVE) {
+        dst[e] = Ua[q * step + mi];
+        for (mi += WAVE; mi >= nm; mi -= nm) ++q;
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  // u of leg a, staged ell value l, mass mi
+  auto u_of = [&](int a, int l, int mi) {
+    if constexpr (SUB) return rows[(a * S + l - bin[a] * S) * nm + mi];
+    else return U[l * step + at + mi];
+  };
   for (int m0 = 0; m0 < nm; m0 += 2 * WAVE) {
     const bool in0 = m0 + lane < nm, in1 = m0 + WAVE + lane < nm;
     const int mi[2] = {in0 ? m0 + lane : nm - 1, in1 ? m0 + WAVE + lane : nm - 1};
     double t[2] = {0.0, 0.0}, h[2] = {0.0, 0.0}, r[2] = {0.0, 0.0};
-    int4 q = lists[e0];
-    for (int e = e0; e < e1;) {
-      const int l0 = q.x, l1 = tri ? q.y : q.x;
-      const double *U0 = U + l0 * step + at, *U1 = U + l1 * step + at;
-      const double u0[2] = {U0[mi[0]], U0[mi[1]]}, u1[2] = {U1[mi[0]], U1[mi[1]]};
-      if (!tri) {
-        const double w = sl.w[e];
-        t[0] += w * (u0[0] * u1[0]);
-        t[1] += w * (u0[1] * u1[1]);
-        if (++e < e1) q = lists[e];
-        continue;
-      }
-      const LegTerm &a0 = legs[(size_t)l0 * T.n_chi + n], &a1 = legs[(size_t)l1 * T.n_chi + n];
-      double v[2] = {0.0, 0.0}, lin = 0.0, resp = 0.0;
-      do {
-        const double w = sl.w[e];
-        const double *U2 = U + q.z * step + at;
-        const LegTerm &a2 = legs[(size_t)q.z * T.n_chi + n];
-        v[0] += w * U2[mi[0]];
-        v[1] += w * U2[mi[1]];
-        lin += w * a2.lin;
-        resp += w * a2.resp;
-        if (++e == e1) break;
-        q = lists[e];
-      } while (q.x == l0 && q.y == l1);
+    if constexpr (SUB) {
+      // a run: the entries that share l0, l1; v, lin and resp sum over their third leg
+      int l0 = -1, l1 = -1;
+      double u0[2] = {0.0, 0.0}, u1[2] = {0.0, 0.0}, v[2] = {0.0, 0.0}, lin = 0.0, resp = 0.0;
+      double lin0 = 0.0, lin1 = 0.0, resp0 = 0.0, resp1 = 0.0;
+      auto run_ends = [&]() {
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const double u01 = u0[j] * u1[j];
-        t[j] += u01 * v[j];
-        h[j] += (a0.lin * u1[j] + a1.lin * u0[j]) * v[j] + u01 * lin;
-        r[j] += (a0.resp * u1[j] + a1.resp * u0[j]) * v[j] + u01 * resp;
+        for (int j = 0; j < 2; ++j) {
+          const double u01 = u0[j] * u1[j];
+          t[j] += u01 * v[j];
+          h[j] += (lin0 * u1[j] + lin1 * u0[j]) * v[j] + u01 * lin;
+          r[j] += (resp0 * u1[j] + resp1 * u0[j]) * v[j] + u01 * resp;
+          v[j] = 0.0;
+        }
+        lin = resp = 0.0;
+      };
+      // 64 entries at a time, one in each lane, and from there to all lanes in turn
+      for (int eb = e0; eb < e1; eb += WAVE) {
+        const int e = min(eb + lane, e1 - 1), cnt = min(WAVE, e1 - eb);
+        const int4 q = lists[e];
+        const double w = weights[e];
+        LegTerm a = {}, b = {}, d = {};
+        if (tri) {
+          a = legs[(size_t)q.x * T.n_chi + n];
+          b = legs[(size_t)q.y * T.n_chi + n];
+          d = legs[(size_t)q.z * T.n_chi + n];
+        }
+        const double wl = w * d.lin, wr = w * d.resp;
+        for (int i = 0; i < cnt; ++i) {
+          const double wi = lane_value(w, i);
+          const int x = __builtin_amdgcn_readlane(q.x, i);
+          if (!tri) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+              const double u = u_of(0, x, mi[j]);
+              t[j] += wi * (u * u);
+            }
+            continue;
+          }
+          const int y = __builtin_amdgcn_readlane(q.y, i), z = __builtin_amdgcn_readlane(q.z, i);
+          if (x != l0 || y != l1) {
+            run_ends();
+            l0 = x;
+            l1 = y;
+            lin0 = lane_value(a.lin, i);
+            lin1 = lane_value(b.lin, i);
+            resp0 = lane_value(a.resp, i);
+            resp1 = lane_value(b.resp, i);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+              u0[j] = u_of(0, x, mi[j]);
+              u1[j] = u_of(1, y, mi[j]);
+            }
+          }
+          v[0] += wi * u_of(2, z, mi[0]);
+          v[1] += wi * u_of(2, z, mi[1]);
+          lin += lane_value(wl, i);
+          resp += lane_value(wr, i);
+        }
+      }
+      if (tri) run_ends();
+    } else {
+      int4 q = lists[e0];
+      for (int e = e0; e < e1;) {
+        const int l0 = q.x, l1 = q.y;
+        const double u0[2] = {u_of(0, l0, mi[0]), u_of(0, l0, mi[1])};
+        if (!tri) {
+          const double w = weights[e];
+          t[0] += w * (u0[0] * u0[0]);
+          t[1] += w * (u0[1] * u0[1]);
+          if (++e < e1) q = lists[e];
+          continue;
+        }
+        const double u1[2] = {u_of(1, l1, mi[0]), u_of(1, l1, mi[1])};
+        const LegTerm &a0 = legs[(size_t)l0 * T.n_chi + n], &a1 = legs[(size_t)l1 * T.n_chi + n];
+        double v[2] = {0.0, 0.0}, lin = 0.0, resp = 0.0;
+        do {
+          const double w = weights[e];
+          const LegTerm &a2 = legs[(size_t)q.z * T.n_chi + n];
+          v[0] += w * u_of(2, q.z, mi[0]);
+          v[1] += w * u_of(2, q.z, mi[1]);
+          lin += w * a2.lin;
+          resp += w * a2.resp;
+          if (++e == e1) break;
+          q = lists[e];
+        } while (q.x == l0 && q.y == l1);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const double u01 = u0[j] * u1[j];
+          t[j] += u01 * v[j];
+          h[j] += (a0.lin * u1[j] + a1.lin * u0[j]) * v[j] + u01 * lin;
+          r[j] += (a0.resp * u1[j] + a1.resp * u0[j]) * v[j] + u01 * resp;
+        }
       }
     }
 #pragma unroll
@@ -298,11 +400,17 @@ __global__ __launch_bounds__(256) void k_spectra(DevTables T, const int32_t *__r
 }
 
 void launch_spectra(const DevTables &T, const int32_t *cfgT, int n_cfg, const SubList &sl, const double *U,
-                    const LegTerm *legs, const double *centres, const double *sw, double sq_omega, int n_mg, double *X,
-                    double *R, double *G, double *Gmax, double *Gsq, hipStream_t s) {
-  const int64_t items = (int64_t)n_cfg * T.n_chi;
-  hipLaunchKernelGGL(k_spectra, dim3((unsigned)((items + 3) / 4)), dim3(256), 0, s, T, cfgT, n_cfg, sl, U, legs,
-                     centres, sw, sq_omega, n_mg, X, R, G, Gmax, Gsq);
+                    const LegTerm *legs, const double *centres, const double *sw, double sq_omega, int n_mg, int n_sub,
+                    double *X, double *R, double *G, double *Gmax, double *Gsq, hipStream_t s) {
+  const int64_t items = (int64_t)n_cfg * T.n_chi, bytes = (int64_t)4 * 3 * n_sub * T.n_m_pts * 8;
+  const dim3 grid((unsigned)((items + 3) / 4));
+  if (n_sub > 1 && bytes <= LDS_U)
+    hipLaunchKernelGGL(k_spectra<true>, grid, dim3(256), (size_t)bytes, s, T, cfgT, n_cfg, sl.off,
+                       (const int4 *)sl.leg, sl.w, U, legs, centres, sw, sq_omega, n_mg, n_sub, X, R, G, Gmax, Gsq);
+  else
+    hipLaunchKernelGGL(k_spectra<false>, grid, dim3(256), 0, s, T, cfgT, n_cfg, sl.off, (const int4 *)sl.leg, sl.w,
+                       U, legs, centres, sw, sq_omega,
+                       n_mg, n_sub, X, R, G, Gmax, Gsq);
 }
 
 // ------------------------------------------------------------- rows

@@ -31,8 +31,8 @@ void launch_stage(const DevTables &T, const double *centres, int n_ls, double *U
 // column then holding sqrt(Omega) chi_n sqrt(sigma_W^2(chi_n)) R[cfg][n] (the
 // super-sample term resolved along chi as one more Gram column).
 void launch_spectra(const DevTables &T, const int32_t *cfgT, int n_cfg, const SubList &sl, const double *U,
-                    const LegTerm *legs, const double *centres, const double *sw, double sq_omega, int n_mg, double *X,
-                    double *R, double *G, double *Gmax, double *Gsq, hipStream_t s);
+                    const LegTerm *legs, const double *centres, const double *sw, double sq_omega, int n_mg, int n_sub,
+                    double *X, double *R, double *G, double *Gmax, double *Gsq, hipStream_t s);
 // last [n_R]: the last chi node where a row's Ts is not zero (-1: none); gd
 // (with Gsq): the diagonal of the Gram product.
 void launch_rows(const DevTables &T, const int32_t *rowR, const int32_t *cfgT, int64_t n_R, const double *F,

@@ -36,7 +36,7 @@ def _rel(a, b):
 @pytest.mark.parametrize("n_m,n_chi,n_k,n_sub,bias,ssc", [
     (2, 3, 2, 1, False, "rank1"), (63, 4, 3, 2, True, "chi"), (64, 64, 65, 1, True, "rank1"),
     (65, 65, 66, 3, False, "chi"), (128, 17, 768, 3, True, "rank1"), (129, 63, 4097, 2, False, "rank1"),
-    (200, 5, 4098, 1, True, "chi")])
+    (200, 5, 4098, 1, True, "chi"), (250, 5, 64, 3, False, "rank1")])
 def test_table_edges(wl, n_m, n_chi, n_k, n_sub, bias, ssc):
     """Sums of positive products and a few differences of the response, in
     FP64 on both sides: the 1e-10 of the other parity tests."""
