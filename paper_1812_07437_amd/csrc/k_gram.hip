@@ -822,35 +822,28 @@ void launch_gram_unpermute(int f32, const void *GP, const int32_t *pos, int64_t 
 // within 2 % of its best beyond.  All bf16 modes take the same count, so a
 // per-tile product (WLC_BF16_AUTO) sums each tile exactly as the one-product
 // or the split-product mode would.  Each slice keeps at least 64 k-blocks.
-// Up to 64 tiles the chip is not full, and one workgroup per CU is worth more
-// than that: 256 / tiles slices, of at least 8 k-blocks, 32 at most (3 tiles
-// at K = 4608 28 us against 86 with two slices, 21 tiles at K = 32768 85 against
-// 191 with four; 36 tiles at K = 4608 44 with six and 54 with eight, two rounds).
 //
-// The FP32 and FP64 kernels aim at 2048 workgroups, but past one per CU only
-// while a slice keeps 8 (FP32) or 24 (FP64) K-steps: 42 FP64 tiles at K = 4608
-// take 182 us with 12 slices, 234 with 32 (at K = 32768 1029 and 900).
-static int pick_split(int64_t n_tiles, int64_t k_pad, int bk, int min_steps) {
-  const int64_t kb = k_pad / bk, round = 256 / n_tiles;  // slices that fill the CUs once
-  int64_t s;
-  if (min_steps == 0) {  // bf16
-    if (n_tiles <= 64)
-      s = std::min<int64_t>({round, kb / 8, 32});
-    else if (n_tiles < 2048)
-      s = std::min<int64_t>(std::clamp<int64_t>((600 + n_tiles - 1) / n_tiles, 2, 4), kb / 64);
-    else
-      s = 1;
-  } else {
-    s = std::min((2048 + n_tiles - 1) / n_tiles, std::max(round, kb / min_steps));
-    s = std::min<int64_t>({s, kb / 4, 32});  // keep at least 4 K-steps per slice
-  }
+// The FP32 kernel aims at enough workgroups to cover the chip several times,
+// with at least 4 K-steps per slice.  How a sum in FP32 is cut decides its last
+// bits, and with them the eighth digit of an S/N: neither rule moves for speed.
+//
+// The FP64 kernels aim at 2048 workgroups too, but past one per CU only while a
+// slice keeps 24 K-steps: 42 tiles at K = 4608 take 182 us with 12 slices, 234
+// with 32 (at K = 32768 1029 and 900).
+static int pick_split(int64_t n_tiles, int64_t k_pad, int bk, int prec) {
+  const int64_t kb = k_pad / bk;
+  int64_t s = (2048 + n_tiles - 1) / n_tiles;
+  if (prec == WLC_FP64) s = std::min(s, std::max(256 / n_tiles, kb / 24));
+  if (prec == WLC_FP64 || prec == WLC_FP32)
+    s = std::min<int64_t>({s, kb / 4, 32});
+  else
+    s = n_tiles >= 2048 ? 1 : std::min<int64_t>(std::clamp<int64_t>((600 + n_tiles - 1) / n_tiles, 2, 4), kb / 64);
   return (int)std::max<int64_t>(s, 1);
 }
 
 static bool is_bf16(int prec) { return prec == WLC_BF16 || prec == WLC_BF16X3 || prec == WLC_BF16_AUTO; }
 static int bf16_mode(int prec) { return prec == WLC_BF16 ? 0 : (prec == WLC_BF16X3 ? 1 : 2); }
 static int gram_tile(int prec) { return is_bf16(prec) ? T2 : TILE; }
-static int gram_min_steps(int prec) { return prec == WLC_FP64 ? 24 : prec == WLC_FP32 ? 8 : 0; }
 static int gram_bk(int prec) { return prec == WLC_FP64 ? 16 : (prec == WLC_FP32 ? 32 : BK2); }
 // the FP64 tile product needs even row pitch (16-byte chunks) and a 256-row
 // panel within one buffer descriptor's 31-bit range
@@ -869,7 +862,7 @@ static int64_t gram_tile_count(int prec, const GramShape &g) {
 }
 
 size_t gram_partial_bytes(int prec, const GramShape &g) {
-  const int s = pick_split(gram_tile_count(prec, g), g.k_pad, gram_bk(prec), gram_min_steps(prec));
+  const int s = pick_split(gram_tile_count(prec, g), g.k_pad, gram_bk(prec), prec);
   if (s <= 1) return 0;
   const size_t el = prec == WLC_FP64 ? 8 : 4;
   return (size_t)(s - 1) * g.r_pad * g.ld_out * el;  // slice 0 goes to the output
@@ -888,7 +881,7 @@ static GramSplit gram_split(int prec, const GramShape &g) {
   q.nt = g.r_pad / gram_tile(prec);
   q.tiles = gram_tile_count(prec, g);
   const int bk = gram_bk(prec);
-  q.ns = pick_split(q.tiles, g.k_pad, bk, gram_min_steps(prec));
+  q.ns = pick_split(q.tiles, g.k_pad, bk, prec);
   q.ksplit = (g.k_pad / bk + q.ns - 1) / q.ns * bk;
   q.pstride = q.ns > 1 ? g.r_pad * g.ld_out : 0;
   q.n_work = q.tiles * q.ns;

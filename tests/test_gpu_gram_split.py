@@ -1,7 +1,6 @@
-"""Slices of the split-K choice for products that do not fill the chip, on the
-exact integer factors of test_gpu_gram_exact: the shortest slices (8 k-blocks),
-every residue mod 3 and both parities, slices left empty by the rounding up,
-the largest number of slices, and either side of 64 tiles."""
+"""Small products and their slices, on the exact integer factors of
+test_gpu_gram_exact: every residue mod 3 and both parities of k-blocks, slices
+cut short, the largest number of slices, and either side of 64 tiles."""
 import numpy as np
 import pytest
 
@@ -11,12 +10,12 @@ from test_gpu_gram_exact import case, wl  # noqa: F401  (fixtures)
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    (256, 512),    # one tile, two slices of 8 k-blocks
-    (200, 8192),   # 32 slices of 8 (2 mod 3, even), padding rows
-    (256, 9216),   # 32 of 9 (0 mod 3, odd)
-    (256, 10240),  # 32 of 10 (1 mod 3)
-    (512, 4672),   # 3 tiles: 18 slices of 9 of 146 k-blocks, one short and one empty
-    (2560, 2048),  # 55 tiles: four slices of 16
+    (256, 512),    # one tile, one slice of 16 k-blocks
+    (200, 8192),   # four slices of 64 (1 mod 3, even), padding rows
+    (256, 9216),   # four of 72 (0 mod 3)
+    (256, 10400),  # four of 82 (1 mod 3), the last 80
+    (512, 4672),   # 3 tiles: two slices of 73 (odd)
+    (2560, 2048),  # 55 tiles: one slice
     (2561, 4096),  # 66 tiles: two slices of 64
 ]
 
