@@ -36,6 +36,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "f64tile.h"
 #include "kernels.h"
@@ -446,6 +447,90 @@ __global__ __launch_bounds__(64 * NW) void k_gram_bf16(const uint16_t *__restric
   if (!gram_work<GRAM_XC>(n_work, n_split, nt, I, J, split)) return;
   gram_bf16_item<MODE, NW>(Ahi, Alo, k_pad, r_pad, k_split, n_split, I, J, split, out, partial, ld, part_stride,
                            panel_f, lim, panel_ext, b0, b1, b2, b3);
+}
+
+// ---------------------------------------------------------------- few tiles
+// The same products for a matrix of few tiles: a wavefront for each 32 x 32 block
+// of an item's tile, which reads its operands from memory into registers, the
+// copies of DEPTH k-blocks in flight.  Every entry's sum runs over the same k
+// in the same order and through the same instructions as in the tile bodies above,
+// so the results are equal to the last bit.  Bound by the latency of the loads,
+// from 10 tiles on by the L2.
+template <bool X3>
+__device__ __forceinline__ void gram_bf16_block(const uint16_t *__restrict__ Ahi, const uint16_t *__restrict__ Alo,
+                                                int64_t k_pad, int64_t r_pad, int64_t k_split, int64_t row0,
+                                                int64_t col0, int split, float *__restrict__ out,
+                                                float *__restrict__ partial, int64_t ld, int64_t part_stride) {
+  constexpr int NOPS = X3 ? 2 : 1, DEPTH = X3 ? 4 : 8;
+  const int lane = threadIdx.x;
+  const int64_t kb = (int64_t)split * k_split;
+  const int64_t ke = max(kb, min(k_pad, kb + k_split));  // an empty slice stores zeros
+  const int64_t n_st = (ke - kb) / BK2, step = r_pad * BK2;
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+  if (n_st > 0) {
+    const uint16_t *src[2] = {Ahi, Alo};
+    const int64_t at = kb / BK2 * step + 8 * (lane >> 5);
+    const int64_t ra = at + (row0 + (lane & 31)) * BK2, rb = at + (col0 + (lane & 31)) * BK2;
+    bf16x8 a[DEPTH][NOPS][2], b[DEPTH][NOPS][2];
+    auto load = [&](int d, int64_t st) {
+#pragma unroll
+      for (int op = 0; op < NOPS; ++op)
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          a[d][op][kk] = *(const bf16x8 *)(src[op] + ra + st * step + 16 * kk);
+          b[d][op][kk] = *(const bf16x8 *)(src[op] + rb + st * step + 16 * kk);
+        }
+    };
+    auto products = [&](int d) {
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int p = 0; p < (X3 ? 3 : 1); ++p)
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[d][p == 2 ? 1 : 0][kk], b[d][p == 1 ? 1 : 0][kk], acc, 0, 0,
+                                                        0);
+    };
+    const int64_t last = n_st - 1;
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) load(d, min((int64_t)d, last));
+    int64_t st = 0;
+    for (; st + DEPTH <= n_st; st += DEPTH)
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d) {
+        products(d);
+        load(d, min(st + d + DEPTH, last));
+      }
+#pragma unroll
+    for (int d = 0; d < DEPTH - 1; ++d)
+      if (st + d < n_st) products(d);
+  }
+  float *dst = gram_dst(out, partial, split, part_stride);
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+    dst[(row0 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * ld + col0 + (lane & 31)] = acc[v];
+}
+
+constexpr int TILE_BLOCKS = (T2 / 32) * (T2 / 32);
+template <int MODE>
+__global__ __launch_bounds__(64) void k_gram_bf16_few(const uint16_t *__restrict__ Ahi,
+                                                      const uint16_t *__restrict__ Alo, int64_t k_pad, int64_t r_pad,
+                                                      int64_t k_split, int n_split, int nt, int64_t n_work,
+                                                      float *__restrict__ out, float *__restrict__ partial, int64_t ld,
+                                                      int64_t part_stride, const double *__restrict__ panel_f,
+                                                      double lim, const int32_t *__restrict__ panel_ext) {
+  int I, J, split;
+  gram_item(blockIdx.x / TILE_BLOCKS, n_work, n_split, nt, I, J, split);
+  const int blk = blockIdx.x % TILE_BLOCKS;
+  const int64_t row0 = (int64_t)I * T2 + blk / 8 * 32, col0 = (int64_t)J * T2 + blk % 8 * 32;
+  if (panel_ext) {
+    k_pad = min(k_pad, (int64_t)max(min(panel_ext[I], panel_ext[J]), 0) * BK2);
+    k_split = (k_pad / BK2 + n_split - 1) / n_split * BK2;
+  }
+  if (MODE != 0 && tile_split<MODE>(panel_f, lim, I, J))
+    gram_bf16_block<true>(Ahi, Alo, k_pad, r_pad, k_split, row0, col0, split, out, partial, ld, part_stride);
+  else
+    gram_bf16_block<false>(Ahi, Ahi, k_pad, r_pad, k_split, row0, col0, split, out, partial, ld, part_stride);
 }
 
 // ---------------------------------------------------------------- batched
@@ -963,6 +1048,15 @@ void launch_gram_reduce(int prec, const GramShape &g, void *out, void *partial, 
                        (float *)out, g.ld_out);
 }
 
+// Up to here a wavefront to a block: an item for each workgroup leaves most CUs
+// idle, and the loads of an item behind its ring.  One product and split product,
+// with the reduction of the slices, tile bodies against blocks: 3 tiles in two
+// slices at K = 4608 52 and 125 -> 14 and 23 us, 10 in four at K = 32768 174 and
+// 436 -> 152 and 338, 45 in one at K = 1024 30 and 64 -> 29 and 52; 15 in four at
+// K = 32768 202 and 525 against 238 and 548, 45 in two at K = 4608 73 and 169
+// against 113 and 221: a block reads every operand from the L2 for itself.
+constexpr int64_t FEW_ITEMS = 48;
+
 void launch_gram(int prec, const GramShape &g, const void *A0, const void *A1, void *out, void *partial,
                  hipStream_t s, const double *panel_f, double split_lim, const int32_t *panel_ext) {
   const GramSplit q = gram_split(prec, g);
@@ -971,21 +1065,26 @@ void launch_gram(int prec, const GramShape &g, const void *A0, const void *A1, v
   const int64_t gq = (int64_t)N_XCD * GRAM_XC;  // whole item groups of the dealt schedules
   const dim3 grid((unsigned)((n_work + gq - 1) / gq * gq));
   const int nti = (int)nt;
+  auto bf16 = [&](auto mode) {
+    constexpr int MODE = decltype(mode)::value;
+    if (n_work <= FEW_ITEMS)
+      hipLaunchKernelGGL(k_gram_bf16_few<MODE>, dim3((unsigned)(n_work * TILE_BLOCKS)), dim3(64), 0, s,
+                         (const uint16_t *)A0, (const uint16_t *)A1, g.k_pad, g.r_pad, ksplit, ns, nti, n_work,
+                         (float *)out, (float *)partial, g.ld_out, pstride, panel_f, split_lim, panel_ext);
+    else
+      hipLaunchKernelGGL((k_gram_bf16<MODE, GRAM_NW>), grid, dim3(64 * GRAM_NW), 0, s, (const uint16_t *)A0,
+                         (const uint16_t *)A1, g.k_pad, g.r_pad, ksplit, ns, nti, n_work, (float *)out,
+                         (float *)partial, g.ld_out, pstride, panel_f, split_lim, panel_ext);
+  };
   switch (prec) {
     case WLC_BF16:
-      hipLaunchKernelGGL((k_gram_bf16<0, GRAM_NW>), grid, dim3(64 * GRAM_NW), 0, s, (const uint16_t *)A0,
-                         (const uint16_t *)A1, g.k_pad, g.r_pad, ksplit, ns, nti, n_work, (float *)out, (float *)partial,
-                         g.ld_out, pstride, panel_f, split_lim, panel_ext);
+      bf16(std::integral_constant<int, 0>{});
       break;
     case WLC_BF16X3:
-      hipLaunchKernelGGL((k_gram_bf16<1, GRAM_NW>), grid, dim3(64 * GRAM_NW), 0, s, (const uint16_t *)A0,
-                         (const uint16_t *)A1, g.k_pad, g.r_pad, ksplit, ns, nti, n_work, (float *)out, (float *)partial,
-                         g.ld_out, pstride, panel_f, split_lim, panel_ext);
+      bf16(std::integral_constant<int, 1>{});
       break;
     case WLC_BF16_AUTO:
-      hipLaunchKernelGGL((k_gram_bf16<2, GRAM_NW>), grid, dim3(64 * GRAM_NW), 0, s, (const uint16_t *)A0,
-                         (const uint16_t *)A1, g.k_pad, g.r_pad, ksplit, ns, nti, n_work, (float *)out, (float *)partial,
-                         g.ld_out, pstride, panel_f, split_lim, panel_ext);
+      bf16(std::integral_constant<int, 2>{});
       break;
     case WLC_FP32:
       hipLaunchKernelGGL(k_gram_x4<float>, grid, dim3(256), 0, s, (const float *)A0, g.k_pad, g.lda, ksplit, ns, nti,

@@ -1,11 +1,12 @@
-"""Small products and their slices, on the exact integer factors of
-test_gpu_gram_exact: every residue mod 3 and both parities of k-blocks, slices
-cut short, the largest number of slices, and either side of 64 tiles."""
+"""Small products (a wavefront to a 32 x 32 block) and their slices, on the
+exact integer factors of test_gpu_gram_exact: remainders of the blocks' k-blocks
+in flight, slices of one k-block and empty ones, panel extents, the largest
+number of slices, and either side of the line to the tile kernels (48 items)."""
 import numpy as np
 import pytest
 
 import test_gpu_gram_exact as exact
-from test_gpu_gram_exact import case, wl  # noqa: F401  (fixtures)
+from test_gpu_gram_exact import case, ext_case, wl  # noqa: F401  (fixtures)
 
 pytestmark = pytest.mark.gpu
 
@@ -15,6 +16,7 @@ CASES = [
     (256, 9216),   # four of 72 (0 mod 3)
     (256, 10400),  # four of 82 (1 mod 3), the last 80
     (512, 4672),   # 3 tiles: two slices of 73 (odd)
+    (2304, 1056),  # 45 tiles: one slice of 34
     (2560, 2048),  # 55 tiles: one slice
     (2561, 4096),  # 66 tiles: two slices of 64
 ]
@@ -28,3 +30,14 @@ def test_slices_exact(wl, case):
     exact._check_tiles(G, lambda I, J: case["split"] if F[I] * F[J] > 0.5 else case["hh"], case["n_pad"])
     # a product's workspace: the slices past the first
     assert wl.wlc_gram_ws_bytes("bf16_auto", case["n"], case["k"]) % (4 * case["n_pad"] ** 2) == 0
+
+
+@pytest.mark.parametrize("ext_case", [(600, 2000), (1100, 2000), (768, 8320)], indirect=True,
+                         ids=lambda c: "n%d_k%d" % c)
+@pytest.mark.parametrize("precision", ["bf16", "bf16x3", "bf16_auto"])
+def test_extents_exact(wl, ext_case, precision):
+    nt = ext_case["n_pad"] // 256
+    F = np.array([1.0 if I % 2 == 0 else 0.1 for I in range(nt)])
+    split = {"bf16": lambda I, J: False, "bf16x3": lambda I, J: True, "bf16_auto": lambda I, J: F[I] * F[J] > 0.5}
+    G = exact._run(wl, ext_case, precision, panel_f=F if precision == "bf16_auto" else None, lim=0.5)
+    exact._check_tiles(G, lambda I, J: ext_case["split" if split[precision](I, J) else "hh"], ext_case["n_pad"])
