@@ -377,7 +377,8 @@ int wlc_gram(int precision, int64_t n, int64_t k, const uint16_t *a_hi, const ui
 /* Work of the last run's one-halo product, into HOST doubles: flops counts
  * one product per tile over the columns it summed (2 x 256 x 256 per column
  * and tile I >= J for the bf16 products, 2 x 128 x 256 on the 128 x 256
- * tiles of the FP64 product, 2 x 128 x 128 on the FP32 product's tiles; each
+ * tiles of the FP64 product (also where few rows are taken by 16 x 16 blocks,
+ * which do less), 2 x 128 x 128 on the FP32 product's tiles; each
  * stops where the shorter of its two 256-row panels' factors ends),
  * mfma_flops the same with the split tiles counted three times.
  * factor_bytes (may be NULL): the bytes of the factor A that

@@ -807,6 +807,62 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
 }
 
+// The same product for a matrix of few tiles: a workgroup for each 16 x 16 block
+// of the lower triangle of the n rows, its eight wavefronts each a stretch of k,
+// added in LDS: no partial buffer and no second launch.  Lane l reads two
+// neighbouring columns of row l % 16 at a time, eight such reads of each operand
+// in flight, and gives one to either of two MFMAs.
+constexpr int FEW_WAVES = 8, FEW_STEP = 8, FEW_DEPTH = 8;
+__global__ __launch_bounds__(64 * FEW_WAVES) void k_gram_f64_few(const double *__restrict__ A, int64_t k_pad,
+                                                                 int64_t lda, double *__restrict__ out, int64_t ld,
+                                                                 const int32_t *__restrict__ panel_ext) {
+  __shared__ double part[FEW_WAVES][256];
+  int I, J;
+  tri_tile(blockIdx.x, I, J);
+  const int64_t row0 = (int64_t)I * 16, col0 = (int64_t)J * 16;
+  if (panel_ext)
+    k_pad = min(k_pad, (int64_t)max(min(panel_ext[row0 / FT_S], panel_ext[col0 / FT_S]), 0) * GRAM_KB);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t steps = k_pad / FEW_STEP, s0 = steps * wave / FEW_WAVES, n_st = steps * (wave + 1) / FEW_WAVES - s0;
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  if (n_st > 0) {
+    const int64_t at = s0 * FEW_STEP + 2 * (lane >> 4);
+    const double *pa = A + (row0 + (lane & 15)) * lda + at, *pb = A + (col0 + (lane & 15)) * lda + at;
+    const int64_t last = n_st - 1;
+    double2 a[FEW_DEPTH], b[FEW_DEPTH];
+    auto load = [&](int d, int64_t st) {
+      a[d] = *(const double2 *)(pa + min(st, last) * FEW_STEP);
+      b[d] = *(const double2 *)(pb + min(st, last) * FEW_STEP);
+    };
+    auto products = [&](int d) {
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[d].x, b[d].x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[d].y, b[d].y, acc, 0, 0, 0);
+    };
+#pragma unroll
+    for (int d = 0; d < FEW_DEPTH; ++d) load(d, d);
+    int64_t st = 0;
+    for (; st + FEW_DEPTH <= n_st; st += FEW_DEPTH)
+#pragma unroll
+      for (int d = 0; d < FEW_DEPTH; ++d) {
+        products(d);
+        load(d, st + d + FEW_DEPTH);
+      }
+#pragma unroll
+    for (int d = 0; d < FEW_DEPTH - 1; ++d)
+      if (st + d < n_st) products(d);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) part[wave][64 * v + lane] = acc[v];
+  __syncthreads();
+  if (threadIdx.x < 256) {
+    double s = part[0][threadIdx.x];
+#pragma unroll
+    for (int w = 1; w < FEW_WAVES; ++w) s += part[w][threadIdx.x];
+    // value v of lane l: row l / 16 + 4 v, column l % 16
+    out[(row0 + (lane >> 4) + 4 * wave) * ld + col0 + (lane & 15)] = s;
+  }
+}
+
 // Mirror of the lower triangle onto the upper one in 64 x 64 tiles (I >= J):
 // tile (I, J) is read row by row, transposed through LDS and written as tile
 // (J, I), so both sides stay coalesced.  On a diagonal tile only the entries
@@ -946,8 +1002,21 @@ static int64_t gram_tile_count(int prec, const GramShape &g) {
   return nt * (nt + 1) / 2;
 }
 
+static int64_t few_blocks(const GramShape &g) {
+  const int64_t nb = (gram_rows(g) + 15) / 16;
+  return nb * (nb + 1) / 2;
+}
+// Up to one block to a CU the blocks are faster at every K (a run of 111 rows at
+// K = 2048 121 -> 101 us, 337 rows at K = 32768 431 -> 391); with more of them
+// the L2 has to serve every operand once for each block (666 blocks at K = 2048
+// 156 against 152, at K = 32768 773 against 595).
+static bool f64_few(int prec, const GramShape &g) { return f64_tiles(prec, g) && few_blocks(g) <= 256; }
+static int gram_slices(int prec, const GramShape &g) {
+  return f64_few(prec, g) ? 1 : pick_split(gram_tile_count(prec, g), g.k_pad, gram_bk(prec), prec);
+}
+
 size_t gram_partial_bytes(int prec, const GramShape &g) {
-  const int s = pick_split(gram_tile_count(prec, g), g.k_pad, gram_bk(prec), prec);
+  const int s = gram_slices(prec, g);
   if (s <= 1) return 0;
   const size_t el = prec == WLC_FP64 ? 8 : 4;
   return (size_t)(s - 1) * g.r_pad * g.ld_out * el;  // slice 0 goes to the output
@@ -966,7 +1035,7 @@ static GramSplit gram_split(int prec, const GramShape &g) {
   q.nt = g.r_pad / gram_tile(prec);
   q.tiles = gram_tile_count(prec, g);
   const int bk = gram_bk(prec);
-  q.ns = pick_split(q.tiles, g.k_pad, bk, prec);
+  q.ns = gram_slices(prec, g);
   q.ksplit = (g.k_pad / bk + q.ns - 1) / q.ns * bk;
   q.pstride = q.ns > 1 ? g.r_pad * g.ld_out : 0;
   q.n_work = q.tiles * q.ns;
@@ -1091,6 +1160,11 @@ void launch_gram(int prec, const GramShape &g, const void *A0, const void *A1, v
                          n_work, (float *)out, (float *)partial, g.ld_out, pstride, panel_ext);
       break;
     default:
+      if (f64_few(prec, g)) {
+        hipLaunchKernelGGL(k_gram_f64_few, dim3((unsigned)few_blocks(g)), dim3(64 * FEW_WAVES), 0, s,
+                           (const double *)A0, g.k_pad, g.lda, (double *)out, g.ld_out, panel_ext);
+        break;
+      }
       if (f64_tiles(prec, g)) {
         hipLaunchKernelGGL(k_gram_f64, grid, dim3(512), 0, s, (const double *)A0, g.k_pad, g.lda, ksplit, ns, n_work,
                            (double *)out, (double *)partial, g.ld_out, pstride, panel_ext, gram_rows(g));

@@ -5,6 +5,8 @@ number of slices, and either side of the line to the tile kernels (48 items)."""
 import numpy as np
 import pytest
 
+import oracle
+import synth
 import test_gpu_gram_exact as exact
 from test_gpu_gram_exact import case, ext_case, wl  # noqa: F401  (fixtures)
 
@@ -41,3 +43,21 @@ def test_extents_exact(wl, ext_case, precision):
     split = {"bf16": lambda I, J: False, "bf16x3": lambda I, J: True, "bf16_auto": lambda I, J: F[I] * F[J] > 0.5}
     G = exact._run(wl, ext_case, precision, panel_f=F if precision == "bf16_auto" else None, lim=0.5)
     exact._check_tiles(G, lambda I, J: ext_case["split" if split[precision](I, J) else "hh"], ext_case["n_pad"])
+
+
+# FP64 products of few rows: one block of 16 and one row past it, a row less and
+# more than a block for each CU would hold, one to nine steps of k for a
+# wavefront
+@pytest.mark.parametrize("n_z,n_ell,ell_max,n_chi,n_m", [
+    (1, 1, 500.0, 3, 2), (1, 4, 500.0, 5, 13), (2, 3, 500.0, 9, 64), (2, 11, 4000.0, 65, 9), (2, 12, 4000.0, 8, 8)])
+def test_f64_few_rows(wl, n_z, n_ell, ell_max, n_chi, n_m):
+    """Sums of positive products, against the oracle to the 1e-10 of the other
+    parity tests."""
+    t = synth.make_tables("tiny", n_z=n_z, n_ell=n_ell, ell_max=ell_max, n_chi=n_chi, n_m=n_m)
+    want = oracle.Oracle(t).covariance()
+    prob = wl.Problem(t.cfg, t.arrays(), precision="fp64")
+    exact._say("case f64 few rows n=%d k=%d" % (prob.sizes.n_data, n_chi * n_m))
+    prob.run()
+    exact.torch.cuda.synchronize()
+    assert np.max(np.abs(prob.covariance_true() / want - 1.0)) < 1e-10
+    prob.close()
