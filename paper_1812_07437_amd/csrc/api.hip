@@ -79,6 +79,10 @@ struct Layout {
   size_t total;
 };
 
+// The flattened product of a run: the layout sizes its partial buffer, and the
+// launches take their slices, from this one shape.
+static GramShape gram_shape(const Plan &p) { return GramShape{p.r_pad, p.k_pad, p.r_pad, p.k_pad, p.n_R}; }
+
 static Layout run_layout(const Plan &p) {
   const auto &c = p.cfg;
   size_t sz[NBUF] = {};
@@ -122,8 +126,7 @@ static Layout run_layout(const Plan &p) {
   }
   const size_t gel = prec_f64(c.precision) ? 8 : 4;
   sz[B_GM] = (size_t)p.r_pad * p.r_pad * gel;
-  GramShape g{p.r_pad, p.k_pad, p.r_pad, p.k_pad};
-  sz[B_PART] = chi ? 0 : gram_partial_bytes(c.precision, g);
+  sz[B_PART] = chi ? 0 : gram_partial_bytes(c.precision, gram_shape(p));
   sz[B_H] = chi ? (size_t)n_cfg * n_cfg * c.n_chi * 8 : 0;
   if (c.flags & WLC_FLAG_NGINS) {
     const int n2 = twoleg_configs(p);
@@ -460,8 +463,6 @@ int run_enqueue_front(const Plan &p, const wlc_tables &tb, void *ws, hipStream_t
   if (hooks) hooks->end(WLC_PHASE_ABUILD);
   return hip_check(hipGetLastError(), "run launch");
 }
-
-static GramShape gram_shape(const Plan &p) { return GramShape{p.r_pad, p.k_pad, p.r_pad, p.k_pad, p.n_R}; }
 
 // WLC_BF16_AUTO: tile (I, J) takes the split product iff
 // (2u + u^2 + K 2^-24) sqrt(F_I F_J) > tol, i.e. F_I F_J > lim, with

@@ -808,13 +808,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 // The same product for a matrix of few tiles: a workgroup for each 16 x 16 block
-// of the lower triangle of the n rows, its eight wavefronts each a stretch of k,
-// added in LDS: no partial buffer and no second launch.  Lane l reads two
+// of the lower triangle of the n rows and slice of k, its eight wavefronts each a
+// stretch of the slice, added in LDS.  Lane l reads two
 // neighbouring columns of row l % 16 at a time, eight such reads of each operand
-// in flight, and gives one to either of two MFMAs.
+// in flight, and gives one to either of two MFMAs.  Bound by those reads (7 us for
+// 1024 columns of a CU's block).
 constexpr int FEW_WAVES = 8, FEW_STEP = 8, FEW_DEPTH = 8;
 __global__ __launch_bounds__(64 * FEW_WAVES) void k_gram_f64_few(const double *__restrict__ A, int64_t k_pad,
-                                                                 int64_t lda, double *__restrict__ out, int64_t ld,
+                                                                 int64_t lda, double *__restrict__ out,
+                                                                 double *__restrict__ partial, int64_t ld,
+                                                                 int64_t part_stride,
                                                                  const int32_t *__restrict__ panel_ext) {
   __shared__ double part[FEW_WAVES][256];
   int I, J;
@@ -823,7 +826,10 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void k_gram_f64_few(const double *_
   if (panel_ext)
     k_pad = min(k_pad, (int64_t)max(min(panel_ext[row0 / FT_S], panel_ext[col0 / FT_S]), 0) * GRAM_KB);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t steps = k_pad / FEW_STEP, s0 = steps * wave / FEW_WAVES, n_st = steps * (wave + 1) / FEW_WAVES - s0;
+  // an even share of the range for each wavefront of each slice; none stores zeros
+  const int64_t steps = k_pad / FEW_STEP, shares = (int64_t)gridDim.y * FEW_WAVES;
+  const int64_t share = (int64_t)blockIdx.y * FEW_WAVES + wave;
+  const int64_t s0 = steps * share / shares, n_st = steps * (share + 1) / shares - s0;
   f64x4 acc = {0.0, 0.0, 0.0, 0.0};
   if (n_st > 0) {
     const int64_t at = s0 * FEW_STEP + 2 * (lane >> 4);
@@ -859,7 +865,8 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void k_gram_f64_few(const double *_
 #pragma unroll
     for (int w = 1; w < FEW_WAVES; ++w) s += part[w][threadIdx.x];
     // value v of lane l: row l / 16 + 4 v, column l % 16
-    out[(row0 + (lane >> 4) + 4 * wave) * ld + col0 + (lane & 15)] = s;
+    double *dst = gram_dst(out, partial, blockIdx.y, part_stride);
+    dst[(row0 + (lane >> 4) + 4 * wave) * ld + col0 + (lane & 15)] = s;
   }
 }
 
@@ -1002,6 +1009,7 @@ static int64_t gram_tile_count(int prec, const GramShape &g) {
   return nt * (nt + 1) / 2;
 }
 
+constexpr int64_t FEW_COLS = 1024;  // 512 the same, 2048 slower (111 rows at K = 4096 110, 110, 117 us)
 static int64_t few_blocks(const GramShape &g) {
   const int64_t nb = (gram_rows(g) + 15) / 16;
   return nb * (nb + 1) / 2;
@@ -1012,7 +1020,13 @@ static int64_t few_blocks(const GramShape &g) {
 // 156 against 152, at K = 32768 773 against 595).
 static bool f64_few(int prec, const GramShape &g) { return f64_tiles(prec, g) && few_blocks(g) <= 256; }
 static int gram_slices(int prec, const GramShape &g) {
-  return f64_few(prec, g) ? 1 : pick_split(gram_tile_count(prec, g), g.k_pad, gram_bk(prec), prec);
+  // slices to fill the CUs once (two workgroups to a CU share its reads: no
+  // faster), of at least FEW_COLS columns, which take what a reduction does: a run
+  // of 168 rows at K = 32768 350 -> 205 us with three, of 9 rows at K = 8192
+  // 139 -> 98 with eight
+  if (f64_few(prec, g))
+    return (int)std::clamp<int64_t>(std::min(256 / few_blocks(g), g.k_pad / FEW_COLS), 1, 32);
+  return pick_split(gram_tile_count(prec, g), g.k_pad, gram_bk(prec), prec);
 }
 
 size_t gram_partial_bytes(int prec, const GramShape &g) {
@@ -1161,8 +1175,9 @@ void launch_gram(int prec, const GramShape &g, const void *A0, const void *A1, v
       break;
     default:
       if (f64_few(prec, g)) {
-        hipLaunchKernelGGL(k_gram_f64_few, dim3((unsigned)few_blocks(g)), dim3(64 * FEW_WAVES), 0, s,
-                           (const double *)A0, g.k_pad, g.lda, (double *)out, g.ld_out, panel_ext);
+        hipLaunchKernelGGL(k_gram_f64_few, dim3((unsigned)few_blocks(g), (unsigned)ns), dim3(64 * FEW_WAVES), 0, s,
+                           (const double *)A0, g.k_pad, g.lda, (double *)out, (double *)partial, g.ld_out, pstride,
+                           panel_ext);
         break;
       }
       if (f64_tiles(prec, g)) {

@@ -47,9 +47,10 @@ def test_extents_exact(wl, ext_case, precision):
 
 # FP64 products of few rows: one block of 16 and one row past it, a row less and
 # more than a block for each CU would hold, one to nine steps of k for a
-# wavefront
+# wavefront, then eight and three slices
 @pytest.mark.parametrize("n_z,n_ell,ell_max,n_chi,n_m", [
-    (1, 1, 500.0, 3, 2), (1, 4, 500.0, 5, 13), (2, 3, 500.0, 9, 64), (2, 11, 4000.0, 65, 9), (2, 12, 4000.0, 8, 8)])
+    (1, 1, 500.0, 3, 2), (1, 4, 500.0, 5, 13), (2, 3, 500.0, 9, 64), (2, 11, 4000.0, 65, 9), (2, 12, 4000.0, 8, 8),
+    (1, 2, 500.0, 128, 65), (2, 5, 1500.0, 64, 50)])
 def test_f64_few_rows(wl, n_z, n_ell, ell_max, n_chi, n_m):
     """Sums of positive products, against the oracle to the 1e-10 of the other
     parity tests."""
