@@ -548,7 +548,6 @@ static AsmArgs asm_args(const Plan &p, void *ws, const Layout &L) {
 int run_enqueue_back(const Plan &p, const wlc_tables &tb, void *ws, double *d, double *r, void *C, int32_t *row_exp2,
                      hipStream_t s, PhaseHooks *hooks) {
   (void)tb;
-  const wlc_config &c = p.cfg;
   const Layout L = run_layout(p);
   void *Gm = at<void>(ws, L, B_GM);
   const AsmArgs a = asm_args(p, ws, L);

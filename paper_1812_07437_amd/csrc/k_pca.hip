@@ -134,7 +134,6 @@ __global__ __launch_bounds__(256) void k_pca_gram(const double *__restrict__ X, 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int pi = blockIdx.x, ks = blockIdx.y;
   const int bp = rr_at(pi, r, n_blk), bq = rr_at(n_blk - 1 - pi, r, n_blk);
-  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
   // this slice's 64-column chunks
   const int all = (int)(n_pad / PR), first = (int)((int64_t)all * ks / gridDim.y);
   const int64_t c0 = (int64_t)first * PR;
