@@ -12,6 +12,8 @@
 // modes and rows.  The row half-widths are exact integer square roots.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace wlc {
@@ -72,7 +74,8 @@ __device__ __forceinline__ U row_pairs(I p, I q, I s) {
 // One triangle per blockIdx.y, LY1 rows y1 >= 0 of q1 by 256 rows y2 of q2 per
 // workgroup: a thread holds its row y2, the half-widths of the rows y1 and
 // y1 + y2 lie in LDS.  Rows y1 > 0 count twice (y -> -y).  With I = int32_t every
-// intermediate fits (or wraps and comes back, mod 2^32) for radii to 16000.
+// intermediate fits (or wraps and comes back, mod 2^32) for radii to 16000.  The
+// workgroups of a triangle are numbered from `base`, the first of this launch.
 //
 // Bound by integer arithmetic, about 120 instructions per pair of rows.  At
 // 10 ell-bins to 3000 (64 triangles) the whole call takes 0.18 ms, against 13.8 ms with interval overlaps
@@ -80,12 +83,12 @@ __device__ __forceinline__ U row_pairs(I p, I q, I s) {
 constexpr int LY1 = 64;
 template <typename I, typename U>
 __global__ __launch_bounds__(256) void k_lattice_tris(const int64_t *__restrict__ thr, const int32_t *__restrict__ tri,
-                                                      int64_t rmax, uint64_t *__restrict__ out) {
+                                                      int64_t rmax, int64_t base, uint64_t *__restrict__ out) {
   __shared__ I w1[LY1][2], w3[LY1 + 256][2];
   __shared__ uint64_t part[256];
   const int t = blockIdx.y, tid = threadIdx.x;
-  const int64_t n2 = (2 * rmax + 256) / 256;
-  const int64_t y1 = (int64_t)(blockIdx.x / n2) * LY1, y2 = (int64_t)(blockIdx.x % n2) * 256 - rmax;
+  const int64_t n2 = (2 * rmax + 256) / 256, wg = base + blockIdx.x;
+  const int64_t y1 = wg / n2 * LY1, y2 = wg % n2 * 256 - rmax;
   const int b1 = tri[3 * t], b2 = tri[3 * t + 1], b3 = tri[3 * t + 2];
   const int64_t lo1 = thr[b1], hi1 = thr[b1 + 1];
   const int64_t lo2 = thr[b2], hi2 = thr[b2 + 1], lo3 = thr[b3], hi3 = thr[b3 + 1];
@@ -150,11 +153,16 @@ void launch_lattice(const int64_t *thr_dev, int64_t thr_max, int n_ell, const in
   }
   if (tris && n_tri > 0) {
     hipLaunchKernelGGL(k_zero_u64, dim3((n_tri + 255) / 256), dim3(256), 0, s, tris, n_tri);
-    const dim3 grid((unsigned)((rmax / LY1 + 1) * ((2 * rmax + 256) / 256)), (unsigned)n_tri);
-    if (rmax <= 16000)
-      hipLaunchKernelGGL((k_lattice_tris<int32_t, uint32_t>), grid, dim3(256), 0, s, thr_dev, tri, rmax, tris);
-    else
-      hipLaunchKernelGGL((k_lattice_tris<int64_t, uint64_t>), grid, dim3(256), 0, s, thr_dev, tri, rmax, tris);
+    // a launch holds fewer than 2^32 threads along x (more are taken modulo 2^32,
+    // without an error): one up to a radius of 262000, then one for every 2^23 workgroups
+    const int64_t wgs = (rmax / LY1 + 1) * ((2 * rmax + 256) / 256), most = (int64_t)1 << 23;
+    for (int64_t base = 0; base < wgs; base += most) {
+      const dim3 grid((unsigned)std::min(most, wgs - base), (unsigned)n_tri);
+      if (rmax <= 16000)
+        hipLaunchKernelGGL((k_lattice_tris<int32_t, uint32_t>), grid, dim3(256), 0, s, thr_dev, tri, rmax, base, tris);
+      else
+        hipLaunchKernelGGL((k_lattice_tris<int64_t, uint64_t>), grid, dim3(256), 0, s, thr_dev, tri, rmax, base, tris);
+    }
   }
 }
 
