@@ -305,7 +305,10 @@ int wlc_snr2_lmax(wlc_plan plan, const void *C, const int32_t *row_exp2, const d
  *   sweeps     (may be NULL) sweeps used.
  * S (DEVICE [n_data][n_data], may be NULL to skip the eigenvectors): row a
  * is the unit eigenvector of lambda[a], its largest entry in magnitude made
- * positive.  ws: DEVICE workspace of ws_pca_bytes.  Synchronises the stream
+ * positive.  Its small entries are accurate at their own size, so that
+ * (S_a . d)^2 / lambda_a gives snr2_mode; for that the rotations run on W^T and
+ * are accumulated (more sweeps, and lambda and snr2_mode equal those without S
+ * to rounding).  ws: DEVICE workspace of ws_pca_bytes.  Synchronises the stream
  * once per sweep.  WLC_ENOTPD if C is not positive definite, WLC_ENOCONV
  * without convergence, WLC_EINVAL if ws_pca_bytes is 0. */
 int wlc_pca(wlc_plan plan, const void *C, const int32_t *row_exp2, const double *d, void *ws, double *lambda,

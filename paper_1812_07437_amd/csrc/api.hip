@@ -1084,14 +1084,21 @@ int wlc_pca(wlc_plan plan, const void *C, const int32_t *row_exp2, const double 
   if (!rc) rc = hip_check(hipStreamSynchronize(s), "pca sync");
   if (rc) return rc;
   if (hflag) return fail(WLC_ENOTPD, "covariance is not positive definite");
-  launch_pca_init(reinterpret_cast<const double *>(ws), ld, row_exp2, perm, n, np, X, y, s);
+  if (S && (size_t)np * np * 8 > (size_t)(n + 1) * ld * 8 + chol_scratch_bytes(n))
+    return fail(WLC_EINVAL, "no room for the rotations in the S/N workspace");
+  launch_pca_init(reinterpret_cast<const double *>(ws), ld, row_exp2, perm, n, np, S != nullptr, X, y, s);
+  // the rotations, with vectors, take the place of the factor and its scratch, no
+  // longer needed: n_pad <= n + 63, the scratch has 256 (n + 1) + 4096 doubles or
+  // more, and (n + 63)^2 < (n + 1)^2 + 256 (n + 1) + 4096
+  double *V = S ? reinterpret_cast<double *>(ws) : nullptr;
+  if (V) launch_pca_identity(np, V, s);
   const double tol = 8.0 * std::sqrt((double)np) * 2.220446049250313e-16;
   const int n_blk = (int)(np / 32);
   int used = 0;
   bool converged = false;
   for (int sweep = 0; sweep < 40 && !converged; ++sweep) {
     launch_fill_i32(reinterpret_cast<int32_t *>(conv), 2, 0, s);
-    for (int r = 0; r < n_blk - 1; ++r) launch_pca_round(X, y, np, r, tol, conv, part, Qg, rot, s);
+    for (int r = 0; r < n_blk - 1; ++r) launch_pca_round(X, V, V ? nullptr : y, np, r, tol, conv, part, Qg, rot, s);
     double hconv = 0.0;
     rc = hip_check(hipMemcpyAsync(&hconv, conv, 8, hipMemcpyDeviceToHost, s), "pca copy");
     if (!rc) rc = hip_check(hipStreamSynchronize(s), "pca sync");
@@ -1101,7 +1108,7 @@ int wlc_pca(wlc_plan plan, const void *C, const int32_t *row_exp2, const double 
   }
   if (sweeps) *sweeps = used;
   if (!converged) return fail(WLC_ENOCONV, "the PCA Jacobi sweeps did not converge");
-  launch_pca_finish(X, y, perm, n, np, lam, snr, rank_lam, rank_snr, lam_out, snr_out, desc, S, s);
+  launch_pca_finish(X, V, y, perm, n, np, lam, snr, rank_lam, rank_snr, lam_out, snr_out, desc, S, s);
   rc = hip_check(hipMemcpyAsync(lambda, lam_out, (size_t)n * 8, hipMemcpyDeviceToHost, s), "pca copy");
   if (!rc) rc = hip_check(hipMemcpyAsync(snr2_mode, snr_out, (size_t)n * 8, hipMemcpyDeviceToHost, s), "pca copy");
   if (!rc) rc = hip_check(hipMemcpyAsync(cum_desc, desc, (size_t)n * 8, hipMemcpyDeviceToHost, s), "pca copy");

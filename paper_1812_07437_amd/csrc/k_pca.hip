@@ -8,19 +8,27 @@
 // (Hestenes) Jacobi, which keeps relative accuracy on graded matrices
 // (Demmel and Veselic 1992): with C = Delta C^ Delta (Delta = 2^-t, the row
 // scaling of the covariance) and C^ = L L^T from the bordered Cholesky,
-// C = W W^T for W = Delta L.  Column rotations W -> W V make the columns w_a
-// orthogonal; then lambda_a = |w_a|^2 and the eigenvectors are w_a / |w_a|, with
-// no rotation accumulated beside W.  Since d = W y (y = L^-1 2^t d, the
+// C = W W^T for W = Delta L.  Column rotations W -> W Q make the columns w_a
+// orthogonal; then lambda_a = |w_a|^2.  Since d = W y (y = L^-1 2^t d, the
 // Cholesky's own forward substitution), D^_a / sqrt(lambda_a) is component a of
-// V^T y: y is rotated along.  The rows are taken in decreasing order of the
+// Q^T y: y is rotated along.  The rows are taken in decreasing order of the
 // diagonal of C before the factorisation, so that the columns of W come graded
 // and the rotations start small (Veselic and Hari 1989): 818 rows of the paper's
 // binning converge in 7 sweeps of a plain cyclic Jacobi instead of 11 on the
 // rows of Delta L, with the same accuracy (327 rows against 80-bit arithmetic:
 // 3.3e-13 on the worst of 17 decades of eigenvalues, 3.1e-13 on the rows).
 //
-// Storage: the columns of W are the rows of X (zero-padded to n_pad), so every
-// vector the method touches is a contiguous row.  Rows are grouped in blocks of
+// The eigenvectors need the other side.  w_a / |w_a| has an error of tol in every
+// entry, but its entry at a row k of much larger variance is as small as
+// sqrt(lambda_a / C_kk), and S_a . d, where d_k is as much larger, takes it at
+// its own size.  With vectors the method therefore works on W^T = L^T Delta:
+// rotations W^T -> W^T V of its columns, those of the rows of W, are accumulated
+// in V, whose columns are the eigenvectors, and an angle between columns of
+// different norms is itself as small as their ratio.  Then lambda_a = |w_a|^2
+// for the columns w_a of W^T V, and D^_a = w_a . y with y as it is.
+//
+// Storage: the columns of W (with vectors of W^T, and of V) are the rows of X
+// (and of V; zero-padded to n_pad), so every vector the method touches is a contiguous row.  Rows are grouped in blocks of
 // 32; each round pairs all blocks (a round-robin tournament over n_blk =
 // n_pad / 32 blocks, n_blk - 1 rounds per sweep); for each pair (p, q) the
 // 64 x 64 Gram matrix of its rows is formed on FP64 MFMA, rotated towards
@@ -77,8 +85,10 @@ __global__ void k_pca_order(const InT *__restrict__ C, const int32_t *__restrict
 }
 
 // X from the bordered factor Wm of the ordered rows (rows 0..n-1: L in the lower
-// triangle, row n: y): X[j][k] = 2^-t_k Wm[k][j] for j <= k < n, else 0;
-// y_pad = row n of Wm.  A 64 x 64 block per workgroup, transposed through LDS.
+// triangle, row n: y): X[j][k] = 2^-t_k Wm[k][j] for j <= k < n, else 0, by way of
+// LDS; with VECTORS its transpose; y_pad = row n of Wm.  A 64 x 64 block per
+// workgroup.
+template <bool VECTORS>
 __global__ __launch_bounds__(256) void k_pca_init(const double *__restrict__ Wm, int64_t ld,
                                                   const int32_t *__restrict__ t, const int32_t *__restrict__ perm,
                                                   int64_t n, int64_t n_pad, double *__restrict__ X,
@@ -88,14 +98,22 @@ __global__ __launch_bounds__(256) void k_pca_init(const double *__restrict__ Wm,
   const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
   for (int r = r0; r < 64; r += 4) {
     const int64_t k = k0 + r, j = j0 + c;
-    tile[r][c] = k < n && j <= k ? ldexp(Wm[k * ld + j], -t[perm[k]]) : 0.0;
+    const double x = k < n && j <= k ? ldexp(Wm[k * ld + j], -t[perm[k]]) : 0.0;
+    if constexpr (VECTORS) X[k * n_pad + j] = x;
+    else tile[r][c] = x;
   }
   __syncthreads();
-  for (int r = r0; r < 64; r += 4) X[(j0 + r) * n_pad + k0 + c] = tile[c][r];
+  if constexpr (!VECTORS)
+    for (int r = r0; r < 64; r += 4) X[(j0 + r) * n_pad + k0 + c] = tile[c][r];
   if (blockIdx.x == 0 && threadIdx.x < 64) {
     const int64_t j = j0 + threadIdx.x;
     y[j] = j < n ? Wm[n * ld + j] : 0.0;
   }
+}
+
+__global__ void k_pca_identity(int64_t n_pad, double *__restrict__ V) {
+  const int64_t j = blockIdx.y, k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < n_pad) V[j * n_pad + k] = j == k ? 1.0 : 0.0;
 }
 
 __device__ __forceinline__ void atomic_max_nonneg(double *addr, double v) {
@@ -107,9 +125,9 @@ __device__ __forceinline__ void atomic_max_nonneg(double *addr, double v) {
 // of each block pair over column slices (FP64 MFMA); (b) k_pca_rot or
 // k_pca_cross, one workgroup per pair: sum the slices in fixed order, measure the largest
 // scaled off-diagonal entry, and unless it is below tol rotate M in LDS, store
-// Q and rotate the pair's components of y (reordering the rotated columns by
+// Q and rotate the pair's components of y, if given (reordering the rotated columns by
 // norm, as in de Rijk's sorting, was measured to break the convergence of the
-// cyclic tournament here); (c) k_pca_apply: rows of X <- Q^T rows, skipped for
+// cyclic tournament here); (c) k_pca_apply: rows of X (and V) <- Q^T rows, skipped for
 // pairs that did not rotate.
 __device__ __forceinline__ int64_t pair_row(int bp, int bq, int j) {
   return j < PB ? (int64_t)bp * PB + j : (int64_t)bq * PB + (j - PB);
@@ -384,6 +402,7 @@ __global__ __launch_bounds__(RT) void k_pca_rot(const double *__restrict__ part,
   }
   double *out = Qg + (int64_t)pi * PR * PR;
   for (int e = tid; e < PR * PR; e += RT) out[e] = QT[(e % PR) * QLD + e / PR];
+  if (!y) return;
   // y of the pair <- Q^T y
   const int bp = rr_at(pi, r, n_blk), bq = rr_at(n_blk - 1 - pi, r, n_blk);
   if (tid < PR) ys[tid] = y[pair_row(bp, bq, tid)];
@@ -486,7 +505,7 @@ __global__ __launch_bounds__(CT) void k_pca_cross(const double *__restrict__ par
         x[p][i] = row + i == j + 16 * p ? 1.0 : 0.0;
         z[p][i] = row + i == H + j + 16 * p ? 1.0 : 0.0;
       }
-    const double y0 = y[pair_row(bp, bq, row)], y1 = y[pair_row(bp, bq, row + 1)];
+    const double y0 = y ? y[pair_row(bp, bq, row)] : 0.0, y1 = y ? y[pair_row(bp, bq, row + 1)] : 0.0;
     __syncthreads();
 #pragma unroll 1
     for (int k = 0; k < H; ++k) {
@@ -531,6 +550,7 @@ __global__ __launch_bounds__(CT) void k_pca_cross(const double *__restrict__ par
       ys[e >> 4][j + 16 * p + H] = z[p][0] * y0 + z[p][1] * y1;
     }
   }
+  if (!y) return;
   __syncthreads();
   // y of the pair <- Q^T y
   if (tid < PR) {
@@ -541,19 +561,26 @@ __global__ __launch_bounds__(CT) void k_pca_cross(const double *__restrict__ par
   }
 }
 
-// Per mode a < n: lambda_a = |x_a|^2 and (S/N)^2_a = y_a^2.
+// Per mode a < n: lambda_a = |x_a|^2 and (S/N)^2_a = y_a^2 (y rotated along), with
+// VECTORS (x_a . y)^2 / lambda_a.
+template <bool VECTORS>
 __global__ void k_pca_modes(const double *__restrict__ X, const double *__restrict__ y, int64_t n, int64_t n_pad,
                             double *__restrict__ lam, double *__restrict__ snr2) {
   const int lane = threadIdx.x & (WAVE - 1);
   const int64_t a = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
   if (a >= n) return;
   const double *x = X + a * n_pad;
-  double nn = 0.0;
-  for (int64_t k = lane; k < n_pad; k += WAVE) nn += x[k] * x[k];
+  double nn = 0.0, dy = 0.0;
+  for (int64_t k = lane; k < n_pad; k += WAVE) {
+    nn += x[k] * x[k];
+    if (VECTORS) dy += x[k] * y[k];
+  }
   nn = wave_sum(nn);
+  if (VECTORS) dy = wave_sum(dy);
   if (lane == 0) {
     lam[a] = nn;
-    snr2[a] = nn > 0.0 ? y[a] * y[a] : 0.0;
+    const double v = VECTORS ? dy / sqrt(nn) : y[a];
+    snr2[a] = nn > 0.0 ? v * v : 0.0;
   }
 }
 
@@ -612,17 +639,16 @@ __global__ void k_pca_cumsum(double *__restrict__ v, int64_t n) {
   }
 }
 
-// Eigenvector rows w_a / |w_a| in ascending-lambda order, back in the data
+// Eigenvector rows in ascending-lambda order, back in the data
 // vector's order, with the sign that makes the largest entry in magnitude
 // positive (the first of them in the data vector's order).
-__global__ void k_pca_vectors(const double *__restrict__ X, const double *__restrict__ lam,
-                              const int32_t *__restrict__ rank_lam, const int32_t *__restrict__ perm, int64_t n,
-                              int64_t n_pad, double *__restrict__ S) {
+__global__ void k_pca_vectors(const double *__restrict__ V, const int32_t *__restrict__ rank_lam,
+                              const int32_t *__restrict__ perm, int64_t n, int64_t n_pad, double *__restrict__ S) {
   __shared__ double bv[256];
   __shared__ int64_t bi[256];
   __shared__ int64_t bk[256];
   const int64_t a = blockIdx.x;
-  const double *v = X + a * n_pad;
+  const double *v = V + a * n_pad;
   double best = -1.0;
   int64_t at = n, bat = 0;
   for (int64_t k = threadIdx.x; k < n; k += blockDim.x) {
@@ -645,8 +671,7 @@ __global__ void k_pca_vectors(const double *__restrict__ X, const double *__rest
     }
     __syncthreads();
   }
-  const double nrm = lam[a] > 0.0 ? 1.0 / sqrt(lam[a]) : 0.0;
-  const double sg = v[bk[0]] < 0.0 ? -nrm : nrm;
+  const double sg = v[bk[0]] < 0.0 ? -1.0 : 1.0;
   double *out = S + (int64_t)rank_lam[a] * n;
   for (int64_t k = threadIdx.x; k < n; k += blockDim.x) out[perm[k]] = sg * v[k];
 }
@@ -660,9 +685,16 @@ void launch_pca_order(const void *C, int c_f32, const int32_t *t, int64_t n, int
 }
 
 void launch_pca_init(const double *Wm, int64_t ld, const int32_t *t, const int32_t *perm, int64_t n, int64_t n_pad,
-                     double *X, double *y, hipStream_t s) {
+                     bool vectors, double *X, double *y, hipStream_t s) {
   const dim3 grid((unsigned)(n_pad / 64), (unsigned)(n_pad / 64));
-  hipLaunchKernelGGL(k_pca_init, grid, dim3(256), 0, s, Wm, ld, t, perm, n, n_pad, X, y);
+  if (vectors)
+    hipLaunchKernelGGL(k_pca_init<true>, grid, dim3(256), 0, s, Wm, ld, t, perm, n, n_pad, X, y);
+  else
+    hipLaunchKernelGGL(k_pca_init<false>, grid, dim3(256), 0, s, Wm, ld, t, perm, n, n_pad, X, y);
+}
+
+void launch_pca_identity(int64_t n_pad, double *V, hipStream_t s) {
+  hipLaunchKernelGGL(k_pca_identity, dim3((unsigned)((n_pad + 255) / 256), (unsigned)n_pad), dim3(256), 0, s, n_pad, V);
 }
 
 // Rotation of a pair's rows.  Q's fragments stay in
@@ -674,9 +706,10 @@ void launch_pca_init(const double *Wm, int64_t ld, const int32_t *t, const int32
 // fall on alternate halves of the banks.  A wavefront copy fills two rows.
 __device__ __forceinline__ int apply_slot(int l, int col) { return l * PR + 2 * ((col >> 1) ^ (8 * (l & 1))) + (col & 1); }
 
-// `per` chunks per workgroup.
-__global__ __launch_bounds__(256) void k_pca_apply(double *__restrict__ Y, int64_t n_pad, int per, int n_blk, int r,
-                                                     const double *__restrict__ Qg, const int32_t *__restrict__ rot) {
+// `per` chunks per workgroup, of X for blockIdx.z = 0 and of V for 1.
+__global__ __launch_bounds__(256) void k_pca_apply(double *__restrict__ X, double *__restrict__ V, int64_t n_pad,
+                                                     int per, int n_blk, int r, const double *__restrict__ Qg,
+                                                     const int32_t *__restrict__ rot) {
   __shared__ __attribute__((aligned(16))) double st0[PR * PR];
   __shared__ __attribute__((aligned(16))) double st1[PR * PR];
   const int pi = blockIdx.x;
@@ -684,6 +717,7 @@ __global__ __launch_bounds__(256) void k_pca_apply(double *__restrict__ Y, int64
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int bp = rr_at(pi, r, n_blk), bq = rr_at(n_blk - 1 - pi, r, n_blk);
   const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
+  double *Y = blockIdx.z == 0 ? X : V;
   // Q fragments: step kk, block x: Q[kk + lane / 16][wr + 16 x + lane % 16]
   const double *q = Qg + (int64_t)pi * PR * PR;
   double qa[PR / 4][2];
@@ -777,7 +811,7 @@ int pca_slices(int64_t n_pad) {
   return ks;
 }
 
-void launch_pca_round(double *X, double *y, int64_t n_pad, int r, double tol, double *conv, double *part, double *Qg,
+void launch_pca_round(double *X, double *V, double *y, int64_t n_pad, int r, double tol, double *conv, double *part, double *Qg,
                       int32_t *rot, hipStream_t s) {
   const int n_blk = (int)(n_pad / PB), pairs = n_blk / 2, ks = pca_slices(n_pad), chunks = (int)(n_pad / PR);
   hipLaunchKernelGGL(k_pca_gram, dim3((unsigned)pairs, (unsigned)ks), dim3(256), 0, s, X, n_pad, n_blk, r, part);
@@ -787,21 +821,25 @@ void launch_pca_round(double *X, double *y, int64_t n_pad, int r, double tol, do
     hipLaunchKernelGGL(k_pca_cross, dim3((unsigned)pairs), dim3(CT), 0, s, part, ks, tol, n_blk, r, y, Qg, rot, conv);
   // chunks per workgroup: eight amortise the 32 KB of Q, fewer while the chip
   // is not filled twice
-  int per = (int)std::min<int64_t>(8, std::max<int64_t>(1, (int64_t)pairs * chunks / 512));
-  hipLaunchKernelGGL(k_pca_apply, dim3((unsigned)pairs, (unsigned)((chunks + per - 1) / per)), dim3(256), 0, s, X,
-                     n_pad, per, n_blk, r, Qg, rot);
+  const int sides = V ? 2 : 1;
+  int per = (int)std::min<int64_t>(8, std::max<int64_t>(1, (int64_t)pairs * chunks * sides / 512));
+  hipLaunchKernelGGL(k_pca_apply, dim3((unsigned)pairs, (unsigned)((chunks + per - 1) / per), sides), dim3(256), 0, s,
+                     X, V, n_pad, per, n_blk, r, Qg, rot);
 }
 
-void launch_pca_finish(const double *X, const double *y, const int32_t *perm, int64_t n, int64_t n_pad, double *lam,
+void launch_pca_finish(const double *X, const double *V, const double *y, const int32_t *perm, int64_t n, int64_t n_pad, double *lam,
                        double *snr2, int32_t *rank_lam, int32_t *rank_snr, double *lam_out, double *snr2_out,
                        double *desc, double *S, hipStream_t s) {
   const dim3 waves((unsigned)((n + 3) / 4));
-  hipLaunchKernelGGL(k_pca_modes, waves, dim3(256), 0, s, X, y, n, n_pad, lam, snr2);
+  if (V)
+    hipLaunchKernelGGL(k_pca_modes<true>, waves, dim3(256), 0, s, X, y, n, n_pad, lam, snr2);
+  else
+    hipLaunchKernelGGL(k_pca_modes<false>, waves, dim3(256), 0, s, X, y, n, n_pad, lam, snr2);
   hipLaunchKernelGGL(k_pca_rank, waves, dim3(256), 0, s, lam, snr2, n, rank_lam, rank_snr);
   hipLaunchKernelGGL(k_pca_scatter, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, lam, snr2, rank_lam, rank_snr,
                      n, lam_out, snr2_out, desc);
   hipLaunchKernelGGL(k_pca_cumsum, dim3(1), dim3(64), 0, s, desc, n);
-  if (S) hipLaunchKernelGGL(k_pca_vectors, dim3((unsigned)n), dim3(256), 0, s, X, lam, rank_lam, perm, n, n_pad, S);
+  if (V) hipLaunchKernelGGL(k_pca_vectors, dim3((unsigned)n), dim3(256), 0, s, V, rank_lam, perm, n, n_pad, S);
 }
 
 }  // namespace wlc

@@ -229,16 +229,18 @@ void launch_woodbury(const WoodArgs &w, hipStream_t s);
 // perm: the rows in decreasing order of the diagonal of C_true
 void launch_pca_order(const void *C, int c_f32, const int32_t *t, int64_t n, int32_t *perm, hipStream_t s);
 void launch_pca_init(const double *Wm, int64_t ld, const int32_t *t, const int32_t *perm, int64_t n, int64_t n_pad,
-                     double *X, double *y, hipStream_t s);
-// one round r of the tournament; part: [pairs][pca_slices][PCA_PART], Qg:
+                     bool vectors, double *X, double *y, hipStream_t s);
+void launch_pca_identity(int64_t n_pad, double *V, hipStream_t s);
+// one round r of the tournament, on the rows of X, and of V and y if given; part: [pairs][pca_slices][PCA_PART], Qg:
 // [pairs][64][64] doubles, rot: [pairs] int32 of scratch
 constexpr int PCA_PART = 10 * 256;  // a slice's lower triangle: ten 16 x 16 tiles
 int pca_slices(int64_t n_pad);
-void launch_pca_round(double *X, double *y, int64_t n_pad, int r, double tol, double *conv, double *part, double *Qg,
-                      int32_t *rot, hipStream_t s);
-void launch_pca_finish(const double *X, const double *y, const int32_t *perm, int64_t n, int64_t n_pad, double *lam,
-                       double *snr2, int32_t *rank_lam, int32_t *rank_snr, double *lam_out, double *snr2_out,
-                       double *desc, double *S, hipStream_t s);
+void launch_pca_round(double *X, double *V, double *y, int64_t n_pad, int r, double tol, double *conv, double *part,
+                      double *Qg, int32_t *rot, hipStream_t s);
+// V: the accumulated rotations of launch_pca_init with vectors, for S
+void launch_pca_finish(const double *X, const double *V, const double *y, const int32_t *perm, int64_t n,
+                       int64_t n_pad, double *lam, double *snr2, int32_t *rank_lam, int32_t *rank_snr, double *lam_out,
+                       double *snr2_out, double *desc, double *S, hipStream_t s);
 
 // ---- lattice counts (k_lattice.hip); thr_max = largest threshold used
 void launch_lattice(const int64_t *thr_dev, int64_t thr_max, int n_ell, const int32_t *tri, int n_tri,
