@@ -269,6 +269,22 @@ __device__ __forceinline__ void jacobi_angle(double a, double b, double m, doubl
   t = sg * m2 * rh * ru * ru;
 }
 
+// Whether m = M_jl is above tol of sqrt(a b), a = M_jj and b = M_ll (false where one
+// of them is zero): squares of mantissas, and the exponents apart, since a b, and
+// m^2 long before it, leaves the range of a double well within that of C.
+__device__ __forceinline__ bool above_tol(double a, double b, double m, double tol2) {
+  const double x = __builtin_amdgcn_frexp_mant(m);
+  const int e = 2 * __builtin_amdgcn_frexp_exp(m) - __builtin_amdgcn_frexp_exp(a) - __builtin_amdgcn_frexp_exp(b);
+  return ldexp(x * x, e) > tol2 * (__builtin_amdgcn_frexp_mant(a) * __builtin_amdgcn_frexp_mant(b)) && a > 0.0 && b > 0.0;
+}
+
+// |m| / sqrt(a b), exponents apart as above; 0 where a or b is zero
+__device__ __forceinline__ double scaled_entry(double a, double b, double m) {
+  const int e = __builtin_amdgcn_frexp_exp(a) + __builtin_amdgcn_frexp_exp(b);
+  const double p = __builtin_amdgcn_frexp_mant(a) * __builtin_amdgcn_frexp_mant(b);
+  return p > 0.0 ? ldexp(fabs(m), -(e >> 1)) / sqrt(e & 1 ? 2.0 * p : p) : 0.0;
+}
+
 // What both rotation kernels begin with, on T threads: M (lower triangle, row >=
 // column) from the slices, in order, and the pair's largest scaled off-diagonal
 // entry; whether it is above tol (else the pair is orthogonal).
@@ -310,9 +326,9 @@ __device__ __forceinline__ bool rot_begin(const double *__restrict__ part, int n
   double off = 0.0;
 #pragma unroll
   for (int q = 0; q < NV; ++q) {
-    const double dc = diag[col[q]], d0 = diag[row[q]] * dc, d1 = diag[row[q] + 4] * dc;
-    if (col[q] < row[q] && d0 > 0.0) off = fmax(off, fabs(v[q].x) / sqrt(d0));
-    if (col[q] < row[q] + 4 && d1 > 0.0) off = fmax(off, fabs(v[q].y) / sqrt(d1));
+    const double dc = diag[col[q]];
+    if (col[q] < row[q]) off = fmax(off, scaled_entry(diag[row[q]], dc, v[q].x));
+    if (col[q] < row[q] + 4) off = fmax(off, scaled_entry(diag[row[q] + 4], dc, v[q].y));
   }
   off = wave_max(off);
   if ((tid & 63) == 0) red[tid / WAVE] = off;
@@ -366,7 +382,7 @@ __global__ __launch_bounds__(RT) void k_pca_rot(const double *__restrict__ part,
       const int j = first(tid), l = second(tid), jl = lower(j, l);
       const double mjj = M[j * PLD + j], mll = M[l * PLD + l], mjl = M[jl];
       double c = 1.0, sn = 0.0;
-      if (mjl * mjl > tol2 * (mjj * mll) && mjj > 0.0 && mll > 0.0) {
+      if (above_tol(mjj, mll, mjl, tol2)) {
         double tt;
         jacobi_angle(mjj, mll, mjl, c, sn, tt);
         M[j * PLD + j] = fma(-tt, mjl, mjj);
@@ -463,7 +479,7 @@ __global__ __launch_bounds__(CT) void k_pca_cross(const double *__restrict__ par
     double c, s, t;
     bool on;
     auto angle = [&]() {
-      on = mjl * mjl > tol2 * (mjj * mll) && mjj > 0.0 && mll > 0.0;
+      on = above_tol(mjj, mll, mjl, tol2);
       jacobi_angle(mjj, mll, mjl, c, s, t);  // no number where both are zero
       c = on ? c : 1.0;
       s = on ? s : 0.0;
