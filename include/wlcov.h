@@ -380,14 +380,14 @@ int wlc_gram(int precision, int64_t n, int64_t k, const uint16_t *a_hi, const ui
 /* Work of the last run's one-halo product, into HOST doubles: flops counts
  * one product per tile over the columns it summed (2 x 256 x 256 per column
  * and tile I >= J for the bf16 products, 2 x 128 x 256 on the 128 x 256
- * tiles of the FP64 product (also where few rows are taken by 16 x 16 blocks,
- * which do less), 2 x 128 x 128 on the FP32 product's tiles; each
+ * tiles of the FP64 product that hold rows, 2 x 16 x 16 on its blocks where
+ * the rows are few, 2 x 128 x 128 on the FP32 product's tiles; each
  * stops where the shorter of its two 256-row panels' factors ends),
  * mfma_flops the same with the split tiles counted three times.
  * factor_bytes (may be NULL): the bytes of the factor A that
- * the product's operands need, over the distinct rows and the K columns (the
- * bf16 factors up to each panel's extent, with the lo half where a tile of
- * the panel can take the split product; FP32 and FP64 over all K).  All 0
+ * the product's operands need, over the distinct rows and the columns up to
+ * each 256-row panel's extent (8 each in FP64, 4 in FP32, 2 in bf16, and 2 more
+ * for the lo half where a tile of the panel can take the split product).  All 0
  * for WLC_FP64_CHI.  ws_run: the DEVICE
  * workspace of a completed wlc_run with this plan; synchronises the device
  * for the copies. */

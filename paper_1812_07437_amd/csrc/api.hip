@@ -960,13 +960,10 @@ int wlc_gram_work(wlc_plan plan, const void *ws_run, double *flops, double *mfma
   if (src) return src;
   // 256-row panels: the units of the panel extents and of the per-tile precision
   const int64_t np = p.r_pad / GRAM_TILE;
-  std::vector<int32_t> ext;
-  if (!p.arow.empty()) {
-    ext.resize((size_t)np);
-    int rc = hip_check(hipMemcpy(ext.data(), static_cast<const char *>(ws_run) + L.off[B_EXT], (size_t)np * 4,
-                                 hipMemcpyDeviceToHost), "panel extent copy");
-    if (rc) return rc;
-  }
+  std::vector<int32_t> ext((size_t)np);
+  src = hip_check(hipMemcpy(ext.data(), static_cast<const char *>(ws_run) + L.off[B_EXT], (size_t)np * 4,
+                            hipMemcpyDeviceToHost), "panel extent copy");
+  if (src) return src;
   std::vector<double> F;
   if (prec == WLC_BF16_AUTO) {
     F.resize((size_t)np + 1);  // per panel, then the largest
@@ -974,16 +971,20 @@ int wlc_gram_work(wlc_plan plan, const void *ws_run, double *flops, double *mfma
                                  hipMemcpyDeviceToHost), "split plan copy");
     if (rc) return rc;
   }
-  // k summed by a tile of panels I and J: up to the shorter extent, or all of K
-  auto k_of = [&](int64_t I, int64_t J) {
-    return ext.empty() ? (double)p.k_pad : (double)GRAM_KB * std::min(ext[(size_t)I], ext[(size_t)J]);
-  };
+  // k summed by a tile of panels I and J: up to the shorter extent
+  auto k_of = [&](int64_t I, int64_t J) { return (double)GRAM_KB * std::min(ext[(size_t)I], ext[(size_t)J]); };
   const double lim = split_lim(p);
   double f = 0.0, m = 0.0;
-  if (prec == WLC_FP64 && gram_f64_tiles(gram_shape(p))) {
-    // two 128 x 256 tiles (row halves of panel P) per panel pair P >= J
-    for (int64_t P = 0; P < np; ++P)
-      for (int64_t J = 0; J <= P; ++J) f += 2.0 * 2.0 * 128.0 * 256.0 * k_of(P, J);
+  if (prec == WLC_FP64 && gram_f64_few(gram_shape(p))) {
+    // 16 x 16 blocks over the lower triangle, 16 to a panel
+    const int64_t nb = (p.n_R + 15) / 16;
+    for (int64_t I = 0; I < nb; ++I)
+      for (int64_t J = 0; J <= I; ++J) f += 2.0 * 16.0 * 16.0 * k_of(I / 16, J / 16);
+    m = f;
+  } else if (prec == WLC_FP64 && gram_f64_tiles(gram_shape(p))) {
+    // 128 x 256 tiles, row halves of the panels P >= J that hold rows
+    for (int64_t h = 0; h * 128 < p.n_R; ++h)
+      for (int64_t J = 0; J <= h / 2; ++J) f += 2.0 * 128.0 * 256.0 * k_of(h / 2, J);
     m = f;
   } else if (prec == WLC_FP64 || prec == WLC_FP32) {
     // 128 x 128 tiles over the lower triangle, in 256-row panels I / 2, J / 2
@@ -1004,17 +1005,14 @@ int wlc_gram_work(wlc_plan plan, const void *ws_run, double *flops, double *mfma
   *flops = f;
   *mfma_flops = m;
   if (factor_bytes) {
+    // the distinct rows lead the A-row order; a panel's rows end at its extent
     double b = 0.0;
-    if (ext.empty() || prec == WLC_FP64) {  // the FP64 factor is counted over all of K
-      b = (double)p.n_R * (double)p.k_len * (prec == WLC_FP64 ? 8.0 : prec == WLC_FP32 ? 4.0 : 2.0);
-    } else {  // the distinct rows lead the A-row order; a panel's rows end at its extent
-      for (int64_t P = 0; P < np; ++P) {
-        const int64_t tile = GRAM_TILE;
-        const double rows = (double)std::max<int64_t>(0, std::min<int64_t>(tile, p.n_R - P * tile));
-        const double k = (double)std::min<int64_t>((int64_t)GRAM_KB * ext[(size_t)P], p.k_len);
-        const bool lo = prec == WLC_BF16X3 || (prec == WLC_BF16_AUTO && F[(size_t)P] * F[(size_t)np] > lim);
-        b += rows * k * (lo ? 4.0 : 2.0);
-      }
+    for (int64_t P = 0; P < np; ++P) {
+      const int64_t tile = GRAM_TILE;
+      const double rows = (double)std::max<int64_t>(0, std::min<int64_t>(tile, p.n_R - P * tile));
+      const double k = (double)std::min<int64_t>((int64_t)GRAM_KB * ext[(size_t)P], p.k_len);
+      const bool lo = prec == WLC_BF16X3 || (prec == WLC_BF16_AUTO && F[(size_t)P] * F[(size_t)np] > lim);
+      b += rows * k * (prec == WLC_FP64 ? 8.0 : prec == WLC_FP32 || lo ? 4.0 : 2.0);
     }
     *factor_bytes = b;
   }

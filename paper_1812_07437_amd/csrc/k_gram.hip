@@ -1019,6 +1019,7 @@ static int64_t few_blocks(const GramShape &g) {
 // the L2 has to serve every operand once for each block (666 blocks at K = 2048
 // 156 against 152, at K = 32768 773 against 595).
 static bool f64_few(int prec, const GramShape &g) { return f64_tiles(prec, g) && few_blocks(g) <= 256; }
+bool gram_f64_few(const GramShape &g) { return f64_few(WLC_FP64, g); }
 static int gram_slices(int prec, const GramShape &g) {
   // slices to fill the CUs once (two workgroups to a CU share its reads: no
   // faster), of at least FEW_COLS columns, which take what a reduction does: a run

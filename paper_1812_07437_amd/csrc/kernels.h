@@ -127,6 +127,8 @@ void launch_gram_unpermute(int f32, const void *GP, const int32_t *pos, int64_t 
 // Whether the FP64 product of this shape runs on 128 x 256 tiles (else on
 // the 128 x 128 tiles of the FP32 product).
 bool gram_f64_tiles(const GramShape &g);
+// Whether its rows are so few that it runs in 16 x 16 blocks.
+bool gram_f64_few(const GramShape &g);
 
 // ---- assembly (k_assemble.hip)
 struct AsmArgs {
