@@ -552,8 +552,8 @@ int run_enqueue_back(const Plan &p, const wlc_tables &tb, void *ws, double *d, d
   void *Gm = at<void>(ws, L, B_GM);
   const AsmArgs a = asm_args(p, ws, L);
   if (hooks) hooks->begin(WLC_PHASE_ASSEMBLE);
-  if (p.arow.empty()) {
-    launch_gram_mirror(a.gm_f32, Gm, p.n_R, p.r_pad, s);
+  if (p.arow.empty()) {  // the product along chi, always FP64
+    launch_gram_mirror(static_cast<double *>(Gm), p.n_R, p.r_pad, s);
   } else {  // the product of the A-rows, made symmetric in the distinct-row order
     launch_gram_unpermute(a.gm_f32, at<void>(ws, L, B_GP), at<int32_t>(ws, L, B_POS), p.n_R, p.r_pad, Gm, s);
   }

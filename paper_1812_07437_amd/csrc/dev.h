@@ -33,30 +33,6 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
-// Bracketing interval of kk on an increasing grid: kg[j] <= kk <= kg[j+1],
-// t the fractional position in ln k.  Returns false outside the grid.
-__device__ __forceinline__ bool bracket_lnk(const double *kg, int nk, double kk, int &j, double &t) {
-  if (!(kk >= kg[0] && kk <= kg[nk - 1])) return false;
-  int lo = 0, hi = nk - 1;
-  while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (kg[mid] <= kk) lo = mid; else hi = mid;
-  }
-  if (lo == nk - 1) lo = nk - 2;
-  j = lo;
-  t = (log(kk) - log(kg[lo])) / (log(kg[lo + 1]) - log(kg[lo]));
-  return true;
-}
-
-// Round-to-nearest-even float -> bf16 bits (finite inputs).
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
-__device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
 // Exponent e with x = f 2^e, f in [0.5, 1); 0 for x == 0.
 __device__ __forceinline__ int exp2_of(double x) {
   int e = 0;

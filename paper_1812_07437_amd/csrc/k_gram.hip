@@ -875,9 +875,8 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void k_gram_f64_few(const double *_
 // (J, I), so both sides stay coalesced.  On a diagonal tile only the entries
 // above the diagonal are written, after the whole tile has been read.  The
 // upper side goes out with non-temporal stores (0.8 ms faster at 33280 rows).
-template <typename T>
-__global__ __launch_bounds__(256) void k_gram_mirror(T *__restrict__ G, int64_t ld) {
-  __shared__ T tile[64][65];
+__global__ __launch_bounds__(256) void k_gram_mirror(double *__restrict__ G, int64_t ld) {
+  __shared__ double tile[64][65];
   int I, J;
   tri_tile(blockIdx.x, I, J);
   const int c = threadIdx.x & 63, rb = (threadIdx.x >> 6) * 16;
@@ -892,13 +891,9 @@ __global__ __launch_bounds__(256) void k_gram_mirror(T *__restrict__ G, int64_t 
   }
 }
 
-void launch_gram_mirror(int f32, void *G, int64_t n, int64_t ld, hipStream_t s) {
+void launch_gram_mirror(double *G, int64_t n, int64_t ld, hipStream_t s) {
   const int64_t nt = (n + 63) / 64;  // nt * 64 <= ld: rows and columns are padded to the Gram tile
-  const unsigned tiles = (unsigned)(nt * (nt + 1) / 2);
-  if (f32)
-    hipLaunchKernelGGL(k_gram_mirror<float>, dim3(tiles), dim3(256), 0, s, (float *)G, ld);
-  else
-    hipLaunchKernelGGL(k_gram_mirror<double>, dim3(tiles), dim3(256), 0, s, (double *)G, ld);
+  hipLaunchKernelGGL(k_gram_mirror, dim3((unsigned)(nt * (nt + 1) / 2)), dim3(256), 0, s, G, ld);
 }
 
 // G in the order of the distinct rows, both triangles, from the lower triangle

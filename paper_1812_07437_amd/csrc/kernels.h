@@ -116,9 +116,9 @@ void launch_gram_reduce(int prec, const GramShape &g, void *out, void *partial, 
 // and sb (bispectrum) rows.
 void launch_chifact(const double *Ts, const double *G, double *H, int n_cfg, int n_chi, int n_m, int nl, int sp,
                     int sb, int n_tri, double *out, int64_t ld, hipStream_t s);
-// Copy the lower triangle of the first n rows/columns of G (row pitch ld,
-// f32 or f64) onto the upper one, so that G is exactly symmetric.
-void launch_gram_mirror(int f32, void *G, int64_t n, int64_t ld, hipStream_t s);
+// Copy the lower triangle of the first n rows/columns of G (row pitch ld) onto
+// the upper one, so that G is exactly symmetric.
+void launch_gram_mirror(double *G, int64_t n, int64_t ld, hipStream_t s);
 // G[e][f] = GP[pos[e]][pos[f]] for e, f < n (both triangles, f32 or f64,
 // pitch ld), from the lower triangle of GP: the product of the A-rows back in
 // the order of the distinct rows, exactly symmetric.
