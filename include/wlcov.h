@@ -260,11 +260,11 @@ int wlc_snr2(wlc_plan plan, const void *C, const int32_t *row_exp2, const double
 /* wlc_snr2 without allocation and without synchronisation, for callers
  * that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc).  The same FP64 bordered
- * Cholesky as wlc_snr2 (same kernels, same split-k choices, so the same
+ * Cholesky as wlc_snr2 (same kernels and batches of panels, so the same
  * result bit for bit), with its workspace in a fixed device array of the
  * library: 64 MiB per device, held by every device the library has run this
  * entry point on until the process ends.  That bounds the data vector to
- * about 2300 rows: WLC_EINVAL (nothing enqueued) when wlc_snr2's workspace,
+ * about 2400 rows: WLC_EINVAL (nothing enqueued) when wlc_snr2's workspace,
  * ws_snr_bytes, exceeds 64 MiB.
  * Inputs as wlc_snr2 (DEVICE C, row_exp2, d).  Outputs (DEVICE): snr2_dev[0]
  * = (S/N)^2, status_dev[0] = 0, or nonzero when a pivot was not positive

@@ -617,8 +617,8 @@ int snr_enqueue(const Plan &p, const void *C, const int32_t *row_exp2, const dou
 }
 
 // ---- fixed device scratch of wlc_snr2_noalloc
-// One array per device, holding the bordered matrix, the Cholesky's split-k
-// partials, the pivot flag and the result of one S/N at a time.  Host code
+// One array per device, holding the bordered matrix, the Cholesky's packed
+// panels, the pivot flag and the result of one S/N at a time.  Host code
 // never uses the array's name as an address: the device address comes from
 // hipGetSymbolAddress, once per device, with that device current.
 constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)64 << 20;

@@ -11,10 +11,10 @@
 // same launch already update and factor the next diagonal block (k_trail), so
 // that the serial chain runs beside the update.
 //
-// Measured, one factorisation (before: 64-wide diagonal blocks in launches of
-// their own, left-looking over 256 columns): n = 818 0.99 -> 0.29 ms, 2420 3.1 ->
-// 0.76 ms, 4550 6.0 -> 1.66 ms, 10000 15.1 -> 7.8 ms, 17059 42.5 -> 29.7 ms, 25044
-// 106 -> 85 ms, 33165 221 -> 189 ms, 82575 2.80 -> 2.81 s.
+// Measured, a call of wlc_snr2 (before: 64-wide diagonal blocks in launches of
+// their own, left-looking over 256 columns; both on one card): n = 818 0.95 -> 0.24
+// ms, 2420 3.1 -> 0.74 ms, 4550 6.0 -> 1.60 ms, 10000 15.1 -> 7.7 ms, 17059 42.7 ->
+// 29.8 ms, 25044 106 -> 84 ms, 33165 219 -> 189 ms, 82575 2.85 -> 2.81 s.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -782,15 +782,23 @@ static void launch_trail(double *Wm, int64_t ld, int64_t r0, int64_t rows, int64
   if (timed) (void)hipEventRecord(probe->ev[2 * probe->count++ + 1], s);
 }
 
+// Panels whose packed rows lie in the scratch, of GROUP that can be used: one up to
+// 1008 rows, three up to 1520, five to 2032, seven to 2544, then eight, and fewer
+// again past 131000 rows (seven to 149726, one from 524205).  Column blocks wait
+// for GAP panels at most, fewer where fewer fit, and groups need more than GAP.
+static int chol_slots(int64_t n) {
+  const int64_t fit = ((int64_t)(chol_scratch_bytes(n) / 8) - PACK_DIAG) / ((n + 64) * NB);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(GROUP, fit));
+}
+
 // Factor columns [0, n) of M (n + 1 rows).  scratch: the packed diagonal block,
-// then the packed rows of up to eight solved panels.  The pivot flag is checked by
+// then the packed rows of chol_slots(n) solved panels.  The pivot flag is checked by
 // the caller after synchronisation.
 int chol_factor(double *Wm, int64_t n, int64_t ld, double *scratch, int *flag, hipStream_t s,
                 KernelProbe *probe) {
   const int64_t rows = n + 1, pack_rows = (n + 64) * NB;  // doubles of a panel's packed rows
   double *pack = scratch, *part = scratch + PACK_DIAG;
-  const int64_t fit = ((int64_t)(chol_scratch_bytes(n) / 8) - PACK_DIAG) / pack_rows;
-  const int slots = (int)std::max<int64_t>(1, std::min<int64_t>(GROUP, fit));
+  const int slots = chol_slots(n);
   hipLaunchKernelGGL(k_diag, dim3(1), dim3(256), 0, s, Wm, ld, 0, (int)std::min<int64_t>(NB, n), pack, flag);
   Panels X{part, pack_rows, slots, 0};
   int begin = 0;     // the panels before this one have reached every column
@@ -822,13 +830,16 @@ int chol_factor(double *Wm, int64_t n, int64_t ld, double *scratch, int *flag, h
   return 0;
 }
 
-// The packed diagonal block and the packed rows of one panel (up to 1023 rows),
-// three (from 1024), five (1536), seven (2048) or eight (2560 to 131000).
+// Scratch, the size that callers know from the workspace queries and that sets
+// where wlc_snr2_noalloc ends (2424 rows at ten ell-bins): 32 KB, and 256 doubles
+// for each of the n + 1 rows and each whole 512 rows of n, at least once and at
+// most 64 times (1 GB in all); or one panel and the packed diagonal block, if
+// that is more.  chol_slots takes what fits.
 size_t chol_scratch_bytes(int64_t n) {
-  const int64_t pairs = std::clamp<int64_t>((n + 15) / 16 / 32, 1, 64);
-  const size_t panels = (size_t)64 * 64 * 8 + (size_t)std::min<int64_t>(524288, pairs * (n + 1)) * 256 * 8;
-  const size_t packed = (size_t)PACK_DIAG * 8 + (n > NB ? (size_t)(n + 64) * NB * 8 : 0);
-  return std::max(panels, packed);
+  const int64_t times = std::clamp<int64_t>((n + 15) / 16 / 32, 1, 64);
+  const size_t rows = (size_t)64 * 64 * 8 + (size_t)std::min<int64_t>(524288, times * (n + 1)) * 256 * 8;
+  const size_t panel = (size_t)PACK_DIAG * 8 + (n > NB ? (size_t)(n + 64) * NB * 8 : 0);
+  return std::max(rows, panel);
 }
 
 // ------------------------------------------------------------- y^T y

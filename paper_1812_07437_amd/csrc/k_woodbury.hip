@@ -186,7 +186,7 @@ __global__ void k_gblock(BlockMap B, const int32_t *__restrict__ cfgT, Qv q, con
 // scaled while column k + 1 is eliminated with, and an elimination divides by the
 // pivot instead (blocks of 35 rows 27 us, of 84 115; in global memory with three
 // barriers 42 and 320).
-constexpr int GCHOL_MAX = 138;  // 138 139 8 bytes, and vectors, in 160 KB
+constexpr int GCHOL_MAX = 138;  // of 160 KB 138 rows take 138 139 8 bytes; eight bins have 120 rows, nine 165
 
 template <bool LDS>
 __global__ __launch_bounds__(256) void k_gchol(BlockMap B, double *__restrict__ Gb, const double *__restrict__ dR,
