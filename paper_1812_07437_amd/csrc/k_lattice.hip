@@ -153,9 +153,8 @@ void launch_lattice(const int64_t *thr_dev, int64_t thr_max, int n_ell, const in
   }
   if (tris && n_tri > 0) {
     hipLaunchKernelGGL(k_zero_u64, dim3((n_tri + 255) / 256), dim3(256), 0, s, tris, n_tri);
-    // a launch holds fewer than 2^32 threads along x (more are taken modulo 2^32,
-    // without an error): one up to a radius of 262000, then one for every 2^23 workgroups
-    const int64_t wgs = (rmax / LY1 + 1) * ((2 * rmax + 256) / 256), most = (int64_t)1 << 23;
+    // one launch up to a radius of 262000
+    const int64_t wgs = (rmax / LY1 + 1) * ((2 * rmax + 256) / 256), most = LAUNCH_THREADS / 256;
     for (int64_t base = 0; base < wgs; base += most) {
       const dim3 grid((unsigned)std::min(most, wgs - base), (unsigned)n_tri);
       if (rmax <= 16000)

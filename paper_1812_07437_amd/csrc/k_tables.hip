@@ -12,6 +12,8 @@
 // at the ends) interpolated linearly in ln k.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace wlc {
@@ -99,10 +101,10 @@ __device__ __forceinline__ int wave_bracket(const double *kg, int nk, double kk,
   return min(lo, nk - 2);
 }
 
-__global__ __launch_bounds__(256) void k_stage(DevTables T, const double *__restrict__ centres, int n_ls, double *U,
-                                               LegTerm *legs, double *F) {
+__global__ __launch_bounds__(256) void k_stage(DevTables T, const double *__restrict__ centres, int n_ls, int base,
+                                               double *U, LegTerm *legs, double *F) {
   const int lane = threadIdx.x & (WAVE - 1);
-  const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * (256 / WAVE) + threadIdx.x / WAVE);
+  const int item = __builtin_amdgcn_readfirstlane(base + blockIdx.x * (256 / WAVE) + threadIdx.x / WAVE);
   const int nm = T.n_m_pts;
   if (item >= n_ls * T.n_chi) {
     const int q = (item - n_ls * T.n_chi) * WAVE + lane;
@@ -145,8 +147,10 @@ __global__ __launch_bounds__(256) void k_stage(DevTables T, const double *__rest
 
 void launch_stage(const DevTables &T, const double *centres, int n_ls, double *U, LegTerm *legs, double *F,
                   hipStream_t s) {
-  const int64_t waves = (int64_t)n_ls * T.n_chi + (4 * T.n_chi + WAVE - 1) / WAVE;
-  hipLaunchKernelGGL(k_stage, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, T, centres, n_ls, U, legs, F);
+  const int64_t waves = (int64_t)n_ls * T.n_chi + (4 * T.n_chi + WAVE - 1) / WAVE, most = LAUNCH_THREADS / WAVE;
+  for (int64_t base = 0; base < waves; base += most)
+    hipLaunchKernelGGL(k_stage, dim3((unsigned)((std::min(most, waves - base) + 3) / 4)), dim3(256), 0, s, T, centres,
+                       n_ls, (int)base, U, legs, F);
 }
 
 // ------------------------------------------------------------- 3-D spectra

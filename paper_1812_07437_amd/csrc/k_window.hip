@@ -13,6 +13,8 @@
 // kernel (linear in ln P against ln k).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace wlc {
@@ -91,11 +93,11 @@ __device__ __forceinline__ double bessel_j1(double x, const double *tab) {
 constexpr int SIG_THREADS = 512;
 constexpr int SIG_NK = 4000;
 template <bool STAGED>
-__global__ __launch_bounds__(SIG_THREADS) void k_sigma_w2(DevTables T, double theta, double *sw) {
+__global__ __launch_bounds__(SIG_THREADS) void k_sigma_w2(DevTables T, double theta, int base, double *sw) {
   extern __shared__ double lds[];  // ln k, ln P [n_k] each
   __shared__ double tab[J1_TAB];
   __shared__ double part[SIG_THREADS / WAVE];
-  const int n = blockIdx.x, nk = T.n_k;
+  const int n = base + blockIdx.x, nk = T.n_k;
   double *lk = lds, *lp = lds + nk;
   for (int i = threadIdx.x; i < J1_TAB; i += SIG_THREADS) tab[i] = bessel_tab(i);
   if constexpr (STAGED)
@@ -140,11 +142,14 @@ __global__ __launch_bounds__(SIG_THREADS) void k_sigma_w2(DevTables T, double th
 }
 
 void launch_sigma_w2(const DevTables &T, double theta, double *sw, hipStream_t s) {
-  if (T.n_k <= SIG_NK)
-    hipLaunchKernelGGL(k_sigma_w2<true>, dim3((unsigned)T.n_chi), dim3(SIG_THREADS), (size_t)T.n_k * 16, s, T, theta,
-                       sw);
-  else
-    hipLaunchKernelGGL(k_sigma_w2<false>, dim3((unsigned)T.n_chi), dim3(SIG_THREADS), 0, s, T, theta, sw);
+  const int most = (int)(LAUNCH_THREADS / SIG_THREADS);
+  for (int base = 0; base < T.n_chi; base += most) {
+    const dim3 grid((unsigned)std::min(most, T.n_chi - base));
+    if (T.n_k <= SIG_NK)
+      hipLaunchKernelGGL(k_sigma_w2<true>, grid, dim3(SIG_THREADS), (size_t)T.n_k * 16, s, T, theta, base, sw);
+    else
+      hipLaunchKernelGGL(k_sigma_w2<false>, grid, dim3(SIG_THREADS), 0, s, T, theta, base, sw);
+  }
 }
 
 }  // namespace wlc

@@ -251,4 +251,8 @@ void launch_lattice(const int64_t *thr_dev, int64_t thr_max, int n_ell, const in
 // ---- utilities (api.hip)
 void launch_fill_i32(int32_t *p, int n, int32_t v, hipStream_t s);
 
+// Threads of a launch along x, at most: the runtime takes a grid modulo 2^32
+// threads, without an error, so a larger one is several launches.
+constexpr int64_t LAUNCH_THREADS = (int64_t)1 << 31;
+
 }  // namespace wlc
