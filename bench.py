@@ -283,7 +283,8 @@ def pca_leg(args, torch, wl):
                snr2_rel_vs_cholesky=abs(cum[-1] - snr_p) / snr_p,
                modes_for_99pct=k99, frac_modes_for_99pct=k99 / npca, modes_for_95pct=k95,
                observables_in_95pct_modes=involved,
-               flops_per_sweep_est=12.0 * (((npca + 63) // 64) * 64) ** 3)
+               # the lower tiles of the pairs' Gram matrices, and two products of rotated rows
+               flops_per_sweep_est=10.5 * (((npca + 63) // 64) * 64) ** 3)
     log("pca %s: N=%d, %.2f s (%.2f s without vectors), %d sweeps, lambda %.2e..%.2e (%.1f decades), "
         "99%% of (S/N)^2 in %d modes (%.1f %%), %d observables in the 95%% modes" % (
             args.pca_workload, npca, t_pca, t_pca_nov, sweeps, lam[0], lam[-1], pca["decades"], k99,

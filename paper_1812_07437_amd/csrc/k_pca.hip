@@ -25,7 +25,11 @@
 // rotations W^T -> W^T V of its columns, those of the rows of W, are accumulated
 // in V, whose columns are the eigenvectors, and an angle between columns of
 // different norms is itself as small as their ratio.  Then lambda_a = |w_a|^2
-// for the columns w_a of W^T V, and D^_a = w_a . y with y as it is.
+// for the columns w_a of W^T V, and D^_a = w_a . y with y as it is.  Largest error of
+// (S_a . d)^2 / lambda_a over the whole S/N at 818, 2420 and 4550 rows: 2e-15, 8e-15
+// and 1e-14, from w_a / |w_a| 3e-5, 4e-5 and 8e-6.  It costs sweeps (11, 17 and 18
+// instead of 7, 10 and 15, the diagonal's order or the natural one alike) and the
+// second product of a round: 12.6, 103 and 473 ms against 6.9, 44 and 259.
 //
 // Storage: the columns of W (with vectors of W^T, and of V) are the rows of X
 // (and of V; zero-padded to n_pad), so every vector the method touches is a contiguous row.  Rows are grouped in blocks of
